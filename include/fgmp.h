@@ -318,8 +318,8 @@ fgmp_status_t fgmp_packed_info(const void *packed, fgmp_packed_info_t *info_host
 /* Threshold for a target fraction of FP8 blocks (Eq. 9): the score below the
  * round(fraction*J) largest of the J device-resident scores; fraction 0 ->
  * +INF, 1 -> -INF.  threshold_host: host.  Found on the device (an exact radix
- * selection: four passes over the scores, which stay where they are); the call
- * allocates a few KB of device memory for its counters, synchronizes `stream`
+ * selection: three passes over the scores, which stay where they are); the call
+ * allocates about 50 KB of device memory for its counters, synchronizes `stream`
  * and frees them. */
 fgmp_status_t fgmp_threshold_for_fraction(const float *scores, int64_t J, double fraction,
                                           float *threshold_host, void *stream);

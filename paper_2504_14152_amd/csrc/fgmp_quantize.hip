@@ -584,7 +584,7 @@ __global__ __launch_bounds__(256) void clip_scales_kernel(QuantParams p, uint8_t
 // no scan launch, no workgroup waits for another.  With kPackWgs workgroups that is under 2% of the first
 // pass for any size.  One wave per tile, one slot per lane.
 // 22016 x 4096 bf16 with per-element sensitivities: counting pass 94 us, one-workgroup scan of plane T (a strided
-// walk: 160 us) and packing pass 110 us before; packing pass 98 us and this kernel 12 us (no FP8 block) or 32 us (10%).
+// walk: 160 us) and packing pass 110 us before; packing pass 114 us and this kernel 15 us (no FP8 block) or 29 us (10%).
 constexpr int kPackWaves = 16, kPackWgs = 512;
 
 template <typename Tin>
@@ -609,10 +609,17 @@ __global__ __launch_bounds__(64 * kPackWaves) void pack_upper_halves_kernel(Quan
     {
         // two words per load; wg_first is even (16 waves)
         const uint4 *m2 = reinterpret_cast<const uint4 *>(masks);
-        for (uint32_t i = tid; i < wg_first / 2; i += 64 * kPackWaves) {
-            const uint4 v = m2[i];
-            before += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+        constexpr uint32_t kStep = 64 * kPackWaves, kFlight = 8;   // loads in flight per thread (one at a time: 20 us for 88064 tiles)
+        auto bits = [](const uint4 &v) { return (uint32_t)(__popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w)); };
+        uint32_t i = tid;
+        for (; i + (kFlight - 1) * kStep < wg_first / 2; i += kFlight * kStep) {
+            uint4 v[kFlight];
+#pragma unroll
+            for (uint32_t u = 0; u < kFlight; ++u) v[u] = m2[i + u * kStep];
+#pragma unroll
+            for (uint32_t u = 0; u < kFlight; ++u) before += bits(v[u]);
         }
+        for (; i < wg_first / 2; i += kStep) before += bits(m2[i]);
         for (uint32_t i = first + lane; i < last; i += 64) count += (uint32_t)__popcll(masks[i]);
     }
     before = wave_sum(before);

@@ -1,14 +1,21 @@
 // Threshold for a target fraction of FP8 blocks (Eq. 9; over several tensors, Eq. 10): an exact order
-// statistic of the scores, found on the device.  The scores stay where the quantizer wrote them: four
-// passes of an 8-bit radix selection over all tensors (most significant digit first) narrow the 32-bit key
-// of the wanted element down digit by digit; a pass counts, per value of the current digit, the elements
-// whose higher digits equal the prefix found so far (one 256-bin histogram, built per workgroup in LDS and
-// merged with 64-bit atomics), and a one-workgroup kernel walks the bins to the one that holds the wanted
-// rank.  Keys order like the numbers: the bit pattern of a non-negative float with the sign bit set, that
-// of a negative one inverted (-0 sorts just below +0; both compare equal to either as a threshold).  Every
-// pass reads every score once -- 16 bytes per lane where the array allows -- so the selection costs four
-// reads of the scores, against a copy to the host and a partial sort there.
+// statistic of the scores, found on the device.  The scores stay where the quantizer wrote them: three
+// passes of a radix selection over all tensors (digits of 11, 11 and 10 bits, most significant first) narrow
+// the 32-bit key of the wanted element down digit by digit; a pass counts, per value of the current digit, the
+// elements whose higher digits equal the prefix found so far, and the workgroup of a pass that finishes last
+// walks the bins to the one that holds the wanted rank.  Keys order like the numbers: the bit pattern of a
+// non-negative float with the sign bit set, that of a negative one inverted (-0 sorts just below +0; both
+// compare equal to either as a threshold).  Every pass reads every score once -- 16 bytes per lane where the
+// array allows -- so the selection costs three reads of the scores, against a copy to the host and a partial
+// sort there.
+//
+// What bounds a pass is not the read (22 MB of scores come out of the caches in 4 us) but the counting: the
+// scores of a tensor share a few exponents, so with a digit of 8 bits -- sign and seven exponent bits -- nearly
+// every lane of a wave added to the same LDS bin in the first pass.  Eleven bits take in two mantissa bits as
+// well, every wave counts into bins of its own, and few, large workgroups (one per compute unit) merge their
+// bins with few global atomics.
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 
 #include "fgmp_internal.hpp"
@@ -17,12 +24,19 @@ namespace fgmp {
 
 namespace {
 
+constexpr int kSelPasses = 3, kSelBins = 2048;
+constexpr int kSelThreads = 1024, kSelCopies = 8, kSelMaxWgs = 256;   // 8 x 2048 bins: 64 KB of LDS; two waves share a copy
+
 struct SelectState {
-    unsigned long long hist[256];   // bins of the pass in progress; zero between passes
+    unsigned long long hist[kSelPasses][kSelBins];   // zeroed by select_init_kernel
     unsigned long long rank;        // wanted element, counted from the smallest among those that match the prefix
-    uint32_t prefix, mask;          // digits found so far, and which bits they occupy
+    uint32_t prefix;                // digits found so far
+    uint32_t arrived;               // workgroups of the pass in progress that have merged their bins
     float result;
 };
+
+__host__ __device__ constexpr int sel_shift(int pass) { return pass == 0 ? 21 : pass == 1 ? 10 : 0; }
+__host__ __device__ constexpr int sel_bits(int pass) { return pass == 2 ? 10 : 11; }
 
 __device__ __forceinline__ uint32_t key_of(float v)
 {
@@ -30,29 +44,67 @@ __device__ __forceinline__ uint32_t key_of(float v)
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-__host__ __device__ inline float value_of(uint32_t key)
+__device__ inline float value_of(uint32_t key)
 {
     const uint32_t b = (key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key;
-#ifdef __HIP_DEVICE_COMPILE__
     return __builtin_bit_cast(float, b);
-#else
-    float f;
-    memcpy(&f, &b, 4);
-    return f;
-#endif
 }
 
-constexpr int kSelThreads = 256;
-
-__global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *__restrict__ s, int64_t n, int shift, SelectState *st)
+// The workgroup that arrives last (all bins of the pass are merged): the bin that holds the wanted rank becomes
+// the next digit of the prefix.
+template <int kPass> __device__ __forceinline__ void narrow(SelectState *st, unsigned long long *part)
 {
-    __shared__ uint32_t bins[256];
-    bins[threadIdx.x] = 0u;
+    constexpr int kBins = 1 << sel_bits(kPass), kPer = kBins / kSelThreads;
+    static_assert(kPer >= 1, "a thread owns at least one bin");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    unsigned long long h[kPer], sum = 0ull;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        h[i] = __hip_atomic_load(&st->hist[kPass][tid * kPer + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sum += h[i];
+    }
+    unsigned long long incl = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned long long v = __shfl_up(incl, d);
+        incl += lane >= d ? v : 0ull;
+    }
+    if (lane == 63) part[wave] = incl;
+    const unsigned long long rank = st->rank;   // (written before this launch)
+    const uint32_t prefix = st->prefix;
     __syncthreads();
-    const uint32_t prefix = st->prefix, mask = st->mask;
+    unsigned long long below = incl - sum;
+    for (int w = 0; w < wave; ++w) below += part[w];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        // exactly one bin of the pass holds the rank
+        if (rank >= below && rank < below + h[i]) {
+            const uint32_t p = prefix | ((uint32_t)(tid * kPer + i) << sel_shift(kPass));
+            st->rank = rank - below;
+            st->prefix = p;
+            if (kPass == kSelPasses - 1) st->result = value_of(p);
+        }
+        below += h[i];
+    }
+    if (tid == 0) st->arrived = 0u;
+}
+
+// One pass over one array; `n_wgs` workgroups take part in the pass over all arrays together.
+template <int kPass>
+__global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *__restrict__ s, int64_t n, uint32_t n_wgs, SelectState *st)
+{
+    constexpr int kBins = 1 << sel_bits(kPass), kShift = sel_shift(kPass);
+    constexpr uint32_t kHigher = kPass == 0 ? 0u : ~0u << sel_shift(kPass - 1);   // bits of the digits found before
+    __shared__ __attribute__((aligned(16))) uint32_t bins[kSelCopies][kBins];
+    __shared__ uint32_t last;
+    const int tid = threadIdx.x;
+    for (int i = tid; i < kSelCopies * kBins / 4; i += kSelThreads) reinterpret_cast<uint4 *>(&bins[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    const uint32_t prefix = kPass == 0 ? 0u : st->prefix;
+    uint32_t *mine = bins[(tid >> 6) % kSelCopies];
     auto take = [&](float v) {
         const uint32_t k = key_of(v);
-        if ((k & mask) == prefix) atomicAdd(&bins[(k >> shift) & 0xFFu], 1u);
+        if ((k & kHigher) == prefix) atomicAdd(&mine[(k >> kShift) & (uint32_t)(kBins - 1)], 1u);
     };
     // the part of the array that is aligned to 16 bytes in quads, the rest one by one
     const int64_t to_aligned = (int64_t)((16 - ((uintptr_t)s & 15)) & 15) / 4;
@@ -60,7 +112,20 @@ __global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *
     const int64_t quads = (n - head) / 4;
     const float4 *q = reinterpret_cast<const float4 *>(s + head);
     const int64_t stride = (int64_t)gridDim.x * kSelThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; i < quads; i += stride) {
+    int64_t i = (int64_t)blockIdx.x * kSelThreads + tid;
+    for (; i + 3 * stride < quads; i += 4 * stride) {   // four loads in flight
+        float4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = q[i + u * stride];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            take(v[u].x);
+            take(v[u].y);
+            take(v[u].z);
+            take(v[u].w);
+        }
+    }
+    for (; i < quads; i += stride) {
         const float4 v = q[i];
         take(v.x);
         take(v.y);
@@ -68,45 +133,46 @@ __global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *
         take(v.w);
     }
     if (blockIdx.x == 0) {
-        for (int64_t i = threadIdx.x; i < head; i += kSelThreads) take(s[i]);
-        for (int64_t i = head + quads * 4 + threadIdx.x; i < n; i += kSelThreads) take(s[i]);
+        for (int64_t j = tid; j < head; j += kSelThreads) take(s[j]);
+        for (int64_t j = head + quads * 4 + tid; j < n; j += kSelThreads) take(s[j]);
     }
     __syncthreads();
-    const uint32_t c = bins[threadIdx.x];
-    if (c != 0u) atomicAdd(&st->hist[threadIdx.x], (unsigned long long)c);
+    for (int b = tid; b < kBins; b += kSelThreads) {
+        uint32_t c = 0u;
+#pragma unroll
+        for (int u = 0; u < kSelCopies; ++u) c += bins[u][b];
+        if (c != 0u)
+            __hip_atomic_fetch_add(&st->hist[kPass][b], (unsigned long long)c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // every atomic of the workgroup has been performed before it counts as arrived
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid == 0)
+        last = __hip_atomic_fetch_add(&st->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_wgs - 1u;
+    __syncthreads();
+    if (last) narrow<kPass>(st, reinterpret_cast<unsigned long long *>(&bins[0][0]));
 }
 
-__global__ void select_init_kernel(SelectState *st, unsigned long long rank)
+__global__ __launch_bounds__(256) void select_init_kernel(SelectState *st, unsigned long long rank)
 {
-    st->hist[threadIdx.x] = 0ull;
-    if (threadIdx.x == 0) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < kSelPasses * kSelBins) (&st->hist[0][0])[i] = 0ull;
+    if (i == 0) {
         st->rank = rank;
         st->prefix = 0u;
-        st->mask = 0u;
+        st->arrived = 0u;
         st->result = 0.0f;
     }
 }
 
-// the bin that holds the wanted rank becomes the next digit of the prefix; the bins go back to zero
-__global__ __launch_bounds__(256) void select_narrow_kernel(int shift, SelectState *st)
+template <int kPass>
+void launch_count(const float *s, int64_t n, unsigned grid, uint32_t n_wgs, SelectState *state, hipStream_t st)
 {
-    __shared__ unsigned long long h[256];
-    h[threadIdx.x] = st->hist[threadIdx.x];
-    st->hist[threadIdx.x] = 0ull;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long rank = st->rank, below = 0ull;
-        uint32_t d = 0;
-        for (; d < 255u; ++d) {
-            if (rank < below + h[d]) break;
-            below += h[d];
-        }
-        st->rank = rank - below;
-        st->prefix |= d << shift;
-        st->mask |= 0xFFu << shift;
-        if (shift == 0) st->result = value_of(st->prefix);
-    }
+    hipLaunchKernelGGL((select_count_kernel<kPass>), dim3(grid), dim3(kSelThreads), 0, st, s, n, n_wgs, state);
 }
+
+// one workgroup per compute unit at most, and not more than have four quads per thread to read
+unsigned count_grid(int64_t n) { return (unsigned)std::min<int64_t>(kSelMaxWgs, (n / 4 + 4 * kSelThreads) / (4 * kSelThreads)); }
 
 }  // namespace
 
@@ -114,17 +180,20 @@ __global__ __launch_bounds__(256) void select_narrow_kernel(int shift, SelectSta
 fgmp_status_t select_rank(const float *const *scores, const int64_t *counts, int32_t n_tensors, int64_t rank, float *result_host,
                           hipStream_t st)
 {
+    uint64_t n_wgs = 0;
+    for (int32_t i = 0; i < n_tensors; ++i) n_wgs += count_grid(counts[i]);
+    if (n_wgs > 0xFFFFFFFFull) return FGMP_ERR_UNSUPPORTED;
     SelectState *state = nullptr;
     if (hipMalloc(&state, sizeof(SelectState)) != hipSuccess) return FGMP_ERR_HIP;
     fgmp_status_t rc = FGMP_OK;
-    hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(256), 0, st, state, (unsigned long long)rank);
-    for (int shift = 24; shift >= 0 && rc == FGMP_OK; shift -= 8) {
+    hipLaunchKernelGGL(select_init_kernel, dim3((kSelPasses * kSelBins + 255) / 256), dim3(256), 0, st, state, (unsigned long long)rank);
+    for (int pass = 0; pass < kSelPasses && rc == FGMP_OK; ++pass) {
         for (int32_t i = 0; i < n_tensors; ++i) {
-            const int64_t quads = counts[i] / 4 + 1;
-            const unsigned grid = (unsigned)std::min<int64_t>(2048, (quads + kSelThreads - 1) / kSelThreads);
-            hipLaunchKernelGGL(select_count_kernel, dim3(grid), dim3(kSelThreads), 0, st, scores[i], counts[i], shift, state);
+            const unsigned grid = count_grid(counts[i]);
+            if (pass == 0) launch_count<0>(scores[i], counts[i], grid, (uint32_t)n_wgs, state, st);
+            else if (pass == 1) launch_count<1>(scores[i], counts[i], grid, (uint32_t)n_wgs, state, st);
+            else launch_count<2>(scores[i], counts[i], grid, (uint32_t)n_wgs, state, st);
         }
-        hipLaunchKernelGGL(select_narrow_kernel, dim3(1), dim3(256), 0, st, shift, state);
         if (hipGetLastError() != hipSuccess) rc = FGMP_ERR_HIP;
     }
     if (rc == FGMP_OK && hipMemcpyAsync(result_host, &state->result, sizeof(float), hipMemcpyDeviceToHost, st) != hipSuccess)
