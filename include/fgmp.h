@@ -361,7 +361,7 @@ fgmp_status_t fgmp_selftest_decode_table(int format, float *out, void *stream);
 fgmp_status_t fgmp_selftest_mfma_rate(int64_t workgroups, int32_t iters, float *sink, void *stream);
 
 /*
- * Measurement hook: the duration of the prefill GEMM kernel inside a fused
+ * Measurement hook: the duration of the GEMM kernel (above 32 rows) inside a fused
  * call.  Only libraries built with FGMP_MEASUREMENT_HOOKS have it (the
  * benchmark's libfgmp_hooks.so); in the shipped library setting a pair returns
  * FGMP_ERR_UNSUPPORTED and the launcher records nothing.  While a pair of HIP events (hipEvent_t, created by the caller with

@@ -17,7 +17,8 @@ from . import listing_check
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfgmp.so")
-SOURCES = ["fgmp_quantize.hip", "fgmp_gemm.hip", "fgmp_gemm_skinny.hip", "fgmp_gemm_stream.hip", "fgmp_gemm_mixed.hip",
+SOURCES = ["fgmp_quantize.hip", "fgmp_gemm.hip", "fgmp_gemm_skinny.hip", "fgmp_gemm_stream.hip", "fgmp_gemm_mid.hip",
+           "fgmp_gemm_mixed.hip",
            "fgmp_select.hip", "fgmp_api.hip"]
 # -ffp-contract=off: the quantizer's FP32 steps are separately rounded.
 # packed-fp32-ops is switched off for the device compiler on purpose.
@@ -83,12 +84,13 @@ def build_one(variant: str | None = None, verbose: bool = False, extra_flags: li
 def build(verbose: bool = False, extra_flags: list[str] | None = None, out: str | None = None,
           variants: bool = True) -> str:
     """Build libfgmp.so (and, unless an explicit output is asked for, its two variants), then check the
-    compiled prefill loop of this very compiler and flag set for load/wait hazards."""
+    compiled loops with hand-counted waits of this very compiler and flag set for load/wait hazards."""
     path = build_one(None, verbose, extra_flags, out)
     if out is None and variants:
         for v in VARIANTS:
             build_one(v, verbose, extra_flags)
     listing_check.check(_hipcc(), FLAGS + (extra_flags or []), os.path.join(CSRC, "fgmp_gemm_mixed.hip"))
+    listing_check.check_mid(_hipcc(), FLAGS + (extra_flags or []), os.path.join(CSRC, "fgmp_gemm_mid.hip"))
     return path
 
 

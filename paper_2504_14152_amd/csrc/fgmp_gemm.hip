@@ -256,9 +256,32 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
     return (size_t)align_up((uint64_t)gemm_skinny_x16_rows(M) * round_up(K, kTileK) * 2, 256);
 }
 
+// Products of a few dozen to a few hundred rows (fgmp_gemm_mid.hip) as long as that beats the prefill kernel by the two
+// models' estimates -- with the time that staging FP32 results takes on top (a launch, a write and a read at 4.5 TB/s):
+// the calls that quantize their results have to quantize exactly what the plain call returns, so both take the same
+// kernel, and only the prefill kernel quantizes in its epilogue.  Measured, microseconds per fused step, this kernel /
+// the prefill kernel, on both sides of the line: 4096 x 22016 (K x N) 256 rows 52 / 63, 512 rows 96 / 94; 4096 x 12288
+// 384 rows 44 / 62, 768 rows 83 / 92, 1024 rows 103 / 99; 11008 x 4096 512 rows 58 / 87, 1024 rows 93 / 114; 512 x 16384
+// 256 rows 16 / 43, 768 rows 38 / 28.
+constexpr int64_t kMidMinRows = 33, kMidMaxRows = 1024;
+static bool use_mid(int64_t M, int64_t N, int64_t K)
+{
+    if (!kUseHwCvt || !prefill_decodes_in_kernel() || M < kMidMinRows || M > kMidMaxRows || !gemm_mid_applies(M, N, K)) return false;
+    const double staging = 6.0 + 8.0 * (double)M * (double)N / 4.5e6;
+    return gemm_mid_micros(M, N, K) + staging <= gemm_mixed_micros(M, N, K);
+}
+
+// their workspace behind the control region: header, FP16 activations, partial sums
+static size_t mid_x16_bytes(int64_t M, int64_t N, int64_t K)
+{
+    return (size_t)align_up((uint64_t)gemm_mid_x16_rows(M, N, K) * round_up(K, kTileK) * 2, 256);
+}
+static size_t mid_bytes(int64_t M, int64_t N, int64_t K) { return (size_t)kHeaderBytes + mid_x16_bytes(M, N, K) + gemm_mid_scratch_bytes(M, N, K); }
+
 // (all of these count the bytes behind the control region)
 size_t gemm_only_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
+    if (use_mid(M, N, K)) return mid_bytes(M, N, K);
     const size_t other = gemm_skinny_applies(M, N, K) ? skinny_x16_bytes(M, K) + gemm_skinny_workspace_bytes(M, N, K)
                                                       : gemm_ws_layout(M, N, K).total;
     return std::max(other, gemm_stream_scratch_bytes(M, N, K));
@@ -270,9 +293,21 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
     return kWsCtrlRegion + (size_t)make_layout(M, K).total_bytes + gemm_only_workspace_bytes(M, N, K);
 }
 
+// The fused call on the prefill kernel: header, FP16 activations, then what a split last round needs
+static bool fused_prefill(int64_t M, int64_t N, int64_t K)
+{
+    return kUseHwCvt && !gemm_skinny_applies(M, N, K) && mixed_kernel_applies(N, K);
+}
+static size_t fused_prefill_split(const GemmWorkspace &w) { return (size_t)align_up((uint64_t)kHeaderBytes + w.off_b, 256); }
+
 size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K)
 {
     if (gemm_stream_applies(M, N, K)) return kWsCtrlRegion + gemm_stream_scratch_bytes(M, N, K);
+    if (use_mid(M, N, K)) return kWsCtrlRegion + mid_bytes(M, N, K);
+    if (fused_prefill(M, N, K)) {
+        const GemmWorkspace w = gemm_ws_layout(M, N, K);
+        return kWsCtrlRegion + fused_prefill_split(w) + (w.total - w.off_split);
+    }
     return gemm_workspace_bytes(M, N, K);
 }
 
@@ -293,6 +328,14 @@ fgmp_status_t gemm_packed(const void *packed_X, int64_t M, const void *packed_W,
     workspace = static_cast<char *>(workspace) + kWsCtrlRegion + skip;
     if (gemm_stream_applies(M, N, K))
         return gemm_stream(2, nullptr, 0, nullptr, 0.0f, 1.0f, packed_X, M, packed_W, N, K, Y, ldy, ctrl, workspace, st);
+    if (use_mid(M, N, K)) {
+        const int64_t ld16 = round_up(K, kTileK);
+        _Float16 *x16 = reinterpret_cast<_Float16 *>(static_cast<char *>(workspace) + kHeaderBytes);
+        const fgmp_status_t rcx = launch_decode_f16(make_decode_job(A, la, x16, ld16, la.n_rt), nullptr, nullptr, 0, st);
+        if (rcx != FGMP_OK) return rcx;
+        return gemm_mid(A.hdr, x16, ld16, packed_W, M, N, K, Y, ldy, ctrl,
+                        static_cast<char *>(workspace) + kHeaderBytes + mid_x16_bytes(M, N, K), st);
+    }
     if (gemm_skinny_applies(M, N, K)) {
         // decode shapes: expand the few activation rows to FP16 once, then stream the weights
         _Float16 *x16 = static_cast<_Float16 *>(workspace);
@@ -349,6 +392,7 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
     // (the decode step quantizes its own results where the caller asks for it)
     const bool stream_pack = pack_out != nullptr && !pack_out->gate && pack_out->one_launch && gemm_stream_packs(M, N, K);
     const bool stream = score_mode == FGMP_SCORE_NVFP4_ERROR && (pack_out == nullptr || stream_pack) && x_fits && gemm_stream_applies(M, N, K);
+    const bool mid = !stream && use_mid(M, N, K);
     if (workspace_bytes < (stream ? (pack_out ? kWsCtrlRegion + gemm_stream_pack_scratch_bytes(M, N, K) : quant_gemm_workspace_need(M, N, K))
                                   : gemm_workspace_bytes(M, N, K)))
         return FGMP_ERR_BUFFER_TOO_SMALL;
@@ -365,7 +409,18 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
         return gemm_stream(dt == FGMP_F32 ? 1 : 0, X, ldx, fisher_k, threshold, scale_x, nullptr, M, packed_W, N, K, Y, ldy,
                            workspace, ws, st, pack_out);
     }
-    const bool in_kernel_prefill = !gemm_skinny_applies(M, N, K) && mixed_kernel_applies(N, K) && kUseHwCvt;
+    if (mid) {
+        if (pack_out != nullptr) return FGMP_ERR_UNSUPPORTED;   // the caller stages the FP32 results
+        // the quantizer writes the FP16 values of the codes it selects, then one launch of the product
+        const int64_t ld16 = round_up(K, kTileK);
+        _Float16 *x16 = reinterpret_cast<_Float16 *>(ws + kHeaderBytes);
+        const fgmp_status_t rc = quantize_tensor(X, dt, M, K, ldx, fisher_k, 0, threshold, scale_x, ws, sizeof(PackedHeader), nullptr,
+                                                 false, st, x16, ld16, nullptr, 0, score_mode);
+        if (rc != FGMP_OK) return rc;
+        return gemm_mid(reinterpret_cast<const PackedHeader *>(ws), x16, ld16, packed_W, M, N, K, Y, ldy, workspace,
+                        ws + kHeaderBytes + mid_x16_bytes(M, N, K), st);
+    }
+    const bool in_kernel_prefill = fused_prefill(M, N, K);
     if (pack_out != nullptr && !in_kernel_prefill) return FGMP_ERR_UNSUPPORTED;   // the caller falls back
     if (gemm_skinny_applies(M, N, K) && kUseHwCvt) {
         // decode shapes: FP16 values of X (rows beyond the last 8-row group stay unwritten: they only
@@ -387,7 +442,7 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
         if (tiles_m * tiles_n > 0x7FFFFFFF) return FGMP_ERR_UNSUPPORTED;
         PackedHeader *hx = reinterpret_cast<PackedHeader *>(ws);
         _Float16 *x16 = reinterpret_cast<_Float16 *>(ws + kHeaderBytes);
-        char *split_region = ws + (size_t)make_layout(M, K).total_bytes + w.off_split;
+        char *split_region = ws + fused_prefill_split(w);
         const SplitTail sp = plan_split_tail(tiles_m * tiles_n, (int)(w.ld / kBK), split_region);
         const fgmp_status_t rc = quantize_tensor(X, dt, M, K, ldx, fisher_k, 0, threshold, scale_x, ws,
                                                  sizeof(PackedHeader), nullptr, false, st, x16, w.ld, sp.counters,

@@ -1,0 +1,559 @@
+// Block-mixed-precision GEMM (Sec. 4.1) for tens to hundreds of activation rows: between the decode step that
+// streams the weights past a handful of rows and the prefill kernel whose 256 x 256 tiles are too few to fill
+// the chip here.
+//
+// What bounds it: at 64 rows the weights' bytes, the activations' way to the compute units, the decode and the
+// matrix instructions take about the same time (3-4 us each for a Llama-2-7B QKV product), there are never enough
+// tiles to occupy 256 compute units, and every pass over memory that is not an operand -- partial sums -- costs as
+// much as the operands do.  Hence:
+//   * K is split inside the workgroup first.  A workgroup of eight waves covers 16 MT rows x 16 NT WN columns; its
+//     WK groups of WN waves take WK consecutive K-tiles (128 elements each) of a "round" and add their
+//     accumulators through LDS at the end: an output tile a quarter of the prefill kernel's, with as much
+//     matrix work per barrier.  Only where that leaves compute units idle, K is split over workgroups as well.
+//   * The weights never touch LDS.  A wave decodes the blocks of its own 16 NT columns straight into the B
+//     operands of 16x16x32 matrix instructions; no other wave of the workgroup needs them, so nothing is
+//     decoded twice.  Lane (n = lane % 16, g = lane / 16) owns blocks 2g, 2g+1 of weight row n of a K-tile;
+//     matrix instruction j reduces over elements 8 (j % 2) .. + 7 of block 2g + j / 2 for g = 0..3.  The first or
+//     second blocks of a K-tile ("half" of it) are decoded between the matrix instructions of the half before: with the
+//     decode in a stretch of its own the two waves of a SIMD decode at the same time and the matrix pipe idles (a round
+//     of MT = 8, NT = 3 took 3.1 us, the sum of both, against 1.5 us of matrix instructions).  The decode has no branch for the
+//     same reason: value = fma(4-bit value, scale, 8-bit value) with the scale, or the 8-bit codes, masked to zero.
+//   * The activations (FP16 values, written by the quantizer) go to LDS directly, two rounds deep, one barrier
+//     per round.  A row of a K-tile is 256 bytes = 16 chunks; stored in an order that
+//     makes the 16-byte operand reads free of bank conflicts.
+//   * Workgroups that run at the same time on an XCD work on the same rows and the same part of K, tile by tile along
+//     N, so the activations come from that XCD's L2.
+// All loads of the loop are assembly with hand-counted waits, two per round: while a direct load to LDS is pending the
+// compiler waits for every load wherever it needs one, and where it does not know of the direct loads its waits are as
+// bad (1.8 us instead of 1.2 for a round of MT = 4, NT = 2: the first wait after the activations' loads waited for them).
+#include <algorithm>
+#include <type_traits>
+
+#include "fgmp_gemm_common.hpp"
+
+namespace fgmp {
+
+// (a build with FGMP_FULL_WAITS waits for every load: nothing to miscount, the same result bit for bit)
+#ifdef FGMP_FULL_WAITS
+#define FGMP_MID_PENDING(n) 0
+#else
+#define FGMP_MID_PENDING(n) (n)
+#endif
+
+constexpr int kMidThreads = 512;
+constexpr uint32_t kMidRsrc = 0x00020000;   // raw buffer, 32-bit data format
+
+// division by a constant that the host knows; exact for dividends below 2^16 and divisors below 2^16
+struct MidDiv {
+    uint32_t d, mul;
+    static MidDiv by(uint32_t d) { return MidDiv{d, d > 1 ? (uint32_t)(0x100000000ull / d) + 1u : 0u}; }
+    __device__ __forceinline__ uint32_t operator()(uint32_t v) const { return d == 1u ? v : __umulhi(v, mul); }
+};
+
+struct MidArgs {
+    const void *w;              // packed weights (header first)
+    const _Float16 *x16;        // [tiles_m * 16 MT][ld16]; rows from M on hold anything
+    float *Y;
+    uint32_t off_L, off_S, off_M, off_T, off_H;          // layout of the packed weights
+    uint32_t ld_bytes;
+    int M, N, n_kt, n_rt;
+    int rounds, parts;          // rounds of a tile; workgroups that share them
+    MidDiv by_tiles_n, by_parts;
+    uint32_t n_wgs;
+    uint32_t partial_bytes;
+    float *partial;
+    uint32_t *counters;         // one per tile; zero between launches
+    const PackedHeader *xh;     // header of the activations (tensor scale, shape check)
+    int64_t ldy;
+    int64_t w_rows, w_K, x_rows, x_K;                    // the shapes the headers must state
+};
+
+template <int MT, int NT, int WN, int WK>
+__global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_mid_kernel(MidArgs a)
+{
+    static_assert(WN * WK == 8, "eight waves");
+    constexpr int kRows = 16 * MT, kCols = 16 * NT * WN;
+    constexpr int kRowB = kTileK * 2;                         // 256 bytes of a row per K-tile
+    constexpr int kGroupBytes = kRows * kRowB;                // one K-tile of activations
+    constexpr int kStage = WK * kGroupBytes;
+    constexpr int kALoads = kRows / (4 * WN);                 // direct loads per wave and round: 1 KB = 4 rows of a K-tile each
+    constexpr int kWLoads = 5 * NT;                           // loads to registers per wave and round: planes L, H, S, M, T
+    constexpr int kRedBytes = (WK - 1) * MT * NT * WN * 1024;
+    constexpr int kLds = 2 * kStage > kRedBytes ? 2 * kStage : kRedBytes;
+    __shared__ __attribute__((aligned(1024))) char lds[kLds];
+    __shared__ uint32_t arrived;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % WN, wk = wave / WN;
+    const int nl = lane & 15, g = lane >> 4;
+
+    // the weights' header: requested now, needed for the first plane-H entries
+    const PackedHeader *wh = static_cast<const PackedHeader *>(a.w);
+    const uint32_t w_magic = wh->magic, w_bytes = (uint32_t)wh->bytes_used;
+    const int64_t w_rows = wh->rows, w_K = wh->K;
+    const float w_scale = wh->tensor_scale;
+
+    // dispatch goes round the XCDs: consecutive indices w belong to one of them
+    uint32_t w = blockIdx.x;
+    if (a.n_wgs % kNumXcd == 0) w = (w % kNumXcd) * (a.n_wgs / kNumXcd) + w / kNumXcd;
+    const uint32_t mp = a.by_tiles_n(w), n_idx = w - mp * a.by_tiles_n.d;
+    const uint32_t m_idx = a.by_parts(mp), part = mp - m_idx * a.by_parts.d;
+    const uint32_t tile = m_idx * a.by_tiles_n.d + n_idx;
+    const int m0 = (int)m_idx * kRows, n0 = (int)n_idx * kCols;
+    const int r0 = (int)a.by_parts(part * (uint32_t)a.rounds), r1 = (int)a.by_parts((part + 1u) * (uint32_t)a.rounds);
+
+    auto k_tile = [&](int r) { return r * WK + wk < a.n_kt ? r * WK + wk : a.n_kt - 1; };   // (past the tensor: never used)
+    // Chunk c of row r sits at position c ^ swizzle(r).  A 16-byte read is served 16 lanes at a time -- lanes 0-3, 12-15, 20-23,
+    // 24-27 first, i.e. rows 0-3, 12-15 of one chunk column and rows 4-11 of the next but three --: with r % 16 alone half of
+    // the LDS cycles were conflicts.
+    auto swizzle = [](int row) { return (row & 15) ^ ((row & 4) << 1); };
+    // ---- activations, direct to LDS: the WN waves of a K group load its K-tile, 4 rows (1 KB) at a time; lane (row lane / 16,
+    // position lane % 16) fetches the chunk that belongs at its position
+    const char *x_wave = reinterpret_cast<const char *>(a.x16) + (int64_t)(m0 + 4 * wn) * a.ld_bytes;
+    const uint32_t x_row = (uint32_t)(lane >> 4) * a.ld_bytes, x_swz = (uint32_t)(nl ^ swizzle(((wn & 3) << 2) | (lane >> 4))) << 4;
+    const uint32_t x_off[2] = {x_row + x_swz, x_row + (WN == 2 ? x_swz ^ 128u : x_swz)};   // (with WN = 2 every second load is 8 rows on)
+    const int64_t x_step = (int64_t)a.ld_bytes * (4 * WN);
+    auto issue_a = [&](int r, int stage, int i) {
+        const char *base = x_wave + (int64_t)k_tile(r) * kRowB + i * x_step;
+        const uint32_t dst = (uint32_t)(uintptr_t)(lds_void_t *)&lds[stage * kStage + wk * kGroupBytes + wn * 1024 + i * (WN * 1024)];
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(x_off[i & 1]), "s"(base) : "memory");
+    };
+    // operand reads: row nl of a 16-row group, chunk 4 g + j
+    const uint32_t f_lds = (uint32_t)(wk * kGroupBytes + nl * kRowB + (((4 * g) ^ swizzle(nl)) << 4));
+
+    // ---- weights: row of the lane in each column group, as the slot of its first block in the first tile of its row-tile
+    // (rows beyond the tensor read a valid tile; their products only reach columns that are never stored)
+    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, (int)a.off_H, kMidRsrc);
+    uint32_t e0[NT], t0[NT];
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+        const int row = n0 + (wn * NT + q) * 16 + nl;
+        const int rt = (row >> 3) < a.n_rt ? row >> 3 : a.n_rt - 1;
+        t0[q] = (uint32_t)rt * (uint32_t)a.n_kt;
+        e0[q] = t0[q] * kTileSlots + (uint32_t)((row & 7) * kTileBlocks + 2 * g);
+    }
+    u32x4_t wl[2][NT], wu[2][NT];   // planes L and H of a round's K-tile
+    uint32_t ws[2][NT];             // plane-S bytes of the lane's two blocks
+    uint64_t is8[2][NT][2];         // lanes whose first, second block is FP8
+    uint32_t ns[NT], nm[NT], nt[NT];
+    auto load_meta = [&](int r, int q) {
+        const uint32_t kt = (uint32_t)__builtin_amdgcn_readfirstlane(k_tile(r));
+        asm volatile("buffer_load_ushort %0, %1, %2, %3 offen" : "=v"(ns[q]) : "v"(a.off_S + e0[q]), "s"(wbuf), "s"(kt * kTileSlots));
+        asm volatile("buffer_load_ubyte %0, %1, %2, %3 offen" : "=v"(nm[q]) : "v"(a.off_M + t0[q] * 8u + (uint32_t)(nl & 7)), "s"(wbuf), "s"(kt * 8u));
+        asm volatile("buffer_load_dword %0, %1, %2, %3 offen" : "=v"(nt[q]) : "v"(a.off_T + t0[q] * 4u), "s"(wbuf), "s"(kt * 4u));
+    };
+    auto load_l = [&](int r, int set, int q) {
+        const uint32_t kt = (uint32_t)__builtin_amdgcn_readfirstlane(k_tile(r));
+        asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "=v"(wl[set][q]) : "v"(a.off_L + e0[q] * 8u), "s"(wbuf), "s"(kt * (kTileSlots * 8u)));
+    };
+    // At most kPending loads outstanding; the named registers hold what was loaded from here on.  (Until the wait that
+    // names it a register must not be touched; every register is named again at the end, so none is reused early.)
+    auto wait_meta = [&](auto pending_c) {
+        (void)ns, (void)nm, (void)nt;
+        if constexpr (NT == 2)
+            asm volatile("s_waitcnt vmcnt(%6)" : "+v"(ns[0]), "+v"(nm[0]), "+v"(nt[0]), "+v"(ns[1]), "+v"(nm[1]), "+v"(nt[1]) : "n"(FGMP_MID_PENDING(decltype(pending_c)::value)) : "memory");
+        else if constexpr (NT == 3)
+            asm volatile("s_waitcnt vmcnt(%9)" : "+v"(ns[0]), "+v"(nm[0]), "+v"(nt[0]), "+v"(ns[1]), "+v"(nm[1]), "+v"(nt[1]), "+v"(ns[2]), "+v"(nm[2]), "+v"(nt[2])
+                         : "n"(FGMP_MID_PENDING(decltype(pending_c)::value)) : "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(%12)" : "+v"(ns[0]), "+v"(nm[0]), "+v"(nt[0]), "+v"(ns[1]), "+v"(nm[1]), "+v"(nt[1]), "+v"(ns[2]), "+v"(nm[2]), "+v"(nt[2]),
+                         "+v"(ns[NT - 1]), "+v"(nm[NT - 1]), "+v"(nt[NT - 1]) : "n"(FGMP_MID_PENDING(decltype(pending_c)::value)) : "memory");
+    };
+    auto landed = [&](u32x4_t (&l)[NT], u32x4_t (&u)[NT]) {   // (no instruction: the wait before it was for younger loads)
+        if constexpr (NT == 2) asm volatile("" : "+v"(l[0]), "+v"(l[1]), "+v"(u[0]), "+v"(u[1]));
+        else if constexpr (NT == 3) asm volatile("" : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(u[0]), "+v"(u[1]), "+v"(u[2]));
+        else asm volatile("" : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[NT - 1]), "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(u[NT - 1]));
+    };
+#pragma unroll
+    for (int q = 0; q < NT; ++q) load_meta(r0, q);
+#pragma unroll
+    for (int i = 0; i < kALoads; ++i) issue_a(r0, 0, i);
+#pragma unroll
+    for (int q = 0; q < NT; ++q) load_l(r0, 0, q);
+    // plane H ends where the header says (a compact tensor may live in a buffer of exactly that size)
+    const bool w_ok = w_magic == kMagic && w_rows == a.w_rows && w_K == a.w_K;
+    const uint32_t w_used = w_ok ? (uint32_t)__builtin_amdgcn_readfirstlane((int)w_bytes) : 0u;
+    const __amdgpu_buffer_rsrc_t hbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, (int)w_used, kMidRsrc);
+    // plane H of the K-tile whose small fields have landed: two consecutive entries, the first block's in the low
+    // half where that is FP8, the second block's in the high half (lanes without an FP8 block ask for nothing).  A K-tile
+    // past the tensor (the K groups of a tile's last round may outnumber its K-tiles) gets zero scales and no FP8 blocks.
+    auto load_h = [&](int r, int set, int q) {
+        // (masks instead of conditions: no branch)
+        const uint32_t inside = (uint32_t)((r * WK + wk - a.n_kt) >> 31);
+        const uint32_t bits = __builtin_amdgcn_ubfe(nm[q], 2u * (uint32_t)g, 2u & inside);
+        // the entry before the second block's where that is FP8, else the first block's
+        const uint32_t entry = nt[q] + __builtin_amdgcn_ubfe(ns[q], (bits & 2u) << 2, 8u) - (bits >> 1);
+        const uint32_t none = (uint32_t)((int)(bits - 1u) >> 31) & 0xFFFFFF00u;
+        asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(wu[set][q]) : "v"((a.off_H + entry * 8u) | none), "s"(hbuf));
+        ws[set][q] = ns[q] & inside;
+        is8[set][q][0] = __builtin_amdgcn_ballot_w64((bits & 1u) != 0u);
+        is8[set][q][1] = __builtin_amdgcn_ballot_w64(bits > 1u);
+    };
+
+    float4_t acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int q = 0; q < NT; ++q) acc[i][q] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // Quarter j of a K-tile: eight values of block 2g + j / 2 of each column group, the operands of matrix instruction j.
+    // Every lane takes the 4-bit route; then the lanes whose block is FP8 overwrite the result, with the other lanes switched
+    // off around the four conversions (a branch would end the stretch that the matrix instructions are scheduled in, and
+    // selecting or adding the two routes' results costs a third more vector instructions).  All exact.
+    // (piece 3 q + p: a third of column group q's eight values)
+    auto decode = [&](int set, auto quarter_c, half2_t (&b)[NT][4], int piece) {
+        constexpr int j = decltype(quarter_c)::value, hb = j / 2;
+        const int q = piece / 3, p = piece % 3;
+        const uint32_t c4 = wl[set][q][j];   // (the lane's eight 4-bit codes; of an FP8 block, half of its first or second 8 bytes)
+        const half2_t sc = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(ws[set][q], 1.0f, false);
+        const half2_t s = half2_t{sc[hb], sc[hb]};
+        if (p == 0) {
+            b[q][0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(c4, 1.0f, 0) * s;
+            b[q][1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(c4, 1.0f, 1) * s;
+            asm volatile("" : "+v"(b[q][0]), "+v"(b[q][1]));
+        } else if (p == 1) {
+            b[q][2] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(c4, 1.0f, 2) * s;
+            b[q][3] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(c4, 1.0f, 3) * s;
+            asm volatile("" : "+v"(b[q][2]), "+v"(b[q][3]));
+        } else {
+            const uint32_t x8 = (j & 1) ? wu[set][q][2 * hb] : wl[set][q][2 * hb];
+            const uint32_t y8 = (j & 1) ? wu[set][q][2 * hb + 1] : wl[set][q][2 * hb + 1];
+            const uint64_t lanes8 = is8[set][q][hb];
+            asm volatile("s_mov_b64 exec, %6\n\t"
+                         "v_cvt_scalef32_pk_f16_fp8 %0, %4, 1.0\n\t"
+                         "v_cvt_scalef32_pk_f16_fp8 %1, %4, 1.0 op_sel:[1,0,0]\n\t"
+                         "v_cvt_scalef32_pk_f16_fp8 %2, %5, 1.0\n\t"
+                         "v_cvt_scalef32_pk_f16_fp8 %3, %5, 1.0 op_sel:[1,0,0]\n\t"
+                         "s_mov_b64 exec, -1"
+                         : "+v"(b[q][0]), "+v"(b[q][1]), "+v"(b[q][2]), "+v"(b[q][3])
+                         : "v"(x8), "v"(y8), "s"(lanes8));
+        }
+    };
+    // operands of a 16-row group, read kAhead groups ahead of their matrix instructions (a quarter reads the first ones of the
+    // next, except across the barrier)
+    constexpr int kAhead = MT < 3 ? MT : 3;
+    half8_t af[kAhead + 1];
+    auto read_a = [&](int stage, int n) {   // n = MT quarter + row group
+        af[n % (kAhead + 1)] = *reinterpret_cast<const half8_t *>(&lds[stage * kStage + (n % MT) * 16 * kRowB + (f_lds ^ ((n / MT) << 4))]);
+    };
+    // One quarter, in the order it is written here (the scheduler is kept from moving anything across a row group): the matrix
+    // instructions of a row group, a share of the next quarter's decode, a share of the loads that are due.
+    auto quarter = [&](int stage, auto j_c, const half2_t (&now)[NT][4], int set, auto next_c, half2_t (&next)[NT][4], auto loads) {
+        constexpr int j = decltype(j_c)::value;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            const int n = j * MT + i;
+            if (n + kAhead < 4 * MT) read_a(stage, n + kAhead);
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+                acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[n % (kAhead + 1)], *reinterpret_cast<const half8_t *>(&now[q][0]), acc[i][q], 0, 0, 0);
+#pragma unroll
+            for (int piece = 0; piece < 3 * NT; ++piece)
+                if (piece * MT / (3 * NT) == i) decode(set, next_c, next, piece);
+            loads(i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // (the compiler does not know what the conversions' assembly writes: no matrix instruction right behind)
+        asm volatile("s_nop 1");
+    };
+    // LDS operations of this wave are done and visible after the barrier; its loads stay in flight across it
+    auto barrier = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+    constexpr std::integral_constant<int, 0> h0{};
+    constexpr std::integral_constant<int, 1> h1{};
+    constexpr std::integral_constant<int, 2> h2{};
+    constexpr std::integral_constant<int, 3> h3{};
+
+    wait_meta(std::integral_constant<int, kALoads + NT>{});
+#pragma unroll
+    for (int q = 0; q < NT; ++q) load_h(r0, 0, q);
+#pragma unroll
+    for (int q = 0; q < NT; ++q) load_meta(r0 + 1, q);
+#pragma unroll
+    for (int q = 0; q < NT; ++q) load_l(r0 + 1, 1, q);
+    wait_meta(std::integral_constant<int, NT>{});                // ... and all that is older: the first round's activations and weights
+    landed(wl[0], wu[0]);
+#pragma unroll
+    for (int q = 0; q < NT; ++q) load_h(r0 + 1, 1, q);
+#pragma unroll
+    for (int q = 0; q < NT; ++q) load_meta(r0 + 2, q);
+    half2_t b0[NT][4], b1[NT][4];
+#pragma unroll
+    for (int piece = 0; piece < 3 * NT; ++piece) decode(0, h0, b0, piece);
+    asm volatile("s_nop 1");
+    barrier();
+
+    // Round r multiplies the K-tiles r WK ... from stage r % 2, a quarter at a time, and decodes the next quarter meanwhile (the
+    // last one: the first of the next round's).  Its first quarter asks for the activations of round r + 1 -- their stage
+    // has been free since the barrier --, its last quarter for the weights of round r + 2, whose registers are free by then.
+    auto round = [&](int r, auto st_c) {
+        constexpr int st = decltype(st_c)::value;
+        auto nothing = [](int) {};
+#pragma unroll
+        for (int n = 0; n < kAhead; ++n) read_a(st, n);
+        __builtin_amdgcn_sched_barrier(0);
+        quarter(st, h0, b0, st, h1, b1, [&](int i) {
+#pragma unroll
+            for (int k = 0; k < kALoads; ++k)
+                if (k * MT / kALoads == i) issue_a(r + 1, st ^ 1, k);
+        });
+        quarter(st, h1, b1, st, h2, b0, nothing);
+        quarter(st, h2, b0, st, h3, b1, nothing);
+        // the small fields of round r + 2 and, older, planes L and H of round r + 1; the activations may stay in flight
+        wait_meta(std::integral_constant<int, kALoads>{});
+        landed(wl[st ^ 1], wu[st ^ 1]);
+        quarter(st, h3, b1, st ^ 1, h0, b0, [&](int i) {
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+                if (q * MT / NT == i) {
+                    load_l(r + 2, st, q);
+                    load_h(r + 2, st, q);
+                    load_meta(r + 3, q);
+                }
+        });
+        // round r + 1's activations have landed: only the weights' loads above are younger
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FGMP_MID_PENDING(kWLoads)) : "memory");
+        barrier();
+    };
+    int r = r0;
+    for (; r + 2 <= r1; r += 2) {
+        round(r, h0);
+        round(r + 1, h1);
+    }
+    if (r < r1) round(r, h0);
+    // (loads past the range are still on their way, to registers and to LDS)
+    wait_meta(h0);
+    landed(wl[0], wu[0]);
+    landed(wl[1], wu[1]);
+    barrier();
+
+    // ---- the K groups' sums: 16-row group i is added up by the waves of K group i % WK, in K order
+    float4_t *red = reinterpret_cast<float4_t *>(lds);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        const int owner = i % WK;
+        if (wk != owner) {
+            const int from = wk < owner ? wk : wk - 1;
+#pragma unroll
+            for (int q = 0; q < NT; ++q) red[(((from * MT + i) * WN + wn) * NT + q) * 64 + lane] = acc[i][q];
+        }
+    }
+    barrier();
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        if (wk != i % WK) continue;
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            float4_t sum = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < WK; ++k) {
+                if (k == i % WK) sum += acc[i][q];
+                else sum += red[((((k < i % WK ? k : k - 1) * MT + i) * WN + wn) * NT + q) * 64 + lane];
+            }
+            acc[i][q] = sum;
+        }
+    }
+
+    const bool x_ok = a.xh->magic == kMagic && a.xh->rows == a.x_rows && a.xh->K == a.x_K;
+    const float ss = w_ok && x_ok ? a.xh->tensor_scale * w_scale : 0.0f;
+    if (a.parts > 1) {
+        // Partials and counters cross XCDs: system-coherent accesses that bypass the per-XCD L2; a workgroup's stores are
+        // complete before it bumps the tile's counter, so the one that arrives last reads complete sums.  It adds them in K
+        // order -- the result does not depend on the order of arrival -- and puts the counter back to zero.
+        constexpr uint32_t kSlotBytes = (uint32_t)kRows * kCols * 4u;
+        const __amdgpu_buffer_rsrc_t pbuf = __builtin_amdgcn_make_buffer_rsrc(a.partial, 0, (int)a.partial_bytes, kMidRsrc);
+        const uint32_t tile_at = tile * (uint32_t)a.parts * kSlotBytes + (uint32_t)(wn * NT) * 1024u + (uint32_t)lane * 16u;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            if (wk != i % WK) continue;
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+                store_coherent16(pbuf, tile_at + part * kSlotBytes + (uint32_t)((i * WN) * NT + q) * 1024u, acc[i][q]);
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (tid == 0) {
+            const uint32_t before = __hip_atomic_fetch_add(&a.counters[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (before == (uint32_t)a.parts - 1u) __hip_atomic_store(&a.counters[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            arrived = before;
+        }
+        __syncthreads();
+        if (arrived != (uint32_t)a.parts - 1u) return;
+        constexpr int kMine = (MT + WK - 1) / WK;   // 16-row groups of a wave: wk, wk + WK, ...
+        float4_t sum[kMine][NT];
+#pragma unroll
+        for (int i = 0; i < kMine; ++i)
+#pragma unroll
+            for (int q = 0; q < NT; ++q) sum[i][q] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int c = 0; c < a.parts; c += 2) {   // two parts' loads in flight (a part past the last one: beyond the tile, added as zero)
+            float4_t p[2][kMine][NT];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int i = 0; i < kMine; ++i)
+#pragma unroll
+                    for (int q = 0; q < NT; ++q) {
+                        const int row_group = wk + i * WK;
+                        const bool there = c + u < a.parts && row_group < MT;
+                        p[u][i][q] = load_coherent16(pbuf, there ? tile_at + (uint32_t)(c + u) * kSlotBytes + (uint32_t)(row_group * WN * NT + q) * 1024u : 0xFFFFFF00u);
+                    }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int i = 0; i < kMine; ++i)
+#pragma unroll
+                    for (int q = 0; q < NT; ++q) sum[i][q] += p[u][i][q];
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+            if (wk == i % WK) {
+#pragma unroll
+                for (int q = 0; q < NT; ++q) acc[i][q] = sum[i / WK][q];
+            }
+    }
+    // acc[i][q][e] = Y[m0 + 16 i + 4 g + e][n0 + 16 (NT wn + q) + nl]
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        if (wk != i % WK) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int m = m0 + 16 * i + 4 * g + e;
+            if (m < a.M) {
+                float *row = a.Y + (int64_t)m * a.ldy;
+#pragma unroll
+                for (int q = 0; q < NT; ++q) {
+                    const int n = n0 + (wn * NT + q) * 16 + nl;
+                    if (n < a.N) row[n] = acc[i][q][e] * ss;
+                }
+            }
+        }
+    }
+}
+
+// ---- host side ----
+
+// Which of the 16 MT x 16 NT WN tiles, and how many workgroups share one: the cheapest by a model of the launch, in
+// cycles of a compute unit.  A round costs what its matrix instructions, its vector instructions (two waves to a SIMD) or
+// its LDS accesses take, whichever is most -- 1.4 times that is measured --, a workgroup 15000 cycles before its first and
+// after its last round, partial sums that meet in memory 6000 and 2000 per part.  A launch takes 1.2 times the model (a
+// fused step 3 us more): 4096 x 12288, 64 rows, 4 x 2 tiles on 192 workgroups 16 us by the model, 19.6 measured (4 x 3 in
+// two parts 21.7, 4 x 4 in two 24.1); 11008 x 4096, 512 rows, 8 x 2 in two parts 52 / 57 (8 x 3 in two 68, 4 x 4 63);
+// 4096 x 22016, 200 rows, 7 x 3 38 / 45 (5 x 3 66, 7 x 2 59).
+struct MidPlan {
+    int mt, nt, wn, wk;
+    int64_t tiles_m, tiles_n, rounds, parts;
+    double cycles;
+    int64_t tiles() const { return tiles_m * tiles_n; }
+    int64_t cols() const { return 16 * nt * wn; }
+    size_t partial_bytes() const { return parts > 1 ? (size_t)(tiles() * parts) * (16 * mt) * cols() * 4 : 0; }
+};
+
+// column groups per wave that fit the 256 registers of two waves per SIMD (accumulators 4 MT NT, weights 38 NT)
+constexpr int mid_most_nt(int mt) { return mt <= 4 ? 4 : 3; }
+
+static MidPlan mid_plan(int64_t M, int64_t N, int64_t K)
+{
+    MidPlan best{};
+    best.cycles = INFINITY;
+    const int64_t n_kt = (K + kTileK - 1) / kTileK, least_m = (M + 127) / 128;
+    for (int64_t tiles_m = least_m; tiles_m <= least_m + 2; ++tiles_m) {
+        const int mt = (int)(((M + tiles_m - 1) / tiles_m + 15) / 16);
+        for (int nt = 2; nt <= mid_most_nt(mt); ++nt) {
+            MidPlan p;
+            p.mt = mt;
+            p.nt = nt;
+            p.wn = mt <= 4 ? 2 : 4;
+            p.wk = 8 / p.wn;
+            p.tiles_m = (M + 16 * mt - 1) / (16 * mt);
+            p.tiles_n = (N + p.cols() - 1) / p.cols();
+            p.rounds = (n_kt + p.wk - 1) / p.wk;
+            const double matrix = 128.0 * mt * nt, vector = 8.0 * (70.0 * nt + 30.0), lds = 256.0 * mt + 32.0 * mt * p.wk;
+            const double per_round = std::max(matrix, std::max(vector, lds)) * 1.4 + 300.0;
+            for (int64_t parts = 1; parts <= std::min<int64_t>(16, p.rounds); ++parts) {
+                p.parts = parts;
+                const int64_t waves = (p.tiles() * parts + 255) / 256;
+                p.cycles = (double)waves * (15000.0 + (double)((p.rounds + parts - 1) / parts) * per_round) +
+                           (parts > 1 ? 6000.0 + 2000.0 * (double)parts : 0.0);
+                if (p.cycles < best.cycles) best = p;
+            }
+        }
+    }
+    return best;
+}
+
+double gemm_mid_micros(int64_t M, int64_t N, int64_t K) { return 3.0 + 1.2 * mid_plan(M, N, K).cycles / 2100.0; }
+
+int64_t gemm_mid_x16_rows(int64_t M, int64_t N, int64_t K)
+{
+    const MidPlan p = mid_plan(M, N, K);
+    return p.tiles_m * 16 * p.mt;
+}
+
+size_t gemm_mid_scratch_bytes(int64_t M, int64_t N, int64_t K) { return (size_t)align_up(mid_plan(M, N, K).partial_bytes(), 256); }
+
+bool gemm_mid_applies(int64_t M, int64_t N, int64_t K)
+{
+    constexpr uint64_t kLimit = 0xFFFFFF00ull;   // 32-bit buffer offsets
+    if (make_layout(N, K).total_bytes >= kLimit) return false;
+    const MidPlan p = mid_plan(M, N, K);
+    return p.partial_bytes() < 0x7FFFFF00ull && p.tiles() * p.parts < 65536 && p.rounds * (p.parts + 1) < 65536 &&
+           p.tiles() <= (int64_t)(kWsCtrlRegion / 4) && align_up(K, kTileK) * 8 < 0x7FFFFFFF;
+}
+
+template <int MT, int NT> static void launch_mid(const MidArgs &a, hipStream_t st)
+{
+    constexpr int WN = MT <= 4 ? 2 : 4;
+    hipLaunchKernelGGL((gemm_mid_kernel<MT, NT, WN, 8 / WN>), dim3(a.n_wgs), dim3(kMidThreads), 0, st, a);
+}
+
+template <int MT> static void launch_mid_nt(int nt, const MidArgs &a, hipStream_t st)
+{
+    if (nt == 2) launch_mid<MT, 2>(a, st);
+    if constexpr (mid_most_nt(MT) >= 3)
+        if (nt == 3) launch_mid<MT, 3>(a, st);
+    if constexpr (mid_most_nt(MT) >= 4)
+        if (nt == 4) launch_mid<MT, 4>(a, st);
+}
+
+fgmp_status_t gemm_mid(const PackedHeader *xh, const _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
+                       int64_t ldy, void *ctrl, void *scratch, hipStream_t st)
+{
+    if (!gemm_mid_applies(M, N, K)) return FGMP_ERR_UNSUPPORTED;
+    const MidPlan p = mid_plan(M, N, K);
+    const PackedLayout lw = make_layout(N, K);
+    MidArgs a;
+    a.w = w; a.xh = xh; a.x16 = x16; a.Y = Y; a.ldy = ldy;
+    a.partial = static_cast<float *>(scratch); a.partial_bytes = (uint32_t)p.partial_bytes();
+    a.counters = static_cast<uint32_t *>(ctrl);
+    a.w_rows = N; a.w_K = K; a.x_rows = M; a.x_K = K;
+    a.off_L = (uint32_t)lw.off_L; a.off_S = (uint32_t)lw.off_S; a.off_M = (uint32_t)lw.off_M;
+    a.off_T = (uint32_t)lw.off_T; a.off_H = (uint32_t)lw.off_H;
+    a.ld_bytes = (uint32_t)(ld16 * 2);
+    a.M = (int)M; a.N = (int)N; a.n_kt = (int)lw.n_kt; a.n_rt = (int)lw.n_rt;
+    a.rounds = (int)p.rounds; a.parts = (int)p.parts;
+    a.by_tiles_n = MidDiv::by((uint32_t)p.tiles_n); a.by_parts = MidDiv::by((uint32_t)p.parts);
+    a.n_wgs = (uint32_t)(p.tiles() * p.parts);
+#ifdef FGMP_MEASUREMENT_HOOKS
+    record_gemm_kernel_event(false, st);
+#endif
+    switch (p.mt) {
+    case 1: launch_mid_nt<1>(p.nt, a, st); break;
+    case 2: launch_mid_nt<2>(p.nt, a, st); break;
+    case 3: launch_mid_nt<3>(p.nt, a, st); break;
+    case 4: launch_mid_nt<4>(p.nt, a, st); break;
+    case 5: launch_mid_nt<5>(p.nt, a, st); break;
+    case 6: launch_mid_nt<6>(p.nt, a, st); break;
+    case 7: launch_mid_nt<7>(p.nt, a, st); break;
+    default: launch_mid_nt<8>(p.nt, a, st); break;
+    }
+#ifdef FGMP_MEASUREMENT_HOOKS
+    record_gemm_kernel_event(true, st);
+#endif
+    return hipGetLastError() == hipSuccess ? FGMP_OK : FGMP_ERR_HIP;
+}
+
+}  // namespace fgmp

@@ -48,10 +48,10 @@ fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, i
                                     int64_t N, const float *fisher_n, float threshold_y, float scale_y,
                                     void *packed_Y, size_t packed_Y_bytes, float *scores_y, void *workspace,
                                     size_t workspace_bytes, hipStream_t st, int epilogue = FGMP_EPILOGUE_NONE);
-// Decode shapes (few rows of X): weight-streaming kernel.  X is given as FP16 values (`x16`,
+// Decode shapes (at most 32 rows of X) that the one-launch kernel does not cover: weight-streaming kernel.  X is given as FP16 values (`x16`,
 // gemm_skinny_x16_rows(M) rows of ld16 halves; rows from M rounded up to 8 on are never used for a
 // stored output) plus the header of its packed form.
-constexpr int64_t kSkinnyMaxRows = 256;   // in chunks of 32 rows, one launch each, while that beats the prefill kernel
+constexpr int64_t kSkinnyMaxRows = 32;
 bool gemm_skinny_applies(int64_t M, int64_t N, int64_t K);
 int64_t gemm_skinny_x16_rows(int64_t M);
 size_t gemm_skinny_workspace_bytes(int64_t M, int64_t N, int64_t K);
@@ -77,6 +77,16 @@ fgmp_status_t gemm_stream(int src, const void *X, int64_t ldx, const float *fish
                           void *scratch, hipStream_t st, const PackOut *po = nullptr);
 bool gemm_stream_packs(int64_t M, int64_t N, int64_t K);
 size_t gemm_stream_pack_scratch_bytes(int64_t M, int64_t N, int64_t K);
+// Tens to hundreds of rows: X as FP16 values (gemm_mid_x16_rows(M, N, K) rows of ld16 halves, zeros up to whole K-tiles; rows
+// from M on may hold anything), the weights decoded in registers.
+// `ctrl`: the workspace's control region; `scratch`: gemm_mid_scratch_bytes bytes.
+bool gemm_mid_applies(int64_t M, int64_t N, int64_t K);
+double gemm_mid_micros(int64_t M, int64_t N, int64_t K);     // estimate of a fused step
+double gemm_mixed_micros(int64_t M, int64_t N, int64_t K);   // the same on the prefill kernel
+int64_t gemm_mid_x16_rows(int64_t M, int64_t N, int64_t K);
+size_t gemm_mid_scratch_bytes(int64_t M, int64_t N, int64_t K);
+fgmp_status_t gemm_mid(const PackedHeader *xh, const _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
+                       int64_t ldy, void *ctrl, void *scratch, hipStream_t st);
 // packed -> zero-padded dense FP16 [8 n_rt_pad][ld]; one launch decodes one or two tensors and
 // can clear `zero_n` 32-bit counters
 struct DecodeJob {
@@ -124,8 +134,11 @@ fgmp_status_t selftest_mfma_rate(int64_t workgroups, int32_t iters, float *sink,
 // element of rank `rank` (0 = smallest) of the union of n_tensors device arrays; result on the host; synchronizes
 fgmp_status_t select_rank(const float *const *scores, const int64_t *counts, int32_t n_tensors, int64_t rank, float *result_host,
                           hipStream_t st);
-// events recorded around every launch of the prefill GEMM kernel (both null: none); false when the
+// events recorded around every launch of the GEMM kernel of more than 32 rows (both null: none); false when the
 // library was built without the measurement hooks
 bool set_gemm_kernel_events(hipEvent_t start, hipEvent_t stop);
+#ifdef FGMP_MEASUREMENT_HOOKS
+void record_gemm_kernel_event(bool stop, hipStream_t st);
+#endif
 
 }  // namespace fgmp

@@ -115,6 +115,54 @@ def check_kernel(lines, prefix) -> list[str]:
     return problems
 
 
+MID_KERNEL = "_ZN4fgmp15gemm_mid_kernel"
+
+
+def mid_kernels(lines) -> list[str]:
+    """The instantiations of the kernel for a few dozen to a few hundred rows in a listing."""
+    return [l.split(":")[0] for l in lines if l.startswith(MID_KERNEL) and ":" in l]
+
+
+def k_loop(body):
+    """The loop that holds matrix instructions (its header may be listed behind its first pass)."""
+    for hdr in (i for i, l in enumerate(body) if "Loop Header" in l):
+        label = body[hdr].split(":")[0]
+        back = [i for i in range(hdr, len(body)) if re.search(r"s_(?:cbranch_\w+|branch)\s+" + re.escape(label) + r"\b", body[i])]
+        if back and any("v_mfma" in l for l in body[hdr : back[-1] + 1]):
+            return body[hdr + 1 : back[-1] + 1]
+    raise RuntimeError("no loop with matrix instructions")
+
+
+def check_mid_kernel(lines, name) -> list[str]:
+    """The same for one instantiation gemm_mid_kernel<MT, NT, WN, WK>: two rounds per turn of its loop, two waits per round."""
+    mt, nt, wn, _ = (int(v) for v in re.search(r"ILi(\d)ELi(\d)ELi(\d)ELi(\d)E", name).groups())
+    problems = []
+    body = kernel_body(lines, name)
+    loop = instructions(k_loop(body))
+    if sum(s.startswith("v_mfma") for s in loop) != 2 * 4 * mt * nt:
+        problems.append("the loop body is not two rounds of four quarters")
+    checked, bad = violations(loop, cyclic=True)
+    if checked != 2 * 5 * nt or bad:
+        problems.append(f"main loop: {checked} loads checked, hazards {bad}")
+    checked, bad = violations(instructions(body), cyclic=False)
+    if checked < 4 * 5 * nt or bad:
+        problems.append(f"whole kernel: {checked} loads checked, hazards {bad}")
+    if [s for s in loop if s.startswith("scratch_")]:
+        problems.append("register spill inside the main loop")
+    waits = [int(m.group(1)) for s in loop for m in [re.match(r"s_waitcnt.*vmcnt\((\d+)\)", s)] if m]
+    if waits != 2 * [4 * mt // wn, 5 * nt]:
+        problems.append(f"waits in the main loop: {waits}")
+    return problems
+
+
+def check_mid(hipcc: str, flags: list[str], src: str) -> None:
+    """Raise if any instantiation of gemm_mid_kernel, compiled as the build compiles it, has a hazard."""
+    lines = make_listing(hipcc, flags, src)
+    found = {n: p for n in mid_kernels(lines) for p in [check_mid_kernel(lines, n)] if p}
+    if found or not mid_kernels(lines):
+        raise RuntimeError(f"gemm_mid_kernel listing check failed: {found}")
+
+
 def check(hipcc: str, flags: list[str], src: str) -> None:
     """Raise if any instantiation of the prefill kernel, compiled as the build compiles it, has a hazard."""
     lines = make_listing(hipcc, flags, src)

@@ -50,3 +50,76 @@ def test_packed_weights_hold_the_same_blocks_as_the_one_pass_layout(rows, K, p):
     assert torch.equal(plane_t, torch.cumsum(counts, 0) - counts)
     off_H = -(-(off_T + 4 * n_tiles) // 256) * 256
     assert info["bytes_used"] == off_H + 8 * max(1, int(counts.sum()))
+
+
+# ------------------------------------------------------------------ products of 33 .. 1024 rows
+
+def _product(M, K, N, dtype, p, seed):
+    x = synth.activations(M, K, seed, 1)
+    w = synth.weights(N, K, seed, 2)
+    fx, fw = synth.fisher_per_channel(K, seed, 3), synth.fisher_per_channel(K, seed, 4)
+    xd = torch.from_numpy(x).to(DEV).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    wd = torch.from_numpy(w).to(DEV)
+    xref = xd.float().cpu().numpy()
+    fxd, fwd = torch.from_numpy(fx).to(DEV), torch.from_numpy(fw).to(DEV)
+    sx, sw = float(synth.default_tensor_scale(xref)), float(synth.default_tensor_scale(w))
+    Tx = fgmp.threshold_for_fraction(fgmp.quantize_activations(xd, fxd, float("inf"), sx, want_scores=True)[1], p)
+    Tw = fgmp.threshold_for_fraction(fgmp.quantize_weights(wd, fwd, float("inf"), sw, want_scores=True)[1], p)
+    pW = fgmp.quantize_weights(wd, fwd, Tw, sw)
+    qx, qw = orc.quantize(xref, fx, Tx, sx), orc.quantize(w, fw, Tw, sw)
+    want, tol = orc.gemm(orc.dequantize(qx["codes"], qx["scales"], qx["mask"]), sx,
+                         orc.dequantize(qw["codes"], qw["scales"], qw["mask"]), sw)
+    return xd, fxd, Tx, sx, pW, want, tol
+
+
+# (M, K, N): every row-group count of a tile (33 .. 128 rows); rows one past a tile; columns that end inside a lane
+# group, an odd number of 8-row weight tiles; K of one block, one K-tile, K groups without a K-tile in the last round,
+# K in several parts across workgroups; more tiles than compute units
+MID_SHAPES = [(33, 16, 24, "f32", 0.1), (48, 128, 264, "bf16", 0.1), (64, 4096, 136, "bf16", 0.2), (77, 2064, 503, "f32", 0.2),
+              (96, 640, 72, "bf16", 0.0), (112, 1168, 1000, "bf16", 1.0), (129, 384, 40, "f32", 0.3), (200, 8192, 200, "bf16", 0.1),
+              (300, 1040, 264, "bf16", 0.1), (512, 2816, 328, "bf16", 0.1), (700, 144, 136, "bf16", 0.1), (1024, 272, 72, "f32", 0.1),
+              (40, 256, 34000, "bf16", 0.1)]
+
+
+@pytest.mark.parametrize("M,K,N,dtype,p", MID_SHAPES)
+def test_products_of_a_few_dozen_to_a_few_hundred_rows_match_oracle(M, K, N, dtype, p):
+    """Within 1e-5 of the sum of magnitudes (FP32 accumulation), equal to the product of the packed activations and to a
+    second call bit for bit, counters left zero, and equal to the build in which every hand-counted wait is a full one."""
+    from paper_2504_14152_amd import build
+    xd, fxd, Tx, sx, pW, want, tol = _product(M, K, N, dtype, p, 70 + M)
+    ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
+    ws[fgmp.WORKSPACE_CONTROL_BYTES:] = 0xFF       # partial sums and rows beyond M start as NaN patterns
+    Y = fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, workspace=ws)
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - want)
+    assert np.all(err <= tol), (err / tol).max()
+    assert int(ws[: fgmp.WORKSPACE_CONTROL_BYTES].sum()) == 0
+    assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, workspace=ws), Y)
+    assert torch.equal(fgmp.gemm(fgmp.quantize_activations(xd, fxd, Tx, sx), pW), Y)
+    with fgmp.use_library(build.lib_path("fullwait")):
+        assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW), Y)
+
+
+def test_products_between_decode_and_prefill_replay_in_a_graph():
+    """K in parts (partial sums, counters that the kernel puts back to zero), replayed with other work between."""
+    xd, fxd, Tx, sx, pW, _, _ = _product(64, 8192, 200, "bf16", 0.1, 91)
+    ws = fgmp.new_workspace(fgmp.workspace_bytes(64, 200, 8192), DEV)
+    Y = torch.empty(64, 200, device=DEV)
+    fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, out=Y, workspace=ws)
+    want = Y.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, out=Y, workspace=ws)
+    for _ in range(4):
+        Y.fill_(float("nan"))
+        ws[fgmp.WORKSPACE_CONTROL_BYTES:] = 0xFF
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, want)
+
+
+def test_static_scratch_takes_products_of_more_than_32_rows():
+    for M, K, N in ((64, 4096, 1024), (300, 1040, 264), (200, 16, 24)):
+        xd, fxd, Tx, sx, pW, _, _ = _product(M, K, N, "bf16", 0.1, 92)
+        got = torch.full((M, N), float("nan"), device=DEV)
+        fgmp.quant_gemm_fused_static_scratch(xd, fxd, Tx, sx, pW, out=got)
+        assert torch.equal(got, fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW))

@@ -105,3 +105,24 @@ def test_decode_kernel_full_wait_variant_counts_nothing():
         waits = [int(m.group(1)) for k in range(i + 1, end) if "#ASMSTART" in lines[k - 1]
                  for m in [re.search(r"s_waitcnt.*vmcnt\((\d+)\)", lines[k])] if m]
         assert len(waits) >= 20 and max(waits) == 0
+
+
+# ---- the kernel for a few dozen to a few hundred rows (fgmp_gemm_mid.hip) ----
+
+MID_SRC = os.path.join(build.CSRC, "fgmp_gemm_mid.hip")
+
+
+def test_mid_kernel_touches_no_register_of_a_load_in_flight():
+    lines = lc.make_listing(HIPCC, build.FLAGS, MID_SRC)
+    names = lc.mid_kernels(lines)
+    assert len(names) >= 20
+    assert {n: p for n in names for p in [lc.check_mid_kernel(lines, n)] if p} == {}
+
+
+def test_mid_kernel_full_wait_variant_counts_nothing():
+    import re
+    lines = lc.make_listing(HIPCC, build.FLAGS + build.VARIANTS["fullwait"], MID_SRC)
+    for name in lc.mid_kernels(lines):
+        loop = lc.instructions(lc.k_loop(lc.kernel_body(lines, name)))
+        waits = [int(m.group(1)) for s in loop for m in [re.match(r"s_waitcnt.*vmcnt\((\d+)\)", s)] if m]
+        assert waits and max(waits) == 0, (name, waits)
