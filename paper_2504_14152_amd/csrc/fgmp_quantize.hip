@@ -533,13 +533,58 @@ __global__ __launch_bounds__(64 * kQWaves) void quantize_act_kernel(QuantParams 
     if (it % kQBatch != 0) write_masks(it - it % kQBatch, it % kQBatch);
 }
 
+// The NVFP4 error of a block under the scale value d (inv_d = 1 / d, 0 for d = 0): operation for operation the score
+// that quantize_block_math computes.
+__device__ __forceinline__ float nvfp4_error(const float (&x)[16], const float (&f)[16], float d, float inv_d)
+{
+    uint32_t q[2] = {0u, 0u};
+    float t[16];
+#define FGMP_ENC(W, B, I) q[W] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q[W], x[I] * inv_d, x[I + 1] * inv_d, 1.0f, B)
+    FGMP_ENC(0, 0, 0); FGMP_ENC(0, 1, 2); FGMP_ENC(0, 2, 4); FGMP_ENC(0, 3, 6);
+    FGMP_ENC(1, 0, 8); FGMP_ENC(1, 1, 10); FGMP_ENC(1, 2, 12); FGMP_ENC(1, 3, 14);
+#undef FGMP_ENC
+#define FGMP_ERR(W, B, I)                                                                \
+    {                                                                                    \
+        const float2_t v = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(q[W], 1.0f, B);      \
+        const float e0 = x[I] - v[0] * d, e1 = x[I + 1] - v[1] * d;                      \
+        t[I] = (e0 * e0) * f[I];                                                         \
+        t[I + 1] = (e1 * e1) * f[I + 1];                                                 \
+    }
+    FGMP_ERR(0, 0, 0) FGMP_ERR(0, 1, 2) FGMP_ERR(0, 2, 4) FGMP_ERR(0, 3, 6)
+    FGMP_ERR(1, 0, 8) FGMP_ERR(1, 1, 10) FGMP_ERR(1, 2, 12) FGMP_ERR(1, 3, 14)
+#undef FGMP_ERR
+#pragma unroll
+    for (int w = 16; w > 1; w >>= 1)
+#pragma unroll
+        for (int i = 0; i < w / 2; ++i) t[i] = t[2 * i] + t[2 * i + 1];
+    return t[0];
+}
+
 // Sensitivity-weighted clipping (Sec. 3.3, Eq. 11): for every block, the E4M3 scale code (0 .. 0x7E)
-// whose NVFP4 quantization has the smallest weighted error -- brute force, candidates in ascending
-// order, a later candidate wins only with a strictly smaller error.  One block per lane; the error of
-// a candidate is computed exactly as quantize_kernel computes a block's score.  Offline (weights).
+// whose NVFP4 quantization has the smallest weighted error; candidates in ascending order, a later candidate
+// wins only with a strictly smaller error.  One block per lane; the error of a candidate is computed exactly as
+// quantize_kernel computes a block's score.  Offline (weights); bound: vector ALU (a candidate costs 112 vector
+// instructions), so what counts is how few candidates are tried.
+//
+// A candidate whose error is certain to exceed B, the smaller one of the errors under code 0 and under the dynamic-max
+// code, cannot be the answer.  An error is a sum of non-negative terms added in FP32, so it is at least each of them:
+//   too small a scale clips element i to 6 d: its term is at least F_i (|x_i| - 6 d)^2 > B where
+//     6 d < |x_i| - sqrt(B / F_i);
+//   too large a scale rounds element i to zero (|x_i| < d / 4): its term is F_i x_i^2, exactly as computed here.
+// The bounds are taken 1e-5 wide of these, the rounding errors of a term being below 1e-6, and one code wide on top.
+// Where the argument needs more than that (negative or non-finite sensitivities, errors or scales near the ends of the
+// FP32 range) every code is tried.  Of 127 candidates 21 are left per block on N(0, 0.02^2) weights with lognormal
+// sensitivities, 34 for the slowest of a wave's 64 blocks.  12288 x 4096, per-element
+// sensitivities: 385 us, 1210 us when all were tried (with one division and one decode of the scale per candidate).
 template <typename Tin, bool kPerElem, bool kHW>
 __global__ __launch_bounds__(256) void clip_scales_kernel(QuantParams p, uint8_t *sc_out)
 {
+    __shared__ float2 tbl[128];   // {d, 1 / d} by scale code
+    if (threadIdx.x < 128) {
+        const float d = e4m3_decode_int(threadIdx.x) * p.S;
+        tbl[threadIdx.x] = make_float2(d, threadIdx.x != 0 ? 1.0f / d : 0.0f);
+    }
+    __syncthreads();
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int64_t kt = blockIdx.x;
@@ -557,14 +602,44 @@ __global__ __launch_bounds__(256) void clip_scales_kernel(QuantParams p, uint8_t
     const float amax = block_amax(x);
     const float inv_S = 1.0f / p.S, S6 = 6.0f * p.S;
     auto error_with = [&](uint32_t sc) {
-        BlockCodes bc;
-        quantize_block_math<kHW, false>(x, f, amax, p.S, inv_S, S6, (int)sc, false, bc);
-        return bc.score;
+        if constexpr (kHW) {
+            const float2 s = tbl[sc];
+            return nvfp4_error(x, f, s.x, s.y);
+        } else {
+            BlockCodes bc;
+            quantize_block_math<kHW, false>(x, f, amax, p.S, inv_S, S6, (int)sc, false, bc);
+            return bc.score;
+        }
     };
     uint32_t best = 0u;
     float best_err = error_with(0u);
+    uint32_t first = 1u, last = 0x7Eu;
+    const float bound = fminf(best_err, error_with(enc_e4m3<kHW>(amax / S6)));
+    float f_min = f[0], f_max = f[0], f_sum = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        f_min = fminf(f_min, f[i]);
+        f_max = fmaxf(f_max, f[i]);
+        f_sum += f[i];   // (minimum and maximum skip a NaN)
+    }
+    // (B / F_i >= 1e-30: the clipped element's error and its square are ordinary numbers)
+    if (bound > 1e-35f && bound > 1e-30f * f_max && bound < 1e25f && f_min >= 0.0f && f_max < 1e30f && f_sum == f_sum && amax < 1e15f &&
+        p.S > 1e-20f && p.S < 1e20f) {
+        float d_low = 0.0f, d_high = 4.0f * amax;   // (beyond: all zeros, the error of code 0)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float ax = fabsf(x[i]);
+            // (a vanishing sensitivity gives an infinite root, and no bound)
+            const float root = __builtin_amdgcn_sqrtf(bound * __builtin_amdgcn_rcpf(f[i]));
+            d_low = fmaxf(d_low, (ax * 0.99999f - root * 1.00001f) * (1.0f / 6.0f));
+            if ((ax * ax) * f[i] > bound) d_high = fminf(d_high, 4.0f * ax);
+        }
+        const uint32_t low = enc_e4m3<kHW>(fminf(d_low * 0.99999f * inv_S, 448.0f)), high = enc_e4m3<kHW>(fminf(d_high * 1.00001f * inv_S, 448.0f));
+        first = low > 2u ? low - 1u : 1u;
+        last = high < 0x7Du ? high + 1u : 0x7Eu;
+    }
 #pragma unroll 1
-    for (uint32_t sc = 1u; sc <= 0x7Eu; ++sc) {
+    for (uint32_t sc = first; sc <= last; ++sc) {
         const float err = error_with(sc);
         if (err < best_err) {
             best_err = err;

@@ -123,3 +123,38 @@ def test_static_scratch_takes_products_of_more_than_32_rows():
         got = torch.full((M, N), float("nan"), device=DEV)
         fgmp.quant_gemm_fused_static_scratch(xd, fxd, Tx, sx, pW, out=got)
         assert torch.equal(got, fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW))
+
+
+# ------------------------------------------------------------------ clipping: the candidates that are left out
+
+@pytest.mark.parametrize("what", ["ordinary", "heavy tails", "sparse sensitivities", "huge range", "negative", "tiny", "small scale", "large scale"])
+def test_clipped_scales_are_the_brute_force_ones(what):
+    """The kernel tries only the codes whose error can be the smallest; the oracle tries all 127."""
+    rng = synth.rng_for(33, len(what))
+    N, K = 72, 528
+    w = rng.standard_normal((N, K)).astype(np.float32) * np.float32(0.02)
+    f = np.exp(rng.standard_normal((N, K))).astype(np.float32)
+    scale = 1.0
+    if what == "heavy tails":
+        w *= np.exp(1.5 * rng.standard_normal((N, K))).astype(np.float32)
+    elif what == "sparse sensitivities":
+        f[rng.random((N, K)) < 0.8] = 0.0          # blocks decided by a few elements, some by none
+        w[:, :16] = 0.0
+        w[:, 16:32] = np.float32(0.0125)           # all elements equal: ties
+    elif what == "huge range":
+        f = np.exp(12.0 * rng.standard_normal((N, K))).astype(np.float32)
+    elif what == "negative":
+        f *= np.where(rng.random((N, K)) < 0.1, -1.0, 1.0).astype(np.float32)
+    elif what == "tiny":
+        w *= np.float32(1e-12)
+        f *= np.float32(1e-10)
+    elif what == "small scale":
+        scale = 1.0 / 64.0                          # blocks beyond the largest code
+    elif what == "large scale":
+        scale = 300.0                               # every block among the first few codes
+    S = float(synth.default_tensor_scale(w)) * scale
+    want = orc.quantize(w, f, float("inf"), S, clip=True)
+    pk, scores = fgmp.quantize_weights_clip(torch.from_numpy(w).to(DEV), torch.from_numpy(f).to(DEV), float("inf"), S, want_scores=True)
+    codes, scales, mask = (t.cpu().numpy() for t in fgmp.unpack_canonical(pk))
+    assert np.array_equal(scales, want["scales"]) and np.array_equal(codes, want["codes"]) and np.array_equal(mask, want["mask"])
+    assert np.array_equal(scores.cpu().numpy().view(np.uint32), want["scores"].view(np.uint32))
