@@ -150,8 +150,15 @@ def _check(rc: int, what: str) -> None:
         raise FgmpError(f"{what} failed: {_ERRORS.get(rc, rc)}")
 
 
+# The current stream's handle without building a torch.cuda.Stream for it: 0.2 us instead of 2.9, of the 8.6 us that
+# issuing a decode step took through this module (4096 x 4096, one row: the GPU needs 5.8).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch._C._cuda_getDevice())
 
 
 def _dtype_code(t: torch.Tensor) -> int:
