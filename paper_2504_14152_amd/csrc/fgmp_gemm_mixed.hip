@@ -25,6 +25,18 @@
 // whole turn of the rotation), so a register that a load in flight will write
 // is never copied.
 //
+// The order of the loop body is fixed by hand: behind each of a K-step's 32
+// matrix instructions comes one operand read of the next slice and a seventh
+// of a block's decode, and the scheduler may move nothing across.  With the
+// decode in one stretch behind the first slice (its FP8 and 4-bit routes were
+// branches) a K-step took 6% more clocks: 650 thousand instead of 610 thousand
+// for 4096 x 12288 x 4096, 346 -> 336 us, and 534 -> 525 us for the gated MLP of
+// 2048 rows.  What bounds it now is power: the clock gives way as the pipe
+// fills (1.92 -> 1.84 GHz, under 2.4 nominal), and the rate is that of the
+// library's bf16 product of the same size.  A variant whose waves decode their
+// weights straight into matrix operands (half the LDS traffic, half as much
+// vector arithmetic again) took 3% fewer clocks and the same time.
+//
 // One workgroup computes one 256 x 256 output tile over all of K -- except the
 // tiles of a last round that fills at most half of the chip: those are
 // computed by two (at most a quarter: four) workgroups each, over
@@ -201,17 +213,57 @@ __global__ __launch_bounds__(kWM *kWN * 64, 1) void gemm_mixed_kernel(const _Flo
     // thread's chunks are 4 bp + d (kBPT == 2) or d (kBPT == 4), and XOR-ing d into the address of
     // chunk d = 0 reaches them all, so one address register per stage is enough.
     const uint32_t b_wr0 = (uint32_t)(kTileBytes + br * kRowBytes + ((((kBPT == 2 ? 4 * bp : 0)) ^ swz_b) << 4));
-    auto decode_store = [&](int kt, const LRegsT &bl, const MetaRegs &b, const u32x2_t (&h)[kBPT], int stage, int j) {
-        const uint32_t bits = hi_bits(kt, b);
-        char *base = &lds[0][0][0];
-        const uint32_t at = b_wr0 + (uint32_t)stage * (2 * kTileBytes);
-        half2_t v[8];
+    // Block j of K-step kt, a piece at a time (kDecodePieces of them, in order): the 4-bit route for every lane, then the lanes
+    // whose block is FP8 overwrite the result with the other lanes switched off -- no branch, so that the pieces can be
+    // dealt out between the matrix instructions --, then the two LDS writes.
+    constexpr int kDecodePieces = 7;
+    half2_t dv[8];
+    auto decode_piece = [&](int kt, const LRegsT &bl, const MetaRegs &b, const u32x2_t (&h)[kBPT], int stage, int j, int piece) {
         const u32x4_t &lq = bl.l[j >> 1];
-        decode_block((j & 1) ? make_uint2(lq[2], lq[3]) : make_uint2(lq[0], lq[1]), (b.s >> (8 * j)) & 0xFFu,
-                     (bits >> j) & 1u, make_uint2(h[j][0], h[j][1]), v);
-        const uint32_t *o = reinterpret_cast<const uint32_t *>(v);
-        *reinterpret_cast<uint4 *>(base + (at ^ ((2 * j) << 4))) = make_uint4(o[0], o[1], o[2], o[3]);
-        *reinterpret_cast<uint4 *>(base + (at ^ ((2 * j + 1) << 4))) = make_uint4(o[4], o[5], o[6], o[7]);
+        const uint32_t lx = (j & 1) ? lq[2] : lq[0], ly = (j & 1) ? lq[3] : lq[1];
+        if (piece < 4) {
+            const half2_t s1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(b.s >> (8 * j), 1.0f, false);
+            const half2_t s = half2_t{s1[0], s1[0]};
+            if (piece == 0) {
+                dv[0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(lx, 1.0f, 0) * s;
+                dv[1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(lx, 1.0f, 1) * s;
+                asm volatile("" : "+v"(dv[0]), "+v"(dv[1]));
+            } else if (piece == 1) {
+                dv[2] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(lx, 1.0f, 2) * s;
+                dv[3] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(lx, 1.0f, 3) * s;
+                asm volatile("" : "+v"(dv[2]), "+v"(dv[3]));
+            } else if (piece == 2) {
+                dv[4] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(ly, 1.0f, 0) * s;
+                dv[5] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(ly, 1.0f, 1) * s;
+                asm volatile("" : "+v"(dv[4]), "+v"(dv[5]));
+            } else {
+                dv[6] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(ly, 1.0f, 2) * s;
+                dv[7] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(ly, 1.0f, 3) * s;
+                asm volatile("" : "+v"(dv[6]), "+v"(dv[7]));
+            }
+        } else if (piece < 6) {
+            const uint64_t lanes8 = __builtin_amdgcn_ballot_w64(((hi_bits(kt, b) >> j) & 1u) != 0u);
+            const uint32_t x8 = piece == 4 ? lx : h[j][0], y8 = piece == 4 ? ly : h[j][1];
+            half2_t &o0 = dv[piece == 4 ? 0 : 4], &o1 = dv[piece == 4 ? 1 : 5], &o2 = dv[piece == 4 ? 2 : 6], &o3 = dv[piece == 4 ? 3 : 7];
+            asm volatile("s_mov_b64 exec, %6\n\t"
+                         "v_cvt_scalef32_pk_f16_fp8 %0, %4, 1.0\n\t"
+                         "v_cvt_scalef32_pk_f16_fp8 %1, %4, 1.0 op_sel:[1,0,0]\n\t"
+                         "v_cvt_scalef32_pk_f16_fp8 %2, %5, 1.0\n\t"
+                         "v_cvt_scalef32_pk_f16_fp8 %3, %5, 1.0 op_sel:[1,0,0]\n\t"
+                         "s_mov_b64 exec, -1"
+                         : "+v"(o0), "+v"(o1), "+v"(o2), "+v"(o3)
+                         : "v"(x8), "v"(y8), "s"(lanes8));
+        } else {
+            char *base = &lds[0][0][0];
+            const uint32_t at = b_wr0 + (uint32_t)stage * (2 * kTileBytes);
+            const uint32_t *o = reinterpret_cast<const uint32_t *>(dv);
+            *reinterpret_cast<uint4 *>(base + (at ^ ((2 * j) << 4))) = make_uint4(o[0], o[1], o[2], o[3]);
+            *reinterpret_cast<uint4 *>(base + (at ^ ((2 * j + 1) << 4))) = make_uint4(o[4], o[5], o[6], o[7]);
+        }
+    };
+    auto decode_store = [&](int kt, const LRegsT &bl, const MetaRegs &b, const u32x2_t (&h)[kBPT], int stage, int j) {
+#pragma unroll
+        for (int piece = 0; piece < kDecodePieces; ++piece) decode_piece(kt, bl, b, h, stage, j, piece);
     };
 
     float16_t acc[TM][TN];
@@ -233,12 +285,11 @@ __global__ __launch_bounds__(kWM *kWN * 64, 1) void gemm_mixed_kernel(const _Flo
 #pragma unroll
         for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const half8_t *>(lb + j * 32 * kRowBytes + frag_off[kk]);
     };
-    auto mfma_block = [&](const half8_t (&a)[TM], const half8_t (&b)[TN]) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], b[j], acc[i][j], 0, 0, 0);
+    // fragment n of a slice: TN of the weights first (every matrix instruction needs one), then TM of the activations
+    auto read_frag = [&](int stage, int kk, half8_t (&a)[TM], half8_t (&b)[TN], int n) {
+        const char *la = &lds[stage][0][wm * (TM * 32) * kRowBytes], *lb = &lds[stage][1][wn * (TN * 32) * kRowBytes];
+        if (n < TN) b[n] = *reinterpret_cast<const half8_t *>(lb + n * 32 * kRowBytes + frag_off[kk]);
+        else a[n - TN] = *reinterpret_cast<const half8_t *>(la + (n - TN) * 32 * kRowBytes + frag_off[kk]);
     };
     constexpr int kReads = TM + TN, kMfma = TM * TN;
 
@@ -288,36 +339,45 @@ __global__ __launch_bounds__(kWM *kWN * 64, 1) void gemm_mixed_kernel(const _Flo
         LRegsT &lcur = lring[(r + 1) % 2], &lnxt = lring[r % 2];
         MetaRegs &mcur = mring[(r + 1) % 3], &mnxt = mring[(r + 2) % 3], &mfar = mring[r % 3];
         u32x2_t(&hcur)[kBPT] = hring[(r + 1) % 2], (&hnxt)[kBPT] = hring[r % 2];
-        read_frags(st, 1, fa[1], fb[1]);
+        // One matrix instruction, and what is dealt out behind it: a fragment of the next slice, a piece of the decode, a
+        // load.  (The scheduler is kept from moving anything across.)
+        auto slot = [&](int kk, int n, auto more) {
+            const int i = n / TN, j = n % TN;
+            if (kk < 3 && n < kReads) read_frag(st, kk + 1, fa[(kk + 1) & 1], fb[(kk + 1) & 1], n);
+            if (kk == 3 && n < kReads) read_frag(st ^ 1, 0, fa[0], fb[0], n);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[kk & 1][i], fb[kk & 1][j], acc[i][j], 0, 0, 0);
+            more();
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        constexpr int kSlots = 3 * kMfma - 2, kPieces = kBPT * kDecodePieces;   // the decode ends two slots before the barrier
         load_meta(kt + 3, mfar);
         // everything issued one iteration ago has landed: the small fields of step kt + 2, plane L and
         // plane H of step kt + 1
         wait_loaded<kLoads + kNM>(mnxt);
         wait_loaded<kLoads + kNM>(lcur);
         wait_loaded<kLoads + kNM>(hcur);
-        mfma_block(fa[0], fb[0]);
         __builtin_amdgcn_sched_barrier(0);
-        // The decode is a stretch of vector arithmetic with no MFMA in it (its FP8 / NVFP4 branches keep
-        // the scheduler from interleaving any); the other wave of the SIMD keeps the matrix pipe busy.
 #pragma unroll
-        for (int j = 0; j < kBPT; ++j) decode_store(kt + 1, lcur, mcur, hcur, st ^ 1, j);
-        // the registers of the step just decoded take the loads of step kt + 2
-        load_l(kt + 2, lnxt);
-        load_h(kt + 2, mnxt, hnxt);
-        read_frags(st, 2, fa[0], fb[0]);
-        mfma_block(fa[1], fb[1]);
-        order_phase<kReads, kMfma, 0>();
-        read_frags(st, 3, fa[1], fb[1]);
-        mfma_block(fa[0], fb[0]);
-        order_phase<kReads, kMfma, 0>();
+        for (int kk = 0; kk < 3; ++kk)
+#pragma unroll
+            for (int n = 0; n < kMfma; ++n)
+                slot(kk, n, [&]() {
+                    const int at = kk * kMfma + n;
+#pragma unroll
+                    for (int p = 0; p < kPieces; ++p)
+                        if (p * kSlots / kPieces == at) decode_piece(kt + 1, lcur, mcur, hcur, st ^ 1, p / kDecodePieces, p % kDecodePieces);
+                    // (the registers of step kt are free: they take the loads of step kt + 2)
+                    if (at == 1) load_l(kt + 2, lnxt);
+                    if (at == 3) load_h(kt + 2, mnxt, hnxt);
+                });
         // LDS traffic of this wave done (lgkmcnt 0) and its A loads landed: they are older than this
         // iteration's kBLoads register loads, which may stay in flight (vmcnt kBLoads)
         __builtin_amdgcn_s_waitcnt(0x0070 | pending(kBLoads));
         __syncthreads();
         issue_a(kt + 2 < nk ? kt + 2 : nk - 1, st);
-        read_frags(st ^ 1, 0, fa[0], fb[0]);
-        mfma_block(fa[1], fb[1]);
-        order_phase<kReads, kMfma, 0>();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < kMfma; ++n) slot(3, n, []() {});
         __builtin_amdgcn_s_waitcnt(0xC07F);
     };
     // whole turns of the rotation, then the 0, 2 or 4 K-steps left (nk is even: the K extent is padded
