@@ -260,7 +260,7 @@ fgmp_status_t fgmp_quant_gemm_fused_packed_out_ex(const void *X, fgmp_dtype_t dt
  * sum_i F_i (w_i - Q_s(w_i))^2 (the smallest such code if several tie) instead of the dynamic-max
  * scale; the block's score (Eq. 6) and the FP8/FP4 decision then use that scale.  Everything else as
  * fgmp_quantize_weights.
- *   workspace  device scratch, at least N*K/16 bytes (the chosen scale codes); contents undefined after
+ *   workspace  device scratch, at least N*K/16 bytes; contents undefined after
  * Errors: as fgmp_quantize_weights; FGMP_ERR_BUFFER_TOO_SMALL for the workspace.
  */
 fgmp_status_t fgmp_quantize_weights_clip(const void *W, fgmp_dtype_t dt, int64_t N, int64_t K, int64_t ldw,

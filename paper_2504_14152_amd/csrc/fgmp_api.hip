@@ -177,7 +177,7 @@ fgmp_status_t fgmp_quantize_weights_clip(const void *W, fgmp_dtype_t dt, int64_t
     if (workspace_bytes < (size_t)(N * (K / kBlock))) return FGMP_ERR_BUFFER_TOO_SMALL;
     return quantize_tensor(W, dt, N, K, ldw, fisher, ld_fisher, threshold, tensor_scale, packed_W,
                            packed_bytes, scores_out, /*compact=*/true, as_stream(stream), nullptr, 0, nullptr, 0,
-                           FGMP_SCORE_NVFP4_ERROR, static_cast<uint8_t *>(workspace));
+                           FGMP_SCORE_NVFP4_ERROR, /*clip=*/true);
 }
 
 fgmp_status_t fgmp_unpack_canonical(const void *packed, int64_t rows, int64_t K, uint8_t *codes,

@@ -36,7 +36,6 @@ struct QuantParams {
     uint32_t *zero;        // words cleared by the first workgroup (counters of the kernel that follows)
     int zero_n;
     bool delta;            // Eq. 8 scoring (see quantize_kernel)
-    const uint8_t *sc_override;   // block scale codes chosen beforehand (clipping), [rows][nb]; or nullptr: dynamic max
 };
 
 // kModeCompact leaves planes T and H to pack_upper_halves_kernel.
@@ -78,6 +77,45 @@ __device__ __forceinline__ void widen(const RawBlock<float> &r, float (&x)[16])
         x[4 * i + 0] = u2f(r.v[i].x); x[4 * i + 1] = u2f(r.v[i].y);
         x[4 * i + 2] = u2f(r.v[i].z); x[4 * i + 3] = u2f(r.v[i].w);
     }
+}
+
+// The planes of one tile, a slot per lane: plane M and the slots' plane-L words and plane-S bytes; in strided mode also planes
+// T and H.  hi: the block is kept in FP8 (ballot: of all lanes).
+template <bool kHW, int kMode, bool kDelta>
+__device__ __forceinline__ void store_tile(const QuantParams &p, int64_t tile, int lane, bool hi, uint64_t ballot, const BlockCodes &bc,
+                                           const float (&x)[16], float amax, float inv_S)
+{
+                const uint32_t prefix = (uint32_t)__popcll(ballot & ((1ull << lane) - 1ull));
+                const uint32_t hbase = (uint32_t)(tile * kTileSlots);
+                if constexpr (kMode == kModeStrided) {
+                    if (lane == 0) p.out.T[tile] = hbase;
+                }
+                if (lane == 0) p.out.M[tile] = ballot;
+
+                uint2 lword = make_uint2(bc.q[0], bc.q[1]);
+                uint32_t sbyte = bc.sc;
+                if (ballot != 0ull) {
+                    // values beyond the FP8 range only occur when the caller's S is below amax / 448
+                    const bool any_big = __ballot(hi && amax * inv_S > 448.0f) != 0ull;
+                    if (hi) {
+                        uint32_t c[4];
+                        if constexpr (kDelta) {
+    #pragma unroll
+                            for (int j = 0; j < 4; ++j) c[j] = bc.c8[j];
+                        } else {
+                            float r[16];
+    #pragma unroll
+                            for (int i = 0; i < 16; ++i) r[i] = x[i] * inv_S;
+                            if (any_big) encode_fp8_block<kHW, true>(r, c);
+                            else encode_fp8_block<kHW, false>(r, c);
+                        }
+                        lword = make_uint2(c[0], c[1]);
+                        if constexpr (kMode == kModeStrided) p.out.H[(uint64_t)hbase + prefix] = make_uint2(c[2], c[3]);
+                        sbyte = prefix;
+                    }
+                }
+                p.out.L[tile * kTileSlots + lane] = lword;
+                p.out.S[tile * kTileSlots + lane] = (uint8_t)sbyte;
 }
 
 // grid.x = K-tiles, grid.y = groups of 4 * rt_per_wave row-tiles; 4 waves per
@@ -141,16 +179,14 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantParams p)
             }
         }
 
-        // block scale (dynamic max, or chosen beforehand), NVFP4 codes, score; in the Eq. 8 mode also the
+        // block scale (dynamic max), NVFP4 codes, score; in the Eq. 8 mode also the
         // FP8 codes of every block (values beyond the FP8 range only occur when the caller's S is below
         // amax / 448: then the wave clamps before converting)
         const float amax = block_amax(x);
         bool clamp8 = false;
         if constexpr (kDelta) clamp8 = __ballot(amax * inv_S > 448.0f) != 0ull;
-        int sc_given = -1;
-        if (p.sc_override != nullptr) sc_given = valid ? (int)p.sc_override[row * p.nb + kb] : 0;
         BlockCodes bc;
-        quantize_block_math<kHW, kDelta>(x, f, amax, p.S, inv_S, S6, sc_given, clamp8, bc);
+        quantize_block_math<kHW, kDelta>(x, f, amax, p.S, inv_S, S6, -1, clamp8, bc);
         const uint32_t sc = bc.sc;
         const uint32_t (&q)[2] = bc.q;
         const uint32_t (&c8)[4] = bc.c8;
@@ -201,37 +237,7 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantParams p)
             dst[0] = pack.v[0];
             dst[1] = pack.v[1];
         } else {
-            const uint32_t prefix = (uint32_t)__popcll(ballot & ((1ull << lane) - 1ull));
-            const uint32_t hbase = (uint32_t)(tile * kTileSlots);
-            if constexpr (kMode == kModeStrided) {
-                if (lane == 0) p.out.T[tile] = hbase;
-            }
-            if (lane == 0) p.out.M[tile] = ballot;
-
-            uint2 lword = make_uint2(q[0], q[1]);
-            uint32_t sbyte = sc;
-            if (ballot != 0ull) {
-                // values beyond the FP8 range only occur when the caller's S is below amax / 448
-                const bool any_big = __ballot(hi && amax * inv_S > 448.0f) != 0ull;
-                if (hi) {
-                    uint32_t c[4];
-                    if constexpr (kDelta) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) c[j] = c8[j];
-                    } else {
-                        float r[16];
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) r[i] = x[i] * inv_S;
-                        if (any_big) encode_fp8_block<kHW, true>(r, c);
-                        else encode_fp8_block<kHW, false>(r, c);
-                    }
-                    lword = make_uint2(c[0], c[1]);
-                    if constexpr (kMode == kModeStrided) p.out.H[(uint64_t)hbase + prefix] = make_uint2(c[2], c[3]);
-                    sbyte = prefix;
-                }
-            }
-            p.out.L[tile * kTileSlots + lane] = lword;
-            p.out.S[tile * kTileSlots + lane] = (uint8_t)sbyte;
+            store_tile<kHW, kMode, kDelta>(p, tile, lane, hi, ballot, bc, x, amax, inv_S);
         }
     };
 
@@ -561,43 +567,58 @@ __device__ __forceinline__ float nvfp4_error(const float (&x)[16], const float (
 }
 
 // Sensitivity-weighted clipping (Sec. 3.3, Eq. 11): for every block, the E4M3 scale code (0 .. 0x7E)
-// whose NVFP4 quantization has the smallest weighted error; candidates in ascending order, a later candidate
-// wins only with a strictly smaller error.  One block per lane; the error of a candidate is computed exactly as
-// quantize_kernel computes a block's score.  Offline (weights); bound: vector ALU (a candidate costs 112 vector
-// instructions), so what counts is how few candidates are tried.
+// whose NVFP4 quantization has the smallest weighted error, the smallest code among equal errors, and the first pass of
+// packing (compact) under the scales found.  One wave per tile, one block per lane; the error of a candidate is computed
+// exactly as quantize_kernel computes a block's score.  Offline (weights); bound: vector ALU (a candidate costs 112 vector
+// instructions, 16 of them conversions at half rate), so what counts is how few candidates are tried.
 //
 // A candidate whose error is certain to exceed B, the smaller one of the errors under code 0 and under the dynamic-max
 // code, cannot be the answer.  An error is a sum of non-negative terms added in FP32, so it is at least each of them:
 //   too small a scale clips element i to 6 d: its term is at least F_i (|x_i| - 6 d)^2 > B where
 //     6 d < |x_i| - sqrt(B / F_i);
-//   too large a scale rounds element i to zero (|x_i| < d / 4): its term is F_i x_i^2, exactly as computed here.
-// The bounds are taken 1e-5 wide of these, the rounding errors of a term being below 1e-6, and one code wide on top.
-// Where the argument needs more than that (negative or non-finite sensitivities, errors or scales near the ends of the
-// FP32 range) every code is tried.  Of 127 candidates 21 are left per block on N(0, 0.02^2) weights with lognormal
-// sensitivities, 34 for the slowest of a wave's 64 blocks.  12288 x 4096, per-element
-// sensitivities: 385 us, 1210 us when all were tried (with one division and one decode of the scale per candidate).
+//   too large a scale rounds element i to zero (|x_i| < d / 4): its term is F_i x_i^2, exactly as computed here; the sum of
+//     these terms only grows with d, so four steps of bisection move the end of the range by up to 15 codes.
+// The bounds are taken 1e-5 wide of these (the sum 1e-4), the rounding errors of a term being below 1e-6, and one code wide
+// on top.  Where the argument needs more than that (negative or non-finite sensitivities, errors or scales near the ends of
+// the FP32 range) every code is tried.
+//
+// The ranges of a wave's 64 blocks differ: on N(0, 0.02^2) weights with lognormal sensitivities 20 codes are left on
+// average, 33 for the longest.  Lanes therefore try the mean number each, and what is left of the longer ranges is dealt out
+// in equal pieces, the blocks going through LDS: 25 rounds instead of 33.
+// 12288 x 4096 bf16, per-element sensitivities, the whole call: 1427 us with all 127 codes tried (and one division and one decode
+// of the scale per candidate), 454 with the single-element bounds, 401 with the ranges dealt out, 328 with the packing
+// pass done here (it read W and the sensitivities again, 65 us), 305 with the bisection.
 template <typename Tin, bool kPerElem, bool kHW>
-__global__ __launch_bounds__(256) void clip_scales_kernel(QuantParams p, uint8_t *sc_out)
+__global__ __launch_bounds__(256) void clip_kernel(QuantParams p)
 {
+    constexpr int kStride = 36;   // floats per block in LDS: 16-byte pieces of neighbouring blocks in different banks
     __shared__ float2 tbl[128];   // {d, 1 / d} by scale code
+    __shared__ __attribute__((aligned(16))) float blocks[4][64 * kStride];
+    __shared__ uint64_t answer[4][64];
+    __shared__ uint32_t pieces[4][64];
     if (threadIdx.x < 128) {
         const float d = e4m3_decode_int(threadIdx.x) * p.S;
         tbl[threadIdx.x] = make_float2(d, threadIdx.x != 0 ? 1.0f / d : 0.0f);
     }
     __syncthreads();
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t kt = blockIdx.x;
     const int64_t kb = kt * kTileBlocks + (lane & 7);
     const int64_t rt = (int64_t)blockIdx.y * 4 + wave;
     const int64_t row = rt * kTileRows + (lane >> 3);
-    if (rt >= p.n_rt || kb >= p.nb || row >= p.rows) return;
-    const Tin *X = static_cast<const Tin *>(p.X);
-    RawBlock<Tin> raw;
-    load_raw(X + row * p.ldx + kb * kBlock, raw);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) write_header(p.out.hdr, p.layout, p.S, p.compact);
+    if (rt >= p.n_rt) return;
+    const bool inside = kb < p.nb && row < p.rows;
     float x[16], f[16];
-    widen(raw, x);
-    load16(p.fisher + (kPerElem ? row * p.ld_fisher : 0) + kb * kBlock, f);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = f[i] = 0.0f;
+    if (inside) {
+        RawBlock<Tin> raw;
+        load_raw(static_cast<const Tin *>(p.X) + row * p.ldx + kb * kBlock, raw);
+        widen(raw, x);
+        load16(p.fisher + (kPerElem ? row * p.ld_fisher : 0) + kb * kBlock, f);
+    }
 
     const float amax = block_amax(x);
     const float inv_S = 1.0f / p.S, S6 = 6.0f * p.S;
@@ -612,7 +633,14 @@ __global__ __launch_bounds__(256) void clip_scales_kernel(QuantParams p, uint8_t
         }
     };
     uint32_t best = 0u;
-    float best_err = error_with(0u);
+    float lost[16], sum[16];   // the error under code 0: every element is lost
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum[i] = lost[i] = (x[i] * x[i]) * f[i];
+#pragma unroll
+    for (int w = 16; w > 1; w >>= 1)
+#pragma unroll
+        for (int i = 0; i < w / 2; ++i) sum[i] = sum[2 * i] + sum[2 * i + 1];
+    float best_err = sum[0];
     uint32_t first = 1u, last = 0x7Eu;
     const float bound = fminf(best_err, error_with(enc_e4m3<kHW>(amax / S6)));
     float f_min = f[0], f_max = f[0], f_sum = 0.0f;
@@ -623,8 +651,10 @@ __global__ __launch_bounds__(256) void clip_scales_kernel(QuantParams p, uint8_t
         f_sum += f[i];   // (minimum and maximum skip a NaN)
     }
     // (B / F_i >= 1e-30: the clipped element's error and its square are ordinary numbers)
-    if (bound > 1e-35f && bound > 1e-30f * f_max && bound < 1e25f && f_min >= 0.0f && f_max < 1e30f && f_sum == f_sum && amax < 1e15f &&
-        p.S > 1e-20f && p.S < 1e20f) {
+    const bool nothing_less = best_err == 0.0f && f_min >= 0.0f && f_sum == f_sum;   // (a block of zeros)
+    const bool bounded = bound > 1e-35f && bound > 1e-30f * f_max && bound < 1e25f && f_min >= 0.0f && f_max < 1e30f && f_sum == f_sum &&
+                         amax < 1e15f && p.S > 1e-20f && p.S < 1e20f;
+    if (bounded) {
         float d_low = 0.0f, d_high = 4.0f * amax;   // (beyond: all zeros, the error of code 0)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -632,21 +662,109 @@ __global__ __launch_bounds__(256) void clip_scales_kernel(QuantParams p, uint8_t
             // (a vanishing sensitivity gives an infinite root, and no bound)
             const float root = __builtin_amdgcn_sqrtf(bound * __builtin_amdgcn_rcpf(f[i]));
             d_low = fmaxf(d_low, (ax * 0.99999f - root * 1.00001f) * (1.0f / 6.0f));
-            if ((ax * ax) * f[i] > bound) d_high = fminf(d_high, 4.0f * ax);
+            if (lost[i] > bound) d_high = fminf(d_high, 4.0f * ax);
         }
         const uint32_t low = enc_e4m3<kHW>(fminf(d_low * 0.99999f * inv_S, 448.0f)), high = enc_e4m3<kHW>(fminf(d_high * 1.00001f * inv_S, 448.0f));
         first = low > 2u ? low - 1u : 1u;
         last = high < 0x7Du ? high + 1u : 0x7Eu;
-    }
-#pragma unroll 1
-    for (uint32_t sc = first; sc <= last; ++sc) {
-        const float err = error_with(sc);
-        if (err < best_err) {
-            best_err = err;
-            best = sc;
+        // all the elements that are rounded to zero together
+#pragma unroll
+        for (uint32_t step = 8u; step > 0u; step >>= 1) {
+            const uint32_t sc = last > step ? last - step + 1u : 1u;
+            const float d4 = tbl[sc].x * 0.24999f;
+            float err = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) err += fabsf(x[i]) < d4 ? lost[i] : 0.0f;
+            if (err * 0.9999f > bound) last = sc - 1u;
         }
     }
-    sc_out[row * p.nb + kb] = (uint8_t)best;
+    if (!inside || nothing_less) last = 0u;
+    // codes [from, to] of the block in x, f
+    auto search = [&](uint32_t from, uint32_t to) {
+#pragma unroll 1
+        for (uint32_t sc = from; sc <= to; ++sc) {
+            const float err = error_with(sc);
+            if (err < best_err) {
+                best_err = err;
+                best = sc;
+            }
+        }
+    };
+    if (__ballot(inside && !bounded && !nothing_less) != 0ull) {
+        search(first, last);
+    } else {
+        // A lane tries up to `own` codes of its block.  What is left of the longer ranges is cut in pieces of `rest` codes,
+        // at most one for each lane: blocks with something left number n < 64 (own is at least the mean), and rounding up
+        // to whole pieces adds less than one piece to each, so rest >= left / (64 - n) is enough.
+        auto wave_sum = [](uint32_t v) {
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
+            return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+        };
+        const uint32_t width = last >= first ? last - first + 1u : 0u;
+        const uint32_t own = (wave_sum(width) + 63u) / 64u;
+        const uint32_t left = width > own ? width - own : 0u;
+        const uint64_t longer = __ballot(left != 0u);
+        search(first, left != 0u ? first + own - 1u : last);
+        if (longer != 0ull) {
+            const uint32_t spare = 64u - (uint32_t)__popcll(longer);
+            const uint32_t rest = (wave_sum(left) + spare - 1u) / spare;
+            const uint32_t n_pieces = (left + rest - 1u) / rest;
+            uint32_t at = n_pieces;   // inclusive prefix sum
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t v = __shfl_up(at, d);
+                at += lane >= d ? v : 0u;
+            }
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)at, 63);
+            at -= n_pieces;
+            // errors are sums of non-negative numbers here: their bit patterns order them, the code decides between equal ones
+            auto key = [&]() { return ((uint64_t)__builtin_bit_cast(uint32_t, best_err) << 32) | best; };
+            float4 *mine = reinterpret_cast<float4 *>(&blocks[wave][lane * kStride]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                mine[i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
+                mine[4 + i] = make_float4(f[4 * i], f[4 * i + 1], f[4 * i + 2], f[4 * i + 3]);
+            }
+            answer[wave][lane] = key();
+            for (uint32_t k = 0; k < n_pieces; ++k) {
+                const uint32_t from = first + own + k * rest, to = from + rest - 1u < last ? from + rest - 1u : last;
+                pieces[wave][at + k] = (uint32_t)lane | (from << 8) | (to << 16);
+            }
+            // (LDS of one wave: its accesses complete in order; nothing to wait for but the compiler)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if ((uint32_t)lane < total) {
+                const uint32_t piece = pieces[wave][lane];
+                const uint32_t from_lane = piece & 0xFFu;
+                const float4 *theirs = reinterpret_cast<const float4 *>(&blocks[wave][from_lane * kStride]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float4 vx = theirs[i], vf = theirs[4 + i];
+                    x[4 * i] = vx.x; x[4 * i + 1] = vx.y; x[4 * i + 2] = vx.z; x[4 * i + 3] = vx.w;
+                    f[4 * i] = vf.x; f[4 * i + 1] = vf.y; f[4 * i + 2] = vf.z; f[4 * i + 3] = vf.w;
+                }
+                best = 0xFFu;
+                best_err = __builtin_inff();
+                search((piece >> 8) & 0xFFu, piece >> 16);
+                atomicMin(reinterpret_cast<unsigned long long *>(&answer[wave][from_lane]), (unsigned long long)key());
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            best = (uint32_t)answer[wave][lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 vx = mine[i], vf = mine[4 + i];
+                x[4 * i] = vx.x; x[4 * i + 1] = vx.y; x[4 * i + 2] = vx.z; x[4 * i + 3] = vx.w;
+                f[4 * i] = vf.x; f[4 * i + 1] = vf.y; f[4 * i + 2] = vf.z; f[4 * i + 3] = vf.w;
+            }
+        }
+    }
+
+    // the block under the scale that was found, exactly as quantize_kernel writes it
+    BlockCodes bc;
+    quantize_block_math<kHW, false>(x, f, amax, p.S, inv_S, S6, (int)best, false, bc);
+    const bool hi = inside && bc.score > p.T;
+    if (p.scores != nullptr && inside) p.scores[row * p.nb + kb] = bc.score;
+    store_tile<kHW, kModeCompact, false>(p, rt * p.n_kt + kt, lane, hi, __ballot(hi), bc, x, amax, inv_S);
 }
 
 // Second and last pass of packing weights (compact): plane T -- the exclusive prefix sum over the tiles of
@@ -877,7 +995,7 @@ fgmp_status_t quantize_tensor(const void *X, fgmp_dtype_t dt, int64_t rows, int6
                               const float *fisher, int64_t ld_fisher, float T, float S, void *packed,
                               size_t packed_bytes, float *scores, bool compact, hipStream_t st,
                               _Float16 *x16, int64_t ld16, uint32_t *zero, int64_t zero_n, int score_mode,
-                              uint8_t *clip_scales)
+                              bool clip)
 {
     if (score_mode != FGMP_SCORE_NVFP4_ERROR && score_mode != FGMP_SCORE_DELTA) return FGMP_ERR_INVALID_ARG;
     if (!X || !fisher || (!packed && !x16)) return FGMP_ERR_INVALID_ARG;
@@ -921,26 +1039,14 @@ fgmp_status_t quantize_tensor(const void *X, fgmp_dtype_t dt, int64_t rows, int6
     if (zero_n < 0 || zero_n > 0x7FFFFFFF || (zero_n > 0 && !zero)) return FGMP_ERR_INVALID_ARG;
     p.zero = zero; p.zero_n = (int)zero_n;
     p.delta = score_mode == FGMP_SCORE_DELTA;
-    p.sc_override = clip_scales;
-    if (clip_scales != nullptr) {
-        // clipping is defined with the NVFP4-error score; the scale search runs first, on the same stream
-        if (p.delta || x16 != nullptr) return FGMP_ERR_UNSUPPORTED;
-        const int64_t gy4 = (l.n_rt + 3) / 4;
-        if (gy4 > 65535) return FGMP_ERR_UNSUPPORTED;
-        const dim3 cgrid((unsigned)l.n_kt, (unsigned)gy4);
-        if (dt == FGMP_F32) {
-            if (per_elem) hipLaunchKernelGGL((clip_scales_kernel<float, true, kUseHwCvt>), cgrid, dim3(256), 0, st, p, clip_scales);
-            else hipLaunchKernelGGL((clip_scales_kernel<float, false, kUseHwCvt>), cgrid, dim3(256), 0, st, p, clip_scales);
-        } else {
-            if (per_elem) hipLaunchKernelGGL((clip_scales_kernel<uint16_t, true, kUseHwCvt>), cgrid, dim3(256), 0, st, p, clip_scales);
-            else hipLaunchKernelGGL((clip_scales_kernel<uint16_t, false, kUseHwCvt>), cgrid, dim3(256), 0, st, p, clip_scales);
-        }
-    }
+    // clipping is defined with the NVFP4-error score, for weights
+    const int64_t clip_gy = (l.n_rt + 3) / 4;
+    if (clip && (p.delta || !compact || clip_gy > 65535)) return FGMP_ERR_UNSUPPORTED;
     // The activation hot path (one pass, NVFP4-error score, one sensitivity per channel, dynamic-max
     // scales) runs on the trimmed kernel when its 32-bit offsets and its shortcut division apply.
     const uint64_t x_bytes = (uint64_t)rows * (uint64_t)ldx * (uint64_t)esz;
     // (offsets: the input plus one stride of the resident set past its end must stay below 2^32)
-    const bool fast = kUseHwCvt && !compact && !per_elem && clip_scales == nullptr &&
+    const bool fast = kUseHwCvt && !compact && !per_elem &&
                       x_bytes < 0x7FFFFF00ull && l.total_bytes < 0xFFFFFF00ull && S >= 1e-30f && S <= 1e30f &&
                       l.n_tiles >= kQMinTiles;
     if (fast) {
@@ -990,7 +1096,14 @@ fgmp_status_t quantize_tensor(const void *X, fgmp_dtype_t dt, int64_t rows, int6
         else launch_quantize<uint16_t>(p, per_elem, grid, st);
     } else {
         p.mode = kModeCompact;
-        if (dt == FGMP_F32) launch_quantize<float>(p, per_elem, grid, st);
+        const dim3 cgrid((unsigned)l.n_kt, (unsigned)clip_gy);
+        if (clip && dt == FGMP_F32) {
+            if (per_elem) hipLaunchKernelGGL((clip_kernel<float, true, kUseHwCvt>), cgrid, dim3(256), 0, st, p);
+            else hipLaunchKernelGGL((clip_kernel<float, false, kUseHwCvt>), cgrid, dim3(256), 0, st, p);
+        } else if (clip) {
+            if (per_elem) hipLaunchKernelGGL((clip_kernel<uint16_t, true, kUseHwCvt>), cgrid, dim3(256), 0, st, p);
+            else hipLaunchKernelGGL((clip_kernel<uint16_t, false, kUseHwCvt>), cgrid, dim3(256), 0, st, p);
+        } else if (dt == FGMP_F32) launch_quantize<float>(p, per_elem, grid, st);
         else launch_quantize<uint16_t>(p, per_elem, grid, st);
         const int64_t waves = (int64_t)kPackWgs * kPackWaves;
         const uint32_t tiles_per_wave = (uint32_t)((l.n_tiles + waves - 1) / waves);

@@ -127,7 +127,7 @@ def test_static_scratch_takes_products_of_more_than_32_rows():
 
 # ------------------------------------------------------------------ clipping: the candidates that are left out
 
-@pytest.mark.parametrize("what", ["ordinary", "heavy tails", "sparse sensitivities", "huge range", "negative", "tiny", "small scale", "large scale"])
+@pytest.mark.parametrize("what", ["ordinary", "heavy tails", "sparse sensitivities", "huge range", "negative", "tiny", "small scale", "large scale", "uneven"])
 def test_clipped_scales_are_the_brute_force_ones(what):
     """The kernel tries only the codes whose error can be the smallest; the oracle tries all 127."""
     rng = synth.rng_for(33, len(what))
@@ -152,6 +152,10 @@ def test_clipped_scales_are_the_brute_force_ones(what):
         scale = 1.0 / 64.0                          # blocks beyond the largest code
     elif what == "large scale":
         scale = 300.0                               # every block among the first few codes
+    elif what == "uneven":                          # a wave's ranges from empty (zeros) over a few codes to most of them
+        f = np.exp(np.repeat(rng.uniform(0.0, 4.0, (N, K // 16)), 16, axis=1) * rng.standard_normal((N, K))).astype(np.float32)
+        w *= np.repeat(rng.random((N, K // 16)) < 0.8, 16, axis=1)
+        w[:, 64:80] *= np.arange(16) == 5           # one element each
     S = float(synth.default_tensor_scale(w)) * scale
     want = orc.quantize(w, f, float("inf"), S, clip=True)
     pk, scores = fgmp.quantize_weights_clip(torch.from_numpy(w).to(DEV), torch.from_numpy(f).to(DEV), float("inf"), S, want_scores=True)
