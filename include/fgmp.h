@@ -239,8 +239,9 @@ fgmp_status_t fgmp_quant_gemm_fused_packed_out(const void *X, fgmp_dtype_t dt, i
  * - n * (ln 2 - 0.693359375) and p the degree-7 Taylor polynomial of e^r by Horner's rule;
  * h = (g / (1 + E(-g))) * u with a correctly rounded division (within 3 ulp of the exact value).
  * `epilogue | FGMP_EPILOGUE_ONE_LAUNCH` (with FGMP_EPILOGUE_NONE): a decode step quantizes its results
- * inside its launch whenever the one-launch kernel handles the shape (nothing is staged; a single kernel
- * per layer for callers who count launches); shapes that no quantizing epilogue covers are staged as before.
+ * inside its launch whenever the one-launch kernel takes the shape (nothing is staged; a single kernel
+ * per layer for callers who count launches); other shapes -- among them 20 to 32 rows of a long product,
+ * N K^2 >= 2^38 -- are staged.
  *   N          N % 64 == 0 with the gate; fisher_n, scores_y and packed_Y then refer to N/2 columns
  *   workspace  >= fgmp_workspace_bytes_packed_out_ex(M, N, K, epilogue)
  * Other arguments and errors as fgmp_quant_gemm_fused_packed_out; an unknown `epilogue` is

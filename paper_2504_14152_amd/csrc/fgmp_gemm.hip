@@ -263,27 +263,43 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
 // the prefill kernel, on both sides of the line: 4096 x 22016 (K x N) 256 rows 52 / 63, 512 rows 96 / 94; 4096 x 12288
 // 384 rows 44 / 62, 768 rows 83 / 92, 1024 rows 103 / 99; 11008 x 4096 512 rows 58 / 87, 1024 rows 93 / 114; 512 x 16384
 // 256 rows 16 / 43, 768 rows 38 / 28.
-constexpr int64_t kMidMinRows = 33, kMidMaxRows = 1024;
-static bool use_mid(int64_t M, int64_t N, int64_t K)
-{
-    if (!kUseHwCvt || !prefill_decodes_in_kernel() || M < kMidMinRows || M > kMidMaxRows || !gemm_mid_applies(M, N, K)) return false;
-    const double staging = 6.0 + 8.0 * (double)M * (double)N / 4.5e6;
-    return gemm_mid_micros(M, N, K) + staging <= gemm_mixed_micros(M, N, K);
-}
+//
+// Up to 32 rows the one-launch step (fgmp_gemm_stream.hip) shares K among as many workgroups as keep a part's rows in LDS --
+// 8 at K = 8192 and 32 rows -- and adds their sums in memory: from N K^2 = 2^38 (parts times weights) and 20 rows on, its
+// quantizer's launch is the cheaper price.  Microseconds per fused step, one launch / this kernel, on both sides: 11008 x 4096
+// 16 rows 18.1 / 15.8, 24 rows 20.1 / 17.2, 32 rows 18.2 / 17.2; 8192 x 4096 17 rows 14.9 / 15.5, 20 rows 16.2 / 15.6, 32 rows
+// 18.7 / 15.4; 4096 x 22016 24 rows 27.6 / 20.9, 32 rows 24.7 / 21.1; 8192 x 57344 17 rows 78 / 85, 20 rows 87 / 85, 32 rows 112 / 86;
+// 16384 x 2048 32 rows 23.9 / 16.5; 4096 x 12288 20 rows 16.9 / 16.4, 32 rows 16.1 / 16.7; 4096 x 4096 12.6 / 16.0;
+// 1024 x 32768 12.7 / 14.8.  (Only where it needs no more workspace than the step it replaces.)
+constexpr int64_t kMidMinRows = 20, kMidMaxRows = 1024;
 
-// their workspace behind the control region: header, FP16 activations, partial sums
+// its workspace behind the control region: header, FP16 activations, partial sums
 static size_t mid_x16_bytes(int64_t M, int64_t N, int64_t K)
 {
     return (size_t)align_up((uint64_t)gemm_mid_x16_rows(M, N, K) * round_up(K, kTileK) * 2, 256);
 }
 static size_t mid_bytes(int64_t M, int64_t N, int64_t K) { return (size_t)kHeaderBytes + mid_x16_bytes(M, N, K) + gemm_mid_scratch_bytes(M, N, K); }
 
+static size_t decode_bytes(int64_t M, int64_t N, int64_t K)
+{
+    return gemm_skinny_applies(M, N, K) ? skinny_x16_bytes(M, K) + gemm_skinny_workspace_bytes(M, N, K) : 0;
+}
+
+static bool use_mid(int64_t M, int64_t N, int64_t K)
+{
+    if (!kUseHwCvt || !prefill_decodes_in_kernel() || M < kMidMinRows || M > kMidMaxRows) return false;
+    if (M <= 32)
+        return (double)N * (double)K * (double)K >= 0x1p38 && gemm_mid_applies(M, N, K) &&
+               mid_bytes(M, N, K) <= (gemm_stream_applies(M, N, K) ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
+    const double staging = 6.0 + 8.0 * (double)M * (double)N / 4.5e6;
+    return gemm_mid_applies(M, N, K) && gemm_mid_micros(M, N, K) + staging <= gemm_mixed_micros(M, N, K);
+}
+
 // (all of these count the bytes behind the control region)
 size_t gemm_only_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
-    if (use_mid(M, N, K)) return mid_bytes(M, N, K);
-    const size_t other = gemm_skinny_applies(M, N, K) ? skinny_x16_bytes(M, K) + gemm_skinny_workspace_bytes(M, N, K)
-                                                      : gemm_ws_layout(M, N, K).total;
+    if (M > 32 && use_mid(M, N, K)) return mid_bytes(M, N, K);
+    const size_t other = gemm_skinny_applies(M, N, K) ? decode_bytes(M, N, K) : gemm_ws_layout(M, N, K).total;
     return std::max(other, gemm_stream_scratch_bytes(M, N, K));
 }
 
@@ -303,7 +319,7 @@ static size_t fused_prefill_split(const GemmWorkspace &w) { return (size_t)align
 size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K)
 {
     if (gemm_stream_applies(M, N, K)) return kWsCtrlRegion + gemm_stream_scratch_bytes(M, N, K);
-    if (use_mid(M, N, K)) return kWsCtrlRegion + mid_bytes(M, N, K);
+    if (M > 32 && use_mid(M, N, K)) return kWsCtrlRegion + mid_bytes(M, N, K);
     if (fused_prefill(M, N, K)) {
         const GemmWorkspace w = gemm_ws_layout(M, N, K);
         return kWsCtrlRegion + fused_prefill_split(w) + (w.total - w.off_split);
@@ -326,9 +342,10 @@ fgmp_status_t gemm_packed(const void *packed_X, int64_t M, const void *packed_W,
     const PackedView B = make_view(const_cast<void *>(packed_W), lb);
     void *const ctrl = workspace;
     workspace = static_cast<char *>(workspace) + kWsCtrlRegion + skip;
-    if (gemm_stream_applies(M, N, K))
+    const bool mid = use_mid(M, N, K);
+    if (!mid && gemm_stream_applies(M, N, K))
         return gemm_stream(2, nullptr, 0, nullptr, 0.0f, 1.0f, packed_X, M, packed_W, N, K, Y, ldy, ctrl, workspace, st);
-    if (use_mid(M, N, K)) {
+    if (mid) {
         const int64_t ld16 = round_up(K, kTileK);
         _Float16 *x16 = reinterpret_cast<_Float16 *>(static_cast<char *>(workspace) + kHeaderBytes);
         const fgmp_status_t rcx = launch_decode_f16(make_decode_job(A, la, x16, ld16, la.n_rt), nullptr, nullptr, 0, st);
@@ -389,11 +406,13 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
     if (((uintptr_t)workspace | (uintptr_t)packed_W | (uintptr_t)Y) % 16 != 0) return FGMP_ERR_BAD_ALIGN;
     // (the one-launch kernel addresses X with 32-bit byte offsets)
     const bool x_fits = ldx > 0 && ldx < (int64_t)0xFFFFFF00 / (M * 4);
-    // (the decode step quantizes its own results where the caller asks for it)
-    const bool stream_pack = pack_out != nullptr && !pack_out->gate && pack_out->one_launch && gemm_stream_packs(M, N, K);
-    const bool stream = score_mode == FGMP_SCORE_NVFP4_ERROR && (pack_out == nullptr || stream_pack) && x_fits && gemm_stream_applies(M, N, K);
-    const bool mid = !stream && use_mid(M, N, K);
-    if (workspace_bytes < (stream ? (pack_out ? kWsCtrlRegion + gemm_stream_pack_scratch_bytes(M, N, K) : quant_gemm_workspace_need(M, N, K))
+    const bool mid = use_mid(M, N, K);
+    // (the decode step quantizes its own results where the caller asks for it -- and where the plain call takes it, too: the
+    // packed results are the same bit for bit either way)
+    const bool stream_pack = pack_out != nullptr && !pack_out->gate && pack_out->one_launch && !mid && gemm_stream_packs(M, N, K);
+    const bool stream_fits = score_mode == FGMP_SCORE_NVFP4_ERROR && (pack_out == nullptr || stream_pack) && x_fits && gemm_stream_applies(M, N, K);
+    const bool stream = stream_fits && !mid;
+    if (workspace_bytes < (stream_fits ? (pack_out ? kWsCtrlRegion + gemm_stream_pack_scratch_bytes(M, N, K) : quant_gemm_workspace_need(M, N, K))
                                   : gemm_workspace_bytes(M, N, K)))
         return FGMP_ERR_BUFFER_TOO_SMALL;
     char *ws = static_cast<char *>(workspace) + kWsCtrlRegion;

@@ -52,7 +52,7 @@ def test_packed_weights_hold_the_same_blocks_as_the_one_pass_layout(rows, K, p):
     assert info["bytes_used"] == off_H + 8 * max(1, int(counts.sum()))
 
 
-# ------------------------------------------------------------------ products of 33 .. 1024 rows
+# ------------------------------------------------------------------ products of 20 .. 1024 rows
 
 def _product(M, K, N, dtype, p, seed):
     x = synth.activations(M, K, seed, 1)
@@ -74,11 +74,13 @@ def _product(M, K, N, dtype, p, seed):
 
 # (M, K, N): every row-group count of a tile (33 .. 128 rows); rows one past a tile; columns that end inside a lane
 # group, an odd number of 8-row weight tiles; K of one block, one K-tile, K groups without a K-tile in the last round,
-# K in several parts across workgroups; more tiles than compute units
+# K in several parts across workgroups; more tiles than compute units; long products of 20 to 32 rows and, with 19 rows or just
+# below N K^2 = 2^38, their neighbours in one launch
 MID_SHAPES = [(33, 16, 24, "f32", 0.1), (48, 128, 264, "bf16", 0.1), (64, 4096, 136, "bf16", 0.2), (77, 2064, 503, "f32", 0.2),
               (96, 640, 72, "bf16", 0.0), (112, 1168, 1000, "bf16", 1.0), (129, 384, 40, "f32", 0.3), (200, 8192, 200, "bf16", 0.1),
               (300, 1040, 264, "bf16", 0.1), (512, 2816, 328, "bf16", 0.1), (700, 144, 136, "bf16", 0.1), (1024, 272, 72, "f32", 0.1),
-              (40, 256, 34000, "bf16", 0.1)]
+              (40, 256, 34000, "bf16", 0.1), (20, 65536, 256, "bf16", 0.1), (19, 65536, 128, "bf16", 0.1), (32, 32768, 264, "f32", 0.1),
+              (32, 32768, 248, "f32", 0.1), (27, 11008, 2400, "bf16", 0.1)]
 
 
 @pytest.mark.parametrize("M,K,N,dtype,p", MID_SHAPES)
@@ -115,6 +117,22 @@ def test_products_between_decode_and_prefill_replay_in_a_graph():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(Y, want)
+
+
+def test_long_products_of_few_rows_quantize_the_results_of_the_plain_call():
+    M, K, N = 28, 16384, 2048
+    xd, fxd, Tx, sx, pW, _, _ = _product(M, K, N, "bf16", 0.1, 93)
+    Y = fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW)
+    f_n = torch.from_numpy(synth.fisher_per_channel(N, 93, 5)).to(DEV)
+    sy = float(Y.abs().max()) / 448.0
+    T_y = fgmp.threshold_for_fraction(fgmp.quantize_activations(Y, f_n, float("inf"), sy, want_scores=True)[1], 0.1)
+    want = fgmp.unpack_canonical(fgmp.quantize_activations(Y, f_n, T_y, sy))
+    for epilogue in (fgmp.EPILOGUE_NONE, fgmp.EPILOGUE_ONE_LAUNCH):
+        got = fgmp.unpack_canonical(fgmp.quant_gemm_fused_packed_out(xd, fxd, Tx, sx, pW, f_n, T_y, sy, epilogue=epilogue))
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+    got = torch.empty(M, N, device=DEV)
+    fgmp.quant_gemm_fused_static_scratch(xd, fxd, Tx, sx, pW, out=got)
+    assert torch.equal(got, Y)
 
 
 def test_static_scratch_takes_products_of_more_than_32_rows():
