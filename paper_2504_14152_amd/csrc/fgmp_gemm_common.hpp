@@ -31,6 +31,13 @@ __device__ __forceinline__ float4_t load_coherent16(__amdgpu_buffer_rsrc_t buf, 
     return __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)byte_off, 0, kCoherent));
 }
 
+// 16 bytes per lane from `base` + `voff` straight to the wave's 1 KB of LDS at byte address `lds`.  M0 carries that address;
+// between its write and the load the instruction set asks for one wait state.
+__device__ __forceinline__ void load_direct16(uint32_t lds, uint32_t voff, const void *base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+}
+
 // ---------------------------------------------------------------------------
 // packed -> FP16 decode
 // ---------------------------------------------------------------------------

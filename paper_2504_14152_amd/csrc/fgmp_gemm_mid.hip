@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
     auto issue_a = [&](int r, int stage, int i) {
         const char *base = x_wave + (int64_t)k_tile(r) * kRowB + i * x_step;
         const uint32_t dst = (uint32_t)(uintptr_t)(lds_void_t *)&lds[stage * kStage + wk * kGroupBytes + wn * 1024 + i * (WN * 1024)];
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(x_off[i & 1]), "s"(base) : "memory");
+        load_direct16(dst, x_off[i & 1], base);
     };
     // operand reads: row nl of a 16-row group, chunk 4 g + j
     const uint32_t f_lds = (uint32_t)(wk * kGroupBytes + nl * kRowB + (((4 * g) ^ swizzle(nl)) << 4));

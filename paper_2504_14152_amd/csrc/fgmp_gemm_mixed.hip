@@ -153,8 +153,7 @@ __global__ __launch_bounds__(kWM *kWN * 64, 1) void gemm_mixed_kernel(const _Flo
         for (int i = 0; i < kLoads; ++i) {
             // M0 carries the LDS address of the wave's 1 KB destination
             const uint32_t dst = (uint32_t)(uintptr_t)(lds_void_t *)&lds[stage][0][(kWaves * i + wave) * 1024];
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(a_off), "s"(base + i * a_step)
-                         : "memory");
+            load_direct16(dst, a_off, base + i * a_step);
         }
     };
 

@@ -166,7 +166,7 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_skinny_kernel(SkinnyArgs a)
         if (chunk < kSkMaxCols * (kTileK / 8) && r < x_load_rows) {
             const uint32_t dst = (uint32_t)(uintptr_t)(lds_void_t *)&xs[r][h * 512];   // M0: the wave's LDS destination
             const uint32_t voff = (uint32_t)(r * x_row_bytes + src_chunk * 16);
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff), "s"(xg) : "memory");
+            load_direct16(dst, voff, xg);
         }
     }
     __builtin_amdgcn_sched_barrier(0);   // keep these loads ahead of all others (see the barrier below)

@@ -94,6 +94,15 @@ def violations(ins, cyclic):
     return checked, bad
 
 
+def direct_loads_without_wait(lines) -> tuple[int, list]:
+    """(number of direct loads to LDS, those right behind the scalar instruction that writes M0).  M0 holds a direct load's
+    LDS address; the instruction set asks for one instruction or s_nop between the two, and the compiler does not look
+    inside inline assembly."""
+    ins = instructions(lines)
+    direct = [i for i, s in enumerate(ins) if re.match(r"(?:global|buffer|scratch)_load", s) and re.search(r"\blds\b|_lds_", s)]
+    return len(direct), [(ins[i - 1], ins[i]) for i in direct if re.match(r"s_\w+ m0,", ins[i - 1])]
+
+
 def check_kernel(lines, prefix) -> list[str]:
     """Problems found in one kernel of the listing (empty: none)."""
     problems = []
@@ -159,6 +168,8 @@ def check_mid(hipcc: str, flags: list[str], src: str) -> None:
     """Raise if any instantiation of gemm_mid_kernel, compiled as the build compiles it, has a hazard."""
     lines = make_listing(hipcc, flags, src)
     found = {n: p for n in mid_kernels(lines) for p in [check_mid_kernel(lines, n)] if p}
+    if direct_loads_without_wait(lines)[1]:
+        found["direct loads"] = direct_loads_without_wait(lines)[1]
     if found or not mid_kernels(lines):
         raise RuntimeError(f"gemm_mid_kernel listing check failed: {found}")
 
@@ -171,5 +182,7 @@ def check(hipcc: str, flags: list[str], src: str) -> None:
         p = check_kernel(lines, prefix)
         if p:
             found[name] = p
+    if direct_loads_without_wait(lines)[1]:
+        found["direct loads"] = direct_loads_without_wait(lines)[1]
     if found:
         raise RuntimeError(f"prefill kernel listing check failed: {found}")

@@ -126,3 +126,11 @@ def test_mid_kernel_full_wait_variant_counts_nothing():
         loop = lc.instructions(lc.k_loop(lc.kernel_body(lines, name)))
         waits = [int(m.group(1)) for s in loop for m in [re.match(r"s_waitcnt.*vmcnt\((\d+)\)", s)] if m]
         assert waits and max(waits) == 0, (name, waits)
+
+
+# ---- direct loads to LDS ----
+
+@pytest.mark.parametrize("src", ["fgmp_gemm.hip", "fgmp_gemm_skinny.hip", "fgmp_gemm_mid.hip", "fgmp_gemm_mixed.hip"])
+def test_no_direct_load_right_behind_the_write_of_its_address(src):
+    n, bad = lc.direct_loads_without_wait(lc.make_listing(HIPCC, build.FLAGS, os.path.join(build.CSRC, src)))
+    assert n > 0 and bad == []
