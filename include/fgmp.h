@@ -88,8 +88,11 @@ const char *fgmp_version(void);
  * including its header and per-tile tables.  0 on a bad argument. */
 size_t fgmp_packed_bytes(int64_t rows, int64_t K);
 
-/* Bytes of workspace fgmp_gemm / fgmp_quant_gemm_fused need for an
- * (M x K) * (N x K)^T product.  0 on a bad argument. */
+/* Bytes of workspace to allocate for fgmp_gemm / fgmp_quant_gemm_fused of an
+ * (M x K) * (N x K)^T product.  0 on a bad argument.  Kernels for different M use
+ * different amounts; a size for more than 32 rows also serves 32 or fewer rows of
+ * the same N, K (a call is refused only if the workspace is smaller than what its
+ * own shape uses, which is never more than this size). */
 size_t fgmp_workspace_bytes(int64_t M, int64_t N, int64_t K);
 
 /*

@@ -295,18 +295,30 @@ static bool use_mid(int64_t M, int64_t N, int64_t K)
     return gemm_mid_applies(M, N, K) && gemm_mid_micros(M, N, K) + staging <= gemm_mixed_micros(M, N, K);
 }
 
-// (all of these count the bytes behind the control region)
-size_t gemm_only_workspace_bytes(int64_t M, int64_t N, int64_t K)
+// what a product of packed operands uses behind the control region
+static size_t gemm_only_need(int64_t M, int64_t N, int64_t K)
 {
     if (M > 32 && use_mid(M, N, K)) return mid_bytes(M, N, K);
     const size_t other = gemm_skinny_applies(M, N, K) ? decode_bytes(M, N, K) : gemm_ws_layout(M, N, K).total;
     return std::max(other, gemm_stream_scratch_bytes(M, N, K));
 }
 
-size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
+// what a call must be given
+size_t gemm_workspace_need(int64_t M, int64_t N, int64_t K)
 {
     // the fused call also keeps the quantized activations here: packed, or header + FP16 values
-    return kWsCtrlRegion + (size_t)make_layout(M, K).total_bytes + gemm_only_workspace_bytes(M, N, K);
+    return kWsCtrlRegion + (size_t)make_layout(M, K).total_bytes + gemm_only_need(M, N, K);
+}
+
+// What callers are told to allocate.  A server allocates for its largest batch and passes smaller ones as well: above 32
+// rows, where the kernels differ in what they use, the size covers the prefill kernel's buffers for that many rows and
+// whatever 32 rows need (partial sums of K in parts: 8.3 MB for 4096 x 12288, where 64 rows use 0.9 MB themselves).
+size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
+{
+    const size_t own = gemm_workspace_need(M, N, K);
+    if (M <= 32) return own;
+    const size_t prefill = kWsCtrlRegion + (size_t)make_layout(M, K).total_bytes + gemm_ws_layout(M, N, K).total;
+    return std::max(std::max(own, prefill), gemm_workspace_need(32, N, K));
 }
 
 // The fused call on the prefill kernel: header, FP16 activations, then what a split last round needs
@@ -324,7 +336,7 @@ size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K)
         const GemmWorkspace w = gemm_ws_layout(M, N, K);
         return kWsCtrlRegion + fused_prefill_split(w) + (w.total - w.off_split);
     }
-    return gemm_workspace_bytes(M, N, K);
+    return gemm_workspace_need(M, N, K);
 }
 
 // `skip`: bytes behind the control region that the caller keeps for itself (the fused call's packed activations)
@@ -336,7 +348,7 @@ fgmp_status_t gemm_packed(const void *packed_X, int64_t M, const void *packed_W,
     if (K % kBlock != 0 || ldy < N) return FGMP_ERR_BAD_SHAPE;
     if (((uintptr_t)packed_X | (uintptr_t)packed_W | (uintptr_t)Y | (uintptr_t)workspace) % 16 != 0)
         return FGMP_ERR_BAD_ALIGN;
-    if (workspace_bytes < kWsCtrlRegion + skip + gemm_only_workspace_bytes(M, N, K)) return FGMP_ERR_BUFFER_TOO_SMALL;
+    if (workspace_bytes < kWsCtrlRegion + skip + gemm_only_need(M, N, K)) return FGMP_ERR_BUFFER_TOO_SMALL;
     const PackedLayout la = make_layout(M, K), lb = make_layout(N, K);
     const PackedView A = make_view(const_cast<void *>(packed_X), la);
     const PackedView B = make_view(const_cast<void *>(packed_W), lb);
@@ -413,7 +425,7 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
     const bool stream_fits = score_mode == FGMP_SCORE_NVFP4_ERROR && (pack_out == nullptr || stream_pack) && x_fits && gemm_stream_applies(M, N, K);
     const bool stream = stream_fits && !mid;
     if (workspace_bytes < (stream_fits ? (pack_out ? kWsCtrlRegion + gemm_stream_pack_scratch_bytes(M, N, K) : quant_gemm_workspace_need(M, N, K))
-                                  : gemm_workspace_bytes(M, N, K)))
+                                  : gemm_workspace_need(M, N, K)))
         return FGMP_ERR_BUFFER_TOO_SMALL;
     char *ws = static_cast<char *>(workspace) + kWsCtrlRegion;
     if (stream) {
@@ -485,12 +497,17 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
 // (FGMP_EPILOGUE_ONE_LAUNCH); otherwise, for other shapes, the gated epilogue at decode sizes and the
 // two-pass path, the FP32 results go to the workspace and the standalone quantizer runs over them -- the
 // same arithmetic on the same values.
-size_t gemm_workspace_bytes_packed_out(int64_t M, int64_t N, int64_t K, int epilogue)
+static size_t staging_bytes(int64_t M, int64_t N, int epilogue)
 {
     // FP32 staging of the product for the shapes whose epilogue cannot quantize, and of the gated values
     const size_t staged = (size_t)align_up((uint64_t)M * N * 4, 256);
     const size_t gated = epilogue == FGMP_EPILOGUE_SILU_GATE ? (size_t)align_up((uint64_t)M * (N / 2) * 4, 256) : 0;
-    return (size_t)align_up(gemm_workspace_bytes(M, N, K), 256) + staged + gated;
+    return staged + gated;
+}
+
+size_t gemm_workspace_bytes_packed_out(int64_t M, int64_t N, int64_t K, int epilogue)
+{
+    return (size_t)align_up(gemm_workspace_bytes(M, N, K), 256) + staging_bytes(M, N, epilogue);
 }
 
 // h[m][32 q + c] = SiLU(y[m][64 q + c]) * y[m][64 q + 32 + c]: the gated activation over a staged product
@@ -525,7 +542,8 @@ fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, i
     if (M * (N / kBlock) >= (int64_t)1 << 32) return FGMP_ERR_UNSUPPORTED;
     const PackedLayout ly = make_layout(M, n_out);
     if (packed_Y_bytes < ly.total_bytes) return FGMP_ERR_BUFFER_TOO_SMALL;
-    if (workspace_bytes < gemm_workspace_bytes_packed_out(M, N, K, epilogue)) return FGMP_ERR_BUFFER_TOO_SMALL;
+    const size_t base_bytes = gemm_workspace_need(M, N, K);
+    if (workspace_bytes < align_up(base_bytes, 256) + staging_bytes(M, N, epilogue)) return FGMP_ERR_BUFFER_TOO_SMALL;
     PackOut po;
     po.out = make_view(packed_Y, ly);
     po.layout = ly;
@@ -535,7 +553,6 @@ fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, i
     po.scores = scores_y;
     po.gate = gate ? 1 : 0;
     po.one_launch = one_launch ? 1 : 0;
-    const size_t base_bytes = gemm_workspace_bytes(M, N, K);
     // (the whole workspace: the one-launch decode step keeps its row groups' decisions behind its partial sums)
     fgmp_status_t rc = quant_gemm(X, dt, M, K, ldx, fisher_k, threshold, scale_x, packed_W, N, nullptr, N, workspace,
                                   workspace_bytes, st, FGMP_SCORE_NVFP4_ERROR, &po);

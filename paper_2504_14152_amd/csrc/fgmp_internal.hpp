@@ -33,11 +33,13 @@ fgmp_status_t unpack_tensor(const void *packed, int64_t rows, int64_t K, uint8_t
 fgmp_status_t gemm_packed(const void *packed_X, int64_t M, const void *packed_W, int64_t N, int64_t K,
                           float *Y, int64_t ldy, void *workspace, size_t workspace_bytes, hipStream_t st,
                           size_t skip = 0);
+// a workspace of the size that callers are told; at least what a call must be given, control region included
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
+size_t gemm_workspace_need(int64_t M, int64_t N, int64_t K);
 // what fgmp_quant_gemm_fused itself uses of a workspace (control region included)
 size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K);
 struct PackOut;
-// quantize X and multiply in one call; `workspace` holds at least gemm_workspace_bytes(M, N, K)
+// quantize X and multiply in one call; `workspace` holds at least gemm_workspace_need(M, N, K)
 fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, int64_t ldx, const float *fisher_k,
                          float threshold, float scale_x, const void *packed_W, int64_t N, float *Y, int64_t ldy,
                          void *workspace, size_t workspace_bytes, hipStream_t st,

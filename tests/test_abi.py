@@ -98,3 +98,17 @@ def test_workspace_sizes_over_the_row_counts_where_the_paths_change():
             assert ws < (1 << 34), (M, N, K, ws)
         assert L.fgmp_workspace_bytes(0, N, K) == 0 and L.fgmp_workspace_bytes(8, N, K + 8) == 0
 
+
+def test_a_workspace_for_a_large_batch_serves_the_smaller_ones():
+    """A server allocates once, for its largest batch: above 32 rows a size is never below that of 32 or fewer rows, nor --
+    within one row of 256 x 256 tiles -- below that of fewer rows, plain and with packed results, whichever kernel each takes."""
+    L = fgmp.lib()
+    for (N, K) in [(12288, 4096), (4096, 4096), (22016, 4096), (4096, 11008), (264, 2048), (57344, 8192), (16384, 512), (64, 65536)]:
+        rows = list(range(1, 33)) + [33, 48, 64, 100, 128, 192, 200, 224, 256, 257, 300, 384, 448, 512, 513, 768, 1024, 1025, 2048, 4096]
+        plain = [int(L.fgmp_workspace_bytes(M, N, K)) for M in rows]
+        for sizes in (plain, [int(L.fgmp_workspace_bytes_packed_out_ex(M, N, K, 0)) for M in rows] if N % 16 == 0 else plain,
+                      [int(L.fgmp_workspace_bytes_packed_out_ex(M, N, K, 1)) for M in rows] if N % 64 == 0 else plain):
+            for i, M in enumerate(rows):
+                for j in range(i):
+                    if M > 32 and (rows[j] <= 32 or (rows[j] - 1) // 256 == (M - 1) // 256):
+                        assert sizes[i] >= sizes[j], (M, rows[j], N, K)

@@ -143,6 +143,22 @@ def test_static_scratch_takes_products_of_more_than_32_rows():
         assert torch.equal(got, fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW))
 
 
+@pytest.mark.parametrize("K,N", [(4096, 4096), (11008, 4096)])
+def test_one_workspace_serves_every_batch_up_to_the_one_it_was_sized_for(K, N):
+    """64 rows use less than 20 or 32 rows, whose K is shared among workgroups; the size of 64 rows is enough for all of them."""
+    xd, fxd, Tx, sx, pW, _, _ = _product(64, K, N, "bf16", 0.1, 94)
+    f_n = torch.ones(N, device=DEV)
+    ws = fgmp.new_workspace(fgmp.workspace_bytes(64, N, K), DEV)
+    ws_packed = fgmp.new_workspace(fgmp.workspace_bytes_packed_out(64, N, K), DEV)
+    for M in (64, 33, 32, 20, 16, 1):
+        want = fgmp.quant_gemm_fused(xd[:M], fxd, Tx, sx, pW)
+        assert torch.equal(fgmp.quant_gemm_fused(xd[:M], fxd, Tx, sx, pW, workspace=ws), want)
+        assert torch.equal(fgmp.gemm(fgmp.quantize_activations(xd[:M], fxd, Tx, sx), pW, workspace=ws), want)
+        got = fgmp.quant_gemm_fused_packed_out(xd[:M], fxd, Tx, sx, pW, f_n, 0.0, 1.0, workspace=ws_packed)
+        for a, b in zip(fgmp.unpack_canonical(got), fgmp.unpack_canonical(fgmp.quantize_activations(want, f_n, 0.0, 1.0))):
+            assert torch.equal(a, b)
+
+
 # ------------------------------------------------------------------ clipping: the candidates that are left out
 
 @pytest.mark.parametrize("what", ["ordinary", "heavy tails", "sparse sensitivities", "huge range", "negative", "tiny", "small scale", "large scale", "uneven"])
