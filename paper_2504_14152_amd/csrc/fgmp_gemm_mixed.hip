@@ -50,6 +50,8 @@
 
 namespace fgmp {
 
+constexpr int kMeetLooks = 16;   // how often the longer of two parts looks for the shorter one's sums (see there)
+
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
 // Per thread and K-step: the plane-L words (needed when the step is decoded) and the small fields
@@ -419,7 +421,12 @@ __global__ __launch_bounds__(kWM *kWN * 64, 1) void gemm_mixed_kernel(const _Flo
         // thread bumps the counter; if the other arrived meanwhile (both stored), the workgroup that
         // bumped second goes on with the sum, the other one is done.  a + b = b + a exactly, so the result
         // does not depend on the order of arrival.  With two parts the first is the shorter one and is
-        // launched first, so it normally is in memory when the second needs it, off the critical path.
+        // launched first, so it normally is in memory when the second needs it, off the critical path.  Over a few
+        // hundred to 1500 elements of K it is only just or not quite there (4 K-steps of head start are 6 us, storing up to
+        // 128 x 256 KB takes as long), and then both store: so the second one looks a few times, half a
+        // microsecond each, before it gives up.  One look / 16 looks, us: 1100 x 512 x 4096 (M, K, N) 29.9 / 26.7,
+        // 1300 x 768 x 4096 34.6 / 30.2, 2048 x 1536 x 4096 48.2 / 44.6, 300 x 512 x 16384 30.0 / 26.1; with 6 looks the
+        // fullest rounds (128 tiles) still lose 3 us; longer K does not notice (2304 x 4096 x 22016 365.5 / 365.9).
         // With four parts, parts 0, 1 and 2, 3 meet first, then the two pair sums: (p0 + p1) + (p2 + p3)
         // whatever the order.  Partials and counters cross XCDs: system-coherent accesses that bypass the
         // per-XCD L2.
@@ -429,11 +436,16 @@ __global__ __launch_bounds__(kWM *kWN * 64, 1) void gemm_mixed_kernel(const _Flo
         uint32_t *arrived = reinterpret_cast<uint32_t *>(&lds[0][0][0]);   // the operand stages are free now
         // (32-row bands of the tile beyond the tensor's last row are not exchanged: nothing of them is stored)
         auto band_has_rows = [&](int i) { return tm * kBM + wm * (TM * 32) + i * 32 < M; };
-        auto meet = [&](int counter, int my_slot, int other_slot) {
+        auto meet = [&](int counter, int my_slot, int other_slot, int looks) {
             const uint32_t mine = (uint32_t)(my_slot * kWaves + wave) * kWaveBytes + lane * 16u;
             const uint32_t other = (uint32_t)(other_slot * kWaves + wave) * kWaveBytes + lane * 16u;
             __syncthreads();
-            if (tid == 0) *arrived = __hip_atomic_load(&sp.counters[counter], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) {
+                uint32_t seen = 0u;
+                for (int look = 0; look < looks && seen == 0u; ++look)
+                    seen = __hip_atomic_load(&sp.counters[counter], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                *arrived = seen;
+            }
             __syncthreads();
             if (*arrived == 0u) {
 #pragma unroll
@@ -469,9 +481,10 @@ __global__ __launch_bounds__(kWM *kWN * 64, 1) void gemm_mixed_kernel(const _Flo
         };
         const bool four = sp.n_parts == 4;
         const int slots = four ? 6 : 2, counters = four ? 3 : 1;   // per tile
-        if (!meet(split_tile * counters + (part >> 1), split_tile * slots + part, split_tile * slots + (part ^ 1))) return;
+        if (!meet(split_tile * counters + (part >> 1), split_tile * slots + part, split_tile * slots + (part ^ 1),
+                  !four && part == 1 ? kMeetLooks : 1)) return;
         if (four && !meet(split_tile * counters + 2, split_tile * slots + 4 + (part >> 1),
-                          split_tile * slots + 4 + ((part >> 1) ^ 1)))
+                          split_tile * slots + 4 + ((part >> 1) ^ 1), 1))
             return;
     }
     if constexpr (!kPackOut) {

@@ -143,6 +143,25 @@ def test_static_scratch_takes_products_of_more_than_32_rows():
         assert torch.equal(got, fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW))
 
 
+# ------------------------------------------------------------------ products of more than 1024 rows
+
+# (M, K, N), all on the 256 x 256 tiles: a round of 70 to 80 tiles, each computed in two parts of K whose sums meet in
+# memory, with 4, 6, 8, 10, 16 and 18 K-steps of 64 -- of which the main loop turns over 6 at a time -- and ragged ends
+@pytest.mark.parametrize("M,K,N", [(1100, 256, 3400), (1100, 272, 4096), (1025, 512, 4096), (1100, 640, 3400), (1279, 1024, 3500), (1100, 1040, 3400)])
+def test_products_in_two_parts_match_oracle(M, K, N):
+    """Within 1e-5 of the sum of magnitudes, and the same bits every time, whichever part comes first."""
+    xd, fxd, Tx, sx, pW, want, tol = _product(M, K, N, "bf16", 0.1, 95)
+    ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
+    ws[fgmp.WORKSPACE_CONTROL_BYTES:] = 0xFF
+    Y = fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, workspace=ws)
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - want)
+    assert np.all(err <= tol), (err / tol).max()
+    px = fgmp.quantize_activations(xd, fxd, Tx, sx)
+    for _ in range(8):
+        assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, workspace=ws), Y)
+        assert torch.equal(fgmp.gemm(px, pW, workspace=ws), Y)
+
+
 @pytest.mark.parametrize("K,N", [(4096, 4096), (11008, 4096)])
 def test_one_workspace_serves_every_batch_up_to_the_one_it_was_sized_for(K, N):
     """64 rows use less than 20 or 32 rows, whose K is shared among workgroups; the size of 64 rows is enough for all of them."""
