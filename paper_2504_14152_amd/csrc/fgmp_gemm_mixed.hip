@@ -423,10 +423,12 @@ __global__ __launch_bounds__(kWM *kWN * 64, 1) void gemm_mixed_kernel(const _Flo
         // does not depend on the order of arrival.  With two parts the first is the shorter one and is
         // launched first, so it normally is in memory when the second needs it, off the critical path.  Over a few
         // hundred to 1500 elements of K it is only just or not quite there (4 K-steps of head start are 6 us, storing up to
-        // 128 x 256 KB takes as long), and then both store: so the second one looks a few times, half a
-        // microsecond each, before it gives up.  One look / 16 looks, us: 1100 x 512 x 4096 (M, K, N) 29.9 / 26.7,
+        // 128 x 256 KB takes as long), and then both store: so the second one looks up to 16
+        // times before it gives up.  One look / 16 looks, us: 1100 x 512 x 4096 (M, K, N) 29.9 / 26.7,
         // 1300 x 768 x 4096 34.6 / 30.2, 2048 x 1536 x 4096 48.2 / 44.6, 300 x 512 x 16384 30.0 / 26.1; with 6 looks the
         // fullest rounds (128 tiles) still lose 3 us; longer K does not notice (2304 x 4096 x 22016 365.5 / 365.9).
+        // With no head start (K of 4 K-steps: 300 x 256 x 4288 23.4 / 25.3) or one of 2 K-steps (6, 10, 14 of them: 384 x 304 x
+        // 4288 24.9 / 25.6, 1040 x 640 x 4096 30.4 / 31.6) waiting costs what storing does: one look.
         // With four parts, parts 0, 1 and 2, 3 meet first, then the two pair sums: (p0 + p1) + (p2 + p3)
         // whatever the order.  Partials and counters cross XCDs: system-coherent accesses that bypass the
         // per-XCD L2.
@@ -482,7 +484,7 @@ __global__ __launch_bounds__(kWM *kWN * 64, 1) void gemm_mixed_kernel(const _Flo
         const bool four = sp.n_parts == 4;
         const int slots = four ? 6 : 2, counters = four ? 3 : 1;   // per tile
         if (!meet(split_tile * counters + (part >> 1), split_tile * slots + part, split_tile * slots + (part ^ 1),
-                  !four && part == 1 ? kMeetLooks : 1)) return;
+                  !four && part == 1 && sp.kt_bound[2] - 2 * sp.kt_bound[1] >= 4 ? kMeetLooks : 1)) return;
         if (four && !meet(split_tile * counters + 2, split_tile * slots + 4 + (part >> 1),
                           split_tile * slots + 4 + ((part >> 1) ^ 1), 1))
             return;
