@@ -91,10 +91,9 @@ fgmp_status_t fgmp_quant_gemm_fused_static_scratch(const void *X, fgmp_dtype_t d
     void *ws = nullptr;
     const fgmp_status_t rc = static_scratch(&ws);
     if (rc != FGMP_OK) return rc;
-    // Above 32 rows the shape alone decides what is used, and that fits: a caller's workspace would also have room for
-    // the other paths.  (A decode step whose X the one-launch kernel cannot address takes another path: checked there.)
-    const size_t room = M > 32 ? std::max((size_t)FGMP_STATIC_SCRATCH_BYTES, gemm_workspace_need(M, N, K)) : (size_t)FGMP_STATIC_SCRATCH_BYTES;
-    return quant_gemm(X, dt, M, K, ldx, fisher_k, threshold, scale_x, packed_W, N, Y, ldy, ws, room, as_stream(stream));
+    // (a decode step whose X the one-launch kernel cannot address takes another path: checked there)
+    return quant_gemm(X, dt, M, K, ldx, fisher_k, threshold, scale_x, packed_W, N, Y, ldy, ws, (size_t)FGMP_STATIC_SCRATCH_BYTES,
+                      as_stream(stream), FGMP_SCORE_NVFP4_ERROR, nullptr, /*tight=*/true);
 }
 
 fgmp_status_t fgmp_quantize_weights_ex(const void *W, fgmp_dtype_t dt, int64_t N, int64_t K, int64_t ldw,

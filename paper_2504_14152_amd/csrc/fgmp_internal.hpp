@@ -39,11 +39,12 @@ size_t gemm_workspace_need(int64_t M, int64_t N, int64_t K);
 // what fgmp_quant_gemm_fused itself uses of a workspace (control region included)
 size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K);
 struct PackOut;
-// quantize X and multiply in one call; `workspace` holds at least gemm_workspace_need(M, N, K)
+// quantize X and multiply in one call; `workspace` holds at least gemm_workspace_need(M, N, K) bytes
+// (`tight`: quant_gemm_workspace_need above 32 rows)
 fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, int64_t ldx, const float *fisher_k,
                          float threshold, float scale_x, const void *packed_W, int64_t N, float *Y, int64_t ldy,
                          void *workspace, size_t workspace_bytes, hipStream_t st,
-                         int score_mode = FGMP_SCORE_NVFP4_ERROR, const PackOut *pack_out = nullptr);
+                         int score_mode = FGMP_SCORE_NVFP4_ERROR, const PackOut *pack_out = nullptr, bool tight = false);
 size_t gemm_workspace_bytes_packed_out(int64_t M, int64_t N, int64_t K, int epilogue = FGMP_EPILOGUE_NONE);
 fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, int64_t ldx,
                                     const float *fisher_k, float threshold, float scale_x, const void *packed_W,

@@ -136,7 +136,8 @@ def test_long_products_of_few_rows_quantize_the_results_of_the_plain_call():
 
 
 def test_static_scratch_takes_products_of_more_than_32_rows():
-    for M, K, N in ((64, 4096, 1024), (300, 1040, 264), (200, 16, 24)):
+    # (the last one: split tiles whose partial sums only fit right behind the activations)
+    for M, K, N in ((64, 4096, 1024), (300, 1040, 264), (200, 16, 24), (1100, 256, 264)):
         xd, fxd, Tx, sx, pW, _, _ = _product(M, K, N, "bf16", 0.1, 92)
         got = torch.full((M, N), float("nan"), device=DEV)
         fgmp.quant_gemm_fused_static_scratch(xd, fxd, Tx, sx, pW, out=got)
