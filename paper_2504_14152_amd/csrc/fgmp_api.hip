@@ -67,7 +67,7 @@ fgmp_status_t fgmp_quantize_activations(const void *X, fgmp_dtype_t dt, int64_t 
 fgmp_status_t fgmp_gemm(const void *packed_X, int64_t M, const void *packed_W, int64_t N, int64_t K,
                         float *Y, int64_t ldy, void *workspace, size_t workspace_bytes, void *stream)
 {
-    return gemm_packed(packed_X, M, packed_W, N, K, Y, ldy, workspace, workspace_bytes, as_stream(stream));
+    return gemm_packed(packed_X, M, packed_W, N, K, Y, ldy, workspace, workspace_bytes, as_stream(stream), gemm_route(M, N, K));
 }
 
 fgmp_status_t fgmp_quant_gemm_fused(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, int64_t ldx,
@@ -76,7 +76,7 @@ fgmp_status_t fgmp_quant_gemm_fused(const void *X, fgmp_dtype_t dt, int64_t M, i
                                     void *workspace, size_t workspace_bytes, void *stream)
 {
     return quant_gemm(X, dt, M, K, ldx, fisher_k, threshold, scale_x, packed_W, N, Y, ldy, workspace,
-                      workspace_bytes, as_stream(stream));
+                      workspace_bytes, as_stream(stream), gemm_route(M, N, K));
 }
 
 fgmp_status_t fgmp_quant_gemm_fused_static_scratch(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, int64_t ldx,
@@ -87,13 +87,14 @@ fgmp_status_t fgmp_quant_gemm_fused_static_scratch(const void *X, fgmp_dtype_t d
     if (M <= 0 || N <= 0 || K <= 0) return FGMP_ERR_INVALID_ARG;
     if (K % kBlock != 0) return FGMP_ERR_BAD_SHAPE;
     // the size check comes first: a product that does not fit must not touch the array
-    if (quant_gemm_workspace_need(M, N, K) > (size_t)FGMP_STATIC_SCRATCH_BYTES) return FGMP_ERR_BUFFER_TOO_SMALL;
+    const GemmRoute route = gemm_route(M, N, K);
+    if (quant_gemm_workspace_need(M, N, K, route) > (size_t)FGMP_STATIC_SCRATCH_BYTES) return FGMP_ERR_BUFFER_TOO_SMALL;
     void *ws = nullptr;
     const fgmp_status_t rc = static_scratch(&ws);
     if (rc != FGMP_OK) return rc;
     // (a decode step whose X the one-launch kernel cannot address takes another path: checked there)
     return quant_gemm(X, dt, M, K, ldx, fisher_k, threshold, scale_x, packed_W, N, Y, ldy, ws, (size_t)FGMP_STATIC_SCRATCH_BYTES,
-                      as_stream(stream), FGMP_SCORE_NVFP4_ERROR, nullptr, /*tight=*/true);
+                      as_stream(stream), route, FGMP_SCORE_NVFP4_ERROR, nullptr, /*tight=*/true);
 }
 
 fgmp_status_t fgmp_quantize_weights_ex(const void *W, fgmp_dtype_t dt, int64_t N, int64_t K, int64_t ldw,
@@ -122,7 +123,7 @@ fgmp_status_t fgmp_quant_gemm_fused_ex(const void *X, fgmp_dtype_t dt, int64_t M
                                        int64_t ldy, void *workspace, size_t workspace_bytes, void *stream)
 {
     return quant_gemm(X, dt, M, K, ldx, fisher_k, threshold, scale_x, packed_W, N, Y, ldy, workspace,
-                      workspace_bytes, as_stream(stream), (int)score_mode);
+                      workspace_bytes, as_stream(stream), gemm_route(M, N, K), (int)score_mode);
 }
 
 size_t fgmp_workspace_bytes_packed_out(int64_t M, int64_t N, int64_t K)

@@ -274,40 +274,46 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
 constexpr int64_t kMidMinRows = 20, kMidMaxRows = 1024;
 
 // its workspace behind the control region: header, FP16 activations, partial sums
-static size_t mid_x16_bytes(int64_t M, int64_t N, int64_t K)
+static size_t mid_x16_bytes(const MidPlan &p, int64_t K)
 {
-    return (size_t)align_up((uint64_t)gemm_mid_x16_rows(M, N, K) * round_up(K, kTileK) * 2, 256);
+    return (size_t)align_up((uint64_t)p.x16_rows() * round_up(K, kTileK) * 2, 256);
 }
-static size_t mid_bytes(int64_t M, int64_t N, int64_t K) { return (size_t)kHeaderBytes + mid_x16_bytes(M, N, K) + gemm_mid_scratch_bytes(M, N, K); }
+static size_t mid_bytes(const MidPlan &p, int64_t K) { return (size_t)kHeaderBytes + mid_x16_bytes(p, K) + p.scratch_bytes(); }
 
 static size_t decode_bytes(int64_t M, int64_t N, int64_t K)
 {
     return gemm_skinny_applies(M, N, K) ? skinny_x16_bytes(M, K) + gemm_skinny_workspace_bytes(M, N, K) : 0;
 }
 
-static bool use_mid(int64_t M, int64_t N, int64_t K)
+GemmRoute gemm_route(int64_t M, int64_t N, int64_t K)
 {
-    if (!kUseHwCvt || !prefill_decodes_in_kernel() || M < kMidMinRows || M > kMidMaxRows) return false;
-    if (M <= 32)
-        return (double)N * (double)K * (double)K >= 0x1p38 && gemm_mid_applies(M, N, K) &&
-               mid_bytes(M, N, K) <= (gemm_stream_applies(M, N, K) ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
-    const double staging = 6.0 + 8.0 * (double)M * (double)N / 4.5e6;
-    return gemm_mid_applies(M, N, K) && gemm_mid_micros(M, N, K) + staging <= gemm_mixed_micros(M, N, K);
+    GemmRoute r{};
+    if (!kUseHwCvt || !prefill_decodes_in_kernel() || M < kMidMinRows || M > kMidMaxRows || N <= 0 || K <= 0) return r;
+    if (M <= 32 && (double)N * (double)K * (double)K < 0x1p38) return r;
+    r.plan = gemm_mid_plan(M, N, K);
+    if (!gemm_mid_applies(r.plan, N, K)) return r;
+    if (M <= 32) {
+        r.mid = mid_bytes(r.plan, K) <= (gemm_stream_applies(M, N, K) ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
+    } else {
+        const double staging = 6.0 + 8.0 * (double)M * (double)N / 4.5e6;
+        r.mid = gemm_mid_micros(r.plan) + staging <= gemm_mixed_micros(M, N, K);
+    }
+    return r;
 }
 
 // what a product of packed operands uses behind the control region
-static size_t gemm_only_need(int64_t M, int64_t N, int64_t K)
+static size_t gemm_only_need(int64_t M, int64_t N, int64_t K, const GemmRoute &route)
 {
-    if (M > 32 && use_mid(M, N, K)) return mid_bytes(M, N, K);
+    if (M > 32 && route.mid) return mid_bytes(route.plan, K);
     const size_t other = gemm_skinny_applies(M, N, K) ? decode_bytes(M, N, K) : gemm_ws_layout(M, N, K).total;
     return std::max(other, gemm_stream_scratch_bytes(M, N, K));
 }
 
 // what a call must be given
-size_t gemm_workspace_need(int64_t M, int64_t N, int64_t K)
+size_t gemm_workspace_need(int64_t M, int64_t N, int64_t K, const GemmRoute &route)
 {
     // the fused call also keeps the quantized activations here: packed, or header + FP16 values
-    return kWsCtrlRegion + (size_t)make_layout(M, K).total_bytes + gemm_only_need(M, N, K);
+    return kWsCtrlRegion + (size_t)make_layout(M, K).total_bytes + gemm_only_need(M, N, K, route);
 }
 
 // What callers are told to allocate.  A server allocates for its largest batch and passes smaller ones as well: above 32
@@ -315,10 +321,10 @@ size_t gemm_workspace_need(int64_t M, int64_t N, int64_t K)
 // whatever 32 rows need (partial sums of K in parts: 8.3 MB for 4096 x 12288, where 64 rows use 0.9 MB themselves).
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
-    const size_t own = gemm_workspace_need(M, N, K);
+    const size_t own = gemm_workspace_need(M, N, K, gemm_route(M, N, K));
     if (M <= 32) return own;
     const size_t prefill = kWsCtrlRegion + (size_t)make_layout(M, K).total_bytes + gemm_ws_layout(M, N, K).total;
-    return std::max(std::max(own, prefill), gemm_workspace_need(32, N, K));
+    return std::max(std::max(own, prefill), gemm_workspace_need(32, N, K, gemm_route(32, N, K)));
 }
 
 // The fused call on the prefill kernel: header, FP16 activations, then what a split last round needs
@@ -328,42 +334,42 @@ static bool fused_prefill(int64_t M, int64_t N, int64_t K)
 }
 static size_t fused_prefill_split(const GemmWorkspace &w) { return (size_t)align_up((uint64_t)kHeaderBytes + w.off_b, 256); }
 
-size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K)
+size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K, const GemmRoute &route)
 {
     if (gemm_stream_applies(M, N, K)) return kWsCtrlRegion + gemm_stream_scratch_bytes(M, N, K);
-    if (M > 32 && use_mid(M, N, K)) return kWsCtrlRegion + mid_bytes(M, N, K);
+    if (M > 32 && route.mid) return kWsCtrlRegion + mid_bytes(route.plan, K);
     if (fused_prefill(M, N, K)) {
         const GemmWorkspace w = gemm_ws_layout(M, N, K);
         return kWsCtrlRegion + fused_prefill_split(w) + (w.total - w.off_split);
     }
-    return gemm_workspace_need(M, N, K);
+    return gemm_workspace_need(M, N, K, route);
 }
 
 // `skip`: bytes behind the control region that the caller keeps for itself (the fused call's packed activations)
 fgmp_status_t gemm_packed(const void *packed_X, int64_t M, const void *packed_W, int64_t N, int64_t K,
-                          float *Y, int64_t ldy, void *workspace, size_t workspace_bytes, hipStream_t st, size_t skip)
+                          float *Y, int64_t ldy, void *workspace, size_t workspace_bytes, hipStream_t st, const GemmRoute &route,
+                          size_t skip)
 {
     if (!packed_X || !packed_W || !Y || !workspace) return FGMP_ERR_INVALID_ARG;
     if (M <= 0 || N <= 0 || K <= 0) return FGMP_ERR_INVALID_ARG;
     if (K % kBlock != 0 || ldy < N) return FGMP_ERR_BAD_SHAPE;
     if (((uintptr_t)packed_X | (uintptr_t)packed_W | (uintptr_t)Y | (uintptr_t)workspace) % 16 != 0)
         return FGMP_ERR_BAD_ALIGN;
-    if (workspace_bytes < kWsCtrlRegion + skip + gemm_only_need(M, N, K)) return FGMP_ERR_BUFFER_TOO_SMALL;
+    if (workspace_bytes < kWsCtrlRegion + skip + gemm_only_need(M, N, K, route)) return FGMP_ERR_BUFFER_TOO_SMALL;
     const PackedLayout la = make_layout(M, K), lb = make_layout(N, K);
     const PackedView A = make_view(const_cast<void *>(packed_X), la);
     const PackedView B = make_view(const_cast<void *>(packed_W), lb);
     void *const ctrl = workspace;
     workspace = static_cast<char *>(workspace) + kWsCtrlRegion + skip;
-    const bool mid = use_mid(M, N, K);
-    if (!mid && gemm_stream_applies(M, N, K))
+    if (!route.mid && gemm_stream_applies(M, N, K))
         return gemm_stream(2, nullptr, 0, nullptr, 0.0f, 1.0f, packed_X, M, packed_W, N, K, Y, ldy, ctrl, workspace, st);
-    if (mid) {
+    if (route.mid) {
         const int64_t ld16 = round_up(K, kTileK);
         _Float16 *x16 = reinterpret_cast<_Float16 *>(static_cast<char *>(workspace) + kHeaderBytes);
         const fgmp_status_t rcx = launch_decode_f16(make_decode_job(A, la, x16, ld16, la.n_rt), nullptr, nullptr, 0, st);
         if (rcx != FGMP_OK) return rcx;
-        return gemm_mid(A.hdr, x16, ld16, packed_W, M, N, K, Y, ldy, ctrl,
-                        static_cast<char *>(workspace) + kHeaderBytes + mid_x16_bytes(M, N, K), st);
+        return gemm_mid(route.plan, A.hdr, x16, ld16, packed_W, M, N, K, Y, ldy, ctrl,
+                        static_cast<char *>(workspace) + kHeaderBytes + mid_x16_bytes(route.plan, K), st);
     }
     if (gemm_skinny_applies(M, N, K)) {
         // decode shapes: expand the few activation rows to FP16 once, then stream the weights
@@ -409,7 +415,7 @@ fgmp_status_t gemm_packed(const void *packed_X, int64_t M, const void *packed_W,
 // and the two-pass path go through the packed activations.
 fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, int64_t ldx, const float *fisher_k,
                          float threshold, float scale_x, const void *packed_W, int64_t N, float *Y, int64_t ldy,
-                         void *workspace, size_t workspace_bytes, hipStream_t st, int score_mode,
+                         void *workspace, size_t workspace_bytes, hipStream_t st, const GemmRoute &route, int score_mode,
                          const PackOut *pack_out, bool tight)
 {
     if (!workspace || !packed_W || (!Y && !pack_out)) return FGMP_ERR_INVALID_ARG;
@@ -418,14 +424,14 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
     if (((uintptr_t)workspace | (uintptr_t)packed_W | (uintptr_t)Y) % 16 != 0) return FGMP_ERR_BAD_ALIGN;
     // (the one-launch kernel addresses X with 32-bit byte offsets)
     const bool x_fits = ldx > 0 && ldx < (int64_t)0xFFFFFF00 / (M * 4);
-    const bool mid = use_mid(M, N, K);
+    const bool mid = route.mid;
     // (the decode step quantizes its own results where the caller asks for it -- and where the plain call takes it, too: the
     // packed results are the same bit for bit either way)
     const bool stream_pack = pack_out != nullptr && !pack_out->gate && pack_out->one_launch && !mid && gemm_stream_packs(M, N, K);
     const bool stream_fits = score_mode == FGMP_SCORE_NVFP4_ERROR && (pack_out == nullptr || stream_pack) && x_fits && gemm_stream_applies(M, N, K);
     const bool stream = stream_fits && !mid;
-    if (workspace_bytes < (stream_fits ? (pack_out ? kWsCtrlRegion + gemm_stream_pack_scratch_bytes(M, N, K) : quant_gemm_workspace_need(M, N, K))
-                                  : tight && M > 32 ? quant_gemm_workspace_need(M, N, K) : gemm_workspace_need(M, N, K)))
+    if (workspace_bytes < (stream_fits ? (pack_out ? kWsCtrlRegion + gemm_stream_pack_scratch_bytes(M, N, K) : quant_gemm_workspace_need(M, N, K, route))
+                                  : tight && M > 32 ? quant_gemm_workspace_need(M, N, K, route) : gemm_workspace_need(M, N, K, route)))
         return FGMP_ERR_BUFFER_TOO_SMALL;
     char *ws = static_cast<char *>(workspace) + kWsCtrlRegion;
     if (stream) {
@@ -448,8 +454,8 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
         const fgmp_status_t rc = quantize_tensor(X, dt, M, K, ldx, fisher_k, 0, threshold, scale_x, ws, sizeof(PackedHeader), nullptr,
                                                  false, st, x16, ld16, nullptr, 0, score_mode);
         if (rc != FGMP_OK) return rc;
-        return gemm_mid(reinterpret_cast<const PackedHeader *>(ws), x16, ld16, packed_W, M, N, K, Y, ldy, workspace,
-                        ws + kHeaderBytes + mid_x16_bytes(M, N, K), st);
+        return gemm_mid(route.plan, reinterpret_cast<const PackedHeader *>(ws), x16, ld16, packed_W, M, N, K, Y, ldy, workspace,
+                        ws + kHeaderBytes + mid_x16_bytes(route.plan, K), st);
     }
     const bool in_kernel_prefill = fused_prefill(M, N, K);
     if (pack_out != nullptr && !in_kernel_prefill) return FGMP_ERR_UNSUPPORTED;   // the caller falls back
@@ -492,7 +498,7 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
                                              nullptr, false, st, nullptr, 0, nullptr, 0, score_mode);
     if (rc != FGMP_OK) return rc;
     // (the packed activations sit behind the control region; the product's own workspace starts with one)
-    return gemm_packed(ws, M, packed_W, N, K, Y, ldy, workspace, workspace_bytes, st, xbytes);
+    return gemm_packed(ws, M, packed_W, N, K, Y, ldy, workspace, workspace_bytes, st, route, xbytes);
 }
 
 // Fused call whose results are quantized and packed instead of stored as FP32 (Sec. 4.2).  Prefill
@@ -545,7 +551,8 @@ fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, i
     if (M * (N / kBlock) >= (int64_t)1 << 32) return FGMP_ERR_UNSUPPORTED;
     const PackedLayout ly = make_layout(M, n_out);
     if (packed_Y_bytes < ly.total_bytes) return FGMP_ERR_BUFFER_TOO_SMALL;
-    const size_t base_bytes = gemm_workspace_need(M, N, K);
+    const GemmRoute route = gemm_route(M, N, K);
+    const size_t base_bytes = gemm_workspace_need(M, N, K, route);
     if (workspace_bytes < align_up(base_bytes, 256) + staging_bytes(M, N, epilogue)) return FGMP_ERR_BUFFER_TOO_SMALL;
     PackOut po;
     po.out = make_view(packed_Y, ly);
@@ -558,10 +565,10 @@ fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, i
     po.one_launch = one_launch ? 1 : 0;
     // (the whole workspace: the one-launch decode step keeps its row groups' decisions behind its partial sums)
     fgmp_status_t rc = quant_gemm(X, dt, M, K, ldx, fisher_k, threshold, scale_x, packed_W, N, nullptr, N, workspace,
-                                  workspace_bytes, st, FGMP_SCORE_NVFP4_ERROR, &po);
+                                  workspace_bytes, st, route, FGMP_SCORE_NVFP4_ERROR, &po);
     if (rc != FGMP_ERR_UNSUPPORTED) return rc;
     float *Yf = reinterpret_cast<float *>(static_cast<char *>(workspace) + align_up(base_bytes, 256));
-    rc = quant_gemm(X, dt, M, K, ldx, fisher_k, threshold, scale_x, packed_W, N, Yf, N, workspace, base_bytes, st,
+    rc = quant_gemm(X, dt, M, K, ldx, fisher_k, threshold, scale_x, packed_W, N, Yf, N, workspace, base_bytes, st, route,
                     FGMP_SCORE_NVFP4_ERROR, nullptr);
     if (rc != FGMP_OK) return rc;
     if (gate) {

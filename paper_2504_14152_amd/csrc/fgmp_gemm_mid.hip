@@ -436,6 +436,9 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
 
 // ---- host side ----
 
+// column groups per wave that fit the 256 registers of two waves per SIMD (accumulators 4 MT NT, weights 38 NT)
+constexpr int mid_most_nt(int mt) { return mt <= 4 ? 4 : 3; }
+
 // Which of the 16 MT x 16 NT WN tiles, and how many workgroups share one: the cheapest by a model of the launch, in
 // cycles of a compute unit.  A round costs what its matrix instructions, its vector instructions (two waves to a SIMD) or
 // its LDS accesses take, whichever is most -- 1.4 times that is measured --, a workgroup 15000 cycles before its first and
@@ -443,19 +446,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
 // fused step 3 us more): 4096 x 12288, 64 rows, 4 x 2 tiles on 192 workgroups 16 us by the model, 19.6 measured (4 x 3 in
 // two parts 21.7, 4 x 4 in two 24.1); 11008 x 4096, 512 rows, 8 x 2 in two parts 52 / 57 (8 x 3 in two 68, 4 x 4 63);
 // 4096 x 22016, 200 rows, 7 x 3 38 / 45 (5 x 3 66, 7 x 2 59).
-struct MidPlan {
-    int mt, nt, wn, wk;
-    int64_t tiles_m, tiles_n, rounds, parts;
-    double cycles;
-    int64_t tiles() const { return tiles_m * tiles_n; }
-    int64_t cols() const { return 16 * nt * wn; }
-    size_t partial_bytes() const { return parts > 1 ? (size_t)(tiles() * parts) * (16 * mt) * cols() * 4 : 0; }
-};
-
-// column groups per wave that fit the 256 registers of two waves per SIMD (accumulators 4 MT NT, weights 38 NT)
-constexpr int mid_most_nt(int mt) { return mt <= 4 ? 4 : 3; }
-
-static MidPlan mid_plan(int64_t M, int64_t N, int64_t K)
+MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K)
 {
     MidPlan best{};
     best.cycles = INFINITY;
@@ -485,23 +476,13 @@ static MidPlan mid_plan(int64_t M, int64_t N, int64_t K)
     return best;
 }
 
-double gemm_mid_micros(int64_t M, int64_t N, int64_t K) { return 3.0 + 1.2 * mid_plan(M, N, K).cycles / 2100.0; }
+double gemm_mid_micros(const MidPlan &p) { return 3.0 + 1.2 * p.cycles / 2100.0; }
 
-int64_t gemm_mid_x16_rows(int64_t M, int64_t N, int64_t K)
-{
-    const MidPlan p = mid_plan(M, N, K);
-    return p.tiles_m * 16 * p.mt;
-}
-
-size_t gemm_mid_scratch_bytes(int64_t M, int64_t N, int64_t K) { return (size_t)align_up(mid_plan(M, N, K).partial_bytes(), 256); }
-
-bool gemm_mid_applies(int64_t M, int64_t N, int64_t K)
+bool gemm_mid_applies(const MidPlan &p, int64_t N, int64_t K)
 {
     constexpr uint64_t kLimit = 0xFFFFFF00ull;   // 32-bit buffer offsets
-    if (make_layout(N, K).total_bytes >= kLimit) return false;
-    const MidPlan p = mid_plan(M, N, K);
-    return p.partial_bytes() < 0x7FFFFF00ull && p.tiles() * p.parts < 65536 && p.rounds * (p.parts + 1) < 65536 &&
-           p.tiles() <= (int64_t)(kWsCtrlRegion / 4) && align_up(K, kTileK) * 8 < 0x7FFFFFFF;
+    return make_layout(N, K).total_bytes < kLimit && p.partial_bytes() < 0x7FFFFF00ull && p.tiles() * p.parts < 65536 &&
+           p.rounds * (p.parts + 1) < 65536 && p.tiles() <= (int64_t)(kWsCtrlRegion / 4) && align_up(K, kTileK) * 8 < 0x7FFFFFFF;
 }
 
 template <int MT, int NT> static void launch_mid(const MidArgs &a, hipStream_t st)
@@ -519,11 +500,10 @@ template <int MT> static void launch_mid_nt(int nt, const MidArgs &a, hipStream_
         if (nt == 4) launch_mid<MT, 4>(a, st);
 }
 
-fgmp_status_t gemm_mid(const PackedHeader *xh, const _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
+fgmp_status_t gemm_mid(const MidPlan &p, const PackedHeader *xh, const _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
                        int64_t ldy, void *ctrl, void *scratch, hipStream_t st)
 {
-    if (!gemm_mid_applies(M, N, K)) return FGMP_ERR_UNSUPPORTED;
-    const MidPlan p = mid_plan(M, N, K);
+    if (!gemm_mid_applies(p, N, K)) return FGMP_ERR_UNSUPPORTED;
     const PackedLayout lw = make_layout(N, K);
     MidArgs a;
     a.w = w; a.xh = xh; a.x16 = x16; a.Y = Y; a.ldy = ldy;

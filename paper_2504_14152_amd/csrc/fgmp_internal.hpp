@@ -30,20 +30,37 @@ fgmp_status_t quantize_traffic_model(const void *X, fgmp_dtype_t dt, int64_t row
 #endif
 fgmp_status_t unpack_tensor(const void *packed, int64_t rows, int64_t K, uint8_t *codes, uint8_t *scales,
                             uint8_t *mask, hipStream_t st);
+// How the kernel for a few dozen to a few hundred rows shares a product out (fgmp_gemm_mid.hip), and whether a product is
+// computed by it.  Comparing the arrangements takes 0.2 to 0.5 us: a call does it once and hands the result on.
+struct MidPlan {
+    int mt, nt, wn, wk;                          // a workgroup: 16 mt rows x 16 nt wn columns, wk K-tiles at a time
+    int64_t tiles_m, tiles_n, rounds, parts;     // tiles; rounds of wk K-tiles; workgroups that share a tile's rounds
+    double cycles;
+    int64_t tiles() const { return tiles_m * tiles_n; }
+    int64_t cols() const { return 16 * nt * wn; }
+    int64_t x16_rows() const { return tiles_m * 16 * mt; }
+    size_t partial_bytes() const { return parts > 1 ? (size_t)(tiles() * parts) * (16 * mt) * cols() * 4 : 0; }
+    size_t scratch_bytes() const { return (size_t)align_up(partial_bytes(), 256); }
+};
+struct GemmRoute {
+    bool mid;
+    MidPlan plan;   // (valid where `mid`)
+};
+GemmRoute gemm_route(int64_t M, int64_t N, int64_t K);
 fgmp_status_t gemm_packed(const void *packed_X, int64_t M, const void *packed_W, int64_t N, int64_t K,
                           float *Y, int64_t ldy, void *workspace, size_t workspace_bytes, hipStream_t st,
-                          size_t skip = 0);
+                          const GemmRoute &route, size_t skip = 0);
 // a workspace of the size that callers are told; at least what a call must be given, control region included
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
-size_t gemm_workspace_need(int64_t M, int64_t N, int64_t K);
+size_t gemm_workspace_need(int64_t M, int64_t N, int64_t K, const GemmRoute &route);
 // what fgmp_quant_gemm_fused itself uses of a workspace (control region included)
-size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K);
+size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K, const GemmRoute &route);
 struct PackOut;
 // quantize X and multiply in one call; `workspace` holds at least gemm_workspace_need(M, N, K) bytes
 // (`tight`: quant_gemm_workspace_need above 32 rows)
 fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, int64_t ldx, const float *fisher_k,
                          float threshold, float scale_x, const void *packed_W, int64_t N, float *Y, int64_t ldy,
-                         void *workspace, size_t workspace_bytes, hipStream_t st,
+                         void *workspace, size_t workspace_bytes, hipStream_t st, const GemmRoute &route,
                          int score_mode = FGMP_SCORE_NVFP4_ERROR, const PackOut *pack_out = nullptr, bool tight = false);
 size_t gemm_workspace_bytes_packed_out(int64_t M, int64_t N, int64_t K, int epilogue = FGMP_EPILOGUE_NONE);
 fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, int64_t ldx,
@@ -80,15 +97,14 @@ fgmp_status_t gemm_stream(int src, const void *X, int64_t ldx, const float *fish
                           void *scratch, hipStream_t st, const PackOut *po = nullptr);
 bool gemm_stream_packs(int64_t M, int64_t N, int64_t K);
 size_t gemm_stream_pack_scratch_bytes(int64_t M, int64_t N, int64_t K);
-// Tens to hundreds of rows: X as FP16 values (gemm_mid_x16_rows(M, N, K) rows of ld16 halves, zeros up to whole K-tiles; rows
+// Tens to hundreds of rows: X as FP16 values (plan.x16_rows() rows of ld16 halves, zeros up to whole K-tiles; rows
 // from M on may hold anything), the weights decoded in registers.
-// `ctrl`: the workspace's control region; `scratch`: gemm_mid_scratch_bytes bytes.
-bool gemm_mid_applies(int64_t M, int64_t N, int64_t K);
-double gemm_mid_micros(int64_t M, int64_t N, int64_t K);     // estimate of a fused step
+// `ctrl`: the workspace's control region; `scratch`: plan.scratch_bytes() bytes.
+MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K);
+bool gemm_mid_applies(const MidPlan &p, int64_t N, int64_t K);
+double gemm_mid_micros(const MidPlan &p);                    // estimate of a fused step
 double gemm_mixed_micros(int64_t M, int64_t N, int64_t K);   // the same on the prefill kernel
-int64_t gemm_mid_x16_rows(int64_t M, int64_t N, int64_t K);
-size_t gemm_mid_scratch_bytes(int64_t M, int64_t N, int64_t K);
-fgmp_status_t gemm_mid(const PackedHeader *xh, const _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
+fgmp_status_t gemm_mid(const MidPlan &p, const PackedHeader *xh, const _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
                        int64_t ldy, void *ctrl, void *scratch, hipStream_t st);
 // packed -> zero-padded dense FP16 [8 n_rt_pad][ld]; one launch decodes one or two tensors and
 // can clear `zero_n` 32-bit counters
