@@ -365,6 +365,18 @@ fgmp_status_t fgmp_selftest_decode_table(int format, float *out, void *stream);
 fgmp_status_t fgmp_selftest_mfma_rate(int64_t workgroups, int32_t iters, float *sink, void *stream);
 
 /*
+ * Which kernel a fused call (Eq. 6 score, FP32 results) takes for a product, and how it is shared out; nothing is
+ * launched.  For tests, which have to know that a shape reaches the kernel it is meant for.  route: host, 6 values:
+ *   route[0] 0  one launch, decode     (all others 0)
+ *            1  two launches, decode   (all others 0)
+ *            2  a few dozen to a few hundred rows: 16-row and 16-column groups of a wave's tile, tiles along M, tiles
+ *               along N, workgroups that share a tile's K range
+ *            3  256 x 256 tiles: K-steps of 64, tiles computed whole, tiles split along K, workgroups per split tile, 0
+ *            4  both operands expanded to FP16 first (all others 0)
+ */
+fgmp_status_t fgmp_selftest_gemm_route(int64_t M, int64_t N, int64_t K, int64_t *route);
+
+/*
  * Measurement hook: the duration of the GEMM kernel (above 32 rows) inside a fused
  * call.  Only libraries built with FGMP_MEASUREMENT_HOOKS have it (the
  * benchmark's libfgmp_hooks.so); in the shipped library setting a pair returns

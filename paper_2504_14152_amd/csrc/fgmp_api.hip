@@ -280,6 +280,14 @@ fgmp_status_t fgmp_selftest_mfma_rate(int64_t workgroups, int32_t iters, float *
     return selftest_mfma_rate(workgroups, iters, sink, as_stream(stream));
 }
 
+fgmp_status_t fgmp_selftest_gemm_route(int64_t M, int64_t N, int64_t K, int64_t *route)
+{
+    if (!route || M <= 0 || N <= 0 || K <= 0) return FGMP_ERR_INVALID_ARG;
+    if (K % kBlock != 0) return FGMP_ERR_BAD_SHAPE;
+    selftest_gemm_route(M, N, K, route);
+    return FGMP_OK;
+}
+
 fgmp_status_t fgmp_selftest_time_gemm_kernel(void *ev_start, void *ev_stop)
 {
     if ((ev_start == nullptr) != (ev_stop == nullptr)) return FGMP_ERR_INVALID_ARG;

@@ -259,10 +259,12 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
 // Products of a few dozen to a few hundred rows (fgmp_gemm_mid.hip) as long as that beats the prefill kernel by the two
 // models' estimates -- with the time that staging FP32 results takes on top (a launch, a write and a read at 4.5 TB/s):
 // the calls that quantize their results have to quantize exactly what the plain call returns, so both take the same
-// kernel, and only the prefill kernel quantizes in its epilogue.  Measured, microseconds per fused step, this kernel /
-// the prefill kernel, on both sides of the line: 4096 x 22016 (K x N) 256 rows 52 / 63, 512 rows 96 / 94; 4096 x 12288
-// 384 rows 44 / 62, 768 rows 83 / 92, 1024 rows 103 / 99; 11008 x 4096 512 rows 58 / 87, 1024 rows 93 / 114; 512 x 16384
-// 256 rows 16 / 43, 768 rows 38 / 28.
+// kernel, and only the prefill kernel quantizes in its epilogue.  Microseconds per call, this kernel / the prefill kernel, with
+// FP32, packed, gated and packed results.  On this kernel: 4096 x 12288 (K x N) 256 rows 43 / 54, 48 / 63, 52 / 65, 448 rows
+// 49 / 63, 55 / 71, 62 / 74; 4096 x 22016 200 rows 45 / 60, 51 / 67, 56 / 70; 512 x 16384 256 rows 15 / 40, 26 / 49, 31 / 52.  On
+// the prefill kernel: 4096 x 22016 512 rows 96 / 94, 106 / 98, 118 / 101; 512 x 16384 768 rows 39 / 28, 50 / 31, 62 / 33.  The
+// line is drawn too early for products whose 256 x 256 tiles leave the chip part empty: 4096 x 12288 512 rows 53 / 63, 61 / 72,
+// 68 / 74; 4096 x 22016 256 rows 51 / 61, 57 / 69, 63 / 71; 4096 x 4096 768 rows 36 / 55, 40 / 65, 44 / 68.
 //
 // Up to 32 rows the one-launch step (fgmp_gemm_stream.hip) shares K among as many workgroups as keep a part's rows in LDS --
 // 8 at K = 8192 and 32 rows -- and adds their sums in memory: from N K^2 = 2^38 (parts times weights) and 20 rows on, its
@@ -580,6 +582,26 @@ fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, i
     }
     return quantize_tensor(Yf, FGMP_F32, M, n_out, n_out, fisher_n, 0, threshold_y, scale_y, packed_Y, packed_Y_bytes,
                            scores_y, /*compact=*/false, st);
+}
+
+// The order of quant_gemm's decisions, for tests.
+void selftest_gemm_route(int64_t M, int64_t N, int64_t K, int64_t *route)
+{
+    std::fill(route, route + 6, (int64_t)0);
+    const GemmRoute r = gemm_route(M, N, K);
+    if (r.mid) {
+        const int64_t v[6] = {2, r.plan.mt, r.plan.nt, r.plan.tiles_m, r.plan.tiles_n, r.plan.parts};
+        std::copy(v, v + 6, route);
+    } else if (gemm_stream_applies(M, N, K)) {
+        route[0] = 0;
+    } else if (fused_prefill(M, N, K)) {
+        const GemmWorkspace w = gemm_ws_layout(M, N, K);
+        const SplitTail sp = plan_split_tail((w.Mp / kBM) * (w.Np / kBN), (int)(w.ld / kBK), route);   // (any address: nothing is written)
+        const int64_t v[6] = {3, w.ld / kBK, sp.n_whole, sp.n_split, sp.n_split > 0 ? sp.n_parts : 1, 0};
+        std::copy(v, v + 6, route);
+    } else {
+        route[0] = gemm_skinny_applies(M, N, K) && kUseHwCvt ? 1 : 4;
+    }
 }
 
 // Measurement reference: independent MFMAs only (8 accumulators per wave, so no instruction waits for

@@ -85,8 +85,8 @@ fgmp_status_t gemm_skinny(const PackedHeader *xh, const PackedLayout &lx, const 
                           const void *w, const PackedLayout &lw, int64_t M, int64_t N, int64_t K, float *Y,
                           int64_t ldy, void *workspace, hipStream_t st);
 // Every workspace starts with a control region: arrival counters that must be zero when a call starts and
-// that every call leaves zero (the caller clears them once, after allocating).  Nothing but the
-// single-launch decode kernel touches it; all other scratch starts behind it.
+// that every call leaves zero (the caller clears them once, after allocating).  The single-launch decode
+// kernel and the kernel for mid-size products keep theirs there; all other scratch starts behind it.
 constexpr size_t kWsCtrlRegion = FGMP_WORKSPACE_CONTROL_BYTES;
 // Decode shapes (M <= 32) in one launch: the activations are quantized (src 0: bf16 X, 1: fp32 X) or
 // decoded (src 2: packed X) inside the kernel that streams the weights.
@@ -149,6 +149,7 @@ void launch_gemm_mixed(const _Float16 *a16, int64_t ld, const PackedView &W, con
 fgmp_status_t selftest_encode_ranges(int format, uint32_t *min_bits, uint32_t *max_bits,
                                      uint32_t *violations, hipStream_t st);
 fgmp_status_t selftest_decode_table(int format, float *out, hipStream_t st);
+void selftest_gemm_route(int64_t M, int64_t N, int64_t K, int64_t *route);
 fgmp_status_t selftest_mfma_rate(int64_t workgroups, int32_t iters, float *sink, hipStream_t st);
 // element of rank `rank` (0 = smallest) of the union of n_tensors device arrays; result on the host; synchronizes
 fgmp_status_t select_rank(const float *const *scores, const int64_t *counts, int32_t n_tensors, int64_t rank, float *result_host,

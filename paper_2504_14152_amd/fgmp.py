@@ -138,6 +138,8 @@ def _load(path: str) -> ctypes.CDLL:
     L.fgmp_selftest_decode_table.argtypes = [ctypes.c_int, vp, vp]
     L.fgmp_selftest_mfma_rate.restype = ctypes.c_int
     L.fgmp_selftest_mfma_rate.argtypes = [ctypes.c_int64, ctypes.c_int32, vp, vp]
+    L.fgmp_selftest_gemm_route.restype = ctypes.c_int
+    L.fgmp_selftest_gemm_route.argtypes = [i64, i64, i64, ctypes.POINTER(i64)]
     L.fgmp_selftest_time_gemm_kernel.restype = ctypes.c_int
     L.fgmp_selftest_time_gemm_kernel.argtypes = [vp, vp]
     L.fgmp_selftest_quantizer_traffic.restype = ctypes.c_int
@@ -441,6 +443,13 @@ def selftest_encode_ranges(fmt: int, device="cuda"):
     torch.cuda.synchronize()
     to_u32 = lambda t: t.cpu().numpy().view("uint32")
     return to_u32(mn), to_u32(mx), int(to_u32(viol)[0])
+
+
+def selftest_gemm_route(M: int, N: int, K: int) -> tuple:
+    """Which kernel a fused call takes and how the product is shared out (include/fgmp.h); launches nothing."""
+    route = (ctypes.c_int64 * 6)()
+    _check(lib().fgmp_selftest_gemm_route(M, N, K, route), "fgmp_selftest_gemm_route")
+    return tuple(route)
 
 
 def selftest_mfma_rate(workgroups: int, iters: int, sink: torch.Tensor) -> None:

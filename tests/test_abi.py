@@ -88,8 +88,8 @@ def test_bench_refuses_more_than_one_gpu():
 
 def test_workspace_sizes_over_the_row_counts_where_the_paths_change():
     """Host-side planning only: every M from decode sizes through the first prefill tiles gets a workspace,
-    whichever kernel the planner picks (row chunks through the weight-streaming kernel, tiles split along
-    K, whole tiles), and it never shrinks below what the FP16 copy of X alone needs."""
+    whichever kernel the planner picks (decode steps, mid-size products, tiles split along K, whole tiles), and it never
+    shrinks below what the FP16 copy of X alone needs."""
     L = fgmp.lib()
     for (N, K) in [(12288, 4096), (4096, 4096), (22016, 4096), (4096, 11008), (264, 2048), (57344, 8192)]:
         for M in list(range(1, 300)) + [511, 512, 513, 1024, 4096]:
@@ -112,3 +112,27 @@ def test_a_workspace_for_a_large_batch_serves_the_smaller_ones():
                 for j in range(i):
                     if M > 32 and (rows[j] <= 32 or (rows[j] - 1) // 256 == (M - 1) // 256):
                         assert sizes[i] >= sizes[j], (M, rows[j], N, K)
+
+
+def test_the_mid_size_shapes_cover_every_arrangement_the_planner_uses():
+    """The GPU tests name the arrangement each shape is meant for; over the kernel's whole range the planner uses no other
+    (16-row groups 2 to 8, column groups 2 to 4 up to 4 of them and 2 to 3 above)."""
+    import random
+    from tests.test_gpu_size_edges import MID_PLANS
+    named = set()
+    for (M, K, N), groups, shared in MID_PLANS:
+        route = fgmp.selftest_gemm_route(M, N, K)
+        assert route[0] == 2 and route[1:3] == groups and (route[5] > 1) == shared, ((M, K, N), route)
+        named.add((groups, shared))
+    rng = random.Random(7)
+    seen = set()
+    for _ in range(60000):
+        r = fgmp.selftest_gemm_route(rng.randint(20, 1024), int(2 ** rng.uniform(3, 16)), 16 * int(2 ** rng.uniform(0, 11)))
+        if r[0] == 2:
+            seen.add((r[1:3], r[5] > 1))
+    assert len(seen) > 20 and seen <= named, seen - named
+    # 33 to 1024 rows of the Llama-2-7B linears, and what the neighbours of the range take
+    assert [fgmp.selftest_gemm_route(M, 12288, 4096)[0] for M in (1, 32, 33, 64, 4096)] == [0, 0, 2, 2, 3]
+    assert fgmp.selftest_gemm_route(8, 24, 1024)[0] == 1 and fgmp.selftest_gemm_route(32, 264, 32768)[0] == 2
+    assert fgmp.lib().fgmp_selftest_gemm_route(8, 24, 24, (ctypes.c_int64 * 6)()) == -2
+    assert fgmp.lib().fgmp_selftest_gemm_route(8, 24, 16, None) == -1

@@ -596,12 +596,15 @@ def test_fused_packed_output_matches_oracle(M, K, N):
     assert np.all(np.abs(Z.cpu().numpy().astype(np.float64) - zw) <= tol)
 
 
-@pytest.mark.parametrize("M,K,N", [(200, 512, 272), (4352, 256, 4096)])
+@pytest.mark.parametrize("M,K,N", [(200, 512, 272), (4352, 256, 4096), (1100, 1040, 272)])
 def test_packed_output_on_random_inputs_is_consistent(M, K, N):
     """On ordinary inputs the FP32 results differ from the oracle's fp64 product in the last bits, so
-    codes cannot be compared one by one; the epilogue must still equal the standalone quantizer run on
-    the very FP32 results the plain fused call writes (same arithmetic, same values).  The second shape
-    has whole tiles and tiles computed in two parts along K in one launch."""
+    codes cannot be compared one by one; the packed results must still equal the standalone quantizer run on
+    the very FP32 results the plain fused call writes (same arithmetic, same values).  The first shape is staged
+    (the kernel for mid-size products does not quantize); the epilogue of the prefill kernel: whole tiles and tiles
+    computed in two parts along K in one launch, and ragged tiles in four parts."""
+    if M > 1024:
+        assert fgmp.selftest_gemm_route(M, N, K)[0] == 3
     c = _quantized_pair(M, K, N, 33, 0.1, per_elem_w=False)
     f_n = torch.from_numpy(synth.fisher_per_channel(N, 33, 9)).to(DEV)
     Y = fgmp.quant_gemm_fused(c["xd"], c["fxd"], c["Tx"], c["sx"], c["pW"])
@@ -859,11 +862,14 @@ def test_packed_results_are_valid_weight_operands(M, K, N):
     assert np.all(np.abs(Z.cpu().numpy().astype(np.float64) - zw) <= tol)
 
 
-@pytest.mark.parametrize("M,K,N", [(200, 512, 320), (4352, 256, 4096), (9, 1024, 192)])
+@pytest.mark.parametrize("M,K,N", [(200, 512, 320), (4352, 256, 4096), (9, 1024, 192), (1100, 1040, 320)])
 def test_gated_packed_output_on_random_inputs_is_consistent(M, K, N):
-    """On ordinary inputs: the gated epilogue equals the oracle's gate applied to the very FP32 results
+    """On ordinary inputs: the gated call equals the oracle's gate applied to the very FP32 results
     the plain fused call writes, then the standalone quantizer -- so the kernel's SiLU is the oracle's,
-    bit for bit, on realistic values (whole and split tiles in the second shape, the staged path in the third)."""
+    bit for bit, on realistic values (staged for mid-size and decode products, the first and the third shape; in the
+    prefill kernel's epilogue with whole tiles and tiles in two parts, and with ragged ones in four)."""
+    if M > 1024:
+        assert fgmp.selftest_gemm_route(M, N, K)[0] == 3
     c = _quantized_pair(M, K, N, 41, 0.1, per_elem_w=False)
     Y = fgmp.quant_gemm_fused(c["xd"], c["fxd"], c["Tx"], c["sx"], c["pW"])
     h = torch.from_numpy(orc.gate_columns(Y.cpu().numpy())).to(DEV)
@@ -1132,9 +1138,9 @@ def test_gemm_fc2_shape_sampled():
                                      (9, 11008, 8200, 0.2), (33, 1024, 520, 0.1), (64, 4096, 4096, 0.1),
                                      (96, 2048, 264, 0.3), (70, 11008, 4096, 0.1), (41, 304, 100, 1.0)])
 def test_gemm_decode_shapes(M, K, N, p):
-    """Weight-streaming path (M <= 32 per launch; more rows in chunks of 32 where that is the faster path): K ranges combined in K order, ragged N
-    and K, FP8 fractions beyond the speculative plane-H window, weight tensors with so many rows that
-    workgroups take 128 instead of 64 of them, last chunks of 1, 9, 6 and 32 rows."""
+    """Decode steps (M <= 32): K ranges combined in K order, ragged N and K, FP8 fractions beyond the speculative plane-H
+    window, weight tensors with so many rows that workgroups take 128 instead of 64 of them; and products of 33 to 96
+    rows, on the kernel for mid-size products."""
     _say(f"gemm decode M={M} K={K} N={N} p={p}")
     c = _quantized_pair(M, K, N, 11, p, per_elem_w=False)
     Y = fgmp.gemm(c["pX"], c["pW"])
@@ -1169,11 +1175,14 @@ def test_gemm_decode_llama_shapes_at_full_size(name):
 
 
 @pytest.mark.parametrize("M,K,N,p", [(4, 1024, 200, 0.1), (24, 2048, 136, 0.3), (300, 512, 264, 0.1),
-                                     (8, 256, 72, 0.0), (300, 256, 72, 0.0)])
+                                     (8, 256, 72, 0.0), (300, 256, 72, 0.0), (1100, 512, 264, 0.1), (1100, 256, 72, 0.0)])
 def test_compact_weights_relocated_to_bytes_used(M, K, N, p):
     """A compact weight tensor copied into a buffer of exactly bytes_used bytes
     (poisoned guard bytes after it) gives the same product, bit for bit, and
-    unpacks to the same codes: no reader depends on bytes beyond bytes_used."""
+    unpacks to the same codes: no reader depends on bytes beyond bytes_used.  Decode kernels, the kernel for mid-size
+    products and the prefill kernel."""
+    if M > 1024:
+        assert fgmp.selftest_gemm_route(M, N, K)[0] == 3
     _say(f"relocated compact weights M={M} K={K} N={N} p={p}")
     c = _quantized_pair(M, K, N, 17, p, per_elem_w=False)
     pW = c["pW"]
@@ -1223,11 +1232,14 @@ def test_mfma_rate_reference_runs():
     assert bool(torch.isfinite(sink).all())
 
 
-def test_gemm_kernel_timing_hook():
-    """The measurement hook (only in the build variant with hooks) brackets the prefill GEMM kernel with the
-    caller's events; cleared, it records nothing; the shipped library has no hook and says so."""
+@pytest.mark.parametrize("M,kernel", [(300, 2), (1100, 3)])
+def test_gemm_kernel_timing_hook(M, kernel):
+    """The measurement hook (only in the build variant with hooks) brackets the GEMM kernel of a product of more than 32
+    rows -- the one for mid-size products and the prefill kernel -- with the caller's events; cleared, it records nothing;
+    the shipped library has no hook and says so."""
     from paper_2504_14152_amd import build
-    c = _quantized_pair(300, 512, 264, 5, 0.1, per_elem_w=False)
+    assert fgmp.selftest_gemm_route(M, 264, 512)[0] == kernel
+    c = _quantized_pair(M, 512, 264, 5, 0.1, per_elem_w=False)
     ea, eb = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     ea.record()
     eb.record()
@@ -1253,13 +1265,16 @@ def test_gemm_kernel_timing_hook():
         assert ea.elapsed_time(eb) == ms
 
 
-@pytest.mark.parametrize("M,K,N", [(4096, 4096, 12288), (4096, 4096, 22016), (4352, 512, 4096), (300, 1040, 264)])
+@pytest.mark.parametrize("M,K,N", [(4096, 4096, 12288), (4096, 4096, 22016), (4352, 512, 4096), (300, 1040, 264),
+                                    (2048, 3072, 8192), (1100, 1040, 3400), (1100, 1040, 264), (1300, 272, 1032)])
 def test_hand_counted_waits_against_full_waits(M, K, N):
     """Runtime guard for the prefill kernel's hand-counted `s_waitcnt vmcnt(N)`: a second build of the same
     sources in which every such wait is a full one (nothing to miscount) must give the same Y bit for bit
     -- same instructions, same summation order, so any difference is a register read before its load
     landed.  QKV and FC1 at full size (FC1 with tiles split in two along K), a shape with four-part split
-    tiles, and a ragged one; whatever the compiler made of the loop."""
+    tiles; K-steps that are a multiple of the loop's six (48 of them, whole tiles; 18 in two and in four ragged parts;
+    6); whatever the compiler made of the loop.  (300 rows: the kernel for mid-size products, the same guard.)"""
+    assert fgmp.selftest_gemm_route(M, N, K)[0] == (3 if M > 1024 else 2)
     from paper_2504_14152_amd import build
     _say(f"counted waits vs full waits {M}x{K}x{N}")
     gen = torch.Generator(device=DEV)
@@ -1327,14 +1342,17 @@ def test_decode_kernel_reads_weights_that_are_not_compact():
     assert torch.equal(Y, Ys)
 
 
-@pytest.mark.parametrize("M,K,N", [(8, 1024, 512), (8, 11008, 512), (24, 2048, 520), (300, 512, 520), (70, 1024, 512)])
+@pytest.mark.parametrize("M,K,N", [(8, 1024, 512), (8, 11008, 512), (24, 2048, 520), (300, 512, 520), (70, 1024, 512),
+                                    (1100, 1040, 520), (1100, 512, 3400)])
 def test_fused_call_replays_in_a_hip_graph(M, K, N):
     """The hot-path calls only enqueue kernels on the caller's stream (no allocation, no synchronization,
     no memset nodes: arrival counters are put back to zero by the kernels that use them), so a
     captured step can be replayed: decode shapes (one launch; with K in one part and in three parts that
-    meet at the row groups' counters; the older two-kernel path for an odd number of row-tiles), a prefill
-    shape whose tiles are computed in two parts, and a decode shape of three row chunks.  Every replay, with eager work and synchronizations in between, must
-    reproduce the eager result bit for bit."""
+    meet at the row groups' counters; the older two-kernel path for an odd number of row-tiles), mid-size products,
+    and prefill shapes whose tiles are computed in four and in two parts.  Every replay, with eager work and
+    synchronizations in between, must reproduce the eager result bit for bit."""
+    if M > 1024:
+        assert fgmp.selftest_gemm_route(M, N, K)[3:5] == ((15, 4) if N == 520 else (70, 2))
     c = _quantized_pair(M, K, N, 43, 0.1, per_elem_w=False)
     ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
     Y_eager = fgmp.quant_gemm_fused(c["xd"], c["fxd"], c["Tx"], c["sx"], c["pW"], workspace=ws).clone()

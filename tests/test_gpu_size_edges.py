@@ -72,10 +72,10 @@ def _product(M, K, N, dtype, p, seed):
     return xd, fxd, Tx, sx, pW, want, tol
 
 
-# (M, K, N): every row-group count of a tile (33 .. 128 rows); rows one past a tile; columns that end inside a lane
-# group, an odd number of 8-row weight tiles; K of one block, one K-tile, K groups without a K-tile in the last round,
-# K in several parts across workgroups; more tiles than compute units; long products of 20 to 32 rows and, with 19 rows or just
-# below N K^2 = 2^38, their neighbours in one launch
+# (M, K, N): rows one past a tile; columns that end inside a lane group, an odd number of 8-row weight tiles; K groups
+# without a K-tile in the last round, K in several parts across workgroups; long products of 20 to 32 rows and, with 19 rows or
+# just below N K^2 = 2^38, their neighbours in one launch; and the neighbours on the prefill kernel, with K of one block, one
+# and two K-tiles
 MID_SHAPES = [(33, 16, 24, "f32", 0.1), (48, 128, 264, "bf16", 0.1), (64, 4096, 136, "bf16", 0.2), (77, 2064, 503, "f32", 0.2),
               (96, 640, 72, "bf16", 0.0), (112, 1168, 1000, "bf16", 1.0), (129, 384, 40, "f32", 0.3), (200, 8192, 200, "bf16", 0.1),
               (300, 1040, 264, "bf16", 0.1), (512, 2816, 328, "bf16", 0.1), (700, 144, 136, "bf16", 0.1), (1024, 272, 72, "f32", 0.1),
@@ -99,6 +99,51 @@ def test_products_of_a_few_dozen_to_a_few_hundred_rows_match_oracle(M, K, N, dty
     assert torch.equal(fgmp.gemm(fgmp.quantize_activations(xd, fxd, Tx, sx), pW), Y)
     with fgmp.use_library(build.lib_path("fullwait")):
         assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW), Y)
+
+
+# (M, K, N), (16-row groups, 16-column groups of a wave), K shared among workgroups: every instantiation that the planner
+# uses, with and without a shared K where it uses both; the last one has 411 workgroups, more than run at once
+MID_PLANS = [((49, 160, 10), (2, 2), False), ((49, 5008, 8), (2, 2), True), ((23, 4368, 17911), (2, 3), False),
+             ((21, 12704, 4636), (2, 3), True), ((21, 3360, 26570), (2, 4), False), ((24, 12704, 6355), (2, 4), True),
+             ((40, 144, 8), (3, 2), False), ((39, 4512, 8), (3, 2), True), ((33, 160, 16503), (3, 3), False),
+             ((65, 5616, 2751), (3, 3), True), ((65, 272, 12409), (3, 4), False), ((36, 9472, 6289), (3, 4), True),
+             ((199, 160, 8), (4, 2), False), ((195, 3632, 9), (4, 2), True), ((153, 272, 5647), (4, 3), False),
+             ((194, 4128, 1347), (4, 3), True), ((160, 416, 8215), (4, 4), False), ((195, 8016, 1579), (4, 4), True),
+             ((331, 144, 8), (5, 2), False), ((327, 1856, 8), (5, 2), True), ((210, 416, 10897), (5, 3), False),
+             ((327, 2416, 1541), (5, 3), True), ((506, 144, 8), (6, 2), False), ((482, 1616, 8), (6, 2), True),
+             ((248, 416, 10953), (6, 3), False), ((482, 2432, 1388), (6, 3), True), ((875, 144, 8), (7, 2), False),
+             ((889, 1344, 8), (7, 2), True), ((297, 1952, 12322), (7, 3), False), ((963, 1600, 1054), (7, 3), True),
+             ((1017, 432, 3224), (8, 2), False), ((1011, 1552, 841), (8, 2), True), ((228, 3792, 17051), (8, 3), False),
+             ((1019, 1552, 1211), (8, 3), True), ((267, 2544, 17421), (6, 2), False)]
+
+
+@pytest.mark.parametrize("shape,groups,shared", MID_PLANS)
+def test_every_arrangement_of_the_mid_size_kernel_matches_oracle(shape, groups, shared):
+    """On 96 columns, first and last among them, within 1e-5 of the sum of magnitudes; whole results equal to a second
+    call and to the build in which every hand-counted wait is a full one, bit for bit."""
+    from paper_2504_14152_amd import build
+    M, K, N = shape
+    route = fgmp.selftest_gemm_route(M, N, K)
+    assert route[0] == 2 and route[1:3] == groups and (route[5] > 1) == shared
+    gen = torch.Generator(device=DEV).manual_seed(M + N)
+    dtype = torch.float32 if M % 2 else torch.bfloat16
+    xd = torch.randn(M, K, generator=gen, device=DEV).to(dtype)
+    wd = (torch.randn(N, K, generator=gen, device=DEV) * 0.02).to(torch.bfloat16)
+    fx, fw = torch.exp(torch.randn(K, generator=gen, device=DEV)), torch.exp(torch.randn(K, generator=gen, device=DEV))
+    sx, sw = float(xd.abs().max()) / 448.0, float(wd.abs().max()) / 448.0
+    Tx = fgmp.threshold_for_fraction(fgmp.quantize_activations(xd, fx, float("inf"), sx, want_scores=True)[1], 0.2)
+    Tw = fgmp.threshold_for_fraction(fgmp.quantize_weights(wd, fw, float("inf"), sw, want_scores=True)[1], 0.2)
+    pW = fgmp.quantize_weights(wd, fw, Tw, sw)
+    Y = fgmp.quant_gemm_fused(xd, fx, Tx, sx, pW)
+    cols = np.unique(np.linspace(0, N - 1, min(N, 96)).astype(np.int64))
+    qx = orc.quantize(xd.float().cpu().numpy(), fx.cpu().numpy(), Tx, sx)
+    qw = orc.quantize(wd[torch.from_numpy(cols).to(DEV)].float().cpu().numpy(), fw.cpu().numpy(), Tw, sw)
+    want, tol = orc.gemm(orc.dequantize(qx["codes"], qx["scales"], qx["mask"]), sx, orc.dequantize(qw["codes"], qw["scales"], qw["mask"]), sw)
+    err = np.abs(Y[:, torch.from_numpy(cols).to(DEV)].cpu().numpy().astype(np.float64) - want)
+    assert np.all(err <= tol), (err / tol).max()
+    assert torch.equal(fgmp.quant_gemm_fused(xd, fx, Tx, sx, pW), Y)
+    with fgmp.use_library(build.lib_path("fullwait")):
+        assert torch.equal(fgmp.quant_gemm_fused(xd, fx, Tx, sx, pW), Y)
 
 
 def test_products_between_decode_and_prefill_replay_in_a_graph():
@@ -151,6 +196,8 @@ def test_static_scratch_takes_products_of_more_than_32_rows():
 @pytest.mark.parametrize("M,K,N", [(1100, 256, 3400), (1100, 272, 4096), (1025, 512, 4096), (1100, 640, 3400), (1279, 1024, 3500), (1100, 1040, 3400)])
 def test_products_in_two_parts_match_oracle(M, K, N):
     """Within 1e-5 of the sum of magnitudes, and the same bits every time, whichever part comes first."""
+    route = fgmp.selftest_gemm_route(M, N, K)
+    assert route[0] == 3 and route[2] == 0 and 64 < route[3] <= 128 and route[4] == 2
     xd, fxd, Tx, sx, pW, want, tol = _product(M, K, N, "bf16", 0.1, 95)
     ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
     ws[fgmp.WORKSPACE_CONTROL_BYTES:] = 0xFF
