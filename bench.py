@@ -632,8 +632,7 @@ def main() -> int:
     if not args.no_extra:
         extra["gated_mlp_llama2_7b_M4096"] = gated_mlp()
         # row counts between the decode and the prefill configurations, on the QKV weights (HBM-cold like the
-        # decode steps): 33..256 rows run as 32-row chunks through the weight-streaming kernel or on
-        # 256-row tiles split along K, whichever the library's cost model expects to be faster
+        # decode steps): the kernel for mid-size products
         ncopies = int(600e6 // pW.buf.numel()) + 1
         pool = [fgmp.Packed(pW.buf.clone(), N, K) for _ in range(ncopies)]
         small = {}

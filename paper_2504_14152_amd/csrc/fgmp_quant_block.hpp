@@ -63,7 +63,7 @@ __device__ __forceinline__ void write_header(PackedHeader *hdr, const PackedLayo
     hdr->off_M = l.off_M;
     hdr->off_T = l.off_T;
     hdr->off_H = l.off_H;
-    hdr->h_entries = (uint64_t)l.n_tiles * kTileSlots;   // a compact tensor's scan overwrites these two
+    hdr->h_entries = (uint64_t)l.n_tiles * kTileSlots;   // (overwritten once a compact tensor's entries are counted, like the next)
     hdr->bytes_used = l.total_bytes;
 }
 

@@ -85,37 +85,37 @@ template <bool kHW, int kMode, bool kDelta>
 __device__ __forceinline__ void store_tile(const QuantParams &p, int64_t tile, int lane, bool hi, uint64_t ballot, const BlockCodes &bc,
                                            const float (&x)[16], float amax, float inv_S)
 {
-                const uint32_t prefix = (uint32_t)__popcll(ballot & ((1ull << lane) - 1ull));
-                const uint32_t hbase = (uint32_t)(tile * kTileSlots);
-                if constexpr (kMode == kModeStrided) {
-                    if (lane == 0) p.out.T[tile] = hbase;
-                }
-                if (lane == 0) p.out.M[tile] = ballot;
+    const uint32_t prefix = (uint32_t)__popcll(ballot & ((1ull << lane) - 1ull));
+    const uint32_t hbase = (uint32_t)(tile * kTileSlots);
+    if constexpr (kMode == kModeStrided) {
+        if (lane == 0) p.out.T[tile] = hbase;
+    }
+    if (lane == 0) p.out.M[tile] = ballot;
 
-                uint2 lword = make_uint2(bc.q[0], bc.q[1]);
-                uint32_t sbyte = bc.sc;
-                if (ballot != 0ull) {
-                    // values beyond the FP8 range only occur when the caller's S is below amax / 448
-                    const bool any_big = __ballot(hi && amax * inv_S > 448.0f) != 0ull;
-                    if (hi) {
-                        uint32_t c[4];
-                        if constexpr (kDelta) {
-    #pragma unroll
-                            for (int j = 0; j < 4; ++j) c[j] = bc.c8[j];
-                        } else {
-                            float r[16];
-    #pragma unroll
-                            for (int i = 0; i < 16; ++i) r[i] = x[i] * inv_S;
-                            if (any_big) encode_fp8_block<kHW, true>(r, c);
-                            else encode_fp8_block<kHW, false>(r, c);
-                        }
-                        lword = make_uint2(c[0], c[1]);
-                        if constexpr (kMode == kModeStrided) p.out.H[(uint64_t)hbase + prefix] = make_uint2(c[2], c[3]);
-                        sbyte = prefix;
-                    }
-                }
-                p.out.L[tile * kTileSlots + lane] = lword;
-                p.out.S[tile * kTileSlots + lane] = (uint8_t)sbyte;
+    uint2 lword = make_uint2(bc.q[0], bc.q[1]);
+    uint32_t sbyte = bc.sc;
+    if (ballot != 0ull) {
+        // values beyond the FP8 range only occur when the caller's S is below amax / 448
+        const bool any_big = __ballot(hi && amax * inv_S > 448.0f) != 0ull;
+        if (hi) {
+            uint32_t c[4];
+            if constexpr (kDelta) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) c[j] = bc.c8[j];
+            } else {
+                float r[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) r[i] = x[i] * inv_S;
+                if (any_big) encode_fp8_block<kHW, true>(r, c);
+                else encode_fp8_block<kHW, false>(r, c);
+            }
+            lword = make_uint2(c[0], c[1]);
+            if constexpr (kMode == kModeStrided) p.out.H[(uint64_t)hbase + prefix] = make_uint2(c[2], c[3]);
+            sbyte = prefix;
+        }
+    }
+    p.out.L[tile * kTileSlots + lane] = lword;
+    p.out.S[tile * kTileSlots + lane] = (uint8_t)sbyte;
 }
 
 // grid.x = K-tiles, grid.y = groups of 4 * rt_per_wave row-tiles; 4 waves per
@@ -774,8 +774,8 @@ __global__ __launch_bounds__(256) void clip_kernel(QuantParams p)
 //
 // A workgroup owns a run of consecutive tiles.  It finds the entries before its run by itself, counting the
 // bits of all earlier mask words (8 bytes per tile out of the L2, half of the plane on average): no counter,
-// no scan launch, no workgroup waits for another.  With kPackWgs workgroups that is under 2% of the first
-// pass for any size.  One wave per tile, one slot per lane.
+// no scan launch, no workgroup waits for another.  That reads 8 x kPackWgs / 2 bytes per tile out of the L2 -- as much as a
+// bf16 tile of W -- whatever the size, 13% of the first pass below.  One wave per tile, one slot per lane.
 // 22016 x 4096 bf16 with per-element sensitivities: counting pass 94 us, one-workgroup scan of plane T (a strided
 // walk: 160 us) and packing pass 110 us before; packing pass 114 us and this kernel 15 us (no FP8 block) or 29 us (10%).
 constexpr int kPackWaves = 16, kPackWgs = 512;
@@ -788,7 +788,7 @@ __global__ __launch_bounds__(64 * kPackWaves) void pack_upper_halves_kernel(Quan
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t n_tiles = (uint32_t)p.layout.n_tiles, n_kt = (uint32_t)p.n_kt;
     const uint32_t wg_tiles = tiles_per_wave * kPackWaves;
-    const uint32_t wg_first = blockIdx.x * wg_tiles;   // (the host checks that this fits 32 bits)
+    const uint32_t wg_first = blockIdx.x * wg_tiles;   // (under 2^32 blocks of 16 in all: the tiles fit 32 bits with room)
     const uint32_t first = wg_first + wave * tiles_per_wave < n_tiles ? wg_first + wave * tiles_per_wave : n_tiles;
     const uint32_t last = first + tiles_per_wave < n_tiles ? first + tiles_per_wave : n_tiles;
     const uint64_t *masks = p.out.M;
