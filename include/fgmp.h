@@ -243,8 +243,8 @@ fgmp_status_t fgmp_quant_gemm_fused_packed_out(const void *X, fgmp_dtype_t dt, i
  * h = (g / (1 + E(-g))) * u with a correctly rounded division (within 3 ulp of the exact value).
  * `epilogue | FGMP_EPILOGUE_ONE_LAUNCH` (with FGMP_EPILOGUE_NONE): a decode step quantizes its results
  * inside its launch whenever the one-launch kernel takes the shape (nothing is staged; a single kernel
- * per layer for callers who count launches); other shapes -- among them 20 to 32 rows of a long product,
- * N K^2 >= 2^38 -- are staged.
+ * per layer for callers who count launches); other shapes -- among them some of 20 to 32
+ * rows of a long product, N K^2 >= 2^38, which the plain call computes in two launches, too -- are staged.
  *   N          N % 64 == 0 with the gate; fisher_n, scores_y and packed_Y then refer to N/2 columns
  *   workspace  >= fgmp_workspace_bytes_packed_out_ex(M, N, K, epilogue)
  * Other arguments and errors as fgmp_quant_gemm_fused_packed_out; an unknown `epilogue` is

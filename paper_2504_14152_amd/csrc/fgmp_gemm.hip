@@ -266,13 +266,18 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
 // line is drawn too early for products whose 256 x 256 tiles leave the chip part empty: 4096 x 12288 512 rows 53 / 63, 61 / 72,
 // 68 / 74; 4096 x 22016 256 rows 51 / 61, 57 / 69, 63 / 71; 4096 x 4096 768 rows 36 / 55, 40 / 65, 44 / 68.
 //
-// Up to 32 rows the one-launch step (fgmp_gemm_stream.hip) shares K among as many workgroups as keep a part's rows in LDS --
-// 8 at K = 8192 and 32 rows -- and adds their sums in memory: from N K^2 = 2^38 (parts times weights) and 20 rows on, its
-// quantizer's launch is the cheaper price.  Microseconds per fused step, one launch / this kernel, on both sides: 11008 x 4096
-// 16 rows 18.1 / 15.8, 24 rows 20.1 / 17.2, 32 rows 18.2 / 17.2; 8192 x 4096 17 rows 14.9 / 15.5, 20 rows 16.2 / 15.6, 32 rows
-// 18.7 / 15.4; 4096 x 22016 24 rows 27.6 / 20.9, 32 rows 24.7 / 21.1; 8192 x 57344 17 rows 78 / 85, 20 rows 87 / 85, 32 rows 112 / 86;
-// 16384 x 2048 32 rows 23.9 / 16.5; 4096 x 12288 20 rows 16.9 / 16.4, 32 rows 16.1 / 16.7; 4096 x 4096 12.6 / 16.0;
-// 1024 x 32768 12.7 / 14.8.  (Only where it needs no more workspace than the step it replaces.)
+// Up to 32 rows the one-launch step (fgmp_gemm_stream.hip) shares K among as many workgroups as keep a part's rows in LDS and runs
+// through its row groups in rounds; with two rounds or more the parts meet that often, and this kernel is taken where the
+// estimates of both, for weights that come from HBM, are in its favour.  Microseconds per fused step, one launch / this kernel,
+// weights from HBM | from the Infinity Cache: 4096 x 22016 (K x N) 20 rows (3 rounds) 28.1 / 25.3 | 27.5 / 21.5, 32 rows (2)
+// 25.1 / 25.2 | 24.9 / 22.2; 8192 x 8192 20 rows (1) 19.8 / 22.0 | 20.0 / 19.6, 24 rows (7) 38.7 / 22.2 | 38 / 20; 11008 x 4096 24
+// rows (2) 20.4 / 19.9 | 20.8 / 17.9, 32 rows (1) 18.3 / 20.2 | 18.4 / 18.0; 5120 x 11008 20 rows (1) 17.3 / 21.9 | 17.5 / 18.7, 28
+// rows (5) 30.1 / 21.9; 8192 x 4096 32 rows (2) 18.9 / 17.2 | 19.2 / 16.0; 6144 x 22016 20 rows (2) 30.9 / 34.3 | 30.7 / 27.0; 16384 x
+// 2048 32 rows (2) 24.0 / 18.3 | 24.4 / 17.0.  Over 420 such steps none is more than 1.5% slower than in one launch.  (From
+// N K^2 = 2^38 on, and only where it needs no more workspace than the step it replaces.)
+//
+// Steps that take two launches anyway -- K in more than 16 parts, an odd number of row-tiles, the Eq. 8 score -- are faster on
+// this kernel throughout: 32768 x 256 32 rows 26.1 / 20.8, 11008 x 4096 with the Eq. 8 score 21.3 / 17.6.
 constexpr int64_t kMidMinRows = 20, kMidMaxRows = 1024;
 
 // its workspace behind the control region: header, FP16 activations, partial sums
@@ -295,7 +300,10 @@ GemmRoute gemm_route(int64_t M, int64_t N, int64_t K)
     r.plan = gemm_mid_plan(M, N, K);
     if (!gemm_mid_applies(r.plan, N, K)) return r;
     if (M <= 32) {
-        r.mid = mid_bytes(r.plan, K) <= (gemm_stream_applies(M, N, K) ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
+        const bool stream = gemm_stream_applies(M, N, K);
+        r.mid_two_launch = mid_bytes(r.plan, K) <= (stream ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
+        int rounds = 0;
+        r.mid = r.mid_two_launch && (!stream || (gemm_mid_few_rows_micros(r.plan, N, K) <= gemm_stream_micros(M, N, K, &rounds) && rounds > 1));
     } else {
         const double staging = 6.0 + 8.0 * (double)M * (double)N / 4.5e6;
         r.mid = gemm_mid_micros(r.plan) + staging <= gemm_mixed_micros(M, N, K);
@@ -426,11 +434,12 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
     if (((uintptr_t)workspace | (uintptr_t)packed_W | (uintptr_t)Y) % 16 != 0) return FGMP_ERR_BAD_ALIGN;
     // (the one-launch kernel addresses X with 32-bit byte offsets)
     const bool x_fits = ldx > 0 && ldx < (int64_t)0xFFFFFF00 / (M * 4);
-    const bool mid = route.mid;
+    const bool one_launch = score_mode == FGMP_SCORE_NVFP4_ERROR && x_fits && gemm_stream_applies(M, N, K);
+    const bool mid = route.mid || (route.mid_two_launch && !one_launch);
     // (the decode step quantizes its own results where the caller asks for it -- and where the plain call takes it, too: the
     // packed results are the same bit for bit either way)
     const bool stream_pack = pack_out != nullptr && !pack_out->gate && pack_out->one_launch && !mid && gemm_stream_packs(M, N, K);
-    const bool stream_fits = score_mode == FGMP_SCORE_NVFP4_ERROR && (pack_out == nullptr || stream_pack) && x_fits && gemm_stream_applies(M, N, K);
+    const bool stream_fits = one_launch && (pack_out == nullptr || stream_pack);
     const bool stream = stream_fits && !mid;
     if (workspace_bytes < (stream_fits ? (pack_out ? kWsCtrlRegion + gemm_stream_pack_scratch_bytes(M, N, K) : quant_gemm_workspace_need(M, N, K, route))
                                   : tight && M > 32 ? quant_gemm_workspace_need(M, N, K, route) : gemm_workspace_need(M, N, K, route)))

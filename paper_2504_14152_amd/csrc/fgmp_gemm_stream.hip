@@ -917,6 +917,17 @@ static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K)
 
 bool gemm_stream_applies(int64_t M, int64_t N, int64_t K) { return kUseHwCvt && stream_plan(M, N, K).ok; }
 
+// A step of 20 to 32 rows in two rounds of row groups or more, estimated, with the weights coming from HBM: what a round costs --
+// its tiles, the meetings of its parts inside the workgroup and across --, the partial sums, the bytes.  Fitted to the 361 of
+// 420 measured steps (K 4096 .. 20480, N 1024 .. 28672) that take more than one round: 5% rms, 15% at most.
+double gemm_stream_micros(int64_t M, int64_t N, int64_t K, int *rounds)
+{
+    const StreamPlan p = stream_plan(M, N, K);
+    *rounds = p.rounds;
+    return -1.0 + 0.924 * p.P_g + (1.59 + 0.467 * p.tiles_in + (p.kp_in > 1 ? 1.52 : 0.0)) * p.rounds +
+           0.25 / kStCus * (double)p.n_groups * p.P_g + 0.048e-6 * (double)N * (double)K;
+}
+
 // Scratch bytes of a call (beyond the control region); the kernel must apply.
 size_t gemm_stream_scratch_bytes(int64_t M, int64_t N, int64_t K)
 {

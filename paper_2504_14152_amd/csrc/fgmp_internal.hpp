@@ -43,8 +43,9 @@ struct MidPlan {
     size_t scratch_bytes() const { return (size_t)align_up(partial_bytes(), 256); }
 };
 struct GemmRoute {
-    bool mid;
-    MidPlan plan;   // (valid where `mid`)
+    bool mid;              // faster than what the product takes otherwise
+    bool mid_two_launch;   // ... if that is two launches as well (up to 32 rows: where the one-launch step cannot serve)
+    MidPlan plan;          // (valid where either)
 };
 GemmRoute gemm_route(int64_t M, int64_t N, int64_t K);
 fgmp_status_t gemm_packed(const void *packed_X, int64_t M, const void *packed_W, int64_t N, int64_t K,
@@ -92,6 +93,7 @@ constexpr size_t kWsCtrlRegion = FGMP_WORKSPACE_CONTROL_BYTES;
 // decoded (src 2: packed X) inside the kernel that streams the weights.
 bool gemm_stream_applies(int64_t M, int64_t N, int64_t K);
 size_t gemm_stream_scratch_bytes(int64_t M, int64_t N, int64_t K);
+double gemm_stream_micros(int64_t M, int64_t N, int64_t K, int *rounds);   // estimate of a fused step of 20 to 32 rows
 fgmp_status_t gemm_stream(int src, const void *X, int64_t ldx, const float *fisher, float T, float S, const void *packed_X,
                           int64_t M, const void *packed_W, int64_t N, int64_t K, float *Y, int64_t ldy, void *ctrl,
                           void *scratch, hipStream_t st, const PackOut *po = nullptr);
@@ -103,6 +105,7 @@ size_t gemm_stream_pack_scratch_bytes(int64_t M, int64_t N, int64_t K);
 MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K);
 bool gemm_mid_applies(const MidPlan &p, int64_t N, int64_t K);
 double gemm_mid_micros(const MidPlan &p);                    // estimate of a fused step
+double gemm_mid_few_rows_micros(const MidPlan &p, int64_t N, int64_t K);   // 20 to 32 rows
 double gemm_mixed_micros(int64_t M, int64_t N, int64_t K);   // the same on the prefill kernel
 fgmp_status_t gemm_mid(const MidPlan &p, const PackedHeader *xh, const _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
                        int64_t ldy, void *ctrl, void *scratch, hipStream_t st);

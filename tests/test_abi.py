@@ -133,6 +133,9 @@ def test_the_mid_size_shapes_cover_every_arrangement_the_planner_uses():
     assert len(seen) > 20 and seen <= named, seen - named
     # 33 to 1024 rows of the Llama-2-7B linears, and what the neighbours of the range take
     assert [fgmp.selftest_gemm_route(M, 12288, 4096)[0] for M in (1, 32, 33, 64, 4096)] == [0, 0, 2, 2, 3]
+    # up to 32 rows: one launch where a workgroup has one round of row groups, whatever the length
+    assert [fgmp.selftest_gemm_route(M, 4096, 11008)[0] for M in (20, 24, 28, 32)] == [2, 2, 0, 0]
+    assert [fgmp.selftest_gemm_route(M, 11008, 5120)[0] for M in (20, 26, 28, 32)] == [0, 0, 2, 2]
     assert fgmp.selftest_gemm_route(8, 24, 1024)[0] == 1 and fgmp.selftest_gemm_route(32, 264, 32768)[0] == 2
     assert fgmp.lib().fgmp_selftest_gemm_route(8, 24, 24, (ctypes.c_int64 * 6)()) == -2
     assert fgmp.lib().fgmp_selftest_gemm_route(8, 24, 16, None) == -1

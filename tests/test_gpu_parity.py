@@ -315,9 +315,10 @@ def test_quantize_weights_delta_score(N, K, per_elem, p):
     assert fgmp.packed_info(pk)["n_fp8_blocks"] == int(want["mask"].sum())
 
 
-@pytest.mark.parametrize("M,K,N", [(200, 304, 136), (8, 1024, 72)])
+@pytest.mark.parametrize("M,K,N", [(200, 304, 136), (8, 1024, 72), (32, 11008, 2304), (1100, 304, 136)])
 def test_fused_delta_score(M, K, N):
-    """Fused call with Eq. 8 scoring (prefill and decode shape) against the oracle."""
+    """Fused call with Eq. 8 scoring against the oracle: mid-size, decode and prefill products, and long dot products of 32
+    rows, which take one launch with the Eq. 6 score and the mid-size kernel with this one."""
     _say(f"fused delta M={M} K={K} N={N}")
     x = synth.activations(M, K, 14, 85)
     w = synth.weights(N, K, 14, 86)
