@@ -29,10 +29,10 @@
 // matrix instructions comes one operand read of the next slice and a seventh
 // of a block's decode, and the scheduler may move nothing across.  With the
 // decode in one stretch behind the first slice (its FP8 and 4-bit routes were
-// branches) a K-step took 6% more clocks: 650 thousand instead of 610 thousand
-// for 4096 x 12288 x 4096, 346 -> 336 us, and 534 -> 525 us for the gated MLP of
-// 2048 rows.  What bounds it now is power: the clock gives way as the pipe
-// fills (1.92 -> 1.84 GHz, under 2.4 nominal), and the rate is that of the
+// branches) a launch took 6% more clocks: 668 thousand instead of 628 thousand
+// for 4096 x 12288 x 4096, 337 -> 331 us per fused step, and 520 -> 511 us for
+// the gated MLP of 2048 rows, timed in turn.  What bounds it now is power: the
+// clock gives way as the pipe fills (1.99 -> 1.91 GHz of 2.4), and the rate is that of the
 // library's bf16 product of the same size.  A variant whose waves decode their
 // weights straight into matrix operands (half the LDS traffic, half as much
 // vector arithmetic again) took 3% fewer clocks and the same time.
