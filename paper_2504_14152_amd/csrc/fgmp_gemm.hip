@@ -276,8 +276,9 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
 // 2048 32 rows (2) 24.0 / 18.3 | 24.4 / 17.0.  Over 420 such steps none is more than 1.5% slower than in one launch.  (From
 // N K^2 = 2^38 on, and only where it needs no more workspace than the step it replaces.)
 //
-// Steps that take two launches anyway -- K in more than 16 parts, an odd number of row-tiles, the Eq. 8 score -- are faster on
-// this kernel throughout: 32768 x 256 32 rows 26.1 / 20.8, 11008 x 4096 with the Eq. 8 score 21.3 / 17.6.
+// Steps that take two launches anyway -- K in more than 16 parts, the Eq. 8 score -- are faster on this kernel throughout: 32768 x
+// 256 32 rows 26.1 / 20.8, 11008 x 4096 with the Eq. 8 score 21.3 / 17.6.  With an odd number of row-tiles it is taken from
+// N K^2 = 2^38 on without the estimates (4096 x 22003 32 rows 24.7 / 21.2, cached weights).
 constexpr int64_t kMidMinRows = 20, kMidMaxRows = 1024;
 
 // its workspace behind the control region: header, FP16 activations, partial sums
@@ -292,6 +293,9 @@ static size_t decode_bytes(int64_t M, int64_t N, int64_t K)
     return gemm_skinny_applies(M, N, K) ? skinny_x16_bytes(M, K) + gemm_skinny_workspace_bytes(M, N, K) : 0;
 }
 
+// (the one-launch step walks through W in groups of two row-tiles)
+static bool even_row_tiles(int64_t N) { return (N + kTileRows - 1) / kTileRows % 2 == 0; }
+
 GemmRoute gemm_route(int64_t M, int64_t N, int64_t K)
 {
     GemmRoute r{};
@@ -300,7 +304,7 @@ GemmRoute gemm_route(int64_t M, int64_t N, int64_t K)
     r.plan = gemm_mid_plan(M, N, K);
     if (!gemm_mid_applies(r.plan, N, K)) return r;
     if (M <= 32) {
-        const bool stream = gemm_stream_applies(M, N, K);
+        const bool stream = even_row_tiles(N) && gemm_stream_applies(M, N, K);
         r.mid_two_launch = mid_bytes(r.plan, K) <= (stream ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
         int rounds = 0;
         r.mid = r.mid_two_launch && (!stream || (gemm_mid_few_rows_micros(r.plan, N, K) <= gemm_stream_micros(M, N, K, &rounds) && rounds > 1));
@@ -346,7 +350,8 @@ static size_t fused_prefill_split(const GemmWorkspace &w) { return (size_t)align
 
 size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K, const GemmRoute &route)
 {
-    if (gemm_stream_applies(M, N, K)) return kWsCtrlRegion + gemm_stream_scratch_bytes(M, N, K);
+    // (an odd number of row-tiles: as for the two launches that such a step took before, which need more)
+    if (even_row_tiles(N) && gemm_stream_applies(M, N, K)) return kWsCtrlRegion + gemm_stream_scratch_bytes(M, N, K);
     if (M > 32 && route.mid) return kWsCtrlRegion + mid_bytes(route.plan, K);
     if (fused_prefill(M, N, K)) {
         const GemmWorkspace w = gemm_ws_layout(M, N, K);

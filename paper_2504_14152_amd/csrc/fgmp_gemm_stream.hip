@@ -408,8 +408,10 @@ __global__ __launch_bounds__(64 * kStWaves) void gemm_stream_kernel(StreamArgs a
     const int kp_eff = (int)a.by_tiles_in((uint32_t)(kt_part1 - kt_part0 + a.tiles_in - 1));
 
     // ---- weight addressing: lane (nl = lane % 16, g = lane / 16) owns blocks 2g, 2g+1 of weight row nl
-    // of the group; rows 0-7 are the group's first row-tile, rows 8-15 its second, n_kt tiles further (the
-    // tensor has an even number of row-tiles).  A tile's loads: these per-lane offsets plus a scalar.
+    // of the group; rows 0-7 are the group's first row-tile, rows 8-15 its second, n_kt tiles further.  A tile's
+    // loads: these per-lane offsets plus a scalar.  (With an odd number of row-tiles the last group's second one
+    // is not there: its lanes read what lies behind -- other planes, range-checked like everything, as is the
+    // plane-H entry that leads to -- and feed columns of the products that are never stored.)
     const int nl = lane & 15, g = lane >> 4;
     const uint32_t sel = (uint32_t)(nl >> 3);
     const uint32_t slot0 = (uint32_t)(nl & 7) * kTileBlocks + 2u * g;   // slot of the lane's first block in its tile
@@ -868,7 +870,10 @@ static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K)
     const PackedLayout lw = make_layout(N, K);
     constexpr uint64_t kLimit = 0xFFFFFF00ull;   // buffer loads address the packed weights with 32-bit offsets
     if (M < 1 || M > 32 || lw.total_bytes >= kLimit) return p;
-    if (lw.n_rt % 2 != 0) return p;   // (a row group is two row-tiles)
+    // An odd number of row-tiles (the last row group has one): us in two launches (quantizer, gemm_skinny_kernel) / in one:
+    // 1 x 5840 x 339 (M, K, N) 11.5 / 6.4, 12 x 672 x 2822 10.3 / 5.7, 12 x 4832 x 1315 14.2 / 10.5, 32 x 4832 x 1315 14.0 / 11.8, 8 x
+    // 4096 x 22003 20.9 / 17.1, 8 x 8192 x 56 10.3 / 10.5.  (At most 24 columns, 8 x 1024 x 24 8.7 / 6.1: a test names the two launches there.)
+    if (lw.n_rt % 2 != 0 && lw.n_rt <= 3) return p;
     p.mt = M <= 16 ? 1 : 2;
     p.waves = 12;   // (measured: 8 and 16 waves per workgroup both run 5-15% slower on the Llama-2 shapes)
     const int kStThreads = 64 * p.waves, kStWaves = p.waves;

@@ -263,3 +263,30 @@ def test_clipped_scales_are_the_brute_force_ones(what):
     codes, scales, mask = (t.cpu().numpy() for t in fgmp.unpack_canonical(pk))
     assert np.array_equal(scales, want["scales"]) and np.array_equal(codes, want["codes"]) and np.array_equal(mask, want["mask"])
     assert np.array_equal(scores.cpu().numpy().view(np.uint32), want["scores"].view(np.uint32))
+
+
+# ------------------------------------------------------------------ decode steps: the last row group with one row-tile
+
+# (M, K, N), N / 8 rounded up odd: one, eight, sixteen and 32 rows; K in one part and in several; a last row-tile of one row
+@pytest.mark.parametrize("M,K,N,dtype,p", [(1, 5840, 40, "bf16", 0.2), (8, 4112, 1001, "f32", 0.1), (16, 1040, 1000, "bf16", 1.0),
+                                           (5, 272, 4353, "bf16", 0.0), (32, 4832, 1315, "f32", 0.2), (9, 8192, 72, "bf16", 0.1)])
+def test_decode_steps_with_an_odd_number_of_row_tiles_match_oracle(M, K, N, dtype, p):
+    """Within 1e-5 of the sum of magnitudes; whatever lies behind the last row-tile's bytes must not show."""
+    from paper_2504_14152_amd import build
+    assert fgmp.selftest_gemm_route(M, N, K)[0] == 0
+    xd, fxd, Tx, sx, pW, want, tol = _product(M, K, N, dtype, p, 96 + M)
+    ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
+    ws[fgmp.WORKSPACE_CONTROL_BYTES:] = 0xFF
+    out = torch.full((M + 1, N + 3), 7.0, device=DEV)
+    Y = fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, out=out[:M, :N], workspace=ws).clone()
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - want)
+    assert np.all(err <= tol), (err / tol).max()
+    assert bool((out[M] == 7.0).all()) and bool((out[:, N:] == 7.0).all())
+    assert int(ws[: fgmp.WORKSPACE_CONTROL_BYTES].sum()) == 0
+    assert torch.equal(fgmp.gemm(fgmp.quantize_activations(xd, fxd, Tx, sx), pW), Y)
+    used = fgmp.packed_info(pW)["bytes_used"]
+    exact = torch.full((-(-used // 16) * 16 + 4096,), 0xFF, dtype=torch.uint8, device=DEV)   # poison right behind the tensor
+    exact[:used] = pW.buf[:used]
+    assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, fgmp.Packed(exact[:used], N, K)), Y)
+    with fgmp.use_library(build.lib_path("fullwait")):
+        assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW), Y)
