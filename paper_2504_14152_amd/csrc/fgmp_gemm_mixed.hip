@@ -490,19 +490,30 @@ __global__ __launch_bounds__(kWM *kWN * 64, 1) void gemm_mixed_kernel(const _Flo
             return;
     }
     if constexpr (!kPackOut) {
+        auto store = [&](auto streaming) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int64_t col = tn * kBN + wn * (TN * 32) + j * 32 + (lane & 31);
+                for (int j = 0; j < TN; ++j) {
+                    const int64_t col = tn * kBN + wn * (TN * 32) + j * 32 + (lane & 31);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int64_t row = tm * kBM + wm * (TM * 32) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    // (streaming stores: the 4 M N bytes of results are not read again here and would only push
-                    // operand panels out of the caches: 1.5% on the Llama-2-7B shapes)
-                    if (row < M && col < N) __builtin_nontemporal_store(acc[i][j][r] * ss, &Y[row * ldy + col]);
+                    for (int r = 0; r < 16; ++r) {
+                        const int64_t row = tm * kBM + wm * (TM * 32) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                        if (row < M && col < N) {
+                            if constexpr (decltype(streaming)::value) __builtin_nontemporal_store(acc[i][j][r] * ss, &Y[row * ldy + col]);
+                            else Y[row * ldy + col] = acc[i][j][r] * ss;
+                        }
+                    }
                 }
-            }
+        };
+        // Streaming stores: the 4 M N bytes of results are not read again here and would only push operand panels out of the
+        // caches: 1.5% on the Llama-2-7B shapes.  Where rows do not start on a cache line the 32 columns of a store are parts of
+        // two, though, which then reach memory one by one instead of whole: beyond 16 MB, where the stores bound the tail of
+        // a tile, ordinary ones, streaming / ordinary, us: 1233 x 1088 x 19268 (M, K, N) 111.9 / 76.3, 3150 x 560 x 11325 144 / 87,
+        // 2702 x 6224 x 6083 248 / 222, 4048 x 2784 x 1182 (19 MB) 58.4 / 56.9.  Below, streaming ones start their way to memory
+        // earlier: 1116 x 2832 x 2628 (12 MB) 56.6 / 59.2, 3539 x 560 x 668 37.4 / 38.6.
+        if ((((uintptr_t)Y | (uintptr_t)ldy * 4u) & 127u) == 0 || M * N <= (int64_t)4 << 20) store(std::integral_constant<bool, true>{});
+        else store(std::integral_constant<bool, false>{});
     } else {
         // Each 32 x 32 accumulator tile is transposed through LDS (wave-private, the operand stages are
         // free now) so that a lane owns one output block: (row = lane % 32, 16 columns = lane / 32).  The

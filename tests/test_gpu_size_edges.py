@@ -290,3 +290,18 @@ def test_decode_steps_with_an_odd_number_of_row_tiles_match_oracle(M, K, N, dtyp
     assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, fgmp.Packed(exact[:used], N, K)), Y)
     with fgmp.use_library(build.lib_path("fullwait")):
         assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW), Y)
+
+
+# ------------------------------------------------------------------ prefill results whose rows do not start on a cache line
+
+# more than 16 MB of results (ordinary stores) and less (streaming ones), both with rows that start anywhere
+@pytest.mark.parametrize("M,K,N", [(1100, 48, 4099), (1100, 48, 1033)])
+def test_prefill_results_in_rows_of_any_alignment_match_oracle(M, K, N):
+    xd, fxd, Tx, sx, pW, want, tol = _product(M, K, N, "bf16", 0.1, 97)
+    assert fgmp.selftest_gemm_route(M, N, K)[0] == 3
+    out = torch.full((M, N + 1), 7.0, device=DEV)
+    Y = fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, out=out[:, :N])
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - want)
+    assert np.all(err <= tol), (err / tol).max()
+    assert bool((out[:, N] == 7.0).all())
+    assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW), Y)
