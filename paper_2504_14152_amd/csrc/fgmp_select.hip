@@ -28,10 +28,10 @@ constexpr int kSelPasses = 3, kSelBins = 2048;
 constexpr int kSelThreads = 1024, kSelCopies = 8, kSelMaxWgs = 256;   // 8 x 2048 bins: 64 KB of LDS; two waves share a copy
 
 struct SelectState {
-    unsigned long long hist[kSelPasses][kSelBins];   // zeroed by select_init_kernel
+    unsigned long long hist[kSelPasses][kSelBins];   // zero between selections: the workgroup that reads a pass's bins clears them
     unsigned long long rank;        // wanted element, counted from the smallest among those that match the prefix
     uint32_t prefix;                // digits found so far
-    uint32_t arrived;               // workgroups of the pass in progress that have merged their bins
+    uint32_t arrived;               // workgroups of the pass in progress that have merged their bins; zero between passes
     float result;
 };
 
@@ -52,7 +52,8 @@ __device__ inline float value_of(uint32_t key)
 
 // The workgroup that arrives last (all bins of the pass are merged): the bin that holds the wanted rank becomes
 // the next digit of the prefix.
-template <int kPass> __device__ __forceinline__ void narrow(SelectState *st, unsigned long long *part)
+template <int kPass>
+__device__ __forceinline__ void narrow(SelectState *st, unsigned long long wanted, float *result_host, unsigned long long *part)
 {
     constexpr int kBins = 1 << sel_bits(kPass), kPer = kBins / kSelThreads;
     static_assert(kPer >= 1, "a thread owns at least one bin");
@@ -63,6 +64,9 @@ template <int kPass> __device__ __forceinline__ void narrow(SelectState *st, uns
         h[i] = __hip_atomic_load(&st->hist[kPass][tid * kPer + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         sum += h[i];
     }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+        if (h[i] != 0ull) __hip_atomic_store(&st->hist[kPass][tid * kPer + i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned long long incl = sum;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -70,8 +74,8 @@ template <int kPass> __device__ __forceinline__ void narrow(SelectState *st, uns
         incl += lane >= d ? v : 0ull;
     }
     if (lane == 63) part[wave] = incl;
-    const unsigned long long rank = st->rank;   // (written before this launch)
-    const uint32_t prefix = st->prefix;
+    const unsigned long long rank = kPass == 0 ? wanted : st->rank;   // (written by the pass before)
+    const uint32_t prefix = kPass == 0 ? 0u : st->prefix;
     __syncthreads();
     unsigned long long below = incl - sum;
     for (int w = 0; w < wave; ++w) below += part[w];
@@ -82,7 +86,10 @@ template <int kPass> __device__ __forceinline__ void narrow(SelectState *st, uns
             const uint32_t p = prefix | ((uint32_t)(tid * kPer + i) << sel_shift(kPass));
             st->rank = rank - below;
             st->prefix = p;
-            if (kPass == kSelPasses - 1) st->result = value_of(p);
+            if (kPass == kSelPasses - 1) {
+                st->result = value_of(p);
+                if (result_host != nullptr) __hip_atomic_store(result_host, value_of(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
         }
         below += h[i];
     }
@@ -91,7 +98,8 @@ template <int kPass> __device__ __forceinline__ void narrow(SelectState *st, uns
 
 // One pass over one array; `n_wgs` workgroups take part in the pass over all arrays together.
 template <int kPass>
-__global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *__restrict__ s, int64_t n, uint32_t n_wgs, SelectState *st)
+__global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *__restrict__ s, int64_t n, uint32_t n_wgs, SelectState *st,
+                                                                   unsigned long long wanted, float *result_host)
 {
     constexpr int kBins = 1 << sel_bits(kPass), kShift = sel_shift(kPass);
     constexpr uint32_t kHigher = kPass == 0 ? 0u : ~0u << sel_shift(kPass - 1);   // bits of the digits found before
@@ -150,26 +158,73 @@ __global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *
     if (tid == 0)
         last = __hip_atomic_fetch_add(&st->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_wgs - 1u;
     __syncthreads();
-    if (last) narrow<kPass>(st, reinterpret_cast<unsigned long long *>(&bins[0][0]));
+    if (last) narrow<kPass>(st, wanted, result_host, reinterpret_cast<unsigned long long *>(&bins[0][0]));
 }
 
-__global__ __launch_bounds__(256) void select_init_kernel(SelectState *st, unsigned long long rank)
+__global__ __launch_bounds__(256) void select_init_kernel(SelectState *st)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < kSelPasses * kSelBins) (&st->hist[0][0])[i] = 0ull;
-    if (i == 0) {
-        st->rank = rank;
-        st->prefix = 0u;
-        st->arrived = 0u;
-        st->result = 0.0f;
-    }
+    if (i == 0) st->arrived = 0u;
 }
 
 template <int kPass>
-void launch_count(const float *s, int64_t n, unsigned grid, uint32_t n_wgs, SelectState *state, hipStream_t st)
+void launch_count(const float *s, int64_t n, unsigned grid, uint32_t n_wgs, SelectState *state, unsigned long long wanted, float *result_host,
+                  hipStream_t st)
 {
-    hipLaunchKernelGGL((select_count_kernel<kPass>), dim3(grid), dim3(kSelThreads), 0, st, s, n, n_wgs, state);
+    hipLaunchKernelGGL((select_count_kernel<kPass>), dim3(grid), dim3(kSelThreads), 0, st, s, n, n_wgs, state, wanted, result_host);
 }
+
+// States that selections borrow, and a pinned word each for the result.  A state allocated and freed per call, cleared by a
+// launch of its own and its result copied to pageable memory: scoring, selecting and packing 1193 x 832 weights 93 us, now 50;
+// 3302 x 2560 106 / 66; 22016 x 4096 374 / 320.  Up to kSelSlots selections per GPU run at a time on these (each holds its own
+// from before its first launch until its stream has been waited for); a further one allocates its state.  The states are part of
+// the module, the result words one allocation of the process.
+constexpr int kSelSlots = 8, kMaxDevices = 64;
+__device__ SelectState g_states[kSelSlots];   // zero when the library is loaded
+std::atomic<uint32_t> g_taken[kMaxDevices];   // slots in use, one bit each
+
+float *result_words()
+{
+    static float *const words = [] {
+        void *p = nullptr;
+        return hipHostMalloc(&p, (size_t)kMaxDevices * kSelSlots * 64, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess
+                   ? static_cast<float *>(p)
+                   : nullptr;
+    }();
+    return words;
+}
+
+struct SelectLease {
+    SelectState *state = nullptr;
+    float *result_host = nullptr;   // null: the state was allocated, and the result is copied from there
+    int dev = -1, slot = -1;
+    bool take()
+    {
+        if (hipGetDevice(&dev) != hipSuccess) return false;
+        SelectState *all = nullptr;
+        if (dev >= 0 && dev < kMaxDevices && result_words() != nullptr &&
+            hipGetSymbolAddress(reinterpret_cast<void **>(&all), HIP_SYMBOL(g_states)) == hipSuccess && all != nullptr) {
+            uint32_t seen = g_taken[dev].load(std::memory_order_relaxed);
+            while (seen != (1u << kSelSlots) - 1u) {
+                const int free = __builtin_ctz(~seen);
+                if (g_taken[dev].compare_exchange_weak(seen, seen | (1u << free), std::memory_order_acquire)) {
+                    slot = free;
+                    state = all + slot;
+                    result_host = result_words() + ((size_t)dev * kSelSlots + slot) * 16;
+                    return true;
+                }
+            }
+        }
+        return hipMalloc(reinterpret_cast<void **>(&state), sizeof(SelectState)) == hipSuccess;
+    }
+    // (a state that a failed selection may have left other than zero is not used again)
+    void give_back(bool clean)
+    {
+        if (slot < 0) (void)hipFree(state);
+        else if (clean) g_taken[dev].fetch_and(~(1u << slot), std::memory_order_release);
+    }
+};
 
 // one workgroup per compute unit at most, and not more than have four quads per thread to read
 unsigned count_grid(int64_t n) { return (unsigned)std::min<int64_t>(kSelMaxWgs, (n / 4 + 4 * kSelThreads) / (4 * kSelThreads)); }
@@ -183,23 +238,30 @@ fgmp_status_t select_rank(const float *const *scores, const int64_t *counts, int
     uint64_t n_wgs = 0;
     for (int32_t i = 0; i < n_tensors; ++i) n_wgs += count_grid(counts[i]);
     if (n_wgs > 0xFFFFFFFFull) return FGMP_ERR_UNSUPPORTED;
-    SelectState *state = nullptr;
-    if (hipMalloc(&state, sizeof(SelectState)) != hipSuccess) return FGMP_ERR_HIP;
+    // (a stream that is being captured cannot be waited for)
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return FGMP_ERR_HIP;
+    SelectLease lease;
+    if (!lease.take()) return FGMP_ERR_HIP;
     fgmp_status_t rc = FGMP_OK;
-    hipLaunchKernelGGL(select_init_kernel, dim3((kSelPasses * kSelBins + 255) / 256), dim3(256), 0, st, state, (unsigned long long)rank);
+    if (lease.result_host != nullptr) *lease.result_host = 0.0f;
+    else hipLaunchKernelGGL(select_init_kernel, dim3((kSelPasses * kSelBins + 255) / 256), dim3(256), 0, st, lease.state);
     for (int pass = 0; pass < kSelPasses && rc == FGMP_OK; ++pass) {
         for (int32_t i = 0; i < n_tensors; ++i) {
             const unsigned grid = count_grid(counts[i]);
-            if (pass == 0) launch_count<0>(scores[i], counts[i], grid, (uint32_t)n_wgs, state, st);
-            else if (pass == 1) launch_count<1>(scores[i], counts[i], grid, (uint32_t)n_wgs, state, st);
-            else launch_count<2>(scores[i], counts[i], grid, (uint32_t)n_wgs, state, st);
+            const unsigned long long wanted = (unsigned long long)rank;
+            if (pass == 0) launch_count<0>(scores[i], counts[i], grid, (uint32_t)n_wgs, lease.state, wanted, lease.result_host, st);
+            else if (pass == 1) launch_count<1>(scores[i], counts[i], grid, (uint32_t)n_wgs, lease.state, wanted, lease.result_host, st);
+            else launch_count<2>(scores[i], counts[i], grid, (uint32_t)n_wgs, lease.state, wanted, lease.result_host, st);
         }
         if (hipGetLastError() != hipSuccess) rc = FGMP_ERR_HIP;
     }
-    if (rc == FGMP_OK && hipMemcpyAsync(result_host, &state->result, sizeof(float), hipMemcpyDeviceToHost, st) != hipSuccess)
+    if (rc == FGMP_OK && lease.result_host == nullptr &&
+        hipMemcpyAsync(result_host, &lease.state->result, sizeof(float), hipMemcpyDeviceToHost, st) != hipSuccess)
         rc = FGMP_ERR_HIP;
     if (hipStreamSynchronize(st) != hipSuccess) rc = FGMP_ERR_HIP;
-    (void)hipFree(state);
+    if (rc == FGMP_OK && lease.result_host != nullptr) *result_host = *static_cast<volatile float *>(lease.result_host);
+    lease.give_back(rc == FGMP_OK);
     return rc;
 }
 

@@ -305,3 +305,35 @@ def test_prefill_results_in_rows_of_any_alignment_match_oracle(M, K, N):
     assert np.all(err <= tol), (err / tol).max()
     assert bool((out[:, N] == 7.0).all())
     assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW), Y)
+
+
+# ------------------------------------------------------------------ selecting thresholds: states that calls borrow
+
+def test_more_selections_at_a_time_than_there_are_states_are_exact():
+    """Twelve threads on streams of their own, eight states; and a selection refused under capture leaves everything usable."""
+    import threading
+    gen = torch.Generator(device=DEV).manual_seed(98)
+    scores = [torch.randn(20011 + 4096 * i, generator=gen, device=DEV) ** 2 for i in range(12)]
+    want = [orc.threshold(s.cpu().numpy(), 0.1) for s in scores]
+    got = [[] for _ in scores]
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(20):
+                got[i].append(fgmp.threshold_for_fraction(scores[i], 0.1))
+
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(scores))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert all(g == [w] * 20 for g, w in zip(got, want))
+    g, x = torch.cuda.CUDAGraph(), torch.zeros(4, device=DEV)
+    with torch.cuda.graph(g):
+        x.add_(1.0)
+        with pytest.raises(fgmp.FgmpError):
+            fgmp.threshold_for_fraction(scores[0], 0.1)
+    g.replay()
+    torch.cuda.synchronize()
+    assert bool((x == 1.0).all()) and fgmp.threshold_for_fraction(scores[0], 0.1) == want[0]
