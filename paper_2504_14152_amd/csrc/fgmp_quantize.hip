@@ -36,6 +36,7 @@ struct QuantParams {
     uint32_t *zero;        // words cleared by the first workgroup (counters of the kernel that follows)
     int zero_n;
     bool delta;            // Eq. 8 scoring (see quantize_kernel)
+    bool no_fp8;           // the threshold is +inf: no block is kept in FP8, and the first pass of packing weights is the only one
 };
 
 // kModeCompact leaves planes T and H to pack_upper_halves_kernel.
@@ -79,6 +80,18 @@ __device__ __forceinline__ void widen(const RawBlock<float> &r, float (&x)[16])
     }
 }
 
+// bytes_used of a compact tensor: at least one entry stays readable, kernels that load plane H unconditionally read entry 0
+__device__ __forceinline__ uint64_t compact_bytes(const PackedLayout &l, uint64_t entries) { return l.off_H + (entries > 0 ? entries : 1) * 8; }
+
+__device__ __forceinline__ void write_packed_header(const QuantParams &p)
+{
+    write_header(p.out.hdr, p.layout, p.S, p.compact);
+    if (p.no_fp8) {
+        p.out.hdr->h_entries = 0;
+        p.out.hdr->bytes_used = compact_bytes(p.layout, 0);
+    }
+}
+
 // The planes of one tile, a slot per lane: plane M and the slots' plane-L words and plane-S bytes; in strided mode also planes
 // T and H.  hi: the block is kept in FP8 (ballot: of all lanes).
 template <bool kHW, int kMode, bool kDelta>
@@ -91,6 +104,9 @@ __device__ __forceinline__ void store_tile(const QuantParams &p, int64_t tile, i
         if (lane == 0) p.out.T[tile] = hbase;
     }
     if (lane == 0) p.out.M[tile] = ballot;
+    if constexpr (kMode == kModeCompact) {
+        if (p.no_fp8 && lane == 0) p.out.T[tile] = 0u;
+    }
 
     uint2 lword = make_uint2(bc.q[0], bc.q[1]);
     uint32_t sbyte = bc.sc;
@@ -146,7 +162,7 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantParams p)
     const float inv_S = 1.0f / p.S;
     const float S6 = 6.0f * p.S;
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && p.out.hdr != nullptr)
-        write_header(p.out.hdr, p.layout, p.S, p.compact);
+        write_packed_header(p);
     if (blockIdx.x == 0 && blockIdx.y == 0)
         for (int i = threadIdx.x; i < p.zero_n; i += 256) p.zero[i] = 0u;
 
@@ -607,7 +623,7 @@ __global__ __launch_bounds__(256) void clip_kernel(QuantParams p)
     const int64_t kb = kt * kTileBlocks + (lane & 7);
     const int64_t rt = (int64_t)blockIdx.y * 4 + wave;
     const int64_t row = rt * kTileRows + (lane >> 3);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) write_header(p.out.hdr, p.layout, p.S, p.compact);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) write_packed_header(p);
     if (rt >= p.n_rt) return;
     const bool inside = kb < p.nb && row < p.rows;
     float x[16], f[16];
@@ -767,7 +783,7 @@ __global__ __launch_bounds__(256) void clip_kernel(QuantParams p)
     store_tile<kHW, kModeCompact, false>(p, rt * p.n_kt + kt, lane, hi, __ballot(hi), bc, x, amax, inv_S);
 }
 
-// Second and last pass of packing weights (compact): plane T -- the exclusive prefix sum over the tiles of
+// Second and last pass of packing weights (compact; none with a threshold of +inf): plane T -- the exclusive prefix sum over the tiles of
 // their numbers of FP8 slots, from plane M --, plane H, and the header fields that depend on the total.  The
 // FP8 upper halves are encoded from W once more, which touches only the rows' FP8 blocks: at 10% a fifth of
 // W and none of the sensitivities, where a counting pass ahead of the packing pass reads all of both.
@@ -900,8 +916,7 @@ __global__ __launch_bounds__(64 * kPackWaves) void pack_upper_halves_kernel(Quan
     // the wave that ends the tensor knows the total
     if (last == n_tiles && first < last && lane == 0) {
         p.out.hdr->h_entries = at;
-        // at least one entry stays readable: kernels that load plane H unconditionally read entry 0
-        p.out.hdr->bytes_used = p.layout.off_H + (uint64_t)(at > 0 ? at : 1) * 8;
+        p.out.hdr->bytes_used = compact_bytes(p.layout, at);
     }
 }
 
@@ -1039,6 +1054,7 @@ fgmp_status_t quantize_tensor(const void *X, fgmp_dtype_t dt, int64_t rows, int6
     if (zero_n < 0 || zero_n > 0x7FFFFFFF || (zero_n > 0 && !zero)) return FGMP_ERR_INVALID_ARG;
     p.zero = zero; p.zero_n = (int)zero_n;
     p.delta = score_mode == FGMP_SCORE_DELTA;
+    p.no_fp8 = compact && T == INFINITY;
     // clipping is defined with the NVFP4-error score, for weights
     const int64_t clip_gy = (l.n_rt + 3) / 4;
     if (clip && (p.delta || !compact || clip_gy > 65535)) return FGMP_ERR_UNSUPPORTED;
@@ -1105,6 +1121,9 @@ fgmp_status_t quantize_tensor(const void *X, fgmp_dtype_t dt, int64_t rows, int6
             else hipLaunchKernelGGL((clip_kernel<uint16_t, false, kUseHwCvt>), cgrid, dim3(256), 0, st, p);
         } else if (dt == FGMP_F32) launch_quantize<float>(p, per_elem, grid, st);
         else launch_quantize<uint16_t>(p, per_elem, grid, st);
+        // Scoring a tensor before its threshold is known: no block is kept in FP8, and the pass above has written what follows
+        // from that.  22016 x 4096 bf16 with per-element sensitivities: 114 us instead of 114 + 22.
+        if (p.no_fp8) return hipGetLastError() == hipSuccess ? FGMP_OK : FGMP_ERR_HIP;
         const int64_t waves = (int64_t)kPackWgs * kPackWaves;
         const uint32_t tiles_per_wave = (uint32_t)((l.n_tiles + waves - 1) / waves);
         const int64_t wg_tiles = (int64_t)tiles_per_wave * kPackWaves;

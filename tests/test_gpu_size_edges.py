@@ -337,3 +337,21 @@ def test_more_selections_at_a_time_than_there_are_states_are_exact():
     g.replay()
     torch.cuda.synchronize()
     assert bool((x == 1.0).all()) and fgmp.threshold_for_fraction(scores[0], 0.1) == want[0]
+
+
+# ------------------------------------------------------------------ packing weights with no block in FP8
+
+@pytest.mark.parametrize("rows,K", [(1, 16), (9, 144), (520, 2064)])
+@pytest.mark.parametrize("clip", [False, True])
+def test_weights_packed_with_an_infinite_threshold_hold_no_upper_half(rows, K, clip):
+    """Written in one pass; the same bytes as with a threshold that no score exceeds, in a buffer that held something else."""
+    g = torch.Generator(device=DEV).manual_seed(rows + K)
+    w = torch.randn(rows, K, generator=g, device=DEV)
+    f = torch.exp(torch.randn(rows, K, generator=g, device=DEV))
+    s = float(w.abs().max()) / 448.0
+    pack = fgmp.quantize_weights_clip if clip else fgmp.quantize_weights
+    bufs = [torch.full((fgmp.packed_bytes(rows, K),), v, dtype=torch.uint8, device=DEV) for v in (0xA5, 0xA5)]
+    for buf, T in zip(bufs, (float("inf"), 3.0e38)):
+        pack(w, f, T, s, out=fgmp.Packed(buf, rows, K))
+    assert torch.equal(*bufs)
+    assert fgmp.packed_info(fgmp.Packed(bufs[0], rows, K))["n_fp8_blocks"] == 0
