@@ -535,18 +535,6 @@ size_t gemm_workspace_bytes_packed_out(int64_t M, int64_t N, int64_t K, int epil
     return (size_t)align_up(gemm_workspace_bytes(M, N, K), 256) + staging_bytes(M, N, epilogue);
 }
 
-// h[m][32 q + c] = SiLU(y[m][64 q + c]) * y[m][64 q + 32 + c]: the gated activation over a staged product
-// (the shapes whose GEMM epilogue cannot apply it)
-__global__ __launch_bounds__(256) void silu_gate_kernel(const float *__restrict__ y, int64_t ldy, int64_t M,
-                                                         int64_t n_out, float *__restrict__ h)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= M * n_out) return;
-    const int64_t m = i / n_out, c = i % n_out;
-    const float *row = y + m * ldy + (c / 32) * kGateGroup + (c % 32);
-    h[i] = silu_mul(row[0], row[32]);
-}
-
 fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, int64_t ldx,
                                     const float *fisher_k, float threshold, float scale_x, const void *packed_W,
                                     int64_t N, const float *fisher_n, float threshold_y, float scale_y,
@@ -587,15 +575,9 @@ fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, i
     rc = quant_gemm(X, dt, M, K, ldx, fisher_k, threshold, scale_x, packed_W, N, Yf, N, workspace, base_bytes, st, route,
                     FGMP_SCORE_NVFP4_ERROR, nullptr);
     if (rc != FGMP_OK) return rc;
-    if (gate) {
-        float *Hf = Yf + align_up((uint64_t)M * N * 4, 256) / 4;
-        const int64_t n = M * n_out;
-        hipLaunchKernelGGL(silu_gate_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, Yf, N, M, n_out, Hf);
-        if (hipGetLastError() != hipSuccess) return FGMP_ERR_HIP;
-        Yf = Hf;
-    }
-    return quantize_tensor(Yf, FGMP_F32, M, n_out, n_out, fisher_n, 0, threshold_y, scale_y, packed_Y, packed_Y_bytes,
-                           scores_y, /*compact=*/false, st);
+    // (the gated activation is applied by the quantizer as it reads the staged product)
+    return quantize_tensor(Yf, FGMP_F32, M, n_out, N, fisher_n, 0, threshold_y, scale_y, packed_Y, packed_Y_bytes, scores_y,
+                           /*compact=*/false, st, nullptr, 0, nullptr, 0, FGMP_SCORE_NVFP4_ERROR, /*clip=*/false, gate);
 }
 
 // The order of quant_gemm's decisions, for tests.

@@ -23,7 +23,7 @@ fgmp_status_t quantize_tensor(const void *X, fgmp_dtype_t dt, int64_t rows, int6
                               size_t packed_bytes, float *scores, bool compact, hipStream_t st,
                               _Float16 *x16 = nullptr, int64_t ld16 = 0, uint32_t *zero = nullptr,
                               int64_t zero_n = 0, int score_mode = FGMP_SCORE_NVFP4_ERROR,
-                              bool clip = false);
+                              bool clip = false, bool gated = false);
 #ifdef FGMP_MEASUREMENT_HOOKS
 fgmp_status_t quantize_traffic_model(const void *X, fgmp_dtype_t dt, int64_t rows, int64_t K, int64_t ldx, const float *fisher,
                                      void *packed, size_t packed_bytes, hipStream_t st);
