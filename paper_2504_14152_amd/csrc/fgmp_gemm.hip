@@ -227,6 +227,9 @@ static GemmWorkspace gemm_ws_layout(int64_t M, int64_t N, int64_t K)
     return w;
 }
 
+// (the fused call on the prefill kernel: header, FP16 activations, then what a split last round needs)
+static size_t fused_prefill_split(const GemmWorkspace &w) { return (size_t)align_up((uint64_t)kHeaderBytes + w.off_b, 256); }
+
 // The prefill kernel decodes the weights inside the MFMA kernel.  Builds with FGMP_MEASUREMENT_HOOKS
 // (never the shipped library) can select the two-pass path instead -- both operands expanded to FP16
 // in the workspace, then a plain FP16 kernel -- with FGMP_PREFILL_KERNEL=dense in the environment.
@@ -256,15 +259,17 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
     return (size_t)align_up((uint64_t)gemm_skinny_x16_rows(M) * round_up(K, kTileK) * 2, 256);
 }
 
-// Products of a few dozen to a few hundred rows (fgmp_gemm_mid.hip) as long as that beats the prefill kernel by the two
-// models' estimates -- with the time that staging FP32 results takes on top (a launch, a write and a read at 4.5 TB/s):
-// the calls that quantize their results have to quantize exactly what the plain call returns, so both take the same
-// kernel, and only the prefill kernel quantizes in its epilogue.  Microseconds per call, this kernel / the prefill kernel, with
-// FP32, packed, gated and packed results.  On this kernel: 4096 x 12288 (K x N) 256 rows 43 / 54, 48 / 63, 52 / 65, 448 rows
-// 49 / 63, 55 / 71, 62 / 74; 4096 x 22016 200 rows 45 / 60, 51 / 67, 56 / 70; 512 x 16384 256 rows 15 / 40, 26 / 49, 31 / 52.  On
-// the prefill kernel: 4096 x 22016 512 rows 96 / 94, 106 / 98, 118 / 101; 512 x 16384 768 rows 39 / 28, 50 / 31, 62 / 33.  The
-// line is drawn too early for products whose 256 x 256 tiles leave the chip part empty: 4096 x 12288 512 rows 53 / 63, 61 / 72,
-// 68 / 74; 4096 x 22016 256 rows 51 / 61, 57 / 69, 63 / 71; 4096 x 4096 768 rows 36 / 55, 40 / 65, 44 / 68.
+// Products of 33 to 4096 rows take the kernel for mid-size products (fgmp_gemm_mid.hip) where the two kernels' estimates say so:
+// where 256 x 256 tiles leave the chip part empty, or K is too short for what a tile pays around its K loop.  Calls that quantize
+// their results have to quantize exactly what the plain call returns, so both take the same kernel, though only the prefill
+// kernel quantizes in its epilogue: staging FP32 results for the quantizer costs what that epilogue costs.  Microseconds per
+// call, this kernel / the prefill kernel, with FP32, packed and gated packed results.  On this kernel: 4096 x 4096 (K x N) 844 rows
+// 38 / 62, 688 x 640 617 rows 14 / 32, 17 / 41, 18 / 43, 656 x 320 42 rows 11 / 20, 13 / 25, 14 / 29, 3136 x 512 1978 rows 29 / 50,
+// 31 / 57, 32 / 59.  On the prefill kernel: 11008 x 4096 1650 rows 198 / 160, 200 / 166, 204 / 168, 272 x 6080 2841 rows 47 / 47, 62 /
+// 60, 65 / 63, 3440 x 18112 2025 rows 277 / 243, 288 / 261, 291 / 268.  Of 1014 products measured with both (33 to 4096 rows) 226
+// changed kernel, none for one that is more than 2% slower; of 631 others 155, 1.46 times as fast on average with
+// either kind of result, and four slower, by 6 to 18% (4464 x 4800 1580 rows 121 / 102).  Above 1024 rows, where a wrong choice costs more, the estimate
+// has to win by 15%; 1025 to 1300 rows over up to 1040 elements stay on the prefill kernel, whose tests run it there.
 //
 // Up to 32 rows the one-launch step (fgmp_gemm_stream.hip) shares K among as many workgroups as keep a part's rows in LDS and runs
 // through its row groups in rounds; with two rounds or more the parts meet that often, and this kernel is taken where the
@@ -279,7 +284,7 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
 // Steps that take two launches anyway -- K in more than 16 parts, the Eq. 8 score -- are faster on this kernel throughout: 32768 x
 // 256 32 rows 26.1 / 20.8, 11008 x 4096 with the Eq. 8 score 21.3 / 17.6.  With an odd number of row-tiles it is taken from
 // N K^2 = 2^38 on without the estimates (4096 x 22003 32 rows 24.7 / 21.2, cached weights).
-constexpr int64_t kMidMinRows = 20, kMidMaxRows = 1024;
+constexpr int64_t kMidMinRows = 20, kMidMaxRows = 4096;
 
 // its workspace behind the control region: header, FP16 activations, partial sums
 static size_t mid_x16_bytes(const MidPlan &p, int64_t K)
@@ -309,16 +314,23 @@ GemmRoute gemm_route(int64_t M, int64_t N, int64_t K)
         int rounds = 0;
         r.mid = r.mid_two_launch && (!stream || (gemm_mid_few_rows_micros(r.plan, N, K) <= gemm_stream_micros(M, N, K, &rounds) && rounds > 1));
     } else {
-        const double staging = 6.0 + 8.0 * (double)M * (double)N / 4.5e6;
-        r.mid = gemm_mid_micros(r.plan) + staging <= gemm_mixed_micros(M, N, K);
+        const double margin = M > 1024 ? 1.15 : 1.0;
+        const bool tested_there = M > 1024 && M <= 1300 && K <= 1040;
+        // (only where it needs no more workspace than the prefill kernel)
+        const GemmWorkspace w = gemm_ws_layout(M, N, K);
+        r.mid = !tested_there && margin * gemm_mid_micros(r.plan, M, N, K) <= gemm_mixed_micros(M, N, K) &&
+                mid_bytes(r.plan, K) <= fused_prefill_split(w) + (w.total - w.off_split);
     }
     return r;
 }
 
+// (above 1024 rows a call asks for what the prefill kernel needs, whichever kernel it takes)
+static bool mid_asks_less(int64_t M, const GemmRoute &route) { return M > 32 && M <= 1024 && route.mid; }
+
 // what a product of packed operands uses behind the control region
 static size_t gemm_only_need(int64_t M, int64_t N, int64_t K, const GemmRoute &route)
 {
-    if (M > 32 && route.mid) return mid_bytes(route.plan, K);
+    if (mid_asks_less(M, route)) return mid_bytes(route.plan, K);
     const size_t other = gemm_skinny_applies(M, N, K) ? decode_bytes(M, N, K) : gemm_ws_layout(M, N, K).total;
     return std::max(other, gemm_stream_scratch_bytes(M, N, K));
 }
@@ -341,18 +353,16 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
     return std::max(std::max(own, prefill), gemm_workspace_need(32, N, K, gemm_route(32, N, K)));
 }
 
-// The fused call on the prefill kernel: header, FP16 activations, then what a split last round needs
 static bool fused_prefill(int64_t M, int64_t N, int64_t K)
 {
     return kUseHwCvt && !gemm_skinny_applies(M, N, K) && mixed_kernel_applies(N, K);
 }
-static size_t fused_prefill_split(const GemmWorkspace &w) { return (size_t)align_up((uint64_t)kHeaderBytes + w.off_b, 256); }
 
 size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K, const GemmRoute &route)
 {
     // (an odd number of row-tiles: as for the two launches that such a step took before, which need more)
     if (even_row_tiles(N) && gemm_stream_applies(M, N, K)) return kWsCtrlRegion + gemm_stream_scratch_bytes(M, N, K);
-    if (M > 32 && route.mid) return kWsCtrlRegion + mid_bytes(route.plan, K);
+    if (mid_asks_less(M, route)) return kWsCtrlRegion + mid_bytes(route.plan, K);
     if (fused_prefill(M, N, K)) {
         const GemmWorkspace w = gemm_ws_layout(M, N, K);
         return kWsCtrlRegion + fused_prefill_split(w) + (w.total - w.off_split);

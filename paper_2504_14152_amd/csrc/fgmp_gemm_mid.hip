@@ -476,7 +476,19 @@ MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K)
     return best;
 }
 
-double gemm_mid_micros(const MidPlan &p) { return 3.0 + 1.2 * p.cycles / 2100.0; }
+// A fused step on this kernel in microseconds, for more than 32 rows: quantizing the activations and storing the results (by their
+// numbers), what a workgroup pays around its rounds, its rounds -- the slowest of matrix, vector and LDS work and half of all
+// three --, and partial sums that meet in memory.  Fitted to 11000 steps of 1076 products (33 to 4096 rows, K and N of the
+// Llama-2-7B linears and 256 .. 11008 by 256 .. 22016, up to nine splits of each, weights in the Infinity Cache): 9% rms.
+double gemm_mid_micros(const MidPlan &p, int64_t M, int64_t N, int64_t K)
+{
+    const int64_t wgs = p.tiles() * p.parts;
+    const double matrix = 0.042 * p.mt * p.nt, vector = 0.236 * p.nt, lds = 0.031 * p.mt * p.wk;
+    const double per_round = std::max(matrix, std::max(vector, lds)) + 0.51 * (matrix + vector + lds);
+    const double meet = p.parts > 1 ? 3.8 + 0.028 * p.mt * p.nt * p.wn * (double)(p.parts - 1) * (double)std::min<int64_t>(wgs, 256) / 256.0 : 0.0;
+    return 5.1 + (double)((wgs + 255) / 256) * (3.8 + (double)((p.rounds + p.parts - 1) / p.parts) * per_round) + meet +
+           (0.92e-6 * (double)K + 1.52e-6 * (double)N) * (double)M;
+}
 
 // The same for 20 to 32 rows with the weights coming from HBM, as those of a model's layers do: 2 to 4 us more than out of the
 // Infinity Cache, for the dependent loads before a workgroup's first round.  Fitted to 552 measured steps: 2% rms, 8% at most.

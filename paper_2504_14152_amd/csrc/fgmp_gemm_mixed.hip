@@ -669,19 +669,19 @@ SplitTail plan_split_tail(int64_t n_tiles, int nk, void *region)
     return sp;
 }
 
-// A fused step on this kernel, estimated: 1.45 us per K-step of 64 and round of 256 tiles, 8 us per round for what is not
-// K loop, and what the parts of a split last round take to meet (4096 x 12288, 512 rows: 69 us against 64 measured, 1024
-// rows 104 / 99; 11008 x 4096, 512 rows 89 / 87; 4096 x 22016, 512 rows 104 / 94).
+// A fused step on this kernel in microseconds: quantizing the activations and storing the results (by their numbers), 1.12 us per
+// K-step of 64 and round of 256 tiles, and what the parts of a split last round take to meet.  Fitted to the same 1076 products
+// as the estimate of the kernel for fewer rows (gemm_mid_micros): 9% rms.
 double gemm_mixed_micros(int64_t M, int64_t N, int64_t K)
 {
     const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN), nk = (K + kTileK - 1) / kTileK * 2;
     const int64_t whole = tiles / kNumCu, split = split_tiles(tiles);
     const bool four = split > 0 && split <= kNumCu / 4 && nk >= 8, two = !four && split > 0 && nk >= 4;
     double steps = (double)(whole * nk), meet = 0.0;
-    if (four) { steps += (double)nk / 4.0; meet = 15.0; }
-    else if (two) { steps += (double)nk * 9.0 / 16.0; meet = 5.0; }
+    if (four) { steps += (double)nk / 4.0; meet = 18.1 + 0.132 * (double)split; }
+    else if (two) { steps += (double)nk * 9.0 / 16.0; meet = 12.6; }
     else if (tiles % kNumCu != 0) steps += (double)nk;
-    return 4.0 + 8.0 * (double)((tiles + kNumCu - 1) / kNumCu) + 1.45 * steps + meet;
+    return 4.0 + 1.12 * steps + meet + (1.31e-6 * (double)K + 1.59e-6 * (double)N) * (double)M;
 }
 
 // Measurement hook (only in builds with FGMP_MEASUREMENT_HOOKS; the shipped launcher records nothing):

@@ -104,7 +104,7 @@ size_t gemm_stream_pack_scratch_bytes(int64_t M, int64_t N, int64_t K);
 // `ctrl`: the workspace's control region; `scratch`: plan.scratch_bytes() bytes.
 MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K);
 bool gemm_mid_applies(const MidPlan &p, int64_t N, int64_t K);
-double gemm_mid_micros(const MidPlan &p);                    // estimate of a fused step
+double gemm_mid_micros(const MidPlan &p, int64_t M, int64_t N, int64_t K);   // estimate of a fused step of more than 32 rows
 double gemm_mid_few_rows_micros(const MidPlan &p, int64_t N, int64_t K);   // 20 to 32 rows
 double gemm_mixed_micros(int64_t M, int64_t N, int64_t K);   // the same on the prefill kernel
 fgmp_status_t gemm_mid(const MidPlan &p, const PackedHeader *xh, const _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,

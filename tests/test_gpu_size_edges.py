@@ -355,3 +355,32 @@ def test_weights_packed_with_an_infinite_threshold_hold_no_upper_half(rows, K, c
         pack(w, f, T, s, out=fgmp.Packed(buf, rows, K))
     assert torch.equal(*bufs)
     assert fgmp.packed_info(fgmp.Packed(bufs[0], rows, K))["n_fp8_blocks"] == 0
+
+
+# ------------------------------------------------------------------ the kernel for mid-size products above 1024 rows
+
+# (M, K, N): one row more than the range in which the prefill kernel is tested; a last tile of a few rows, K shared among workgroups;
+# more tiles than run at once; the most rows it takes
+@pytest.mark.parametrize("M,K,N", [(1301, 272, 264), (1545, 3088, 320), (2500, 144, 1408), (4096, 528, 136)])
+def test_mid_size_kernel_above_1024_rows_matches_oracle(M, K, N):
+    """Plain, packed and gated calls, in a workspace of the size that a call is told and with its control region left zero."""
+    from paper_2504_14152_amd import build
+    assert fgmp.selftest_gemm_route(M, N, K)[0] == 2
+    xd, fxd, Tx, sx, pW, want, tol = _product(M, K, N, "bf16", 0.1, 99)
+    ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
+    ws[fgmp.WORKSPACE_CONTROL_BYTES:] = 0xFF
+    Y = fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, workspace=ws).clone()
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - want)
+    assert np.all(err <= tol), (err / tol).max()
+    assert int(ws[: fgmp.WORKSPACE_CONTROL_BYTES].sum()) == 0
+    assert torch.equal(fgmp.gemm(fgmp.quantize_activations(xd, fxd, Tx, sx), pW, workspace=ws), Y)
+    with fgmp.use_library(build.lib_path("fullwait")):
+        assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW), Y)
+    f_n = torch.from_numpy(synth.fisher_per_channel(N, 99, 5)).to(DEV)
+    s_y = float(Y.abs().max()) / 448.0
+    for epilogue in (fgmp.EPILOGUE_NONE, fgmp.EPILOGUE_SILU_GATE)[: 2 if N % 64 == 0 else 1 if N % 16 == 0 else 0]:
+        h = torch.from_numpy(orc.gate_columns(Y.cpu().numpy())).to(DEV) if epilogue else Y
+        f_h = f_n[: h.shape[1]].contiguous()
+        ref = fgmp.unpack_canonical(fgmp.quantize_activations(h.contiguous(), f_h, 1e-4, s_y))
+        got = fgmp.unpack_canonical(fgmp.quant_gemm_fused_packed_out(xd, fxd, Tx, sx, pW, f_h, 1e-4, s_y, epilogue=epilogue))
+        assert all(torch.equal(a, b) for a, b in zip(got, ref))
