@@ -384,3 +384,21 @@ def test_mid_size_kernel_above_1024_rows_matches_oracle(M, K, N):
         ref = fgmp.unpack_canonical(fgmp.quantize_activations(h.contiguous(), f_h, 1e-4, s_y))
         got = fgmp.unpack_canonical(fgmp.quant_gemm_fused_packed_out(xd, fxd, Tx, sx, pW, f_h, 1e-4, s_y, epilogue=epilogue))
         assert all(torch.equal(a, b) for a, b in zip(got, ref))
+
+
+# ------------------------------------------------------------------ decode steps: K shared among more than four workgroups
+
+# (M, K): 5, 6, 7 and 13 parts, added up six at a time; 5, 8, 11 and 16 parts, four at a time
+@pytest.mark.parametrize("M,K", [(16, 10128), (9, 12288), (16, 12304), (13, 26000), (32, 5008), (17, 8192), (32, 11008), (29, 16384)])
+def test_decode_steps_in_many_parts_match_oracle(M, K):
+    N = 48
+    assert fgmp.selftest_gemm_route(M, N, K)[0] == 0
+    xd, fxd, Tx, sx, pW, want, tol = _product(M, K, N, "bf16", 0.1, 100 + M)
+    ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
+    ws[fgmp.WORKSPACE_CONTROL_BYTES:] = 0xFF       # partial sums start as NaN patterns
+    Y = fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, workspace=ws).clone()
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - want)
+    assert np.all(err <= tol), (err / tol).max()
+    assert int(ws[: fgmp.WORKSPACE_CONTROL_BYTES].sum()) == 0
+    for _ in range(4):
+        assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, workspace=ws), Y)
