@@ -594,7 +594,7 @@ __global__ __launch_bounds__(64 * kQWaves) void quantize_act_kernel(QuantParams 
 // that quantize_block_math computes.
 __device__ __forceinline__ float nvfp4_error(const float (&x)[16], const float (&f)[16], float d, float inv_d)
 {
-    uint32_t q[2] = {0u, 0u};
+    uint32_t q[2] = {any_value(), any_value()};
     float t[16];
 #define FGMP_ENC(W, B, I) q[W] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q[W], x[I] * inv_d, x[I + 1] * inv_d, 1.0f, B)
     FGMP_ENC(0, 0, 0); FGMP_ENC(0, 1, 2); FGMP_ENC(0, 2, 4); FGMP_ENC(0, 3, 6);
