@@ -617,6 +617,30 @@ __device__ __forceinline__ float nvfp4_error(const float (&x)[16], const float (
     return t[0];
 }
 
+// Nearly the same error for less than two thirds of the instructions: sum of (g_i x_i - v_i (g_i d))^2 with g_i the root of the
+// sensitivity.  t = x / d and gd = g d belong to a scale whose mantissa is the candidate's; the candidate's scale is `up` (a power
+// of two) times that one, which the conversions apply exactly.
+__device__ __forceinline__ float nvfp4_error_estimate(const float (&t)[16], const float (&gd)[16], const float (&y)[16], float up)
+{
+    uint32_t q[2] = {any_value(), any_value()};
+    float sum[2] = {0.0f, 0.0f};
+#define FGMP_ENC(W, B, I) q[W] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q[W], t[I], t[I + 1], up, B)
+    FGMP_ENC(0, 0, 0); FGMP_ENC(0, 1, 2); FGMP_ENC(0, 2, 4); FGMP_ENC(0, 3, 6);
+    FGMP_ENC(1, 0, 8); FGMP_ENC(1, 1, 10); FGMP_ENC(1, 2, 12); FGMP_ENC(1, 3, 14);
+#undef FGMP_ENC
+#define FGMP_ERR(W, B, I)                                                                \
+    {                                                                                    \
+        const float2_t v = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(q[W], up, B);        \
+        const float e0 = __builtin_fmaf(-v[0], gd[I], y[I]), e1 = __builtin_fmaf(-v[1], gd[I + 1], y[I + 1]); \
+        sum[0] = __builtin_fmaf(e0, e0, sum[0]);                                         \
+        sum[1] = __builtin_fmaf(e1, e1, sum[1]);                                         \
+    }
+    FGMP_ERR(0, 0, 0) FGMP_ERR(0, 1, 2) FGMP_ERR(0, 2, 4) FGMP_ERR(0, 3, 6)
+    FGMP_ERR(1, 0, 8) FGMP_ERR(1, 1, 10) FGMP_ERR(1, 2, 12) FGMP_ERR(1, 3, 14)
+#undef FGMP_ERR
+    return sum[0] + sum[1];
+}
+
 // Sensitivity-weighted clipping (Sec. 3.3, Eq. 11): for every block, the E4M3 scale code (0 .. 0x7E)
 // whose NVFP4 quantization has the smallest weighted error, the smallest code among equal errors, and the first pass of
 // packing (compact) under the scales found.  One wave per tile, one block per lane; the error of a candidate is computed
@@ -638,10 +662,15 @@ __device__ __forceinline__ float nvfp4_error(const float (&x)[16], const float (
 // in equal pieces, the blocks going through LDS: 25 rounds instead of 33.
 // 12288 x 4096 bf16, per-element sensitivities, the whole call: 1427 us with all 127 codes tried (and one division and one decode
 // of the scale per candidate), 454 with the single-element bounds, 401 with the ranges dealt out, 328 with the packing
-// pass done here (it read W and the sensitivities again, 65 us), 305 with the bisection.
+// pass done here (it read W and the sensitivities again, 65 us), 304 with the bisection, 250 with the candidates ranked by an
+// estimate (74 instructions a candidate, its share of the preparation included, instead of 127) and one root per element for bounds and
+// estimates.  6144 x 4096: FP32 171 / 142, pruned to a half 169 / 160, three values only 157 / 136 (equal errors), one sensitivity
+// for all 152 / 123; 4-bit integers with one sensitivity, where four codes and more tie in every wave, 162 / 164, tails so heavy that most
+// blocks lie below code 8 133 / 139.
 template <typename Tin, bool kPerElem, bool kHW>
-__global__ __launch_bounds__(256) void clip_kernel(QuantParams p)
+__global__ __launch_bounds__(256, 4) void clip_kernel(QuantParams p)
 {
+    constexpr uint32_t kOwnMore = 2;   // (codes beyond the mean number by estimate, the cheaper ones: 0 and 4 measure 1.5% more)
     constexpr int kStride = 36;   // floats per block in LDS: 16-byte pieces of neighbouring blocks in different banks
     __shared__ float2 tbl[128];   // {d, 1 / d} by scale code
     __shared__ __attribute__((aligned(16))) float blocks[4][64 * kStride];
@@ -705,14 +734,22 @@ __global__ __launch_bounds__(256) void clip_kernel(QuantParams p)
     const bool nothing_less = best_err == 0.0f && f_min >= 0.0f && f_sum == f_sum;   // (a block of zeros)
     const bool bounded = bound > 1e-35f && bound > 1e-30f * f_max && bound < 1e25f && f_min >= 0.0f && f_max < 1e30f && f_sum == f_sum &&
                          amax < 1e15f && p.S > 1e-20f && p.S < 1e20f;
+    // (the estimate takes the root of a sensitivity and squares what is weighted with it: ordinary numbers as well; zeros pass)
+    uint32_t f_least = ~0u;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) f_least = min(f_least, __builtin_bit_cast(uint32_t, f[i]) - 1u);
+    const bool estimable = bounded && bound > 1e-30f && f_least >= __builtin_bit_cast(uint32_t, 1e-30f);
+    float g[16];   // root of the sensitivity, by the reciprocal root that the bounds take
     if (bounded) {
         float d_low = 0.0f, d_high = 4.0f * amax;   // (beyond: all zeros, the error of code 0)
+        const float root_bound = __builtin_amdgcn_sqrtf(bound) * 1.00001f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const float ax = fabsf(x[i]);
             // (a vanishing sensitivity gives an infinite root, and no bound)
-            const float root = __builtin_amdgcn_sqrtf(bound * __builtin_amdgcn_rcpf(f[i]));
-            d_low = fmaxf(d_low, (ax * 0.99999f - root * 1.00001f) * (1.0f / 6.0f));
+            const float inv_root = __builtin_amdgcn_rsqf(f[i]);
+            g[i] = f[i] * fminf(inv_root, 1e30f);
+            d_low = fmaxf(d_low, __builtin_fmaf(-root_bound, inv_root, ax * 0.99999f) * (1.0f / 6.0f));
             if (lost[i] > bound) d_high = fminf(d_high, 4.0f * ax);
         }
         const uint32_t low = enc_e4m3<kHW>(fminf(d_low * 0.99999f * inv_S, 448.0f)), high = enc_e4m3<kHW>(fminf(d_high * 1.00001f * inv_S, 448.0f));
@@ -722,15 +759,30 @@ __global__ __launch_bounds__(256) void clip_kernel(QuantParams p)
 #pragma unroll
         for (uint32_t step = 8u; step > 0u; step >>= 1) {
             const uint32_t sc = last > step ? last - step + 1u : 1u;
-            const float d4 = tbl[sc].x * 0.24999f;
+            // (1 - |x| / (d / 4), times 2^30, clamped to 0 .. 1: no more than 1, 0 for an element that is not lost)
+            const float inv_d4 = tbl[sc].y * (4.0001f * 0x1p30f);
             float err = 0.0f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) err += fabsf(x[i]) < d4 ? lost[i] : 0.0f;
+            for (int i = 0; i < 16; ++i) {
+                const float is_lost = __builtin_amdgcn_fmed3f(__builtin_fmaf(-fabsf(x[i]), inv_d4, 0x1p30f), 0.0f, 1.0f);
+                err = __builtin_fmaf(is_lost, lost[i], err);
+            }
             if (err * 0.9999f > bound) last = sc - 1u;
         }
     }
     if (!inside || nothing_less) last = 0u;
-    // codes [from, to] of the block in x, f
+    // a block's x and f in LDS (of one wave: its accesses complete in order; nothing to wait for but the compiler)
+    const float4 *const mine = reinterpret_cast<const float4 *>(&blocks[wave][lane * kStride]);
+    auto fetch = [&](const float4 *from) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 vx = from[i], vf = from[4 + i];
+            x[4 * i] = vx.x; x[4 * i + 1] = vx.y; x[4 * i + 2] = vx.z; x[4 * i + 3] = vx.w;
+            f[4 * i] = vf.x; f[4 * i + 1] = vf.y; f[4 * i + 2] = vf.z; f[4 * i + 3] = vf.w;
+        }
+    };
+    // codes from .. to of the block in x, f
     auto search = [&](uint32_t from, uint32_t to) {
 #pragma unroll 1
         for (uint32_t sc = from; sc <= to; ++sc) {
@@ -739,6 +791,62 @@ __global__ __launch_bounds__(256) void clip_kernel(QuantParams p)
                 best_err = err;
                 best = sc;
             }
+        }
+    };
+    // The first `own` codes (wave-uniform) of a range that ends at `to`, by estimates: codes 8 apart share a mantissa, so the block
+    // is multiplied by one reciprocal for all of them.  With u = 2^-24, E the error and C that under code 0, estimate and error differ
+    // by at most 40 u E + 8 u sqrt(C E) (the errors' own sums 6 u E, the estimate's 9 u E, the root 6 u E; per element u |x|, 2 u |v d| and
+    // 2 u |e|, weighted and summed by Cauchy-Schwarz), so the code with the smallest error is among those whose estimate is within twice
+    // that of the smallest one; `limit` allows another factor of two and the seven bits that the code replaces in a key.  Up to three
+    // of them are compared by their errors; where there are more, all the codes are.
+    auto search_by_estimate = [&](uint32_t start, uint32_t to, uint32_t own) {
+        const float c0_err = best_err;
+        uint32_t k1 = ~0u, k2 = ~0u, k3 = ~0u, k4 = ~0u;   // the four smallest: estimate, code in the low seven bits
+        float y[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) y[i] = g[i] * x[i];
+#pragma unroll 1
+        for (uint32_t j = 0; j < 8u && j < own; ++j) {
+            const float2 s = tbl[start + j < 127u ? start + j : 127u];
+            float t[16], gd[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                t[i] = x[i] * s.y;
+                gd[i] = g[i] * s.x;
+            }
+            float up = 1.0f;
+#pragma unroll 1
+            for (uint32_t k = j; k < own; k += 8u) {
+                const uint32_t sc = start + k;
+                const float err = nvfp4_error_estimate(t, gd, y, up);
+                const uint32_t key = sc <= to ? (__builtin_bit_cast(uint32_t, err) & ~127u) | sc : ~0u;
+                const uint32_t l1 = max(k1, key), l2 = max(k2, l1), l3 = max(k3, l2);
+                k1 = min(k1, key);
+                k2 = min(k2, l1);
+                k3 = min(k3, l2);
+                k4 = min(k4, l3);
+                up *= 2.0f;
+            }
+        }
+        fetch(mine);   // (x and f need no registers in the loop above)
+        auto estimate = [](uint32_t key) { return __builtin_bit_cast(float, key & ~127u); };
+        const float least = estimate(k1);
+        const float limit = least * 1.00004f + 2e-6f * __builtin_amdgcn_sqrtf(c0_err * least) + 1e-12f * c0_err;
+        auto close = [&](uint32_t key) { return key != ~0u && estimate(key) <= limit; };
+        if (close(k4)) {
+            search(start, to);
+        } else {
+            auto consider = [&](uint32_t key) {
+                const uint32_t sc = key & 127u;
+                const float err = error_with(sc);
+                if (err < best_err || (err == best_err && sc < best)) {
+                    best_err = err;
+                    best = sc;
+                }
+            };
+            if (k1 != ~0u) consider(k1);
+            if (close(k2)) consider(k2);
+            if (close(k3)) consider(k3);
         }
     };
     if (__ballot(inside && !bounded && !nothing_less) != 0ull) {
@@ -753,10 +861,21 @@ __global__ __launch_bounds__(256) void clip_kernel(QuantParams p)
             return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
         };
         const uint32_t width = last >= first ? last - first + 1u : 0u;
-        const uint32_t own = (wave_sum(width) + 63u) / 64u;
+        float4 *stage = reinterpret_cast<float4 *>(&blocks[wave][lane * kStride]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            stage[i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
+            stage[4 + i] = make_float4(f[4 * i], f[4 * i + 1], f[4 * i + 2], f[4 * i + 3]);
+        }
+        // (The estimates' preparation and the final comparison cost as much as eight codes save; the start of a second search a few more.  Below code 8 scales are not normal numbers.)
+        const uint32_t mean = (wave_sum(width) + 63u) / 64u;
+        const bool by_estimate = kHW && mean >= 14u && __ballot(width != 0u && !(estimable && first >= 8u)) == 0ull;
+        const uint32_t own = mean + (by_estimate ? kOwnMore : 0u);
         const uint32_t left = width > own ? width - own : 0u;
         const uint64_t longer = __ballot(left != 0u);
-        search(first, left != 0u ? first + own - 1u : last);
+        const uint32_t own_last = left != 0u ? first + own - 1u : last;
+        if (by_estimate) search_by_estimate(first, own_last, own);
+        else search(first, own_last);
         if (longer != 0ull) {
             const uint32_t spare = 64u - (uint32_t)__popcll(longer);
             const uint32_t rest = (wave_sum(left) + spare - 1u) / spare;
@@ -771,29 +890,16 @@ __global__ __launch_bounds__(256) void clip_kernel(QuantParams p)
             at -= n_pieces;
             // errors are sums of non-negative numbers here: their bit patterns order them, the code decides between equal ones
             auto key = [&]() { return ((uint64_t)__builtin_bit_cast(uint32_t, best_err) << 32) | best; };
-            float4 *mine = reinterpret_cast<float4 *>(&blocks[wave][lane * kStride]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                mine[i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
-                mine[4 + i] = make_float4(f[4 * i], f[4 * i + 1], f[4 * i + 2], f[4 * i + 3]);
-            }
             answer[wave][lane] = key();
             for (uint32_t k = 0; k < n_pieces; ++k) {
                 const uint32_t from = first + own + k * rest, to = from + rest - 1u < last ? from + rest - 1u : last;
                 pieces[wave][at + k] = (uint32_t)lane | (from << 8) | (to << 16);
             }
-            // (LDS of one wave: its accesses complete in order; nothing to wait for but the compiler)
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             if ((uint32_t)lane < total) {
                 const uint32_t piece = pieces[wave][lane];
                 const uint32_t from_lane = piece & 0xFFu;
-                const float4 *theirs = reinterpret_cast<const float4 *>(&blocks[wave][from_lane * kStride]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float4 vx = theirs[i], vf = theirs[4 + i];
-                    x[4 * i] = vx.x; x[4 * i + 1] = vx.y; x[4 * i + 2] = vx.z; x[4 * i + 3] = vx.w;
-                    f[4 * i] = vf.x; f[4 * i + 1] = vf.y; f[4 * i + 2] = vf.z; f[4 * i + 3] = vf.w;
-                }
+                fetch(reinterpret_cast<const float4 *>(&blocks[wave][from_lane * kStride]));
                 best = 0xFFu;
                 best_err = __builtin_inff();
                 search((piece >> 8) & 0xFFu, piece >> 16);
@@ -801,12 +907,7 @@ __global__ __launch_bounds__(256) void clip_kernel(QuantParams p)
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             best = (uint32_t)answer[wave][lane];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float4 vx = mine[i], vf = mine[4 + i];
-                x[4 * i] = vx.x; x[4 * i + 1] = vx.y; x[4 * i + 2] = vx.z; x[4 * i + 3] = vx.w;
-                f[4 * i] = vf.x; f[4 * i + 1] = vf.y; f[4 * i + 2] = vf.z; f[4 * i + 3] = vf.w;
-            }
+            fetch(mine);
         }
     }
 

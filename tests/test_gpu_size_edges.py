@@ -265,6 +265,42 @@ def test_clipped_scales_are_the_brute_force_ones(what):
     assert np.array_equal(scores.cpu().numpy().view(np.uint32), want["scores"].view(np.uint32))
 
 
+@pytest.mark.parametrize("what", ["three values", "codes already", "across code 8", "wide ranges", "close seconds", "vanishing sensitivities"])
+def test_clipped_scales_found_by_estimates_are_the_brute_force_ones(what):
+    """Candidates are ranked by an estimate of their error; equal and nearly equal errors, errors of zero and scales that are not
+    normal numbers are where that could show."""
+    rng = synth.rng_for(37, len(what))
+    N, K = 136, 656
+    w = rng.standard_normal((N, K)).astype(np.float32) * np.float32(0.02)
+    f = np.exp(rng.standard_normal((N, K))).astype(np.float32)
+    scale = 1.0
+    if what == "three values":                      # many codes with the same error: every code is compared
+        w = (np.sign(w) * (np.abs(w) > 0.01) * 0.03).astype(np.float32)
+    elif what == "codes already":                   # reconstructed exactly under some code (S is a power of two)
+        grid = np.array([0, 0.5, 1, 1.5, 2, 3, 4, 6], np.float32)
+        w = grid[rng.integers(0, 8, (N, K))] * np.where(rng.random((N, K)) < 0.5, -1, 1) * np.repeat(2.0 ** rng.integers(-3, 3, (N, K // 16)), 16, axis=1)
+        w = w.astype(np.float32)
+        w[0, 0] = 448.0
+    elif what == "across code 8":
+        w *= np.repeat(2.0 ** -rng.uniform(0.0, 6.0, (N, K // 16)), 16, axis=1).astype(np.float32)
+        scale = 12.0
+    elif what == "wide ranges":
+        f = np.exp(3.0 * rng.standard_normal((N, K))).astype(np.float32)
+        f[:, ::3] *= np.float32(1e-6)
+    elif what == "close seconds":                   # two halves that trade places from code to code
+        w[:, 1::2] = w[:, ::2] * np.float32(1.0 + 2.0 ** -22)
+        f[:, 1::2] = f[:, ::2]
+    elif what == "vanishing sensitivities":         # on both sides of where the estimate is not used
+        f[: N // 2] *= np.where(rng.random((N // 2, K)) < 0.02, 1e-33, 1.0).astype(np.float32)
+        f[N // 2:] *= np.float32(1e-26)
+    S = float(synth.default_tensor_scale(w)) * scale
+    want = orc.quantize(w, f, float("inf"), S, clip=True)
+    pk, scores = fgmp.quantize_weights_clip(torch.from_numpy(w).to(DEV), torch.from_numpy(f).to(DEV), float("inf"), S, want_scores=True)
+    codes, scales, mask = (t.cpu().numpy() for t in fgmp.unpack_canonical(pk))
+    assert np.array_equal(scales, want["scales"]) and np.array_equal(codes, want["codes"]) and np.array_equal(mask, want["mask"])
+    assert np.array_equal(scores.cpu().numpy().view(np.uint32), want["scores"].view(np.uint32))
+
+
 # ------------------------------------------------------------------ decode steps: the last row group with one row-tile
 
 # (M, K, N), N / 8 rounded up odd: one, eight, sixteen and 32 rows; K in one part and in several; a last row-tile of one row
