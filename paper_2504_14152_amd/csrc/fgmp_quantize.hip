@@ -746,8 +746,8 @@ __global__ __launch_bounds__(256, 4) void clip_kernel(QuantParams p)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const float ax = fabsf(x[i]);
-            // (a vanishing sensitivity gives an infinite root, and no bound)
-            const float inv_root = __builtin_amdgcn_rsqf(f[i]);
+            // (a vanishing sensitivity gives an infinite root, and no bound; of -0.0, too, whose own reciprocal root is -inf)
+            const float inv_root = __builtin_amdgcn_rsqf(fabsf(f[i]));
             g[i] = f[i] * fminf(inv_root, 1e30f);
             d_low = fmaxf(d_low, __builtin_fmaf(-root_bound, inv_root, ax * 0.99999f) * (1.0f / 6.0f));
             if (lost[i] > bound) d_high = fminf(d_high, 4.0f * ax);

@@ -301,6 +301,40 @@ def test_clipped_scales_found_by_estimates_are_the_brute_force_ones(what):
     assert np.array_equal(scores.cpu().numpy().view(np.uint32), want["scores"].view(np.uint32))
 
 
+def _assert_clipped_as_by_the_oracle(w, f, S):
+    want = orc.quantize(w, f, float("inf"), S, clip=True)
+    pk, scores = fgmp.quantize_weights_clip(torch.from_numpy(w).to(DEV), torch.from_numpy(f).to(DEV), float("inf"), S, want_scores=True)
+    codes, scales, mask = (t.cpu().numpy() for t in fgmp.unpack_canonical(pk))
+    assert np.array_equal(scales, want["scales"]), f"{int((scales != want['scales']).sum())} of {scales.size} scales"
+    assert np.array_equal(codes, want["codes"]) and np.array_equal(mask, want["mask"])
+    assert np.array_equal(scores.cpu().numpy().view(np.uint32), want["scores"].view(np.uint32))
+
+
+@pytest.mark.parametrize("what", ["one in a block", "beside zero weights", "one in each short block", "per channel"])
+def test_clipped_scales_with_sensitivities_of_minus_zero_are_the_brute_force_ones(what):
+    """-0.0 compares equal to zero and weighs nothing, as zero does; its root and its reciprocal are negative, though."""
+    rng = synth.rng_for(38, len(what))
+    N, K = 72, 528
+    w = rng.standard_normal((N, K)).astype(np.float32) * np.float32(0.02)
+    f = np.exp(rng.standard_normal((N, K))).astype(np.float32)
+    at = 16 * np.arange(K // 16) + rng.integers(0, 16, (N, K // 16))
+    scale = 1.0
+    if what == "beside zero weights":
+        w[np.arange(N)[:, None], at ^ 1] = 0.0
+        w[: N // 2][np.arange(N // 2)[:, None], at[: N // 2]] = 0.0
+    elif what == "one in each short block":         # ranges too short for estimates
+        scale = 300.0
+    if what == "per channel":
+        f = f[0].copy()
+        f[at[0]] = np.float32(-0.0)
+    else:
+        some = rng.random((N, K // 16)) < 0.5       # blocks with and without one in the same wave
+        np.put_along_axis(f, at, np.where(some, np.float32(-0.0), np.take_along_axis(f, at, 1)), 1)
+        f[:, 32:48] = np.float32(-0.0)              # a whole block
+    assert (np.signbit(f) & (f == 0)).any()
+    _assert_clipped_as_by_the_oracle(w, f, float(synth.default_tensor_scale(w)) * scale)
+
+
 # ------------------------------------------------------------------ decode steps: the last row group with one row-tile
 
 # (M, K, N), N / 8 rounded up odd: one, eight, sixteen and 32 rows; K in one part and in several; a last row-tile of one row
