@@ -831,7 +831,9 @@ __global__ __launch_bounds__(256, 4) void clip_kernel(QuantParams p)
         fetch(mine);   // (x and f need no registers in the loop above)
         auto estimate = [](uint32_t key) { return __builtin_bit_cast(float, key & ~127u); };
         const float least = estimate(k1);
-        const float limit = least * 1.00004f + 2e-6f * __builtin_amdgcn_sqrtf(c0_err * least) + 1e-12f * c0_err;
+        // (C E itself is below FP32's range for small sensitivities, and the root takes no subnormal number)
+        const float root_ce = __builtin_amdgcn_sqrtf(c0_err) * __builtin_amdgcn_sqrtf(fmaxf(least, 0x1p-126f));
+        const float limit = least * 1.00004f + 2e-6f * root_ce + 1e-12f * c0_err;
         auto close = [&](uint32_t key) { return key != ~0u && estimate(key) <= limit; };
         if (close(k4)) {
             search(start, to);

@@ -335,6 +335,21 @@ def test_clipped_scales_with_sensitivities_of_minus_zero_are_the_brute_force_one
     _assert_clipped_as_by_the_oracle(w, f, float(synth.default_tensor_scale(w)) * scale)
 
 
+@pytest.mark.parametrize("sensitivity", [1.0, 1e-14, 1e-16, 1e-18])
+@pytest.mark.parametrize("noise", [1e-3, 1e-4])
+def test_clipped_scales_of_nearly_reproduced_blocks_are_the_brute_force_ones(noise, sensitivity):
+    """Values nearly 4, 2 and 1 times some scale: codes an octave apart are all off by the noise alone, far below the error under
+    code 0 that an estimate's distance grows with; with small sensitivities the product of the two errors is no FP32 number."""
+    rng = synth.rng_for(39, int(-np.log10(noise)))
+    N, K = 128, 1024
+    code = rng.integers(40, 100, (N, K // 16))
+    S = np.float32(0.015)
+    base = np.repeat(4.0 * (1.0 + code % 8 / 8.0) * 2.0 ** (code // 8 - 7.0) * float(S), 16, axis=1)
+    w = base * rng.choice([1.0, 0.5, 0.25, -1.0, -0.5, -0.25], (N, K)) * (1.0 + noise * rng.standard_normal((N, K)))
+    f = np.exp(rng.standard_normal((N, K))) * sensitivity
+    _assert_clipped_as_by_the_oracle(w.astype(np.float32), f.astype(np.float32), float(S))
+
+
 # ------------------------------------------------------------------ decode steps: the last row group with one row-tile
 
 # (M, K, N), N / 8 rounded up odd: one, eight, sixteen and 32 rows; K in one part and in several; a last row-tile of one row
