@@ -664,9 +664,10 @@ __device__ __forceinline__ float nvfp4_error_estimate(const float (&t)[16], cons
 // of the scale per candidate), 454 with the single-element bounds, 401 with the ranges dealt out, 328 with the packing
 // pass done here (it read W and the sensitivities again, 65 us), 304 with the bisection, 250 with the candidates ranked by an
 // estimate (74 instructions a candidate, its share of the preparation included, instead of 127) and one root per element for bounds and
-// estimates.  6144 x 4096: FP32 171 / 142, pruned to a half 169 / 160, three values only 157 / 136 (equal errors), one sensitivity
-// for all 152 / 123; 4-bit integers with one sensitivity, where four codes and more tie in every wave, 162 / 164, tails so heavy that most
-// blocks lie below code 8 133 / 139.
+// estimates.  6144 x 4096, FP32, without / with estimates: 153 / 118, pruned to a half 163 / 131, three values only 144 / 118, one
+// sensitivity for all 143 / 112.  Where more than three codes tie in a block -- often in 4-bit integers with one sensitivity, and in
+// weights with heavy tails, whose blocks are one or two elements and nothing -- its whole range is dealt out with what is left of
+// the longer ones: 154 / 126 and 133 / 115 (tried by the block's own lane while the other 63 wait: 152 and 140).
 template <typename Tin, bool kPerElem, bool kHW>
 __global__ __launch_bounds__(256, 4) void clip_kernel(QuantParams p)
 {
@@ -734,12 +735,7 @@ __global__ __launch_bounds__(256, 4) void clip_kernel(QuantParams p)
     const bool nothing_less = best_err == 0.0f && f_min >= 0.0f && f_sum == f_sum;   // (a block of zeros)
     const bool bounded = bound > 1e-35f && bound > 1e-30f * f_max && bound < 1e25f && f_min >= 0.0f && f_max < 1e30f && f_sum == f_sum &&
                          amax < 1e15f && p.S > 1e-20f && p.S < 1e20f;
-    // (the estimate takes the root of a sensitivity and squares what is weighted with it: ordinary numbers as well; zeros pass)
-    uint32_t f_least = ~0u;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) f_least = min(f_least, __builtin_bit_cast(uint32_t, f[i]) - 1u);
-    const bool estimable = bounded && bound > 1e-30f && f_least >= __builtin_bit_cast(uint32_t, 1e-30f);
-    float g[16];   // root of the sensitivity, by the reciprocal root that the bounds take
+    float inv_root[16];   // reciprocal roots of the sensitivities
     if (bounded) {
         float d_low = 0.0f, d_high = 4.0f * amax;   // (beyond: all zeros, the error of code 0)
         const float root_bound = __builtin_amdgcn_sqrtf(bound) * 1.00001f;
@@ -747,9 +743,8 @@ __global__ __launch_bounds__(256, 4) void clip_kernel(QuantParams p)
         for (int i = 0; i < 16; ++i) {
             const float ax = fabsf(x[i]);
             // (a vanishing sensitivity gives an infinite root, and no bound; of -0.0, too, whose own reciprocal root is -inf)
-            const float inv_root = __builtin_amdgcn_rsqf(fabsf(f[i]));
-            g[i] = f[i] * fminf(inv_root, 1e30f);
-            d_low = fmaxf(d_low, __builtin_fmaf(-root_bound, inv_root, ax * 0.99999f) * (1.0f / 6.0f));
+            inv_root[i] = __builtin_amdgcn_rsqf(fabsf(f[i]));
+            d_low = fmaxf(d_low, __builtin_fmaf(-root_bound, inv_root[i], ax * 0.99999f) * (1.0f / 6.0f));
             if (lost[i] > bound) d_high = fminf(d_high, 4.0f * ax);
         }
         const uint32_t low = enc_e4m3<kHW>(fminf(d_low * 0.99999f * inv_S, 448.0f)), high = enc_e4m3<kHW>(fminf(d_high * 1.00001f * inv_S, 448.0f));
@@ -798,13 +793,16 @@ __global__ __launch_bounds__(256, 4) void clip_kernel(QuantParams p)
     // by at most 40 u E + 8 u sqrt(C E) (the errors' own sums 6 u E, the estimate's 9 u E, the root 6 u E; per element u |x|, 2 u |v d| and
     // 2 u |e|, weighted and summed by Cauchy-Schwarz), so the code with the smallest error is among those whose estimate is within twice
     // that of the smallest one; `limit` allows another factor of two and the seven bits that the code replaces in a key.  Up to three
-    // of them are compared by their errors; where there are more, all the codes are.
-    auto search_by_estimate = [&](uint32_t start, uint32_t to, uint32_t own) {
+    // of them are compared by their errors; false where there are more.
+    auto search_by_estimate = [&](uint32_t start, uint32_t to, uint32_t own) -> bool {
         const float c0_err = best_err;
         uint32_t k1 = ~0u, k2 = ~0u, k3 = ~0u, k4 = ~0u;   // the four smallest: estimate, code in the low seven bits
-        float y[16];
+        float g[16], y[16];   // root of the sensitivity
 #pragma unroll
-        for (int i = 0; i < 16; ++i) y[i] = g[i] * x[i];
+        for (int i = 0; i < 16; ++i) {
+            g[i] = f[i] * fminf(inv_root[i], 1e30f);
+            y[i] = g[i] * x[i];
+        }
 #pragma unroll 1
         for (uint32_t j = 0; j < 8u && j < own; ++j) {
             const float2 s = tbl[start + j < 127u ? start + j : 127u];
@@ -835,51 +833,67 @@ __global__ __launch_bounds__(256, 4) void clip_kernel(QuantParams p)
         const float root_ce = __builtin_amdgcn_sqrtf(c0_err) * __builtin_amdgcn_sqrtf(fmaxf(least, 0x1p-126f));
         const float limit = least * 1.00004f + 2e-6f * root_ce + 1e-12f * c0_err;
         auto close = [&](uint32_t key) { return key != ~0u && estimate(key) <= limit; };
-        if (close(k4)) {
-            search(start, to);
-        } else {
-            auto consider = [&](uint32_t key) {
-                const uint32_t sc = key & 127u;
-                const float err = error_with(sc);
-                if (err < best_err || (err == best_err && sc < best)) {
-                    best_err = err;
-                    best = sc;
-                }
-            };
-            if (k1 != ~0u) consider(k1);
-            if (close(k2)) consider(k2);
-            if (close(k3)) consider(k3);
-        }
+        if (close(k4)) return false;
+        auto consider = [&](uint32_t key) {
+            const uint32_t sc = key & 127u;
+            const float err = error_with(sc);
+            if (err < best_err || (err == best_err && sc < best)) {
+                best_err = err;
+                best = sc;
+            }
+        };
+        if (k1 != ~0u) consider(k1);
+        if (close(k2)) consider(k2);
+        if (close(k3)) consider(k3);
+        return true;
     };
     if (__ballot(inside && !bounded && !nothing_less) != 0ull) {
         search(first, last);
     } else {
-        // A lane tries up to `own` codes of its block.  What is left of the longer ranges is cut in pieces of `rest` codes,
-        // at most one for each lane: blocks with something left number n < 64 (own is at least the mean), and rounding up
-        // to whole pieces adds less than one piece to each, so rest >= left / (64 - n) is enough.
+        // A lane tries up to `own` codes of its block.  What is left of the longer ranges -- and all of a range that estimates have
+        // not narrowed down -- is cut in pieces of `rest` codes, at most one for each lane: rounding up to whole pieces adds less
+        // than one piece to each of the n blocks with something left, so rest >= left / (64 - n) is enough (n = 64: one piece each).
         auto wave_sum = [](uint32_t v) {
 #pragma unroll
             for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
             return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
         };
         const uint32_t width = last >= first ? last - first + 1u : 0u;
-        float4 *stage = reinterpret_cast<float4 *>(&blocks[wave][lane * kStride]);
+        auto stage = [&]() {
+            float4 *to = reinterpret_cast<float4 *>(&blocks[wave][lane * kStride]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            stage[i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
-            stage[4 + i] = make_float4(f[4 * i], f[4 * i + 1], f[4 * i + 2], f[4 * i + 3]);
-        }
-        // (The estimates' preparation and the final comparison cost as much as eight codes save; the start of a second search a few more.  Below code 8 scales are not normal numbers.)
+            for (int i = 0; i < 4; ++i) {
+                to[i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
+                to[4 + i] = make_float4(f[4 * i], f[4 * i + 1], f[4 * i + 2], f[4 * i + 3]);
+            }
+        };
+        // The estimate takes the root of a sensitivity and squares what is weighted with it: ordinary numbers as well, or zero.
+        auto estimable = [&]() {
+            uint32_t f_least = ~0u;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) f_least = min(f_least, __builtin_bit_cast(uint32_t, f[i]) - 1u);
+            return bounded && bound > 1e-30f && f_least >= __builtin_bit_cast(uint32_t, 1e-30f);
+        };
+        // (The estimates' preparation and the final comparison cost as much as eight codes save; the start of a second search a few
+        // more.  Below code 8 scales are not normal numbers.)
         const uint32_t mean = (wave_sum(width) + 63u) / 64u;
-        const bool by_estimate = kHW && mean >= 14u && __ballot(width != 0u && !(estimable && first >= 8u)) == 0ull;
+        const bool by_estimate = kHW && mean >= 14u && __ballot(width != 0u && first < 8u) == 0ull && __ballot(width != 0u && !estimable()) == 0ull;
         const uint32_t own = mean + (by_estimate ? kOwnMore : 0u);
-        const uint32_t left = width > own ? width - own : 0u;
-        const uint64_t longer = __ballot(left != 0u);
+        uint32_t left = width > own ? width - own : 0u, left_from = first + own;
         const uint32_t own_last = left != 0u ? first + own - 1u : last;
-        if (by_estimate) search_by_estimate(first, own_last, own);
-        else search(first, own_last);
+        if (by_estimate) {
+            stage();
+            if (!search_by_estimate(first, own_last, own)) {
+                left = width;
+                left_from = first;
+            }
+        } else {
+            search(first, own_last);
+        }
+        const uint64_t longer = __ballot(left != 0u);
         if (longer != 0ull) {
-            const uint32_t spare = 64u - (uint32_t)__popcll(longer);
+            if (!by_estimate) stage();
+            const uint32_t spare = longer != ~0ull ? 64u - (uint32_t)__popcll(longer) : 1u;
             const uint32_t rest = (wave_sum(left) + spare - 1u) / spare;
             const uint32_t n_pieces = (left + rest - 1u) / rest;
             uint32_t at = n_pieces;   // inclusive prefix sum
@@ -894,7 +908,7 @@ __global__ __launch_bounds__(256, 4) void clip_kernel(QuantParams p)
             auto key = [&]() { return ((uint64_t)__builtin_bit_cast(uint32_t, best_err) << 32) | best; };
             answer[wave][lane] = key();
             for (uint32_t k = 0; k < n_pieces; ++k) {
-                const uint32_t from = first + own + k * rest, to = from + rest - 1u < last ? from + rest - 1u : last;
+                const uint32_t from = left_from + k * rest, to = from + rest - 1u < last ? from + rest - 1u : last;
                 pieces[wave][at + k] = (uint32_t)lane | (from << 8) | (to << 16);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

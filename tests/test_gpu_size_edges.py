@@ -350,6 +350,20 @@ def test_clipped_scales_of_nearly_reproduced_blocks_are_the_brute_force_ones(noi
     _assert_clipped_as_by_the_oracle(w.astype(np.float32), f.astype(np.float32), float(S))
 
 
+@pytest.mark.parametrize("share", [1.0, 0.98, 0.5, 0.02])
+def test_clipped_scales_of_blocks_with_equal_errors_are_the_brute_force_ones(share):
+    """Values of +-12 times a power of two and one small one: seven scales of the same error, more than are compared one by one.
+    All 64 blocks of a wave, nearly all of them, half and one of them; the others are ordinary ones."""
+    rng = synth.rng_for(40, int(100 * share))
+    N, K = 72, 528
+    w = 6.0 * rng.standard_normal((N, K))
+    f = np.exp(rng.standard_normal((N, K)))
+    tied = np.repeat(rng.random((N, K // 16)) < share, 16, axis=1)
+    w[tied] = (12.0 * 2.0 ** np.repeat(rng.integers(-2, 3, (N, K // 16)), 16, axis=1) * rng.choice([-1.0, 1.0], (N, K)))[tied]
+    w[:, 5::16] = 0.01
+    _assert_clipped_as_by_the_oracle(w.astype(np.float32), f.astype(np.float32), 2.0 ** -3)
+
+
 # ------------------------------------------------------------------ decode steps: the last row group with one row-tile
 
 # (M, K, N), N / 8 rounded up odd: one, eight, sixteen and 32 rows; K in one part and in several; a last row-tile of one row
