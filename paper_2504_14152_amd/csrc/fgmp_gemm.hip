@@ -286,13 +286,6 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
 // N K^2 = 2^38 on without the estimates (4096 x 22003 32 rows 24.7 / 21.2, cached weights).
 constexpr int64_t kMidMinRows = 20, kMidMaxRows = 4096;
 
-// its workspace behind the control region: header, FP16 activations, partial sums
-static size_t mid_x16_bytes(const MidPlan &p, int64_t K)
-{
-    return (size_t)align_up((uint64_t)p.x16_rows() * round_up(K, kTileK) * 2, 256);
-}
-static size_t mid_bytes(const MidPlan &p, int64_t K) { return (size_t)kHeaderBytes + mid_x16_bytes(p, K) + p.scratch_bytes(); }
-
 static size_t decode_bytes(int64_t M, int64_t N, int64_t K)
 {
     return gemm_skinny_applies(M, N, K) ? skinny_x16_bytes(M, K) + gemm_skinny_workspace_bytes(M, N, K) : 0;
@@ -306,20 +299,25 @@ GemmRoute gemm_route(int64_t M, int64_t N, int64_t K)
     GemmRoute r{};
     if (!kUseHwCvt || !prefill_decodes_in_kernel() || M < kMidMinRows || M > kMidMaxRows || N <= 0 || K <= 0) return r;
     if (M <= 32 && (double)N * (double)K * (double)K < 0x1p38) return r;
-    r.plan = gemm_mid_plan(M, N, K);
+    const GemmWorkspace w = gemm_ws_layout(M, N, K);
+    const size_t fused = fused_prefill_split(w) + (w.total - w.off_split);   // what a fused call uses on the prefill kernel
+    // 33 to 1024 rows: K in as many parts as the sums have room for where the prefill kernel has its operands and sums, or in the
+    // static scratch array (a call asks for no more than on the prefill kernel, and the array serves what it serves there).  Left to
+    // the prefill kernel where the best plan has no room, us there / here: 695 x 7808 x 394 (M, K, N) 69.6 / 25.5, 497 x 9744 x 385 76.2 /
+    // 29.2 (four parts; 25.5 with the eight that need more), 647 x 7040 x 11796 143 / 120.
+    const size_t room = std::min(w.total, std::max(fused, (size_t)FGMP_STATIC_SCRATCH_BYTES - kWsCtrlRegion));
+    r.plan = gemm_mid_plan(M, N, K, M > 32 && M <= 1024 ? room : SIZE_MAX);
     if (!gemm_mid_applies(r.plan, N, K)) return r;
     if (M <= 32) {
         const bool stream = even_row_tiles(N) && gemm_stream_applies(M, N, K);
-        r.mid_two_launch = mid_bytes(r.plan, K) <= (stream ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
+        r.mid_two_launch = r.plan.bytes(K) <= (stream ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
         int rounds = 0;
         r.mid = r.mid_two_launch && (!stream || (gemm_mid_few_rows_micros(r.plan, N, K) <= gemm_stream_micros(M, N, K, &rounds) && rounds > 1));
     } else {
         const double margin = M > 1024 ? 1.15 : 1.0;
         const bool tested_there = M > 1024 && M <= 1300 && K <= 1040;
-        // (only where it needs no more workspace than the prefill kernel)
-        const GemmWorkspace w = gemm_ws_layout(M, N, K);
         r.mid = !tested_there && margin * gemm_mid_micros(r.plan, M, N, K) <= gemm_mixed_micros(M, N, K) &&
-                mid_bytes(r.plan, K) <= fused_prefill_split(w) + (w.total - w.off_split);
+                (M <= 1024 || r.plan.bytes(K) <= fused);
     }
     return r;
 }
@@ -330,7 +328,7 @@ static bool mid_asks_less(int64_t M, const GemmRoute &route) { return M > 32 && 
 // what a product of packed operands uses behind the control region
 static size_t gemm_only_need(int64_t M, int64_t N, int64_t K, const GemmRoute &route)
 {
-    if (mid_asks_less(M, route)) return mid_bytes(route.plan, K);
+    if (mid_asks_less(M, route)) return route.plan.bytes(K);
     const size_t other = gemm_skinny_applies(M, N, K) ? decode_bytes(M, N, K) : gemm_ws_layout(M, N, K).total;
     return std::max(other, gemm_stream_scratch_bytes(M, N, K));
 }
@@ -362,7 +360,7 @@ size_t quant_gemm_workspace_need(int64_t M, int64_t N, int64_t K, const GemmRout
 {
     // (an odd number of row-tiles: as for the two launches that such a step took before, which need more)
     if (even_row_tiles(N) && gemm_stream_applies(M, N, K)) return kWsCtrlRegion + gemm_stream_scratch_bytes(M, N, K);
-    if (mid_asks_less(M, route)) return kWsCtrlRegion + mid_bytes(route.plan, K);
+    if (mid_asks_less(M, route)) return kWsCtrlRegion + route.plan.bytes(K);
     if (fused_prefill(M, N, K)) {
         const GemmWorkspace w = gemm_ws_layout(M, N, K);
         return kWsCtrlRegion + fused_prefill_split(w) + (w.total - w.off_split);
@@ -394,7 +392,7 @@ fgmp_status_t gemm_packed(const void *packed_X, int64_t M, const void *packed_W,
         const fgmp_status_t rcx = launch_decode_f16(make_decode_job(A, la, x16, ld16, la.n_rt), nullptr, nullptr, 0, st);
         if (rcx != FGMP_OK) return rcx;
         return gemm_mid(route.plan, A.hdr, x16, ld16, packed_W, M, N, K, Y, ldy, ctrl,
-                        static_cast<char *>(workspace) + kHeaderBytes + mid_x16_bytes(route.plan, K), st);
+                        static_cast<char *>(workspace) + kHeaderBytes + route.plan.x16_bytes(K), st);
     }
     if (gemm_skinny_applies(M, N, K)) {
         // decode shapes: expand the few activation rows to FP16 once, then stream the weights
@@ -481,7 +479,7 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
                                                  false, st, x16, ld16, nullptr, 0, score_mode);
         if (rc != FGMP_OK) return rc;
         return gemm_mid(route.plan, reinterpret_cast<const PackedHeader *>(ws), x16, ld16, packed_W, M, N, K, Y, ldy, workspace,
-                        ws + kHeaderBytes + mid_x16_bytes(route.plan, K), st);
+                        ws + kHeaderBytes + route.plan.x16_bytes(K), st);
     }
     const bool in_kernel_prefill = fused_prefill(M, N, K);
     if (pack_out != nullptr && !in_kernel_prefill) return FGMP_ERR_UNSUPPORTED;   // the caller falls back

@@ -446,7 +446,7 @@ constexpr int mid_most_nt(int mt) { return mt <= 4 ? 4 : 3; }
 // fused step 3 us more): 4096 x 12288, 64 rows, 4 x 2 tiles on 192 workgroups 16 us by the model, 19.6 measured (4 x 3 in
 // two parts 21.7, 4 x 4 in two 24.1); 11008 x 4096, 512 rows, 8 x 2 in two parts 52 / 57 (8 x 3 in two 68, 4 x 4 63);
 // 4096 x 22016, 200 rows, 7 x 3 38 / 45 (5 x 3 66, 7 x 2 59).
-MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K)
+MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K, size_t most_bytes)
 {
     MidPlan best{};
     best.cycles = INFINITY;
@@ -469,7 +469,7 @@ MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K)
                 const int64_t waves = (p.tiles() * parts + 255) / 256;
                 p.cycles = (double)waves * (15000.0 + (double)((p.rounds + parts - 1) / parts) * per_round) +
                            (parts > 1 ? 6000.0 + 2000.0 * (double)parts : 0.0);
-                if (p.cycles < best.cycles) best = p;
+                if (p.cycles < best.cycles && p.bytes(K) <= most_bytes) best = p;
             }
         }
     }
@@ -502,7 +502,7 @@ double gemm_mid_few_rows_micros(const MidPlan &p, int64_t N, int64_t K)
 bool gemm_mid_applies(const MidPlan &p, int64_t N, int64_t K)
 {
     constexpr uint64_t kLimit = 0xFFFFFF00ull;   // 32-bit buffer offsets
-    return make_layout(N, K).total_bytes < kLimit && p.partial_bytes() < 0x7FFFFF00ull && p.tiles() * p.parts < 65536 &&
+    return p.tiles_m > 0 && make_layout(N, K).total_bytes < kLimit && p.partial_bytes() < 0x7FFFFF00ull && p.tiles() * p.parts < 65536 &&
            p.rounds * (p.parts + 1) < 65536 && p.tiles() <= (int64_t)(kWsCtrlRegion / 4) && align_up(K, kTileK) * 8 < 0x7FFFFFFF;
 }
 

@@ -41,6 +41,9 @@ struct MidPlan {
     int64_t x16_rows() const { return tiles_m * 16 * mt; }
     size_t partial_bytes() const { return parts > 1 ? (size_t)(tiles() * parts) * (16 * mt) * cols() * 4 : 0; }
     size_t scratch_bytes() const { return (size_t)align_up(partial_bytes(), 256); }
+    // its workspace behind the control region: header, FP16 activations, partial sums
+    size_t x16_bytes(int64_t K) const { return (size_t)align_up((uint64_t)x16_rows() * align_up((uint64_t)K, kTileK) * 2, 256); }
+    size_t bytes(int64_t K) const { return (size_t)kHeaderBytes + x16_bytes(K) + scratch_bytes(); }
 };
 struct GemmRoute {
     bool mid;              // faster than what the product takes otherwise
@@ -102,7 +105,7 @@ size_t gemm_stream_pack_scratch_bytes(int64_t M, int64_t N, int64_t K);
 // Tens to hundreds of rows: X as FP16 values (plan.x16_rows() rows of ld16 halves, zeros up to whole K-tiles; rows
 // from M on may hold anything), the weights decoded in registers.
 // `ctrl`: the workspace's control region; `scratch`: plan.scratch_bytes() bytes.
-MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K);
+MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K, size_t most_bytes);   // (tiles_m 0: none with so little workspace)
 bool gemm_mid_applies(const MidPlan &p, int64_t N, int64_t K);
 double gemm_mid_micros(const MidPlan &p, int64_t M, int64_t N, int64_t K);   // estimate of a fused step of more than 32 rows
 double gemm_mid_few_rows_micros(const MidPlan &p, int64_t N, int64_t K);   // 20 to 32 rows

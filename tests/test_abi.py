@@ -139,3 +139,19 @@ def test_the_mid_size_shapes_cover_every_arrangement_the_planner_uses():
     assert fgmp.selftest_gemm_route(8, 24, 1024)[0] == 1 and fgmp.selftest_gemm_route(32, 264, 32768)[0] == 2
     assert fgmp.lib().fgmp_selftest_gemm_route(8, 24, 24, (ctypes.c_int64 * 6)()) == -2
     assert fgmp.lib().fgmp_selftest_gemm_route(8, 24, 16, None) == -1
+
+
+def test_long_products_of_few_columns_keep_the_mid_size_kernel_within_their_workspace():
+    """Sums of K in many parts can need more than the prefill kernel does: fewer parts then, not another kernel; and what the static
+    scratch array serves on the prefill kernel it serves with them."""
+    L = fgmp.lib()
+    for (M, K, N) in [(695, 7808, 394), (260, 10224, 16566), (497, 9744, 385), (744, 6960, 491), (609, 10160, 12095), (449, 8816, 486)]:
+        route = fgmp.selftest_gemm_route(M, N, K)
+        assert route[0] == 2, ((M, K, N), route)
+        mp = -(-M // 256) * 256
+        assert L.fgmp_workspace_bytes(M, N, K) <= L.fgmp_workspace_bytes(mp, N, K)
+        tiles = mp // 256 * -(-N // 256) % 256           # of a last round: FP32 sums of four parts, or two
+        fused = mp * (-(-K // 128) * 128) * 2 + (0 if tiles > 128 else tiles * (2 if tiles > 64 else 6) << 18)
+        if fused + 65536 + 4096 <= fgmp.STATIC_SCRATCH_BYTES:
+            too_small = -4                                # FGMP_ERR_BUFFER_TOO_SMALL, decided before the arguments are looked at
+            assert L.fgmp_quant_gemm_fused_static_scratch(None, 0, M, K, K, None, 0.0, 1.0, None, N, None, N, None) != too_small

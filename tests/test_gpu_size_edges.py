@@ -456,6 +456,25 @@ def test_weights_packed_with_an_infinite_threshold_hold_no_upper_half(rows, K, c
     assert fgmp.packed_info(fgmp.Packed(bufs[0], rows, K))["n_fp8_blocks"] == 0
 
 
+# ------------------------------------------------------------------ the same with K in fewer parts than would be fastest
+
+@pytest.mark.parametrize("M,K,N", [(497, 9744, 385), (439, 9616, 507)])
+def test_long_products_in_the_parts_that_have_room_match_oracle(M, K, N):
+    """In a workspace of the size a call is told, and on the static scratch array; with its control region left zero."""
+    assert fgmp.selftest_gemm_route(M, N, K)[0] == 2
+    xd, fxd, Tx, sx, pW, want, tol = _product(M, K, N, "bf16", 0.1, 98)
+    ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
+    ws[fgmp.WORKSPACE_CONTROL_BYTES:] = 0xFF
+    Y = fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, workspace=ws).clone()
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - want)
+    assert np.all(err <= tol), (err / tol).max()
+    assert int(ws[: fgmp.WORKSPACE_CONTROL_BYTES].sum()) == 0
+    assert torch.equal(fgmp.gemm(fgmp.quantize_activations(xd, fxd, Tx, sx), pW, workspace=ws), Y)
+    got = torch.full((M, N), float("nan"), device=DEV)
+    fgmp.quant_gemm_fused_static_scratch(xd, fxd, Tx, sx, pW, out=got)
+    assert torch.equal(got, Y)
+
+
 # ------------------------------------------------------------------ the kernel for mid-size products above 1024 rows
 
 # (M, K, N): one row more than the range in which the prefill kernel is tested; a last tile of a few rows, K shared among workgroups;
