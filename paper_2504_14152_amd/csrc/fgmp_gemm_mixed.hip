@@ -512,7 +512,10 @@ __global__ __launch_bounds__(kWM *kWN * 64, 1) void gemm_mixed_kernel(const _Flo
         // a tile, ordinary ones, streaming / ordinary, us: 1233 x 1088 x 19268 (M, K, N) 111.9 / 76.3, 3150 x 560 x 11325 144 / 87,
         // 2702 x 6224 x 6083 248 / 222, 4048 x 2784 x 1182 (19 MB) 58.4 / 56.9.  Below, streaming ones start their way to memory
         // earlier: 1116 x 2832 x 2628 (12 MB) 56.6 / 59.2, 3539 x 560 x 668 37.4 / 38.6.
-        if ((((uintptr_t)Y | (uintptr_t)ldy * 4u) & 127u) == 0 || M * N <= (int64_t)4 << 20) store(std::integral_constant<bool, true>{});
+        // Rows that start on half lines (N = 16 (mod 32)) lose less: 40 MB.  2542 x 1344 x 2992 (29 MB) 39.3 / 41.0, 1338 x 2032 x
+        // 5136 (26 MB) 47.8 / 49.1, 2276 x 864 x 7120 (62 MB) 45.3 / 42.2; over 389 such products a fiftieth either way.
+        const uintptr_t start = (uintptr_t)Y | (uintptr_t)ldy * 4u;
+        if ((start & 127u) == 0 || M * N <= (int64_t)((start & 63u) == 0 ? 10 : 4) << 20) store(std::integral_constant<bool, true>{});
         else store(std::integral_constant<bool, false>{});
     } else {
         // Each 32 x 32 accumulator tile is transposed through LDS (wave-private, the operand stages are

@@ -406,6 +406,20 @@ def test_prefill_results_in_rows_of_any_alignment_match_oracle(M, K, N):
     assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW), Y)
 
 
+# rows that start on half lines, up to 40 MB (streaming stores) and beyond (ordinary ones)
+@pytest.mark.parametrize("M,K,N", [(2257, 320, 3888), (2947, 256, 4016)])
+def test_prefill_results_in_rows_on_half_lines_are_those_of_whole_lines(M, K, N):
+    assert fgmp.selftest_gemm_route(M, N, K)[0] == 3 and N % 32 == 16
+    g = torch.Generator(device=DEV).manual_seed(M)
+    x, w = torch.randn(M, K, generator=g, device=DEV), torch.randn(N, K, generator=g, device=DEV)
+    f = torch.ones(K, device=DEV)
+    pW = fgmp.quantize_weights(w, f, 0.1, 0.01)
+    whole, half = torch.full((M, N + 16), 7.0, device=DEV), torch.full((M, N + 32), 7.0, device=DEV)
+    Y = fgmp.quant_gemm_fused(x, f, 0.1, 0.01, pW, out=whole[:, :N])
+    assert torch.equal(fgmp.quant_gemm_fused(x, f, 0.1, 0.01, pW, out=half[:, :N]), Y) and float(Y.std()) > 1.0
+    assert bool((whole[:, N:] == 7.0).all()) and bool((half[:, N:] == 7.0).all())
+
+
 # ------------------------------------------------------------------ selecting thresholds: states that calls borrow
 
 def test_more_selections_at_a_time_than_there_are_states_are_exact():
