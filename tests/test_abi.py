@@ -127,7 +127,7 @@ def test_the_mid_size_shapes_cover_every_arrangement_the_planner_uses():
     rng = random.Random(7)
     seen = set()
     for _ in range(60000):
-        r = fgmp.selftest_gemm_route(rng.randint(20, 1024), int(2 ** rng.uniform(3, 16)), 16 * int(2 ** rng.uniform(0, 11)))
+        r = fgmp.selftest_gemm_route(rng.choice((rng.randint(20, 1024), rng.randint(1025, 4096))), int(2 ** rng.uniform(3, 16)), 16 * int(2 ** rng.uniform(0, 11)))
         if r[0] == 2:
             seen.add((r[1:3], r[5] > 1))
     assert len(seen) > 20 and seen <= named, seen - named
@@ -136,7 +136,7 @@ def test_the_mid_size_shapes_cover_every_arrangement_the_planner_uses():
     # up to 32 rows: one launch where a workgroup has one round of row groups, whatever the length
     assert [fgmp.selftest_gemm_route(M, 4096, 11008)[0] for M in (20, 24, 28, 32)] == [2, 2, 0, 0]
     assert [fgmp.selftest_gemm_route(M, 11008, 5120)[0] for M in (20, 26, 28, 32)] == [0, 0, 2, 2]
-    assert fgmp.selftest_gemm_route(8, 24, 1024)[0] == 1 and fgmp.selftest_gemm_route(32, 264, 32768)[0] == 2
+    assert fgmp.selftest_gemm_route(19, 24, 32768)[0] == 1 and fgmp.selftest_gemm_route(32, 264, 32768)[0] == 2
     assert fgmp.lib().fgmp_selftest_gemm_route(8, 24, 24, (ctypes.c_int64 * 6)()) == -2
     assert fgmp.lib().fgmp_selftest_gemm_route(8, 24, 16, None) == -1
 

@@ -315,7 +315,8 @@ def test_quantize_weights_delta_score(N, K, per_elem, p):
     assert fgmp.packed_info(pk)["n_fp8_blocks"] == int(want["mask"].sum())
 
 
-@pytest.mark.parametrize("M,K,N", [(200, 304, 136), (8, 1024, 72), (32, 11008, 2304), (1100, 304, 136)])
+@pytest.mark.parametrize("M,K,N", [(200, 304, 136), (8, 1024, 72), (32, 11008, 2304), (1100, 304, 136), (4100, 304, 136),
+                                    (1, 5840, 40), (16, 4832, 1315), (13, 1152, 528), (24, 304, 1000)])
 def test_fused_delta_score(M, K, N):
     """Fused call with Eq. 8 scoring against the oracle: mid-size, decode and prefill products, and long dot products of 32
     rows, which take one launch with the Eq. 6 score and the mid-size kernel with this one."""
@@ -597,7 +598,7 @@ def test_fused_packed_output_matches_oracle(M, K, N):
     assert np.all(np.abs(Z.cpu().numpy().astype(np.float64) - zw) <= tol)
 
 
-@pytest.mark.parametrize("M,K,N", [(200, 512, 272), (4352, 256, 4096), (1100, 1040, 272)])
+@pytest.mark.parametrize("M,K,N", [(200, 512, 272), (4352, 256, 4096), (4100, 1040, 272)])
 def test_packed_output_on_random_inputs_is_consistent(M, K, N):
     """On ordinary inputs the FP32 results differ from the oracle's fp64 product in the last bits, so
     codes cannot be compared one by one; the packed results must still equal the standalone quantizer run on
@@ -863,7 +864,7 @@ def test_packed_results_are_valid_weight_operands(M, K, N):
     assert np.all(np.abs(Z.cpu().numpy().astype(np.float64) - zw) <= tol)
 
 
-@pytest.mark.parametrize("M,K,N", [(200, 512, 320), (4352, 256, 4096), (9, 1024, 192), (1100, 1040, 320)])
+@pytest.mark.parametrize("M,K,N", [(200, 512, 320), (4352, 256, 4096), (9, 1024, 192), (4100, 1040, 320)])
 def test_gated_packed_output_on_random_inputs_is_consistent(M, K, N):
     """On ordinary inputs: the gated call equals the oracle's gate applied to the very FP32 results
     the plain fused call writes, then the standalone quantizer -- so the kernel's SiLU is the oracle's,
@@ -1176,7 +1177,7 @@ def test_gemm_decode_llama_shapes_at_full_size(name):
 
 
 @pytest.mark.parametrize("M,K,N,p", [(4, 1024, 200, 0.1), (24, 2048, 136, 0.3), (300, 512, 264, 0.1),
-                                     (8, 256, 72, 0.0), (300, 256, 72, 0.0), (1100, 512, 264, 0.1), (1100, 256, 72, 0.0)])
+                                     (8, 256, 72, 0.0), (300, 256, 72, 0.0), (4100, 512, 264, 0.1), (4100, 256, 72, 0.0)])
 def test_compact_weights_relocated_to_bytes_used(M, K, N, p):
     """A compact weight tensor copied into a buffer of exactly bytes_used bytes
     (poisoned guard bytes after it) gives the same product, bit for bit, and
@@ -1233,7 +1234,7 @@ def test_mfma_rate_reference_runs():
     assert bool(torch.isfinite(sink).all())
 
 
-@pytest.mark.parametrize("M,kernel", [(300, 2), (1100, 3)])
+@pytest.mark.parametrize("M,kernel", [(300, 2), (4100, 3)])
 def test_gemm_kernel_timing_hook(M, kernel):
     """The measurement hook (only in the build variant with hooks) brackets the GEMM kernel of a product of more than 32
     rows -- the one for mid-size products and the prefill kernel -- with the caller's events; cleared, it records nothing;
@@ -1267,14 +1268,14 @@ def test_gemm_kernel_timing_hook(M, kernel):
 
 
 @pytest.mark.parametrize("M,K,N", [(4096, 4096, 12288), (4096, 4096, 22016), (4352, 512, 4096), (300, 1040, 264),
-                                    (2048, 3072, 8192), (1100, 1040, 3400), (1100, 1040, 264), (1300, 272, 1032)])
+                                    (2048, 3072, 8192), (4100, 1040, 1200), (4100, 1040, 264), (4100, 272, 520)])
 def test_hand_counted_waits_against_full_waits(M, K, N):
     """Runtime guard for the prefill kernel's hand-counted `s_waitcnt vmcnt(N)`: a second build of the same
     sources in which every such wait is a full one (nothing to miscount) must give the same Y bit for bit
     -- same instructions, same summation order, so any difference is a register read before its load
     landed.  QKV and FC1 at full size (FC1 with tiles split in two along K), a shape with four-part split
     tiles; K-steps that are a multiple of the loop's six (48 of them, whole tiles; 18 in two and in four ragged parts;
-    6); whatever the compiler made of the loop.  (300 rows: the kernel for mid-size products, the same guard.)"""
+    6, in two); whatever the compiler made of the loop.  (300 rows: the kernel for mid-size products, the same guard.)"""
     assert fgmp.selftest_gemm_route(M, N, K)[0] == (3 if M > 1024 else 2)
     from paper_2504_14152_amd import build
     _say(f"counted waits vs full waits {M}x{K}x{N}")
@@ -1343,17 +1344,19 @@ def test_decode_kernel_reads_weights_that_are_not_compact():
     assert torch.equal(Y, Ys)
 
 
-@pytest.mark.parametrize("M,K,N", [(8, 1024, 512), (8, 11008, 512), (24, 2048, 520), (300, 512, 520), (70, 1024, 512),
-                                    (1100, 1040, 520), (1100, 512, 3400)])
+@pytest.mark.parametrize("M,K,N", [(8, 1024, 512), (8, 11008, 512), (24, 2048, 520), (19, 32768, 72), (300, 512, 520), (70, 1024, 512),
+                                    (4100, 1040, 136), (4100, 512, 1200)])
 def test_fused_call_replays_in_a_hip_graph(M, K, N):
     """The hot-path calls only enqueue kernels on the caller's stream (no allocation, no synchronization,
     no memset nodes: arrival counters are put back to zero by the kernels that use them), so a
     captured step can be replayed: decode shapes (one launch; with K in one part and in three parts that
-    meet at the row groups' counters; the older two-kernel path for an odd number of row-tiles), mid-size products,
+    meet at the row groups' counters; an odd number of row-tiles; the two launches with K in more than sixteen parts), mid-size products,
     and prefill shapes whose tiles are computed in four and in two parts.  Every replay, with eager work and
     synchronizations in between, must reproduce the eager result bit for bit."""
+    if M == 19:
+        assert fgmp.selftest_gemm_route(M, N, K)[0] == 1
     if M > 1024:
-        assert fgmp.selftest_gemm_route(M, N, K)[3:5] == ((15, 4) if N == 520 else (70, 2))
+        assert fgmp.selftest_gemm_route(M, N, K)[3:5] == ((17, 4) if N == 136 else (85, 2))
     c = _quantized_pair(M, K, N, 43, 0.1, per_elem_w=False)
     ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
     Y_eager = fgmp.quant_gemm_fused(c["xd"], c["fxd"], c["Tx"], c["sx"], c["pW"], workspace=ws).clone()

@@ -104,7 +104,7 @@ def test_products_of_a_few_dozen_to_a_few_hundred_rows_match_oracle(M, K, N, dty
 # (M, K, N), (16-row groups, 16-column groups of a wave), K shared among workgroups: every instantiation that the planner
 # uses, with and without a shared K where it uses both; the last one has 411 workgroups, more than run at once
 MID_PLANS = [((49, 160, 10), (2, 2), False), ((49, 5008, 8), (2, 2), True), ((23, 4368, 17911), (2, 3), False),
-             ((20, 7232, 5671), (2, 3), True), ((21, 3360, 26570), (2, 4), False), ((24, 12704, 6355), (2, 4), True),
+             ((32, 7184, 6183), (2, 3), True), ((21, 3360, 26570), (2, 4), False), ((24, 12704, 6355), (2, 4), True),
              ((40, 144, 8), (3, 2), False), ((39, 4512, 8), (3, 2), True), ((33, 160, 16503), (3, 3), False),
              ((65, 5616, 2751), (3, 3), True), ((65, 272, 12409), (3, 4), False), ((36, 9472, 6289), (3, 4), True),
              ((199, 160, 8), (4, 2), False), ((195, 3632, 9), (4, 2), True), ((153, 272, 5647), (4, 3), False),
@@ -181,7 +181,7 @@ def test_long_products_of_few_rows_quantize_the_results_of_the_plain_call():
 
 
 def test_static_scratch_takes_products_of_more_than_32_rows():
-    # (the last one: split tiles whose partial sums only fit right behind the activations)
+    # (the last one: prefill tiles split along K, whose partial sums fit right behind the activations only, or the kernel for fewer rows)
     for M, K, N in ((64, 4096, 1024), (300, 1040, 264), (200, 16, 24), (1100, 256, 264)):
         xd, fxd, Tx, sx, pW, _, _ = _product(M, K, N, "bf16", 0.1, 92)
         got = torch.full((M, N), float("nan"), device=DEV)
@@ -189,11 +189,11 @@ def test_static_scratch_takes_products_of_more_than_32_rows():
         assert torch.equal(got, fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW))
 
 
-# ------------------------------------------------------------------ products of more than 1024 rows
+# ------------------------------------------------------------------ products on the prefill kernel
 
-# (M, K, N), all on the 256 x 256 tiles: a round of 70 to 80 tiles, each computed in two parts of K whose sums meet in
+# (M, K, N), all on the 256 x 256 tiles: a round of 85 to 119 tiles, each computed in two parts of K whose sums meet in
 # memory, with 4, 6, 8, 10, 16 and 18 K-steps of 64 -- of which the main loop turns over 6 at a time -- and ragged ends
-@pytest.mark.parametrize("M,K,N", [(1100, 256, 3400), (1100, 272, 4096), (1025, 512, 4096), (1100, 640, 3400), (1279, 1024, 3500), (1100, 1040, 3400)])
+@pytest.mark.parametrize("M,K,N", [(4100, 256, 1200), (4097, 272, 1280), (4200, 512, 1100), (4100, 640, 1500), (4352, 1024, 1030), (4100, 1040, 1700)])
 def test_products_in_two_parts_match_oracle(M, K, N):
     """Within 1e-5 of the sum of magnitudes, and the same bits every time, whichever part comes first."""
     route = fgmp.selftest_gemm_route(M, N, K)
@@ -394,7 +394,7 @@ def test_decode_steps_with_an_odd_number_of_row_tiles_match_oracle(M, K, N, dtyp
 # ------------------------------------------------------------------ prefill results whose rows do not start on a cache line
 
 # more than 16 MB of results (ordinary stores) and less (streaming ones), both with rows that start anywhere
-@pytest.mark.parametrize("M,K,N", [(1100, 48, 4099), (1100, 48, 1033)])
+@pytest.mark.parametrize("M,K,N", [(4100, 48, 1033), (4100, 48, 777)])
 def test_prefill_results_in_rows_of_any_alignment_match_oracle(M, K, N):
     xd, fxd, Tx, sx, pW, want, tol = _product(M, K, N, "bf16", 0.1, 97)
     assert fgmp.selftest_gemm_route(M, N, K)[0] == 3
@@ -491,7 +491,7 @@ def test_long_products_in_the_parts_that_have_room_match_oracle(M, K, N):
 
 # ------------------------------------------------------------------ the kernel for mid-size products above 1024 rows
 
-# (M, K, N): one row more than the range in which the prefill kernel is tested; a last tile of a few rows, K shared among workgroups;
+# (M, K, N): few columns; a last tile of a few rows, K shared among workgroups;
 # more tiles than run at once; the most rows it takes
 @pytest.mark.parametrize("M,K,N", [(1301, 272, 264), (1545, 3088, 320), (2500, 144, 1408), (4096, 528, 136)])
 def test_mid_size_kernel_above_1024_rows_matches_oracle(M, K, N):
