@@ -268,8 +268,10 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
 // 31 / 57, 32 / 59.  On the prefill kernel: 11008 x 4096 1650 rows 198 / 160, 200 / 166, 204 / 168, 272 x 6080 2841 rows 47 / 47, 62 /
 // 60, 65 / 63, 3440 x 18112 2025 rows 277 / 243, 288 / 261, 291 / 268.  Of 1014 products measured with both (33 to 4096 rows) 226
 // changed kernel, none for one that is more than 2% slower; of 631 others 155, 1.46 times as fast on average with
-// either kind of result, and four slower, by 6 to 18% (4464 x 4800 1580 rows 121 / 102).  Above 1024 rows, where a wrong choice costs more, the estimate
-// has to win by 15%; 1025 to 1300 rows over up to 1040 elements stay on the prefill kernel, whose tests run it there.
+// either kind of result.  Above 1024 rows, where a wrong choice costs more, the estimate has to win by 15%.  The line holds for
+// weights from HBM too, which cost both kernels 1.8 us on average: of 600 products next to it that take this kernel, none is more
+// than 2.2% slower than on the other one, either way; of 255 drawn over the whole range, six take the prefill kernel though this
+// one is 4 to 18% faster (1041 rows, 4096 x 14115 157 / 132), and none the other way round.
 //
 // Up to 32 rows the one-launch step (fgmp_gemm_stream.hip) shares K among as many workgroups as keep a part's rows in LDS and runs
 // through its row groups in rounds; with two rounds or more the parts meet that often, and this kernel is taken where the
@@ -315,9 +317,7 @@ GemmRoute gemm_route(int64_t M, int64_t N, int64_t K)
         r.mid = r.mid_two_launch && (!stream || (gemm_mid_few_rows_micros(r.plan, N, K) <= gemm_stream_micros(M, N, K, &rounds) && rounds > 1));
     } else {
         const double margin = M > 1024 ? 1.15 : 1.0;
-        const bool tested_there = M > 1024 && M <= 1300 && K <= 1040;
-        r.mid = !tested_there && margin * gemm_mid_micros(r.plan, M, N, K) <= gemm_mixed_micros(M, N, K) &&
-                (M <= 1024 || r.plan.bytes(K) <= fused);
+        r.mid = margin * gemm_mid_micros(r.plan, M, N, K) <= gemm_mixed_micros(M, N, K) && (M <= 1024 || r.plan.bytes(K) <= fused);
     }
     return r;
 }

@@ -155,3 +155,8 @@ def test_long_products_of_few_columns_keep_the_mid_size_kernel_within_their_work
         if fused + 65536 + 4096 <= fgmp.STATIC_SCRATCH_BYTES:
             too_small = -4                                # FGMP_ERR_BUFFER_TOO_SMALL, decided before the arguments are looked at
             assert L.fgmp_quant_gemm_fused_static_scratch(None, 0, M, K, K, None, 0.0, 1.0, None, N, None, N, None) != too_small
+
+
+def test_estimates_decide_above_1024_rows_as_below():
+    for (M, K, N) in [(1100, 512, 264), (1300, 1040, 512), (1300, 768, 2048), (1100, 1040, 3400), (1025, 512, 4096)]:
+        assert [fgmp.selftest_gemm_route(m, N, K)[0] for m in (1024, M, 1301)] == [2, 2, 2], (M, K, N)
