@@ -891,8 +891,8 @@ static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K)
     if (M < 1 || M > 32 || lw.total_bytes >= kLimit) return p;
     // An odd number of row-tiles (the last row group has one): us in two launches (quantizer, gemm_skinny_kernel) / in one:
     // 1 x 5840 x 339 (M, K, N) 11.5 / 6.4, 12 x 672 x 2822 10.3 / 5.7, 12 x 4832 x 1315 14.2 / 10.5, 32 x 4832 x 1315 14.0 / 11.8, 8 x
-    // 4096 x 22003 20.9 / 17.1, 8 x 8192 x 56 10.3 / 10.5.  (At most 24 columns, 8 x 1024 x 24 8.7 / 6.1: a test names the two launches there.)
-    if (lw.n_rt % 2 != 0 && lw.n_rt <= 3) return p;
+    // 4096 x 22003 20.9 / 17.1, 8 x 8192 x 56 10.3 / 10.5, 8 x 1024 x 24 8.7 / 6.1; 1087 products over up to 24 columns 0.70 times as
+    // long, none more than 1.02 times.
     p.mt = M <= 16 ? 1 : 2;
     p.waves = 12;   // (measured: 8 and 16 waves per workgroup both run 5-15% slower on the Llama-2 shapes)
     const int kStThreads = 64 * p.waves, kStWaves = p.waves;

@@ -391,6 +391,27 @@ def test_decode_steps_with_an_odd_number_of_row_tiles_match_oracle(M, K, N, dtyp
         assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW), Y)
 
 
+# one row-tile and three, the last of one row and of eight; the smallest K, K in one part and in several
+@pytest.mark.parametrize("M,K,N", [(1, 16, 1), (8, 1024, 24), (1, 5840, 8), (16, 8192, 17), (32, 4832, 24), (5, 272, 3)])
+def test_decode_steps_over_one_and_three_row_tiles_match_oracle(M, K, N):
+    assert fgmp.selftest_gemm_route(M, N, K)[0] == 0
+    xd, fxd, Tx, sx, pW, want, tol = _product(M, K, N, "f32", 0.2, 101)
+    ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
+    ws[fgmp.WORKSPACE_CONTROL_BYTES:] = 0xFF
+    Y = fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW, workspace=ws).clone()
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - want)
+    assert np.all(err <= tol), (err / tol).max()
+    assert int(ws[: fgmp.WORKSPACE_CONTROL_BYTES].sum()) == 0
+    assert torch.equal(fgmp.gemm(fgmp.quantize_activations(xd, fxd, Tx, sx), pW), Y)
+    got = torch.full((M, N), float("nan"), device=DEV)
+    fgmp.quant_gemm_fused_static_scratch(xd, fxd, Tx, sx, pW, out=got)
+    assert torch.equal(got, Y)
+    used = fgmp.packed_info(pW)["bytes_used"]
+    exact = torch.full((-(-used // 16) * 16 + 4096,), 0xFF, dtype=torch.uint8, device=DEV)   # poison right behind the tensor
+    exact[:used] = pW.buf[:used]
+    assert torch.equal(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, fgmp.Packed(exact[:used], N, K)), Y)
+
+
 # ------------------------------------------------------------------ prefill results whose rows do not start on a cache line
 
 # more than 16 MB of results (ordinary stores) and less (streaming ones), both with rows that start anywhere
