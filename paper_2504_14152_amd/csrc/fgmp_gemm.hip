@@ -284,8 +284,11 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
 // N K^2 = 2^38 on, and only where it needs no more workspace than the step it replaces.)
 //
 // Steps that take two launches anyway -- K in more than 16 parts, the Eq. 8 score -- are faster on this kernel throughout: 32768 x
-// 256 32 rows 26.1 / 20.8, 11008 x 4096 with the Eq. 8 score 21.3 / 17.6.  With an odd number of row-tiles it is taken from
-// N K^2 = 2^38 on without the estimates (4096 x 22003 32 rows 24.7 / 21.2, cached weights).
+// 256 32 rows 26.1 / 20.8, 11008 x 4096 with the Eq. 8 score 21.3 / 17.6.
+//
+// An odd number of row-tiles is nothing special to either kernel.  Of 1348 such products from N K^2 = 2^38 on, weights from HBM, the
+// estimates leave 511 to the one launch, which all took two: 6352 x 8788 22 rows (one launch / this kernel) 17.2 / 24.2, 6960 x 6195
+// 24 rows 17.1 / 18.9, 0.90 times as long on average, eleven of them 3 to 7% longer (8064 x 18835 30 rows 37.6 / 35.3).
 constexpr int64_t kMidMinRows = 20, kMidMaxRows = 4096;
 
 static size_t decode_bytes(int64_t M, int64_t N, int64_t K)
@@ -293,7 +296,7 @@ static size_t decode_bytes(int64_t M, int64_t N, int64_t K)
     return gemm_skinny_applies(M, N, K) ? skinny_x16_bytes(M, K) + gemm_skinny_workspace_bytes(M, N, K) : 0;
 }
 
-// (the one-launch step walks through W in groups of two row-tiles)
+// (what a decode step is told to bring: with an odd number of row-tiles, what the two launches use, which once served it)
 static bool even_row_tiles(int64_t N) { return (N + kTileRows - 1) / kTileRows % 2 == 0; }
 
 GemmRoute gemm_route(int64_t M, int64_t N, int64_t K)
@@ -311,8 +314,8 @@ GemmRoute gemm_route(int64_t M, int64_t N, int64_t K)
     r.plan = gemm_mid_plan(M, N, K, M > 32 && M <= 1024 ? room : SIZE_MAX);
     if (!gemm_mid_applies(r.plan, N, K)) return r;
     if (M <= 32) {
-        const bool stream = even_row_tiles(N) && gemm_stream_applies(M, N, K);
-        r.mid_two_launch = r.plan.bytes(K) <= (stream ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
+        const bool stream = gemm_stream_applies(M, N, K);
+        r.mid_two_launch = r.plan.bytes(K) <= (stream && even_row_tiles(N) ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
         int rounds = 0;
         r.mid = r.mid_two_launch && (!stream || (gemm_mid_few_rows_micros(r.plan, N, K) <= gemm_stream_micros(M, N, K, &rounds) && rounds > 1));
     } else {

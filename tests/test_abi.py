@@ -160,3 +160,11 @@ def test_long_products_of_few_columns_keep_the_mid_size_kernel_within_their_work
 def test_estimates_decide_above_1024_rows_as_below():
     for (M, K, N) in [(1100, 512, 264), (1300, 1040, 512), (1300, 768, 2048), (1100, 1040, 3400), (1025, 512, 4096)]:
         assert [fgmp.selftest_gemm_route(m, N, K)[0] for m in (1024, M, 1301)] == [2, 2, 2], (M, K, N)
+
+
+def test_an_odd_number_of_row_tiles_takes_the_kernel_of_its_even_neighbours():
+    """20 to 32 rows, long products; where the neighbours differ, the estimates are next to each other."""
+    for (M, K, N) in [(20, 5120, 11000), (20, 8192, 8184), (32, 11008, 4088), (24, 11008, 4088), (28, 5120, 11000), (20, 4096, 22008)]:
+        near = {fgmp.selftest_gemm_route(M, n, K)[0] for n in (N - 8, N + 8)}
+        assert -(-N // 8) % 2 == 1 and near == {fgmp.selftest_gemm_route(M, N, K)[0]}, (M, K, N)
+    assert fgmp.selftest_gemm_route(20, 8184, 8192)[0] == 0 and fgmp.selftest_gemm_route(24, 4088, 11008)[0] == 2

@@ -368,7 +368,8 @@ def test_clipped_scales_of_blocks_with_equal_errors_are_the_brute_force_ones(sha
 
 # (M, K, N), N / 8 rounded up odd: one, eight, sixteen and 32 rows; K in one part and in several; a last row-tile of one row
 @pytest.mark.parametrize("M,K,N,dtype,p", [(1, 5840, 40, "bf16", 0.2), (8, 4112, 1001, "f32", 0.1), (16, 1040, 1000, "bf16", 1.0),
-                                           (5, 272, 4353, "bf16", 0.0), (32, 4832, 1315, "f32", 0.2), (9, 8192, 72, "bf16", 0.1)])
+                                           (5, 272, 4353, "bf16", 0.0), (32, 4832, 1315, "f32", 0.2), (9, 8192, 72, "bf16", 0.1),
+                                           (25, 14816, 1287, "bf16", 0.1)])
 def test_decode_steps_with_an_odd_number_of_row_tiles_match_oracle(M, K, N, dtype, p):
     """Within 1e-5 of the sum of magnitudes; whatever lies behind the last row-tile's bytes must not show."""
     from paper_2504_14152_amd import build
