@@ -533,17 +533,12 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
 // (FGMP_EPILOGUE_ONE_LAUNCH); otherwise, for other shapes, the gated epilogue at decode sizes and the
 // two-pass path, the FP32 results go to the workspace and the standalone quantizer runs over them -- the
 // same arithmetic on the same values.
-static size_t staging_bytes(int64_t M, int64_t N, int epilogue)
-{
-    // FP32 staging of the product for the shapes whose epilogue cannot quantize, and of the gated values
-    const size_t staged = (size_t)align_up((uint64_t)M * N * 4, 256);
-    const size_t gated = epilogue == FGMP_EPILOGUE_SILU_GATE ? (size_t)align_up((uint64_t)M * (N / 2) * 4, 256) : 0;
-    return staged + gated;
-}
+// (the gated activation is applied as the quantizer reads the product: no room of its own)
+static size_t staging_bytes(int64_t M, int64_t N) { return (size_t)align_up((uint64_t)M * N * 4, 256); }
 
-size_t gemm_workspace_bytes_packed_out(int64_t M, int64_t N, int64_t K, int epilogue)
+size_t gemm_workspace_bytes_packed_out(int64_t M, int64_t N, int64_t K)
 {
-    return (size_t)align_up(gemm_workspace_bytes(M, N, K), 256) + staging_bytes(M, N, epilogue);
+    return (size_t)align_up(gemm_workspace_bytes(M, N, K), 256) + staging_bytes(M, N);
 }
 
 fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, int64_t ldx,
@@ -568,7 +563,7 @@ fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, i
     if (packed_Y_bytes < ly.total_bytes) return FGMP_ERR_BUFFER_TOO_SMALL;
     const GemmRoute route = gemm_route(M, N, K);
     const size_t base_bytes = gemm_workspace_need(M, N, K, route);
-    if (workspace_bytes < align_up(base_bytes, 256) + staging_bytes(M, N, epilogue)) return FGMP_ERR_BUFFER_TOO_SMALL;
+    if (workspace_bytes < align_up(base_bytes, 256) + staging_bytes(M, N)) return FGMP_ERR_BUFFER_TOO_SMALL;
     PackOut po;
     po.out = make_view(packed_Y, ly);
     po.layout = ly;

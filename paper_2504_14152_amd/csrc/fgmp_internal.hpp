@@ -66,7 +66,7 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
                          float threshold, float scale_x, const void *packed_W, int64_t N, float *Y, int64_t ldy,
                          void *workspace, size_t workspace_bytes, hipStream_t st, const GemmRoute &route,
                          int score_mode = FGMP_SCORE_NVFP4_ERROR, const PackOut *pack_out = nullptr, bool tight = false);
-size_t gemm_workspace_bytes_packed_out(int64_t M, int64_t N, int64_t K, int epilogue = FGMP_EPILOGUE_NONE);
+size_t gemm_workspace_bytes_packed_out(int64_t M, int64_t N, int64_t K);
 fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, int64_t ldx,
                                     const float *fisher_k, float threshold, float scale_x, const void *packed_W,
                                     int64_t N, const float *fisher_n, float threshold_y, float scale_y,

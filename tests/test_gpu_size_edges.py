@@ -540,6 +540,24 @@ def test_mid_size_kernel_above_1024_rows_matches_oracle(M, K, N):
         assert all(torch.equal(a, b) for a, b in zip(got, ref))
 
 
+# ------------------------------------------------------------------ gated products in a workspace of just the size
+
+# staged for a decode step, with K in parts, and for the mid-size kernel; in the prefill kernel's epilogue
+@pytest.mark.parametrize("M,K,N", [(9, 1024, 192), (16, 8192, 128), (200, 512, 320), (4100, 272, 320)])
+def test_gated_products_stay_within_the_workspace_they_are_told(M, K, N):
+    xd, fxd, Tx, sx, pW, _, _ = _product(M, K, N, "bf16", 0.1, 102)
+    f_h = torch.ones(N // 2, device=DEV)
+    size = fgmp.workspace_bytes_packed_out(M, N, K, fgmp.EPILOGUE_SILU_GATE)
+    assert size == fgmp.workspace_bytes_packed_out(M, N, K, fgmp.EPILOGUE_NONE)
+    room = fgmp.new_workspace(size + 65536, DEV)
+    room[fgmp.WORKSPACE_CONTROL_BYTES:] = 0xA5
+    got = fgmp.quant_gemm_fused_packed_out(xd, fxd, Tx, sx, pW, f_h, 1e-4, 0.05, workspace=room[:size], epilogue=fgmp.EPILOGUE_SILU_GATE)
+    assert bool((room[size:] == 0xA5).all())
+    h = torch.from_numpy(orc.gate_columns(fgmp.quant_gemm_fused(xd, fxd, Tx, sx, pW).cpu().numpy())).to(DEV)
+    for a, b in zip(fgmp.unpack_canonical(got), fgmp.unpack_canonical(fgmp.quantize_activations(h.contiguous(), f_h, 1e-4, 0.05))):
+        assert torch.equal(a, b)
+
+
 # ------------------------------------------------------------------ decode steps: K shared among more than four workgroups
 
 # (M, K): 5, 6, 7 and 13 parts, added up six at a time; 5, 8, 11 and 16 parts, four at a time
