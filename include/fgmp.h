@@ -210,7 +210,7 @@ fgmp_status_t fgmp_quant_gemm_fused_ex(const void *X, fgmp_dtype_t dt, int64_t M
  * compared with `threshold_y` and stored as FP8 or NVFP4 in `packed_Y`, a packed M x N activation
  * tensor (tensor scale `scale_y`) that the next layer's fgmp_gemm consumes.  The values that are
  * quantized are exactly the FP32 numbers fgmp_quant_gemm_fused would have written.  For shapes that
- * run on the prefill kernel this happens in its epilogue; smaller M stage the FP32 results in the
+ * run on the prefill kernel this happens in its epilogue; others stage the FP32 results in the
  * workspace and launch the standalone quantizer.  A decode step (M <= 32) can also do it inside its one
  * launch (FGMP_EPILOGUE_ONE_LAUNCH of the _ex form): the wave that holds the final sums of 16 output
  * columns quantizes them, and the eight such waves behind one 128-column tile of packed_Y settle the

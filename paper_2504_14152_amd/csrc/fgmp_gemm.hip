@@ -288,7 +288,8 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
 //
 // An odd number of row-tiles is nothing special to either kernel.  Of 1348 such products from N K^2 = 2^38 on, weights from HBM, the
 // estimates leave 511 to the one launch, which all took two: 6352 x 8788 22 rows (one launch / this kernel) 17.2 / 24.2, 6960 x 6195
-// 24 rows 17.1 / 18.9, 0.90 times as long on average, eleven of them 3 to 7% longer (8064 x 18835 30 rows 37.6 / 35.3).
+// 24 rows 17.1 / 18.9, 0.90 times as long on average, eleven of them 3 to 7% longer (8064 x 18835 30 rows 37.6 / 35.3).  Out of the
+// Infinity Cache, which these estimates are not made for, 1.06 times (10864 x 12228 24 rows 29.9 / 26.1).
 constexpr int64_t kMidMinRows = 20, kMidMaxRows = 4096;
 
 static size_t decode_bytes(int64_t M, int64_t N, int64_t K)

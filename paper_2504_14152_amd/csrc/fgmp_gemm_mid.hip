@@ -1,6 +1,6 @@
-// Block-mixed-precision GEMM (Sec. 4.1) for tens to hundreds of activation rows: between the decode step that
-// streams the weights past a handful of rows and the prefill kernel whose 256 x 256 tiles are too few to fill
-// the chip here.
+// Block-mixed-precision GEMM (Sec. 4.1) for tens to hundreds of activation rows, and up to 4096 over few columns or a short
+// K: between the decode step that streams the weights past a handful of rows and the prefill kernel whose 256 x 256
+// tiles are too few to fill the chip here.
 //
 // What bounds it: at 64 rows the weights' bytes, the activations' way to the compute units, the decode and the
 // matrix instructions take about the same time (3-4 us each for a Llama-2-7B QKV product), there are never enough

@@ -30,7 +30,7 @@ fgmp_status_t quantize_traffic_model(const void *X, fgmp_dtype_t dt, int64_t row
 #endif
 fgmp_status_t unpack_tensor(const void *packed, int64_t rows, int64_t K, uint8_t *codes, uint8_t *scales,
                             uint8_t *mask, hipStream_t st);
-// How the kernel for a few dozen to a few hundred rows shares a product out (fgmp_gemm_mid.hip), and whether a product is
+// How the kernel for mid-size products (20 to 4096 rows) shares a product out (fgmp_gemm_mid.hip), and whether a product is
 // computed by it.  Comparing the arrangements takes 0.2 to 0.5 us: a call does it once and hands the result on.
 struct MidPlan {
     int mt, nt, wn, wk;                          // a workgroup: 16 mt rows x 16 nt wn columns, wk K-tiles at a time
