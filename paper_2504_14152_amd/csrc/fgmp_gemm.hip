@@ -395,7 +395,7 @@ fgmp_status_t gemm_packed(const void *packed_X, int64_t M, const void *packed_W,
         _Float16 *x16 = reinterpret_cast<_Float16 *>(static_cast<char *>(workspace) + kHeaderBytes);
         const fgmp_status_t rcx = launch_decode_f16(make_decode_job(A, la, x16, ld16, la.n_rt), nullptr, nullptr, 0, st);
         if (rcx != FGMP_OK) return rcx;
-        return gemm_mid(route.plan, A.hdr, x16, ld16, packed_W, M, N, K, Y, ldy, ctrl,
+        return gemm_mid(route.plan, MidInput{A.hdr}, x16, ld16, packed_W, M, N, K, Y, ldy, ctrl,
                         static_cast<char *>(workspace) + kHeaderBytes + route.plan.x16_bytes(K), st);
     }
     if (gemm_skinny_applies(M, N, K)) {
@@ -476,13 +476,20 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
     }
     if (mid) {
         if (pack_out != nullptr) return FGMP_ERR_UNSUPPORTED;   // the caller stages the FP32 results
-        // the quantizer writes the FP16 values of the codes it selects, then one launch of the product
+        // the FP16 values of the codes that the quantizer selects: made by the launch of the product, or by one before it
         const int64_t ld16 = round_up(K, kTileK);
         _Float16 *x16 = reinterpret_cast<_Float16 *>(ws + kHeaderBytes);
-        const fgmp_status_t rc = quantize_tensor(X, dt, M, K, ldx, fisher_k, 0, threshold, scale_x, ws, sizeof(PackedHeader), nullptr,
-                                                 false, st, x16, ld16, nullptr, 0, score_mode);
-        if (rc != FGMP_OK) return rc;
-        return gemm_mid(route.plan, reinterpret_cast<const PackedHeader *>(ws), x16, ld16, packed_W, M, N, K, Y, ldy, workspace,
+        MidInput in{reinterpret_cast<const PackedHeader *>(ws)};
+        if (gemm_mid_quantizes(route.plan, M, N, K, ldx > 0 && ldx < INT64_MAX / 4 ? ldx * (dt == FGMP_F32 ? 4 : 2) : 0)) {
+            const fgmp_status_t rc = check_quantizer_input(X, dt, M, K, ldx, fisher_k, threshold, scale_x, score_mode);
+            if (rc != FGMP_OK) return rc;
+            in = MidInput{nullptr, X, ldx, fisher_k, threshold, scale_x, dt == FGMP_F32, score_mode == FGMP_SCORE_DELTA};
+        } else {
+            const fgmp_status_t rc = quantize_tensor(X, dt, M, K, ldx, fisher_k, 0, threshold, scale_x, ws, sizeof(PackedHeader), nullptr,
+                                                     false, st, x16, ld16, nullptr, 0, score_mode);
+            if (rc != FGMP_OK) return rc;
+        }
+        return gemm_mid(route.plan, in, x16, ld16, packed_W, M, N, K, Y, ldy, workspace,
                         ws + kHeaderBytes + route.plan.x16_bytes(K), st);
     }
     const bool in_kernel_prefill = fused_prefill(M, N, K);

@@ -21,15 +21,23 @@
 //   * The activations (FP16 values, written by the quantizer) go to LDS directly, two rounds deep, one barrier
 //     per round.  A row of a K-tile is 256 bytes = 16 chunks; stored in an order that
 //     makes the 16-byte operand reads free of bank conflicts.
+//   * Where the activations are at most one block per thread of the launch, the launch quantizes them (kQuantize): a workgroup
+//     makes its share of the FP16 values, says so, asks for its first weights and waits for the other shares.  A quantizer
+//     launch costs 4 us of which 1.5 are work, this 2 us more before the first round: 64 rows 4096 x 12288 18.3 / 16.7, 77 rows 2064
+//     x 5003 13.2 / 11.5, 120 rows 368 x 603 8.5 / 7.2, 200 rows 4096 x 22016 44.7 / 43.7 us.  With two blocks per thread the
+//     shares take as long as the launch they replace (872 x 3408 x 764 (M, K, N) 22.8 / 23.2, 512 x 11008 x 4096 with three 56.8 /
+//     58.0), and workgroups beyond the first 256 would wait again (663 x 4096 x 22016 127 / 130).
 //   * Workgroups that run at the same time on an XCD work on the same rows and the same part of K, tile by tile along
 //     N, so the activations come from that XCD's L2.
 // All loads of the loop are assembly with hand-counted waits, two per round: while a direct load to LDS is pending the
 // compiler waits for every load wherever it needs one, and where it does not know of the direct loads its waits are as
 // bad (1.8 us instead of 1.2 for a round of MT = 4, NT = 2: the first wait after the activations' loads waited for them).
 #include <algorithm>
+#include <cstdlib>
 #include <type_traits>
 
 #include "fgmp_gemm_common.hpp"
+#include "fgmp_quant_block.hpp"
 
 namespace fgmp {
 
@@ -41,6 +49,14 @@ namespace fgmp {
 #endif
 
 constexpr int kMidThreads = 512;
+// Workgroups that share the quantizing, at most; how often one looks whether the others are done (0.7 us a look; the shares take 2
+// us) before it makes a missing share itself.
+constexpr uint32_t kMidMaxUnits = 256;
+constexpr int kMidPatience = 8;
+// Behind the units' words: how many workgroups wait no longer, in sixteen counters on lines of their own (192 additions to one
+// word took 2 us), then how many of these are complete.
+constexpr uint32_t kMidPassed = kMidMaxUnits, kMidPassedGroups = 16, kMidPassedStep = 16;
+constexpr uint32_t kMidPassedAll = kMidPassed + kMidPassedGroups * kMidPassedStep, kMidDoneWords = kMidPassedAll + 16;
 constexpr uint32_t kMidRsrc = 0x00020000;   // raw buffer, 32-bit data format
 
 // division by a constant that the host knows; exact for dividends below 2^16 and divisors below 2^16
@@ -48,6 +64,21 @@ struct MidDiv {
     uint32_t d, mul;
     static MidDiv by(uint32_t d) { return MidDiv{d, d > 1 ? (uint32_t)(0x100000000ull / d) + 1u : 0u}; }
     __device__ __forceinline__ uint32_t operator()(uint32_t v) const { return d == 1u ? v : __umulhi(v, mul); }
+};
+
+// Activations that the launch quantizes itself.  They are dealt out 64 blocks at a time: chunk c to wave c / n_units of
+// workgroup c % n_units.
+struct MidQuant {
+    const void *X;
+    const float *fisher;
+    float T, S;
+    int f32, delta;             // FP32 input (else bf16); the Eq. 8 score
+    uint32_t x_bytes, row_bytes;
+    uint32_t nb;                // blocks of a row
+    uint32_t row_blocks, row_mul;   // blocks of a row in whole K-tiles, and its divisor's multiplier
+    uint32_t n_chunks, n_units;
+    int patience;
+    uint32_t *done;             // one word per unit, then counters (kMidPassed); zero between launches
 };
 
 struct MidArgs {
@@ -66,9 +97,90 @@ struct MidArgs {
     const PackedHeader *xh;     // header of the activations (tensor scale, shape check)
     int64_t ldy;
     int64_t w_rows, w_K, x_rows, x_K;                    // the shapes the headers must state
+    MidQuant q;
 };
 
-template <int MT, int NT, int WN, int WK>
+// A block of the activations on its way: chunk c of the launch, a lane's block.
+struct MidBlock {
+    u32x4_t x[4], f[4];   // (bf16: two of x)
+    bool valid;
+};
+__device__ __forceinline__ void mid_place(const MidQuant &q, uint32_t b, uint32_t &m, uint32_t &kb)
+{
+    m = __umulhi(b, q.row_mul);
+    kb = b - m * q.row_blocks;
+}
+// (loads outside the tensor: beyond the buffers, zeros)
+__device__ __forceinline__ void mid_load_block(const MidArgs &a, uint32_t c, int lane, MidBlock &r)
+{
+    const MidQuant &q = a.q;
+    uint32_t m, kb;
+    mid_place(q, c * 64u + (uint32_t)lane, m, kb);
+    r.valid = c < q.n_chunks && m < (uint32_t)a.M && kb < q.nb;
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(q.X), 0, (int)q.x_bytes, kMidRsrc);
+    const __amdgpu_buffer_rsrc_t fbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(q.fisher), 0, (int)(q.nb * (kBlock * 4u)), kMidRsrc);
+    const uint32_t xoff = r.valid ? m * q.row_bytes + kb * (q.f32 ? kBlock * 4u : kBlock * 2u) : 0xFFFFFF00u;
+    const uint32_t foff = r.valid ? kb * (kBlock * 4u) : 0xFFFFFF00u;
+    r.x[0] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)xoff, 0, 0);
+    r.x[1] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)xoff + 16, 0, 0);
+    if (q.f32) {
+        r.x[2] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)xoff + 32, 0, 0);
+        r.x[3] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (int)xoff + 48, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.f[i] = __builtin_amdgcn_raw_buffer_load_b128(fbuf, (int)foff + 16 * i, 0, 0);
+}
+// FP16 values of the chunk's blocks, in memory when the wave's stores are complete (coherent across XCDs: other workgroups read
+// them in this launch).  A lane's block is 32 bytes; through LDS (2 KB of the wave's own) every store instruction writes whole lines.
+__device__ __forceinline__ void mid_quantize_block(const MidArgs &a, uint32_t c, int lane, const MidBlock &r, char *lds_wave)
+{
+    const MidQuant &q = a.q;
+    float x[16], f[16];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[4 * i + e] = u2f(r.f[i][e]);
+    if (q.f32) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[4 * i + e] = u2f(r.x[i][e]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {   // bf16 -> fp32 is a 16-bit shift
+                x[8 * i + 2 * e] = u2f(r.x[i][e] << 16);
+                x[8 * i + 2 * e + 1] = u2f(r.x[i][e] & 0xFFFF0000u);
+            }
+    }
+    half2_t o[8];
+    if (q.delta) quantize_block_f16<true>(x, f, r.valid, q.T, q.S, 1.0f / q.S, 6.0f * q.S, o);
+    else quantize_block_f16<false>(x, f, r.valid, q.T, q.S, 1.0f / q.S, 6.0f * q.S, o);
+    union { half2_t h[8]; u32x4_t v[2]; } pack;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) pack.h[j] = o[j];
+    u32x4_t *mine = reinterpret_cast<u32x4_t *>(lds_wave + lane * 32);
+    mine[0] = pack.v[0];
+    mine[1] = pack.v[1];
+    // (one wave's LDS accesses are served in order; nobody else uses this part of the LDS)
+    const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16 *>(a.x16), 0, (int)((uint32_t)a.M * a.ld_bytes), kMidRsrc);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        uint32_t m, kb;
+        mid_place(q, c * 64u + (uint32_t)(j * 32 + (lane >> 1)), m, kb);
+        const u32x4_t v = *reinterpret_cast<const u32x4_t *>(lds_wave + j * 1024 + lane * 16);
+        const uint32_t at = m < (uint32_t)a.M ? m * a.ld_bytes + kb * (kBlock * 2u) + (uint32_t)(lane & 1) * 16u : 0xFFFFFF00u;
+        __builtin_amdgcn_raw_buffer_store_b128(v, out, (int)at, 0, kCoherent);
+    }
+}
+// kQuantize: the activations are quantized by this launch (Sec. 4.2), a share by every workgroup, which then waits for the others'.
+// No workgroup depends on another one running: one whose patience ends makes the missing shares itself, the same values (two
+// launches that fill the chip together on two streams would wait for each other's workgroups to leave).  The values
+// are stored past the L2s (system-coherent), complete before the share's word is set, and read through the reader's L2 only after
+// that: no L2 holds an older copy, since a launch starts with its L2 lines of earlier launches invalidated and reads none
+// of the values before the words say so.
+template <int MT, int NT, int WN, int WK, bool kQuantize>
 __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_mid_kernel(MidArgs a)
 {
     static_assert(WN * WK == 8, "eight waves");
@@ -172,10 +284,21 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
         else if constexpr (NT == 3) asm volatile("" : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(u[0]), "+v"(u[1]), "+v"(u[2]));
         else asm volatile("" : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[NT - 1]), "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(u[NT - 1]));
     };
+    if constexpr (kQuantize) {
+        const uint32_t c = blockIdx.x < a.q.n_units ? (uint32_t)wave * a.q.n_units + blockIdx.x : a.q.n_chunks;
+        if (c < a.q.n_chunks) {
+            MidBlock b;
+            mid_load_block(a, c, lane, b);
+            mid_quantize_block(a, c, lane, b, lds + wave * 2048);
+        }
+        asm volatile("" ::: "memory");   // (its stores are older than the loads that follow: a wait counts on it)
+    }
 #pragma unroll
     for (int q = 0; q < NT; ++q) load_meta(wbuf_of(r0), r0, q);
+    if constexpr (!kQuantize) {
 #pragma unroll
-    for (int i = 0; i < kALoads; ++i) issue_a(r0, 0, i);
+        for (int i = 0; i < kALoads; ++i) issue_a(r0, 0, i);
+    }
 #pragma unroll
     for (int q = 0; q < NT; ++q) load_l(wbuf_of(r0), r0, 0, q);
     // The weights' header, needed for the first plane-H entries: asked for behind the loads above (scalar loads in front of them
@@ -279,19 +402,91 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     };
+    auto done_buf = [&]() { return __builtin_amdgcn_make_buffer_rsrc(a.q.done, 0, (int)(kMidMaxUnits * 4u), kMidRsrc); };
+    auto set_done = [&](uint32_t unit) { __builtin_amdgcn_raw_buffer_store_b32(1u, done_buf(), (int)unit * 4, 0, kCoherent); };
     constexpr std::integral_constant<int, 0> h0{};
     constexpr std::integral_constant<int, 1> h1{};
     constexpr std::integral_constant<int, 2> h2{};
     constexpr std::integral_constant<int, 3> h3{};
 
-    wait_meta(std::integral_constant<int, kALoads + NT>{});
+    if constexpr (kQuantize) {
+        // this wave's values are in memory when only the loads above are outstanding; then the workgroup says so
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FGMP_MID_PENDING(4 * NT)) : "memory");
+        barrier();
+        if (tid == 0 && blockIdx.x < a.q.n_units) set_done(blockIdx.x);   // (landed when the look below finds it)
+    }
+    wait_meta(std::integral_constant<int, (kQuantize ? 0 : kALoads) + NT>{});
 #pragma unroll
     for (int q = 0; q < NT; ++q) load_h(r0, 0, q);
 #pragma unroll
     for (int q = 0; q < NT; ++q) load_meta(wbuf_of(r0 + 1), r0 + 1, q);
 #pragma unroll
     for (int q = 0; q < NT; ++q) load_l(wbuf_of(r0 + 1), r0 + 1, 1, q);
-    wait_meta(std::integral_constant<int, NT>{});                // ... and all that is older: the first round's activations and weights
+    uint32_t passed = 0u;
+    if constexpr (kQuantize) {
+        // Looking is what delays the others most -- hundreds of workgroups that read the same few lines hold up the stores to them --,
+        // so those with nothing to quantize sleep first (40 x 64 clocks: about as long as a chunk takes), and all let the stores
+        // through (us with no sleep / first sleeps only where there is no share / both: 132 x 496 x 5069 (M, K, N) 9.6 / 8.1 / 7.8, 77 x
+        // 2064 x 5003 12.0 / 12.0 / 11.6; bytes instead of words, on fewer lines: 11.3, 13.4).  The last wave looks: it has the
+        // least to quantize, so its own loads are the first to be out of the way.
+        if (wave == 7) {
+            if (blockIdx.x >= a.q.n_units) __builtin_amdgcn_s_sleep(40);
+            __builtin_amdgcn_s_sleep(12);
+        }
+        int looks = a.q.patience;
+        for (;;) {
+            if (wave == 7) {
+                uint32_t unit = kMidMaxUnits;
+                for (;;) {
+                    asm volatile("" ::: "memory");   // (loaded again every time)
+                    const u32x4_t d = __builtin_amdgcn_raw_buffer_load_b128(done_buf(), lane * 16, 0, kCoherent);
+                    bool mine = false;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) mine = mine || (d[e] == 0u && (uint32_t)(lane * 4 + e) < a.q.n_units);
+                    const uint64_t missing = __builtin_amdgcn_ballot_w64(mine);
+                    if (missing == 0ull) break;
+                    if (--looks < 0) {
+                        // a unit that is missing, another one for each workgroup as far as there are several
+                        const uint32_t turn = blockIdx.x * 29u & 63u;
+                        const uint32_t from = ((uint32_t)__builtin_ctzll(missing >> turn | missing << (-turn & 63u)) + turn) & 63u;
+                        uint32_t first = 0u;
+#pragma unroll
+                        for (int e = 3; e >= 0; --e)
+                            if (d[e] == 0u && (uint32_t)(lane * 4 + e) < a.q.n_units) first = (uint32_t)e;
+                        unit = 4u * from + (uint32_t)__builtin_amdgcn_readlane((int)first, (int)from);
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(4);
+                }
+                if (lane == 0) arrived = unit;
+            }
+            barrier();
+            const uint32_t unit = (uint32_t)__builtin_amdgcn_readfirstlane((int)arrived);
+            if (unit >= kMidMaxUnits) break;
+            // its workgroup is not running, for other kernels' sake perhaps: its share is made here, and there again, the same values
+            wait_meta(h0);
+            landed(wl[0], wu[0]);
+            landed(wl[1], wu[1]);
+            const uint32_t c = (uint32_t)wave * a.q.n_units + unit;
+            if (c < a.q.n_chunks) {
+                MidBlock b;
+                mid_load_block(a, c, lane, b);
+                mid_quantize_block(a, c, lane, b, lds + wave * 2048);
+            }
+            __builtin_amdgcn_s_waitcnt(0);
+            barrier();
+            if (tid == 448) set_done(unit);   // (by the wave that looks: landed when its next look has)
+            looks = 0;
+        }
+#pragma unroll
+        for (int i = 0; i < kALoads; ++i) issue_a(r0, 0, i);
+        if (tid == 448) passed = __hip_atomic_fetch_add(&a.q.done[kMidPassed + blockIdx.x % kMidPassedGroups * kMidPassedStep], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    wait_meta(std::integral_constant<int, kQuantize ? 0 : NT>{});   // ... and all that is older: the first round's activations and weights
+    // (this workgroup was the last of its group to pass the wait)
+    bool last_of_group = false;
+    if constexpr (kQuantize)
+        last_of_group = wave == 7 && (uint32_t)__builtin_amdgcn_readfirstlane((int)passed) == (a.n_wgs - blockIdx.x % kMidPassedGroups - 1u) / kMidPassedGroups;
     landed(wl[0], wu[0]);
 #pragma unroll
     for (int q = 0; q < NT; ++q) load_h(r0 + 1, 1, q);
@@ -348,6 +543,10 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
     landed(wl[1], wu[1]);
     barrier();
 
+    passed = 0u;
+    if constexpr (kQuantize)
+        if (last_of_group && lane == 0) passed = __hip_atomic_fetch_add(&a.q.done[kMidPassedAll], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
     // ---- the K groups' sums: 16-row group i is added up by the waves of K group i % WK, in K order
     float4_t *red = reinterpret_cast<float4_t *>(lds);
 #pragma unroll
@@ -375,8 +574,25 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
         }
     }
 
-    const bool x_ok = a.xh->magic == kMagic && a.xh->rows == a.x_rows && a.xh->K == a.x_K;
-    const float ss = w_ok && x_ok ? a.xh->tensor_scale * w_scale : 0.0f;
+    if constexpr (kQuantize) {
+        // every workgroup has passed its wait: all words back to zero
+        const uint32_t groups = a.n_wgs < kMidPassedGroups ? a.n_wgs : kMidPassedGroups;
+        if (last_of_group && (uint32_t)__builtin_amdgcn_readfirstlane((int)passed) == groups - 1u) {
+            const __amdgpu_buffer_rsrc_t dbuf = __builtin_amdgcn_make_buffer_rsrc(a.q.done, 0, (int)(kMidDoneWords * 4u), kMidRsrc);
+#pragma unroll
+            for (uint32_t at = 0; at < kMidDoneWords * 4u; at += 1024u)   // (beyond the words: outside the buffer)
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{0u, 0u, 0u, 0u}, dbuf, (int)(at + lane * 16u), 0, kCoherent);
+        }
+    }
+    bool x_ok = true;
+    float x_scale;
+    if constexpr (kQuantize) {
+        x_scale = a.q.S;
+    } else {
+        x_ok = a.xh->magic == kMagic && a.xh->rows == a.x_rows && a.xh->K == a.x_K;
+        x_scale = a.xh->tensor_scale;
+    }
+    const float ss = w_ok && x_ok ? x_scale * w_scale : 0.0f;
     if (a.parts > 1) {
         // Partials and counters cross XCDs: system-coherent accesses that bypass the per-XCD L2; a workgroup's stores are
         // complete before it bumps the tile's counter, so the one that arrives last reads complete sums.  It adds them in K
@@ -526,7 +742,8 @@ bool gemm_mid_applies(const MidPlan &p, int64_t N, int64_t K)
 template <int MT, int NT> static void launch_mid(const MidArgs &a, hipStream_t st)
 {
     constexpr int WN = MT <= 4 ? 2 : 4;
-    hipLaunchKernelGGL((gemm_mid_kernel<MT, NT, WN, 8 / WN>), dim3(a.n_wgs), dim3(kMidThreads), 0, st, a);
+    if (a.q.X != nullptr) hipLaunchKernelGGL((gemm_mid_kernel<MT, NT, WN, 8 / WN, true>), dim3(a.n_wgs), dim3(kMidThreads), 0, st, a);
+    else hipLaunchKernelGGL((gemm_mid_kernel<MT, NT, WN, 8 / WN, false>), dim3(a.n_wgs), dim3(kMidThreads), 0, st, a);
 }
 
 template <int MT> static void launch_mid_nt(int nt, const MidArgs &a, hipStream_t st)
@@ -538,12 +755,45 @@ template <int MT> static void launch_mid_nt(int nt, const MidArgs &a, hipStream_
         if (nt == 4) launch_mid<MT, 4>(a, st);
 }
 
-fgmp_status_t gemm_mid(const MidPlan &p, const PackedHeader *xh, const _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
+// The words that say whose share of the activations is done lie at the end of the control region, behind the tiles' counters.
+constexpr size_t kMidDoneAt = kWsCtrlRegion / 4 - kMidDoneWords;
+
+bool gemm_mid_quantizes(const MidPlan &p, int64_t M, int64_t N, int64_t K, int64_t row_bytes)
+{
+    constexpr int64_t kLimit = 0x7FFFFF00;   // 32-bit buffer offsets
+    const int64_t row_blocks = (K + kTileK - 1) / kTileK * kTileBlocks, blocks = M * row_blocks;
+    if (!gemm_mid_applies(p, N, K) || p.tiles() > (int64_t)kMidDoneAt || (blocks + 64) * row_blocks >= (int64_t)1 << 32 ||
+        blocks * 32 >= kLimit || row_bytes <= 0 || row_bytes >= kLimit / M)
+        return false;
+    const int64_t wgs = p.tiles() * p.parts;
+    return wgs <= kMidMaxUnits && blocks <= wgs * kMidThreads;
+}
+
+fgmp_status_t gemm_mid(const MidPlan &p, const MidInput &in, _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
                        int64_t ldy, void *ctrl, void *scratch, hipStream_t st)
 {
     if (!gemm_mid_applies(p, N, K)) return FGMP_ERR_UNSUPPORTED;
     const PackedLayout lw = make_layout(N, K);
-    MidArgs a;
+    MidArgs a{};
+    const PackedHeader *const xh = in.packed;
+    if (in.X != nullptr) {
+        const int64_t row_bytes = in.ldx * (in.f32 ? 4 : 2);
+        if (!gemm_mid_quantizes(p, M, N, K, row_bytes)) return FGMP_ERR_UNSUPPORTED;
+        MidQuant &q = a.q;
+        q.X = in.X; q.fisher = in.fisher; q.T = in.T; q.S = in.S; q.f32 = in.f32; q.delta = in.delta;
+        q.x_bytes = (uint32_t)((M - 1) * row_bytes + K * (in.f32 ? 4 : 2));
+        q.row_bytes = (uint32_t)row_bytes;
+        q.nb = (uint32_t)(K / kBlock);
+        q.row_blocks = (uint32_t)(lw.n_kt * kTileBlocks);
+        q.row_mul = (uint32_t)(0x100000000ull / q.row_blocks) + 1u;
+        q.n_chunks = (uint32_t)((M * q.row_blocks + 63) / 64);
+        q.n_units = std::min((uint32_t)(p.tiles() * p.parts), q.n_chunks);
+        q.done = static_cast<uint32_t *>(ctrl) + kMidDoneAt;
+        q.patience = kMidPatience;
+#ifdef FGMP_MEASUREMENT_HOOKS
+        if (const char *e = getenv("FGMP_MID_PATIENCE")) q.patience = atoi(e);   // (0: every workgroup makes what is missing at its first look)
+#endif
+    }
     a.w = w; a.xh = xh; a.x16 = x16; a.Y = Y; a.ldy = ldy;
     a.partial = static_cast<float *>(scratch); a.partial_bytes = (uint32_t)p.partial_bytes();
     a.counters = static_cast<uint32_t *>(ctrl);

@@ -119,33 +119,7 @@ struct StreamArgs {
 __device__ __forceinline__ void stream_quantize_block(const StreamArgs &a, bool inside, const float (&x)[16], const float (&f)[16],
                                                       float inv_S, float S6, half2_t (&o)[8])
 {
-    const float amax = block_amax(x);
-    BlockCodes bc;
-    quantize_block_math<true, false>(x, f, amax, a.S, inv_S, S6, -1, false, bc);
-    const bool hi = inside && bc.score > a.T;
-    if (hi) {
-        float r[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) r[i] = x[i] * inv_S;
-        uint32_t c[4];
-        if (amax * inv_S > 448.0f) encode_fp8_block<true, true>(r, c);
-        else encode_fp8_block<true, false>(r, c);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            o[2 * j] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(c[j], 1.0f, false);
-            o[2 * j + 1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(c[j], 1.0f, true);
-        }
-    } else {
-        const half2_t s = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(bc.sc | (bc.sc << 8), 1.0f, false);
-        o[0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[0], 1.0f, 0) * s;
-        o[1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[0], 1.0f, 1) * s;
-        o[2] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[0], 1.0f, 2) * s;
-        o[3] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[0], 1.0f, 3) * s;
-        o[4] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[1], 1.0f, 0) * s;
-        o[5] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[1], 1.0f, 1) * s;
-        o[6] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[1], 1.0f, 2) * s;
-        o[7] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[1], 1.0f, 3) * s;
-    }
+    quantize_block_f16<false>(x, f, inside, a.T, a.S, inv_S, S6, o);
 }
 
 template <int kSrc>

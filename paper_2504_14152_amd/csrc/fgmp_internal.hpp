@@ -24,6 +24,8 @@ fgmp_status_t quantize_tensor(const void *X, fgmp_dtype_t dt, int64_t rows, int6
                               _Float16 *x16 = nullptr, int64_t ld16 = 0, uint32_t *zero = nullptr,
                               int64_t zero_n = 0, int score_mode = FGMP_SCORE_NVFP4_ERROR,
                               bool clip = false, bool gated = false);
+fgmp_status_t check_quantizer_input(const void *X, fgmp_dtype_t dt, int64_t rows, int64_t K, int64_t ldx, const float *fisher, float T, float S,
+                                    int score_mode, int64_t ld_fisher = 0, const void *packed = nullptr, const float *scores = nullptr);
 #ifdef FGMP_MEASUREMENT_HOOKS
 fgmp_status_t quantize_traffic_model(const void *X, fgmp_dtype_t dt, int64_t rows, int64_t K, int64_t ldx, const float *fisher,
                                      void *packed, size_t packed_bytes, hipStream_t st);
@@ -110,7 +112,18 @@ bool gemm_mid_applies(const MidPlan &p, int64_t N, int64_t K);
 double gemm_mid_micros(const MidPlan &p, int64_t M, int64_t N, int64_t K);   // estimate of a fused step of more than 32 rows
 double gemm_mid_few_rows_micros(const MidPlan &p, int64_t N, int64_t K);   // 20 to 32 rows
 double gemm_mixed_micros(int64_t M, int64_t N, int64_t K);   // the same on the prefill kernel
-fgmp_status_t gemm_mid(const MidPlan &p, const PackedHeader *xh, const _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
+// The activations: a packed tensor's header, their FP16 values being in place, or the input that the launch quantizes into x16
+// (only where gemm_mid_quantizes).
+struct MidInput {
+    const PackedHeader *packed;
+    const void *X;
+    int64_t ldx;
+    const float *fisher;
+    float T, S;
+    int f32, delta;
+};
+bool gemm_mid_quantizes(const MidPlan &p, int64_t M, int64_t N, int64_t K, int64_t row_bytes);
+fgmp_status_t gemm_mid(const MidPlan &p, const MidInput &in, _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
                        int64_t ldy, void *ctrl, void *scratch, hipStream_t st);
 // packed -> zero-padded dense FP16 [8 n_rt_pad][ld]; one launch decodes one or two tensors and
 // can clear `zero_n` 32-bit counters

@@ -172,4 +172,45 @@ __device__ __forceinline__ void quantize_block_math(const float (&x)[16], const 
     for (int j = 0; j < 4; ++j) o.c8[j] = c8[j];
 }
 
+// FP16 values (exact) of the codes that a block is stored as: what the products multiply.  valid: the block lies inside the tensor
+// (outside, x and f are zeros and so are the values).
+template <bool kDelta>
+__device__ __forceinline__ void quantize_block_f16(const float (&x)[16], const float (&f)[16], bool valid, float T, float S, float inv_S, float S6,
+                                                   half2_t (&o)[8])
+{
+    const float amax = block_amax(x);
+    // values beyond the FP8 range only occur when the caller's S is below amax / 448
+    const bool big = amax * inv_S > 448.0f;
+    BlockCodes bc;
+    quantize_block_math<true, kDelta>(x, f, amax, S, inv_S, S6, -1, kDelta && big, bc);
+    if (valid && bc.score > T) {
+        uint32_t c[4];
+        if constexpr (kDelta) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) c[j] = bc.c8[j];
+        } else {
+            float r[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) r[i] = x[i] * inv_S;
+            if (big) encode_fp8_block<true, true>(r, c);
+            else encode_fp8_block<true, false>(r, c);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            o[2 * j] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(c[j], 1.0f, false);
+            o[2 * j + 1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(c[j], 1.0f, true);
+        }
+    } else {
+        const half2_t s = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(bc.sc | (bc.sc << 8), 1.0f, false);
+        o[0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[0], 1.0f, 0) * s;
+        o[1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[0], 1.0f, 1) * s;
+        o[2] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[0], 1.0f, 2) * s;
+        o[3] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[0], 1.0f, 3) * s;
+        o[4] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[1], 1.0f, 0) * s;
+        o[5] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[1], 1.0f, 1) * s;
+        o[6] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[1], 1.0f, 2) * s;
+        o[7] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(bc.q[1], 1.0f, 3) * s;
+    }
+}
+
 }  // namespace fgmp

@@ -1158,14 +1158,12 @@ fgmp_status_t quantize_traffic_model(const void *X, fgmp_dtype_t dt, int64_t row
 }
 #endif
 
-fgmp_status_t quantize_tensor(const void *X, fgmp_dtype_t dt, int64_t rows, int64_t K, int64_t ldx,
-                              const float *fisher, int64_t ld_fisher, float T, float S, void *packed,
-                              size_t packed_bytes, float *scores, bool compact, hipStream_t st,
-                              _Float16 *x16, int64_t ld16, uint32_t *zero, int64_t zero_n, int score_mode,
-                              bool clip, bool gated)
+// What every quantizing call asks of its arguments.
+fgmp_status_t check_quantizer_input(const void *X, fgmp_dtype_t dt, int64_t rows, int64_t K, int64_t ldx, const float *fisher, float T, float S,
+                                    int score_mode, int64_t ld_fisher, const void *packed, const float *scores)
 {
     if (score_mode != FGMP_SCORE_NVFP4_ERROR && score_mode != FGMP_SCORE_DELTA) return FGMP_ERR_INVALID_ARG;
-    if (!X || !fisher || (!packed && !x16)) return FGMP_ERR_INVALID_ARG;
+    if (!X || !fisher) return FGMP_ERR_INVALID_ARG;
     if (rows <= 0 || K <= 0) return FGMP_ERR_INVALID_ARG;
     if (!(S > 0.0f) || !(S < INFINITY) || T != T) return FGMP_ERR_INVALID_ARG;
     if (dt != FGMP_F32 && dt != FGMP_BF16) return FGMP_ERR_UNSUPPORTED;
@@ -1175,6 +1173,18 @@ fgmp_status_t quantize_tensor(const void *X, fgmp_dtype_t dt, int64_t rows, int6
     if (((uintptr_t)X | (uintptr_t)fisher | (uintptr_t)packed | (uintptr_t)scores) % 16 != 0 ||
         (ldx * esz) % 16 != 0 || (ld_fisher * 4) % 16 != 0)
         return FGMP_ERR_BAD_ALIGN;
+    return FGMP_OK;
+}
+
+fgmp_status_t quantize_tensor(const void *X, fgmp_dtype_t dt, int64_t rows, int64_t K, int64_t ldx,
+                              const float *fisher, int64_t ld_fisher, float T, float S, void *packed,
+                              size_t packed_bytes, float *scores, bool compact, hipStream_t st,
+                              _Float16 *x16, int64_t ld16, uint32_t *zero, int64_t zero_n, int score_mode,
+                              bool clip, bool gated)
+{
+    if (!packed && !x16) return FGMP_ERR_INVALID_ARG;
+    const fgmp_status_t rc = check_quantizer_input(X, dt, rows, K, ldx, fisher, T, S, score_mode, ld_fisher, packed, scores);
+    if (rc != FGMP_OK) return rc;
     const PackedLayout l = make_layout(rows, K);
     if (x16 != nullptr) {
         // FP16 output: the packed buffer only receives the header
@@ -1214,7 +1224,7 @@ fgmp_status_t quantize_tensor(const void *X, fgmp_dtype_t dt, int64_t rows, int6
     if (gated && (dt != FGMP_F32 || p.delta || compact || x16 != nullptr || per_elem || ldx < 2 * K)) return FGMP_ERR_UNSUPPORTED;
     // The activation hot path (one pass, NVFP4-error score, one sensitivity per channel, dynamic-max
     // scales) runs on the trimmed kernel when its 32-bit offsets and its shortcut division apply.
-    const uint64_t x_bytes = (uint64_t)rows * (uint64_t)ldx * (uint64_t)esz;
+    const uint64_t x_bytes = (uint64_t)rows * (uint64_t)ldx * (dt == FGMP_F32 ? 4u : 2u);
     // (offsets: the input plus one stride of the resident set past its end must stay below 2^32)
     const bool fast = kUseHwCvt && !compact && !per_elem && !gated &&
                       x_bytes < 0x7FFFFF00ull && l.total_bytes < 0xFFFFFF00ull && S >= 1e-30f && S <= 1e30f &&

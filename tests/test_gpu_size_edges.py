@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from oracle import fgmp_oracle as orc
-from paper_2504_14152_amd import fgmp, synth
+from paper_2504_14152_amd import build, fgmp, synth
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -162,6 +162,36 @@ def test_products_between_decode_and_prefill_replay_in_a_graph():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(Y, want)
+
+
+# (M, K, N): a last chunk of 64 blocks that ends inside the tensor, rows in K-tiles of which part lies beyond K, fewer
+# chunks than workgroups and more, 256 workgroups, one block per thread exactly and one past it (which takes two launches), a
+# partial sum across workgroups
+@pytest.mark.parametrize("M,K,N", [(33, 144, 136), (77, 2064, 503), (64, 4096, 12288), (120, 368, 603), (96, 640, 72), (512, 4096, 4096),
+                                   (516, 4096, 4096), (49, 7696, 5491), (154, 10976, 4810)])
+@pytest.mark.parametrize("dtype,mode", [("bf16", None), ("f32", "delta")])
+@pytest.mark.parametrize("patience", [None, "0"])
+def test_products_that_quantize_in_their_launch_are_those_of_packed_activations(M, K, N, dtype, mode, patience, monkeypatch):
+    """Against the product of activations packed beforehand, which the oracle pins above: the same kernel over the same values, so
+    every bit agrees.  Without patience (a switch of the build with measurement hooks) every workgroup makes the shares that it finds missing."""
+    assert fgmp.selftest_gemm_route(M, N, K)[0] == 2
+    g = torch.Generator(device=DEV).manual_seed(M + K + N)
+    w = torch.randn(N, K, generator=g, device=DEV) * 0.02
+    f = torch.exp(torch.randn(K, generator=g, device=DEV))
+    pW = fgmp.quantize_weights(w, f, 1e-5, float(w.abs().max()) / 448.0)
+    ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
+    if patience is not None:
+        monkeypatch.setenv("FGMP_MID_PATIENCE", patience)
+    with fgmp.use_library(build.lib_path("hooks" if patience is not None else None)):
+        for call in range(3):   # other inputs each time, in the place where the earlier ones' values lie
+            x = torch.randn(M, K, generator=g, device=DEV).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+            s = float(x.float().abs().max()) / 448.0
+            ws[fgmp.WORKSPACE_CONTROL_BYTES:].fill_(0xFF)   # NaN wherever nothing is written
+            got = fgmp.quant_gemm_fused(x, f, 0.5, s, pW, workspace=ws, score_mode=mode)
+            want = fgmp.gemm(fgmp.quantize_activations(x, f, 0.5, s, score_mode=mode), pW)
+            assert torch.equal(got, want), call
+            assert int(ws[: fgmp.WORKSPACE_CONTROL_BYTES].count_nonzero()) == 0
+
 
 
 def test_long_products_of_few_rows_quantize_the_results_of_the_plain_call():
