@@ -93,7 +93,8 @@ struct MidArgs {
     uint32_t n_wgs;
     uint32_t partial_bytes;
     float *partial;
-    uint32_t *counters;         // one per tile; zero between launches
+    uint32_t *counters;         // one per tile, 2^counter_shift words apart; zero between launches
+    int counter_shift;
     const PackedHeader *xh;     // header of the activations (tensor scale, shape check)
     int64_t ldy;
     int64_t w_rows, w_K, x_rows, x_K;                    // the shapes the headers must state
@@ -543,9 +544,16 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
     landed(wl[1], wu[1]);
     barrier();
 
+    // (the lane's number is found again, so that nothing of it is kept in registers through the rounds)
+    int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(lane_e));
+    const bool first_lane = wave == 0 && lane_e == 0;
     passed = 0u;
     if constexpr (kQuantize)
-        if (last_of_group && lane == 0) passed = __hip_atomic_fetch_add(&a.q.done[kMidPassedAll], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (last_of_group && lane_e == 0) passed = __hip_atomic_fetch_add(&a.q.done[kMidPassedAll], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+    uint32_t ticket = 0u;
+    if (a.parts > 1 && first_lane) ticket = __hip_atomic_fetch_add(&a.counters[tile << a.counter_shift], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // ---- the K groups' sums: 16-row group i is added up by the waves of K group i % WK, in K order
     float4_t *red = reinterpret_cast<float4_t *>(lds);
@@ -555,10 +563,13 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
         if (wk != owner) {
             const int from = wk < owner ? wk : wk - 1;
 #pragma unroll
-            for (int q = 0; q < NT; ++q) red[(((from * MT + i) * WN + wn) * NT + q) * 64 + lane] = acc[i][q];
+            for (int q = 0; q < NT; ++q) red[(((from * MT + i) * WN + wn) * NT + q) * 64 + lane_e] = acc[i][q];
         }
     }
     barrier();
+    // (in registers of their own: 16-row groups wk, wk + WK, ...)
+    constexpr int kMine = (MT + WK - 1) / WK;
+    float4_t own[kMine][NT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
         if (wk != i % WK) continue;
@@ -568,9 +579,9 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
             for (int k = 0; k < WK; ++k) {
                 if (k == i % WK) sum += acc[i][q];
-                else sum += red[((((k < i % WK ? k : k - 1) * MT + i) * WN + wn) * NT + q) * 64 + lane];
+                else sum += red[((((k < i % WK ? k : k - 1) * MT + i) * WN + wn) * NT + q) * 64 + lane_e];
             }
-            acc[i][q] = sum;
+            own[i / WK][q] = sum;
         }
     }
 
@@ -581,7 +592,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
             const __amdgpu_buffer_rsrc_t dbuf = __builtin_amdgcn_make_buffer_rsrc(a.q.done, 0, (int)(kMidDoneWords * 4u), kMidRsrc);
 #pragma unroll
             for (uint32_t at = 0; at < kMidDoneWords * 4u; at += 1024u)   // (beyond the words: outside the buffer)
-                __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{0u, 0u, 0u, 0u}, dbuf, (int)(at + lane * 16u), 0, kCoherent);
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{0u, 0u, 0u, 0u}, dbuf, (int)(at + lane_e * 16u), 0, kCoherent);
         }
     }
     bool x_ok = true;
@@ -594,35 +605,43 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
     }
     const float ss = w_ok && x_ok ? x_scale * w_scale : 0.0f;
     if (a.parts > 1) {
-        // Partials and counters cross XCDs: system-coherent accesses that bypass the per-XCD L2; a workgroup's stores are
-        // complete before it bumps the tile's counter, so the one that arrives last reads complete sums.  It adds them in K
-        // order -- the result does not depend on the order of arrival -- and puts the counter back to zero.
+        // Partials and counters cross XCDs: system-coherent accesses that bypass the per-XCD L2.  The tile's word counts tickets
+        // in its low half and parts that are complete in memory in its high half.  All but the workgroup with the last ticket store
+        // their sums and leave.  That one keeps its own in registers and waits for the others' -- which are all past their
+        // tickets, running, and wait for nothing --, adds in K order (the result does not depend on who it is) and puts the word back
+        // to zero.  us with all parts stored before the counting, the last to arrive reading every one back, its own too / now:
+        // 512 x 11008 x 4096 (M, K, N, two parts) 57.6 / 55.4, 512 x 4096 x 4096 (two) 29.9 / 28.1, 667 x 2464 x 1248 (five)
+        // 23.6 / 22.1, 326 x 9104 x 996 (six) 23.0 / 22.7.  Words on lines of their own: side by side, tickets and looks hold
+        // each other up (50 x 10880 x 1291 16.2, with lines 12.9).
         constexpr uint32_t kSlotBytes = (uint32_t)kRows * kCols * 4u;
         const __amdgpu_buffer_rsrc_t pbuf = __builtin_amdgcn_make_buffer_rsrc(a.partial, 0, (int)a.partial_bytes, kMidRsrc);
-        const uint32_t tile_at = tile * (uint32_t)a.parts * kSlotBytes + (uint32_t)(wn * NT) * 1024u + (uint32_t)lane * 16u;
+        const uint32_t tile_at = tile * (uint32_t)a.parts * kSlotBytes + (uint32_t)(wn * NT) * 1024u + (uint32_t)lane_e * 16u;
+        if (first_lane) arrived = ticket & 0xFFFFu;
+        barrier();
+        if (arrived != (uint32_t)a.parts - 1u) {
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            if (wk != i % WK) continue;
+            for (int i = 0; i < kMine; ++i) {
+                if (wk + i * WK >= MT) continue;
 #pragma unroll
-            for (int q = 0; q < NT; ++q)
-                store_coherent16(pbuf, tile_at + part * kSlotBytes + (uint32_t)((i * WN) * NT + q) * 1024u, acc[i][q]);
+                for (int q = 0; q < NT; ++q)
+                    store_coherent16(pbuf, tile_at + part * kSlotBytes + (uint32_t)((wk + i * WK) * WN * NT + q) * 1024u, own[i][q]);
+            }
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            if (first_lane) __hip_atomic_fetch_add(&a.counters[tile << a.counter_shift], 0x10000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
         }
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (tid == 0) {
-            const uint32_t before = __hip_atomic_fetch_add(&a.counters[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (before == (uint32_t)a.parts - 1u) __hip_atomic_store(&a.counters[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            arrived = before;
+        if (first_lane) {
+            while (__hip_atomic_load(&a.counters[tile << a.counter_shift], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16 != (uint32_t)a.parts - 1u) __builtin_amdgcn_s_sleep(2);
+            __hip_atomic_store(&a.counters[tile << a.counter_shift], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
-        if (arrived != (uint32_t)a.parts - 1u) return;
-        constexpr int kMine = (MT + WK - 1) / WK;   // 16-row groups of a wave: wk, wk + WK, ...
         float4_t sum[kMine][NT];
 #pragma unroll
         for (int i = 0; i < kMine; ++i)
 #pragma unroll
             for (int q = 0; q < NT; ++q) sum[i][q] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        for (int c = 0; c < a.parts; c += 2) {   // two parts' loads in flight (a part past the last one: beyond the tile, added as zero)
+        for (int c = 0; c < a.parts; c += 2) {   // two parts' loads in flight (its own, or a part past the last one: beyond the buffer, zeros)
             float4_t p[2][kMine][NT];
 #pragma unroll
             for (int u = 0; u < 2; ++u)
@@ -631,7 +650,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
                     for (int q = 0; q < NT; ++q) {
                         const int row_group = wk + i * WK;
-                        const bool there = c + u < a.parts && row_group < MT;
+                        const bool there = c + u < a.parts && c + u != (int)part && row_group < MT;
                         p[u][i][q] = load_coherent16(pbuf, there ? tile_at + (uint32_t)(c + u) * kSlotBytes + (uint32_t)(row_group * WN * NT + q) * 1024u : 0xFFFFFF00u);
                     }
 #pragma unroll
@@ -639,28 +658,26 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
                 for (int i = 0; i < kMine; ++i)
 #pragma unroll
-                    for (int q = 0; q < NT; ++q) sum[i][q] += p[u][i][q];
+                    for (int q = 0; q < NT; ++q) sum[i][q] += c + u == (int)part ? own[i][q] : p[u][i][q];
         }
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
-            if (wk == i % WK) {
+        for (int i = 0; i < kMine; ++i)
 #pragma unroll
-                for (int q = 0; q < NT; ++q) acc[i][q] = sum[i / WK][q];
-            }
+            for (int q = 0; q < NT; ++q) own[i][q] = sum[i][q];
     }
-    // acc[i][q][e] = Y[m0 + 16 i + 4 g + e][n0 + 16 (NT wn + q) + nl]
+    // own[i][q][e] = Y[m0 + 16 (wk + i WK) + 4 g + e][n0 + 16 (NT wn + q) + nl]
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-        if (wk != i % WK) continue;
+    for (int i = 0; i < kMine; ++i) {
+        if (wk + i * WK >= MT) continue;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int m = m0 + 16 * i + 4 * g + e;
+            const int m = m0 + 16 * (wk + i * WK) + 4 * (lane_e >> 4) + e;
             if (m < a.M) {
                 float *row = a.Y + (int64_t)m * a.ldy;
 #pragma unroll
                 for (int q = 0; q < NT; ++q) {
-                    const int n = n0 + (wn * NT + q) * 16 + nl;
-                    if (n < a.N) row[n] = acc[i][q][e] * ss;
+                    const int n = n0 + (wn * NT + q) * 16 + (lane_e & 15);
+                    if (n < a.N) row[n] = own[i][q][e] * ss;
                 }
             }
         }
@@ -798,6 +815,7 @@ fgmp_status_t gemm_mid(const MidPlan &p, const MidInput &in, _Float16 *x16, int6
     a.partial = static_cast<float *>(scratch); a.partial_bytes = (uint32_t)p.partial_bytes();
     a.counters = static_cast<uint32_t *>(ctrl);
     a.w_rows = N; a.w_K = K; a.x_rows = M; a.x_K = K;
+    for (a.counter_shift = 5; a.counter_shift > 0 && p.tiles() << a.counter_shift > (int64_t)kMidDoneAt; --a.counter_shift) {}
     a.off_L = (uint32_t)lw.off_L; a.off_S = (uint32_t)lw.off_S; a.off_M = (uint32_t)lw.off_M;
     a.off_T = (uint32_t)lw.off_T; a.off_H = (uint32_t)lw.off_H;
     a.ld_bytes = (uint32_t)(ld16 * 2);
