@@ -92,7 +92,8 @@ struct StreamArgs {
     uint32_t *dec;              // [row group] which of the M blocks it produced are FP8 (bit m), until the tile's mask word is made
     uint32_t *uctr;             // one arrival counter per 8 row groups (= one K-tile of the packed result); zero between calls
     // scratch
-    uint32_t *gctr;             // one arrival counter per row group (P_g > 1); zero between calls
+    uint32_t *gctr;             // one arrival counter per row group (P_g > 1), 2^gctr_shift words apart; zero between calls
+    int gctr_shift;
     uint32_t x_bytes;           // extent of the input X
     float *partial;             // [row group][part of K][MT][64 lanes] x 16 bytes (P_g > 1)
     uint32_t partial_bytes;
@@ -723,7 +724,7 @@ __global__ __launch_bounds__(64 * kStWaves) void gemm_stream_kernel(StreamArgs a
                 for (int mt = 0; mt < MT; ++mt) store_coherent16(pbuf, base + (uint32_t)kp_g * (MT * 1024u) + mt * 1024u, acc[mt]);
                 __builtin_amdgcn_s_waitcnt(0);
                 uint32_t before = 0;
-                if (lane == 0) before = __hip_atomic_fetch_add(&a.gctr[grp], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (lane == 0) before = __hip_atomic_fetch_add(&a.gctr[grp << a.gctr_shift], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 before = (uint32_t)__builtin_amdgcn_readfirstlane((int)before);
                 if (before == (uint32_t)(a.P_g - 1)) {
                     float4_t sum[MT];
@@ -755,7 +756,7 @@ __global__ __launch_bounds__(64 * kStWaves) void gemm_stream_kernel(StreamArgs a
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt) acc[mt] = sum[mt];
                     final_sums = true;
-                    if (lane == 0) __hip_atomic_store(&a.gctr[grp], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (lane == 0) __hip_atomic_store(&a.gctr[grp << a.gctr_shift], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
             if (final_sums) emit(acc, grp);
@@ -1001,6 +1002,7 @@ fgmp_status_t gemm_stream(int src, const void *X, int64_t ldx, const float *fish
         a.uctr = static_cast<uint32_t *>(ctrl) + kStUnitCtr0;
     }
     a.gctr = static_cast<uint32_t *>(ctrl);
+    for (a.gctr_shift = 5; a.gctr_shift > 0 && (int64_t)p.n_groups << a.gctr_shift > kStUnitCtr0; --a.gctr_shift) {}
     a.partial = static_cast<float *>(scratch);
     a.partial_bytes = p.partial_bytes;
     a.x_bytes = src == 2 ? 0u : (uint32_t)((uint64_t)M * (uint64_t)ldx * (src == 1 ? 4u : 2u));
