@@ -1,10 +1,12 @@
-"""Thin ctypes binding of libfgmp.so (include/fgmp.h): argument marshalling
-only.  PyTorch supplies device memory and the current HIP stream; every step
+"""Thin binding of libfgmp.so (include/fgmp.h), ctypes and a small extension
+module (csrc/fgmp_call.c): argument marshalling only.  PyTorch supplies device memory and the current HIP stream; every step
 of the path runs in the library's kernels.  There is no fallback: if the
 shared library is missing or a call fails, an exception is raised."""
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from dataclasses import dataclass
 
@@ -16,6 +18,7 @@ F32, BF16 = 0, 1
 _ERRORS = {-1: "INVALID_ARG", -2: "BAD_SHAPE", -3: "BAD_ALIGN", -4: "BUFFER_TOO_SMALL",
            -5: "UNSUPPORTED", -6: "HIP_ERROR"}
 _lib = None
+_call = None
 
 
 class FgmpError(RuntimeError):
@@ -52,11 +55,24 @@ def _library_file() -> str:
 
 def lib() -> ctypes.CDLL:
     """Load libfgmp.so (see _library_file) and declare its entry points."""
-    global _lib
+    global _lib, _call
     if _lib is not None:
         return _lib
+    if _call is None:
+        _call = _load_call()
     _lib = _load(_library_file())
     return _lib
+
+
+def _load_call():
+    """The extension module that passes the fused call's arguments on, built from its source where it is missing or older."""
+    path = _build.CALL
+    if not os.path.exists(path) or os.path.getmtime(path) < os.path.getmtime(_build.CALL_SOURCE):
+        _build.build_call()
+    loader = importlib.machinery.ExtensionFileLoader("_fgmp_call", path)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fgmp_call", loader))
+    loader.exec_module(module)
+    return module
 
 
 class use_library:
@@ -117,6 +133,7 @@ def _load(path: str) -> ctypes.CDLL:
     L.fgmp_quant_gemm_fused.restype = ctypes.c_int
     L.fgmp_quant_gemm_fused.argtypes = [vp, ctypes.c_int, i64, i64, i64, vp, f32, f32, vp, i64, vp, i64,
                                         vp, sz, vp]
+    L.fused_entry = ctypes.cast(L.fgmp_quant_gemm_fused, ctypes.c_void_p).value
     L.fgmp_quant_gemm_fused_static_scratch.restype = ctypes.c_int
     L.fgmp_quant_gemm_fused_static_scratch.argtypes = [vp, ctypes.c_int, i64, i64, i64, vp, f32, f32, vp, i64, vp, i64, vp]
     L.fgmp_unpack_canonical.restype = ctypes.c_int
@@ -299,6 +316,15 @@ def gemm(pX: Packed, pW: Packed, out: torch.Tensor | None = None, workspace: tor
 def quant_gemm_fused(X: torch.Tensor, fisher_k: torch.Tensor, threshold: float, scale_x: float, pW: Packed,
                      out: torch.Tensor | None = None, workspace: torch.Tensor | None = None,
                      score_mode: str | None = None):
+    if out is not None and workspace is not None and score_mode is None:
+        # (a server's call, which brings its buffers; None: something below has to be said about the arguments)
+        L = lib()
+        rc = _call.quant_gemm_fused(L.fused_entry, torch.float32, torch.bfloat16, X, fisher_k, threshold, scale_x, pW, out,
+                                    workspace, _stream())
+        if rc is not None:
+            if rc != 0:
+                _check(rc, "fgmp_quant_gemm_fused")
+            return out
     _require_cuda(X, fisher_k)
     M, K = X.shape
     if K != pW.K:

@@ -5,6 +5,10 @@ import ctypes
 import os
 import re
 
+import numpy as np
+import pytest
+import torch
+
 from paper_2504_14152_amd import build, fgmp
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -168,3 +172,44 @@ def test_an_odd_number_of_row_tiles_takes_the_kernel_of_its_even_neighbours():
         near = {fgmp.selftest_gemm_route(M, n, K)[0] for n in (N - 8, N + 8)}
         assert -(-N // 8) % 2 == 1 and near == {fgmp.selftest_gemm_route(M, N, K)[0]}, (M, K, N)
     assert fgmp.selftest_gemm_route(20, 8184, 8192)[0] == 0 and fgmp.selftest_gemm_route(24, 4088, 11008)[0] == 2
+
+
+class _Pretend:
+    """What the binding asks of a GPU tensor, without one."""
+    is_cuda = True
+
+    def __init__(self, at, shape, dtype=torch.float32, cuda=True):
+        self.at, self.shape, self.dtype, self.is_cuda = at, torch.Size(shape), dtype, cuda
+
+    def data_ptr(self):
+        return self.at
+
+    def stride(self, dim):
+        return (self.shape[1] + 8, 1)[dim]
+
+    def numel(self):
+        return self.shape.numel()
+
+
+@pytest.mark.parametrize("dtype,code", [(torch.float32, 0), (torch.bfloat16, 1)])
+def test_the_extension_hands_on_what_it_is_given(dtype, code):
+    got = []
+    i64, f32, vp = ctypes.c_int64, ctypes.c_float, ctypes.c_void_p
+    proto = ctypes.CFUNCTYPE(ctypes.c_int, vp, ctypes.c_int, i64, i64, i64, vp, f32, f32, vp, i64, vp, i64, vp, ctypes.c_size_t, vp)
+    entry = proto(lambda *a: got.append(a) or -4)
+    fgmp.lib()
+    top = 1 << 47
+
+    def call(X, f, T, S, w, Y, ws):
+        return fgmp._call.quant_gemm_fused(ctypes.cast(entry, vp).value, torch.float32, torch.bfloat16, X, f, T, S, w, Y, ws, 0x77)
+
+    X, f, Y = _Pretend(top + 16, (3, 32), dtype), _Pretend(top + 32, (32,)), _Pretend(top + 48, (3, 40))
+    w, ws = fgmp.Packed(_Pretend(top + 64, (999,)), 40, 32), _Pretend(top + 80, (12345,))
+    assert call(X, f, 0.25, np.float32(1.5), w, Y, ws) == -4
+    assert got == [(top + 16, code, 3, 32, 40, top + 32, 0.25, 1.5, top + 64, 40, top + 48, 48, top + 80, 12345, 0x77)]
+    # whatever the general path refuses, or takes in a way of its own, is left to it, and nothing is called
+    bad = [(_Pretend(16, (3, 32), dtype, cuda=False), f, 0.25, 1.5, w, Y, ws), (X, _Pretend(32, (32,), cuda=False), 0.25, 1.5, w, Y, ws),
+           (_Pretend(16, (3, 48), dtype), f, 0.25, 1.5, w, Y, ws), (_Pretend(16, (3, 32), torch.float16), f, 0.25, 1.5, w, Y, ws),
+           (_Pretend(16, (32,), dtype), f, 0.25, 1.5, w, Y, ws), (X, f, None, 1.5, w, Y, ws), (X, f, 0.25, 1.5, w, "out", ws),
+           (X, f, 0.25, 1.5, w, Y, None), (X, f, 0.25, 1.5, None, Y, ws)]
+    assert [call(*b) for b in bad] == [None] * len(bad) and len(got) == 1
