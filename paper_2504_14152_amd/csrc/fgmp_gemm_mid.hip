@@ -728,7 +728,7 @@ MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K, size_t most_bytes)
 
 // A fused step on this kernel in microseconds, for more than 32 rows: quantizing the activations and storing the results (by their
 // numbers), what a workgroup pays around its rounds, its rounds -- the slowest of matrix, vector and LDS work and half of all
-// three --, and partial sums that meet in memory.  Fitted to 11000 steps of 1076 products (33 to 4096 rows, K and N of the
+// three --, and partial sums that meet in memory.  Fitted, with a quantizer launch in front of every one, to 11000 steps of 1076 products (33 to 4096 rows, K and N of the
 // Llama-2-7B linears and 256 .. 11008 by 256 .. 22016, up to nine splits of each, weights in the Infinity Cache): 9% rms.
 double gemm_mid_micros(const MidPlan &p, int64_t M, int64_t N, int64_t K)
 {
