@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
         // this wave's values are in memory when only the loads above are outstanding; then the workgroup says so
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FGMP_MID_PENDING(4 * NT)) : "memory");
         barrier();
-        if (tid == 0 && blockIdx.x < a.q.n_units) set_done(blockIdx.x);   // (landed when the look below finds it)
+        if (tid == 0 && blockIdx.x < a.q.n_units) set_done(blockIdx.x);
     }
     wait_meta(std::integral_constant<int, (kQuantize ? 0 : kALoads) + NT>{});
 #pragma unroll
@@ -460,6 +460,9 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
                     __builtin_amdgcn_s_sleep(4);
                 }
                 if (lane == 0) arrived = unit;
+            } else if (wave == 0) {
+                // (the word it set has landed before this workgroup counts as past the wait, whoever else has set it, too)
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
             barrier();
             const uint32_t unit = (uint32_t)__builtin_amdgcn_readfirstlane((int)arrived);
