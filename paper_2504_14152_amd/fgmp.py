@@ -55,11 +55,9 @@ def _library_file() -> str:
 
 def lib() -> ctypes.CDLL:
     """Load libfgmp.so (see _library_file) and declare its entry points."""
-    global _lib, _call
+    global _lib
     if _lib is not None:
         return _lib
-    if _call is None:
-        _call = _load_call()
     _lib = _load(_library_file())
     return _lib
 
@@ -97,6 +95,9 @@ class use_library:
 
 
 def _load(path: str) -> ctypes.CDLL:
+    global _call
+    if _call is None:
+        _call = _load_call()
     L = ctypes.CDLL(path)
     vp, i64, f32, sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
     L.fgmp_version.restype = ctypes.c_char_p
