@@ -6,7 +6,8 @@ written until a wait has guaranteed the load has landed.  Loads complete in
 issue order, so `s_waitcnt vmcnt(N)` guarantees every load that has at least N
 younger memory operations behind it.  The functions below read the gfx950
 listing the build's own flags produce and verify that property instruction by
-instruction, and that the loop holds neither register spills nor a full
+instruction, along every path through the kernel (a wait in one branch says
+nothing about the others), and that the loop holds neither register spills nor a full
 `vmcnt(0)` wait (the stall the assembly loads exist to avoid).  build() runs
 check() on every build, with the compiler and flags of that build, and fails
 the build if it trips; the tests call the same functions.
@@ -94,6 +95,63 @@ def violations(ins, cyclic):
     return checked, bad
 
 
+def whole_kernel(lines, prefix):
+    """The lines of a kernel, blocks listed behind its first s_endpgm included."""
+    start = next(i for i, l in enumerate(lines) if l.startswith(prefix) and ":" in l)
+    end = next(i for i in range(start, len(lines)) if lines[i].startswith(".Lfunc_end"))
+    return lines[start + 1 : end]
+
+
+def flow_violations(body):
+    """(number of loads to registers, touches of a destination that some path reaches with the load in flight).  Walks the
+    control-flow graph of a kernel's lines: what is in flight at a label is what any way to it leaves in flight, with the fewest
+    younger memory operations of all ways."""
+    code, at = [], {}
+    for l in body:
+        label = re.match(r"(\.?\w+):", l)
+        if label:
+            at[label.group(1)] = len(code)
+        elif instructions([l]):
+            code.append(l.split(";")[0].strip())
+    known = {}   # state in front of an instruction: register -> (younger memory operations, the load)
+    bad = {}
+    todo = [(0, {})]
+    while todo:
+        i, state = todo.pop()
+        while i < len(code):
+            seen = known.get(i)
+            if seen is None:
+                merged = dict(state)
+            else:
+                merged = dict(seen)
+                for r, v in state.items():
+                    if r not in merged or v[0] < merged[r][0]:
+                        merged[r] = v
+                if merged == seen:
+                    break
+            known[i] = merged
+            state = dict(merged)
+            ins = code[i]
+            wait = re.match(r"s_waitcnt.*vmcnt\((\d+)\)", ins)
+            if wait:
+                state = {r: v for r, v in state.items() if v[0] < int(wait.group(1))}
+            for r in _regs(ins) & state.keys():
+                bad[(state[r][1], ins)] = None
+                del state[r]   # (once is enough)
+            if _is_vmem(ins):
+                state = {r: (min(y + 1, 64), load) for r, (y, load) in state.items()}
+                if re.match(r"(?:buffer|global|scratch)_load", ins) and not re.search(r"\blds\b|_lds_", ins):
+                    state.update((r, (0, ins)) for r in _regs(ins.split(",")[0]))
+            jump = re.match(r"s_(cbranch_\w+|branch)\s+(\.?\w+)", ins)
+            if jump and jump.group(2) in at:
+                todo.append((at[jump.group(2)], state))
+            if ins.startswith("s_endpgm") or (jump and jump.group(1) == "branch"):
+                break
+            i += 1
+    loads = sum(ins.startswith("buffer_load") and not re.search(r"\blds\b", ins) for ins in code)
+    return loads, list(bad)
+
+
 def direct_loads_without_wait(lines) -> tuple[int, list]:
     """(number of direct loads to LDS, those right behind the scalar instruction that writes M0).  M0 holds a direct load's
     LDS address; the instruction set asks for one instruction or s_nop between the two, and the compiler does not look
@@ -113,7 +171,7 @@ def check_kernel(lines, prefix) -> list[str]:
     checked, bad = violations(loop, cyclic=True)
     if checked < 6 * 6 or bad:
         problems.append(f"main loop: {checked} loads checked, hazards {bad}")
-    checked, bad = violations(instructions(body), cyclic=False)   # prologue -> loop -> remainder -> epilogue
+    checked, bad = flow_violations(whole_kernel(lines, prefix))   # prologue -> loop -> remainder -> epilogue
     if checked < 60 or bad:
         problems.append(f"whole kernel: {checked} loads checked, hazards {bad}")
     if [s for s in loop if s.startswith("scratch_")]:
@@ -153,7 +211,7 @@ def check_mid_kernel(lines, name) -> list[str]:
     checked, bad = violations(loop, cyclic=True)
     if checked != 2 * 5 * nt or bad:
         problems.append(f"main loop: {checked} loads checked, hazards {bad}")
-    checked, bad = violations(instructions(body), cyclic=False)
+    checked, bad = flow_violations(whole_kernel(lines, name))
     if checked < 4 * 5 * nt or bad:
         problems.append(f"whole kernel: {checked} loads checked, hazards {bad}")
     if [s for s in loop if s.startswith("scratch_")]:

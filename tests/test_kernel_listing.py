@@ -38,6 +38,30 @@ def test_checker_catches_a_planted_hazard():
     assert lc.violations(too_weak, cyclic=False)[1]
 
 
+def _listing(text):
+    return [l if l.endswith(":") else "\t" + l for l in text.strip().split("\n")]
+
+
+def test_checker_follows_every_path():
+    """A wait that only one side of a branch passes, the load's destination touched where both meet; the same with the wait in
+    front of the branch; a touch on a path that the load is not on; and a loop whose second turn meets the load of its first."""
+    load = "buffer_load_dword v5, v1, s[0:3], 0 offen\n"
+    one_side = load + "s_cbranch_scc1 .LBB0_2\ns_waitcnt vmcnt(0)\n.LBB0_2:\nv_mov_b32_e32 v6, v5\ns_endpgm"
+    both = load + "s_waitcnt vmcnt(0)\ns_cbranch_scc1 .LBB0_2\nv_mov_b32_e32 v7, 0\n.LBB0_2:\nv_mov_b32_e32 v6, v5\ns_endpgm"
+    elsewhere = ("s_cbranch_scc1 .LBB0_2\n" + load + "s_waitcnt vmcnt(0)\ns_branch .LBB0_3\n.LBB0_2:\nv_mov_b32_e32 v5, 1\n.LBB0_3:\n"
+                 "v_mov_b32_e32 v6, v5\ns_endpgm")
+    behind_the_end = "s_cbranch_scc1 .LBB0_2\ns_endpgm\n.LBB0_2:\n" + load + "v_mov_b32_e32 v6, v5\ns_endpgm"
+    fewest = (load + "s_cbranch_scc1 .LBB0_2\nbuffer_load_dword v9, v1, s[0:3], 0 offen\n.LBB0_2:\ns_waitcnt vmcnt(1)\n"
+              "v_mov_b32_e32 v6, v5\ns_waitcnt vmcnt(0)\ns_endpgm")
+    loop = ".LBB0_1:\nv_mov_b32_e32 v6, v5\n" + load + "s_cbranch_scc1 .LBB0_1\ns_waitcnt vmcnt(0)\ns_endpgm"
+    assert lc.flow_violations(_listing(both)) == (1, []) and lc.flow_violations(_listing(elsewhere)) == (1, [])
+    for planted in (one_side, behind_the_end, fewest, loop):
+        n, bad = lc.flow_violations(_listing(planted))
+        assert n >= 1 and [b[1] for b in bad] == ["v_mov_b32_e32 v6, v5"], planted
+    # (read from top to bottom, which is not how waves go, the first one looks sound)
+    assert lc.violations(lc.instructions(_listing(one_side)), cyclic=False) == (1, [])
+
+
 def test_full_wait_variant_has_only_full_waits_in_the_loop():
     """The build variant that the runtime guard compares with (every hand-counted wait replaced by a full
     one): its main loop waits with vmcnt(0) only, so it cannot be wrong about how many loads are behind."""
