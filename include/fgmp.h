@@ -376,6 +376,11 @@ fgmp_status_t fgmp_selftest_mfma_rate(int64_t workgroups, int32_t iters, float *
  */
 fgmp_status_t fgmp_selftest_gemm_route(int64_t M, int64_t N, int64_t K, int64_t *route);
 
+/* How many workgroups of such a call's product, where route[0] is 2, quantize the activations (FP32, rows without
+ * padding) for all of them; 0: a launch in front of the product does, or the kernel is another one.  A negative
+ * fgmp_status_t for bad arguments.  For tests, like the route. */
+int64_t fgmp_selftest_quantizing_workgroups(int64_t M, int64_t N, int64_t K);
+
 /*
  * Measurement hook: the duration of the GEMM kernel (above 32 rows) inside a fused
  * call.  Only libraries built with FGMP_MEASUREMENT_HOOKS have it (the

@@ -288,6 +288,13 @@ fgmp_status_t fgmp_selftest_gemm_route(int64_t M, int64_t N, int64_t K, int64_t 
     return FGMP_OK;
 }
 
+int64_t fgmp_selftest_quantizing_workgroups(int64_t M, int64_t N, int64_t K)
+{
+    if (M <= 0 || N <= 0 || K <= 0) return FGMP_ERR_INVALID_ARG;
+    if (K % kBlock != 0) return FGMP_ERR_BAD_SHAPE;
+    return selftest_quantizing_workgroups(M, N, K);
+}
+
 fgmp_status_t fgmp_selftest_time_gemm_kernel(void *ev_start, void *ev_stop)
 {
     if ((ev_start == nullptr) != (ev_stop == nullptr)) return FGMP_ERR_INVALID_ARG;

@@ -595,6 +595,12 @@ fgmp_status_t quant_gemm_packed_out(const void *X, fgmp_dtype_t dt, int64_t M, i
 }
 
 // The order of quant_gemm's decisions, for tests.
+int64_t selftest_quantizing_workgroups(int64_t M, int64_t N, int64_t K)
+{
+    const GemmRoute r = gemm_route(M, N, K);
+    return r.mid ? gemm_mid_shares(r.plan, M, N, K, K * 4) : 0;
+}
+
 void selftest_gemm_route(int64_t M, int64_t N, int64_t K, int64_t *route)
 {
     std::fill(route, route + 6, (int64_t)0);

@@ -50,13 +50,15 @@ namespace fgmp {
 
 constexpr int kMidThreads = 512;
 // Workgroups that share the quantizing, at most; how often one looks whether the others are done (0.7 us a look; the shares take 2
-// us) before it makes a missing share itself.
+// us) before it makes a share itself that another one has begun.
 constexpr uint32_t kMidMaxUnits = 256;
 constexpr int kMidPatience = 8;
 // Behind the units' words: how many workgroups wait no longer, in sixteen counters on lines of their own (192 additions to one
 // word took 2 us), then how many of these are complete.
 constexpr uint32_t kMidPassed = kMidMaxUnits, kMidPassedGroups = 16, kMidPassedStep = 16;
-constexpr uint32_t kMidPassedAll = kMidPassed + kMidPassedGroups * kMidPassedStep, kMidDoneWords = kMidPassedAll + 16;
+constexpr uint32_t kMidPassedAll = kMidPassed + kMidPassedGroups * kMidPassedStep;
+// ... and a second word per unit: somebody has begun its share.
+constexpr uint32_t kMidBegun = kMidPassedAll + 16, kMidDoneWords = kMidBegun + kMidMaxUnits;
 constexpr uint32_t kMidRsrc = 0x00020000;   // raw buffer, 32-bit data format
 
 // division by a constant that the host knows; exact for dividends below 2^16 and divisors below 2^16
@@ -78,7 +80,7 @@ struct MidQuant {
     uint32_t row_blocks, row_mul;   // blocks of a row in whole K-tiles, and its divisor's multiplier
     uint32_t n_chunks, n_units;
     int patience;
-    uint32_t *done;             // one word per unit, then counters (kMidPassed); zero between launches
+    uint32_t *done;             // one word per unit, then counters (kMidPassed), words again (kMidBegun); zero between launches
 };
 
 struct MidArgs {
@@ -176,8 +178,9 @@ __device__ __forceinline__ void mid_quantize_block(const MidArgs &a, uint32_t c,
     }
 }
 // kQuantize: the activations are quantized by this launch (Sec. 4.2), a share by every workgroup, which then waits for the others'.
-// No workgroup depends on another one running: one whose patience ends makes the missing shares itself, the same values (two
-// launches that fill the chip together on two streams would wait for each other's workgroups to leave).  The values
+// No workgroup depends on another one running: a share that nobody has begun at its second look it makes itself, one that is begun
+// and does not come when its patience ends, too, the same values (two launches that fill the chip together on two streams would
+// wait for each other's workgroups to leave).  The values
 // are stored past the L2s (system-coherent), complete before the share's word is set, and read through the reader's L2 only after
 // that: no L2 holds an older copy, since a launch starts with its L2 lines of earlier launches invalidated and reads none
 // of the values before the words say so.
@@ -285,11 +288,15 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
         else if constexpr (NT == 3) asm volatile("" : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(u[0]), "+v"(u[1]), "+v"(u[2]));
         else asm volatile("" : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[NT - 1]), "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(u[NT - 1]));
     };
+    auto words = [&](uint32_t from) { return __builtin_amdgcn_make_buffer_rsrc(a.q.done + from, 0, (int)(kMidMaxUnits * 4u), kMidRsrc); };
     if constexpr (kQuantize) {
         const uint32_t c = blockIdx.x < a.q.n_units ? (uint32_t)wave * a.q.n_units + blockIdx.x : a.q.n_chunks;
         if (c < a.q.n_chunks) {
             MidBlock b;
             mid_load_block(a, c, lane, b);
+            // (by the first lane, the others' beyond the buffer: no branch, behind which a wait for the loads would be one for the store, too;
+            // in front of the loads it is what they wait for, 0.3 us)
+            __builtin_amdgcn_raw_buffer_store_b32(1u, words(kMidBegun), (int)(tid == 0 ? blockIdx.x * 4u : 0xFFFFFF00u), 0, kCoherent);
             mid_quantize_block(a, c, lane, b, lds + wave * 2048);
         }
         asm volatile("" ::: "memory");   // (its stores are older than the loads that follow: a wait counts on it)
@@ -403,8 +410,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     };
-    auto done_buf = [&]() { return __builtin_amdgcn_make_buffer_rsrc(a.q.done, 0, (int)(kMidMaxUnits * 4u), kMidRsrc); };
-    auto set_done = [&](uint32_t unit) { __builtin_amdgcn_raw_buffer_store_b32(1u, done_buf(), (int)unit * 4, 0, kCoherent); };
+    auto set_word = [&](uint32_t from, uint32_t unit) { __builtin_amdgcn_raw_buffer_store_b32(1u, words(from), (int)unit * 4, 0, kCoherent); };
     constexpr std::integral_constant<int, 0> h0{};
     constexpr std::integral_constant<int, 1> h1{};
     constexpr std::integral_constant<int, 2> h2{};
@@ -414,7 +420,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
         // this wave's values are in memory when only the loads above are outstanding; then the workgroup says so
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FGMP_MID_PENDING(4 * NT)) : "memory");
         barrier();
-        if (tid == 0 && blockIdx.x < a.q.n_units) set_done(blockIdx.x);
+        if (tid == 0 && blockIdx.x < a.q.n_units) set_word(0, blockIdx.x);
     }
     wait_meta(std::integral_constant<int, (kQuantize ? 0 : kALoads) + NT>{});
 #pragma unroll
@@ -434,43 +440,58 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
             if (blockIdx.x >= a.q.n_units) __builtin_amdgcn_s_sleep(40);
             __builtin_amdgcn_s_sleep(12);
         }
-        int looks = a.q.patience;
-        for (;;) {
+        auto load_words = [&](uint32_t from) { return __builtin_amdgcn_raw_buffer_load_b128(words(from), lane * 16, 0, kCoherent); };
+        auto unset = [&](const u32x4_t &d, int e) { return d[e] == 0u && (uint32_t)(lane * 4 + e) < a.q.n_units; };
+        auto any_unset = [&](const u32x4_t &d) { return __builtin_amdgcn_ballot_w64(unset(d, 0) || unset(d, 1) || unset(d, 2) || unset(d, 3)) != 0ull; };
+        // a unit whose word is not set (there is one), the last ones first, since workgroups start in the order of their numbers, and
+        // another one for each workgroup as far as there are several
+        auto pick = [&](const u32x4_t &d) {
+            uint32_t below = 0u, n = 0u;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint64_t m = __builtin_amdgcn_ballot_w64(unset(d, e));
+                below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, below));
+                n += (uint32_t)__builtin_popcountll(m);
+            }
+            uint32_t skip = n - 1u - blockIdx.x % n - below, mine = kMidMaxUnits;   // (unset words of lower lanes: skipped, or, wrapped, past it)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (unset(d, e) && skip-- == 0u) mine = (uint32_t)(lane * 4 + e);
+            return (uint32_t)__builtin_amdgcn_readlane((int)mine, __builtin_ctzll(__builtin_amdgcn_ballot_w64(mine != kMidMaxUnits)));
+        };
+        for (int look = 0;; ++look) {
             if (wave == 7) {
                 uint32_t unit = kMidMaxUnits;
-                for (;;) {
+                for (;; ++look) {
                     asm volatile("" ::: "memory");   // (loaded again every time)
-                    const u32x4_t d = __builtin_amdgcn_raw_buffer_load_b128(done_buf(), lane * 16, 0, kCoherent);
-                    bool mine = false;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) mine = mine || (d[e] == 0u && (uint32_t)(lane * 4 + e) < a.q.n_units);
-                    const uint64_t missing = __builtin_amdgcn_ballot_w64(mine);
-                    if (missing == 0ull) break;
-                    if (--looks < 0) {
-                        // a unit that is missing, another one for each workgroup as far as there are several
-                        const uint32_t turn = blockIdx.x * 29u & 63u;
-                        const uint32_t from = ((uint32_t)__builtin_ctzll(missing >> turn | missing << (-turn & 63u)) + turn) & 63u;
-                        uint32_t first = 0u;
-#pragma unroll
-                        for (int e = 3; e >= 0; --e)
-                            if (d[e] == 0u && (uint32_t)(lane * 4 + e) < a.q.n_units) first = (uint32_t)e;
-                        unit = 4u * from + (uint32_t)__builtin_amdgcn_readlane((int)first, (int)from);
+                    const u32x4_t d = load_words(0);
+                    u32x4_t begun = {1u, 1u, 1u, 1u};
+                    if (look > 0) begun = load_words(kMidBegun);
+                    if (!any_unset(d)) {
+                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the words it set itself have landed, too)
+                        break;
+                    }
+                    if (look >= a.q.patience) begun = d;
+                    if (__builtin_expect(any_unset(begun), 0)) {
+                        unit = pick(begun);
                         break;
                     }
                     __builtin_amdgcn_s_sleep(4);
                 }
-                if (lane == 0) arrived = unit;
+                if (lane == 0) {
+                    arrived = unit;
+                    if (unit != kMidMaxUnits) set_word(kMidBegun, unit);
+                }
             } else if (wave == 0) {
                 // (the word it set has landed before this workgroup counts as past the wait, whoever else has set it, too)
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
             barrier();
             const uint32_t unit = (uint32_t)__builtin_amdgcn_readfirstlane((int)arrived);
-            if (unit >= kMidMaxUnits) break;
-            // its workgroup is not running, for other kernels' sake perhaps: its share is made here, and there again, the same values
-            wait_meta(h0);
-            landed(wl[0], wu[0]);
-            landed(wl[1], wu[1]);
+            if (__builtin_expect(unit >= kMidMaxUnits, 1)) break;
+            // its workgroup has not started, for other kernels' sake perhaps: its share is made here, and there again, the same values
+            // (all loads have landed; named here, in a loop, the registers would be other ones in front of it, copied from those in flight)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             const uint32_t c = (uint32_t)wave * a.q.n_units + unit;
             if (c < a.q.n_chunks) {
                 MidBlock b;
@@ -479,8 +500,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
             }
             __builtin_amdgcn_s_waitcnt(0);
             barrier();
-            if (tid == 448) set_done(unit);   // (by the wave that looks: landed when its next look has)
-            looks = 0;
+            if (tid == 448) set_word(0, unit);   // (by the wave that looks)
         }
 #pragma unroll
         for (int i = 0; i < kALoads; ++i) issue_a(r0, 0, i);
@@ -778,6 +798,22 @@ template <int MT> static void launch_mid_nt(int nt, const MidArgs &a, hipStream_
 // The words that say whose share of the activations is done lie at the end of the control region, behind the tiles' counters.
 constexpr size_t kMidDoneAt = kWsCtrlRegion / 4 - kMidDoneWords;
 
+// Workgroups that hold a share of the quantizing: all, where the chip holds two such launches; else the first ones, a chunk for every
+// second wave (one per SIMD), as far as there are so many workgroups.  These are the first to start, so that a workgroup that finds
+// shares missing has, as a rule, their holders running beside it: dealt out over all workgroups, a launch that holds part of the
+// chip, another stream's the rest, waits for workgroups that have not started.  us per round of one product a stream, on one | two |
+// four streams (a quantizer launch in front, all workgroups hold shares and make missing ones after eight looks, now): 64 x 4096 x
+// 12288 (M, K, N) 18.8 17.4 17.5 | 29.2 36.8 27.7 | 49.2 80.1 50.6, 77 x 2064 x 5003 12.8 12.2 12.0 | 22.3 30.5 18.9 | 34.1 72.6 31.6, 200 x
+// 4096 x 22016 45.2 42.9 43.2 | 83.4 86.3 81.3 | 169 206 176.  On one stream alone four chunks
+// to a workgroup cost up to 2% (one / four: 16.78 / 16.92, 11.77 / 11.91, 42.5 / 42.5).  Where shares take more than half of all waves, overlapping launches
+// still pay more than a quantizer launch (512 x 4096 x 4096 30.6 28.8 29.1 | 49.6 60.4 57.9 | 92 136 110, 207 x 6496 x 720 16.0 14.6 14.6 | 25.1
+// 32.8 33.3 | 41.2 91.5 63.9).  Eight chunks a workgroup, half as many: two streams up to 15% faster, one 1 to 10% slower.
+static uint32_t mid_units(const MidPlan &p, uint32_t n_chunks)
+{
+    const uint32_t wgs = (uint32_t)(p.tiles() * p.parts);
+    return std::min(wgs, 2 * wgs <= kMidMaxUnits ? n_chunks : (n_chunks + 3) / 4);
+}
+
 bool gemm_mid_quantizes(const MidPlan &p, int64_t M, int64_t N, int64_t K, int64_t row_bytes)
 {
     constexpr int64_t kLimit = 0x7FFFFF00;   // 32-bit buffer offsets
@@ -787,6 +823,11 @@ bool gemm_mid_quantizes(const MidPlan &p, int64_t M, int64_t N, int64_t K, int64
         return false;
     const int64_t wgs = p.tiles() * p.parts;
     return wgs <= kMidMaxUnits && blocks <= wgs * kMidThreads;
+}
+
+uint32_t gemm_mid_shares(const MidPlan &p, int64_t M, int64_t N, int64_t K, int64_t row_bytes)
+{
+    return gemm_mid_quantizes(p, M, N, K, row_bytes) ? mid_units(p, (uint32_t)((M * ((K + kTileK - 1) / kTileK * kTileBlocks) + 63) / 64)) : 0u;
 }
 
 fgmp_status_t gemm_mid(const MidPlan &p, const MidInput &in, _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
@@ -807,7 +848,7 @@ fgmp_status_t gemm_mid(const MidPlan &p, const MidInput &in, _Float16 *x16, int6
         q.row_blocks = (uint32_t)(lw.n_kt * kTileBlocks);
         q.row_mul = (uint32_t)(0x100000000ull / q.row_blocks) + 1u;
         q.n_chunks = (uint32_t)((M * q.row_blocks + 63) / 64);
-        q.n_units = std::min((uint32_t)(p.tiles() * p.parts), q.n_chunks);
+        q.n_units = mid_units(p, q.n_chunks);
         q.done = static_cast<uint32_t *>(ctrl) + kMidDoneAt;
         q.patience = kMidPatience;
 #ifdef FGMP_MEASUREMENT_HOOKS

@@ -123,6 +123,7 @@ struct MidInput {
     int f32, delta;
 };
 bool gemm_mid_quantizes(const MidPlan &p, int64_t M, int64_t N, int64_t K, int64_t row_bytes);
+uint32_t gemm_mid_shares(const MidPlan &p, int64_t M, int64_t N, int64_t K, int64_t row_bytes);   // workgroups that do (0: a launch of its own)
 fgmp_status_t gemm_mid(const MidPlan &p, const MidInput &in, _Float16 *x16, int64_t ld16, const void *w, int64_t M, int64_t N, int64_t K, float *Y,
                        int64_t ldy, void *ctrl, void *scratch, hipStream_t st);
 // packed -> zero-padded dense FP16 [8 n_rt_pad][ld]; one launch decodes one or two tensors and
@@ -169,6 +170,7 @@ fgmp_status_t selftest_encode_ranges(int format, uint32_t *min_bits, uint32_t *m
                                      uint32_t *violations, hipStream_t st);
 fgmp_status_t selftest_decode_table(int format, float *out, hipStream_t st);
 void selftest_gemm_route(int64_t M, int64_t N, int64_t K, int64_t *route);
+int64_t selftest_quantizing_workgroups(int64_t M, int64_t N, int64_t K);
 fgmp_status_t selftest_mfma_rate(int64_t workgroups, int32_t iters, float *sink, hipStream_t st);
 // element of rank `rank` (0 = smallest) of the union of n_tensors device arrays; result on the host; synchronizes
 fgmp_status_t select_rank(const float *const *scores, const int64_t *counts, int32_t n_tensors, int64_t rank, float *result_host,

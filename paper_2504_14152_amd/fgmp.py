@@ -158,6 +158,8 @@ def _load(path: str) -> ctypes.CDLL:
     L.fgmp_selftest_mfma_rate.argtypes = [ctypes.c_int64, ctypes.c_int32, vp, vp]
     L.fgmp_selftest_gemm_route.restype = ctypes.c_int
     L.fgmp_selftest_gemm_route.argtypes = [i64, i64, i64, ctypes.POINTER(i64)]
+    L.fgmp_selftest_quantizing_workgroups.restype = i64
+    L.fgmp_selftest_quantizing_workgroups.argtypes = [i64, i64, i64]
     L.fgmp_selftest_time_gemm_kernel.restype = ctypes.c_int
     L.fgmp_selftest_time_gemm_kernel.argtypes = [vp, vp]
     L.fgmp_selftest_quantizer_traffic.restype = ctypes.c_int
@@ -477,6 +479,14 @@ def selftest_gemm_route(M: int, N: int, K: int) -> tuple:
     route = (ctypes.c_int64 * 6)()
     _check(lib().fgmp_selftest_gemm_route(M, N, K, route), "fgmp_selftest_gemm_route")
     return tuple(route)
+
+
+def selftest_quantizing_workgroups(M: int, N: int, K: int) -> int:
+    """Workgroups of a fused call's product that quantize its activations (0: another launch does); launches nothing."""
+    n = lib().fgmp_selftest_quantizing_workgroups(M, N, K)
+    if n < 0:
+        _check(n, "fgmp_selftest_quantizing_workgroups")
+    return n
 
 
 def selftest_mfma_rate(workgroups: int, iters: int, sink: torch.Tensor) -> None:

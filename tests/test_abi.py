@@ -3,6 +3,7 @@ symbol the public header declares, and rejects bad arguments before launching
 anything."""
 import ctypes
 import os
+import random
 import re
 
 import numpy as np
@@ -172,6 +173,26 @@ def test_an_odd_number_of_row_tiles_takes_the_kernel_of_its_even_neighbours():
         near = {fgmp.selftest_gemm_route(M, n, K)[0] for n in (N - 8, N + 8)}
         assert -(-N // 8) % 2 == 1 and near == {fgmp.selftest_gemm_route(M, N, K)[0]}, (M, K, N)
     assert fgmp.selftest_gemm_route(20, 8184, 8192)[0] == 0 and fgmp.selftest_gemm_route(24, 4088, 11008)[0] == 2
+
+
+def test_the_first_workgroups_quantize_for_all():
+    """Products of 33 rows on that quantize in their launch: where the chip does not hold two such launches, no more workgroups hold a
+    share than it takes at four pieces of 64 blocks each (dealt out over all of them, overlapping launches wait for workgroups that
+    have not started), and never more than eight pieces, one per wave, fall to one."""
+    rng = random.Random(5)
+    seen = 0
+    for M, K, N in [(64, 4096, 12288), (77, 2064, 5003), (200, 4096, 22016), (512, 4096, 4096), (33, 160, 16503)] + [
+            (int(2 ** rng.uniform(5.1, 10)), 16 * int(2 ** rng.uniform(0, 9.5)), int(2 ** rng.uniform(3, 14.5))) for _ in range(400)]:
+        route = fgmp.selftest_gemm_route(M, N, K)
+        holders = fgmp.selftest_quantizing_workgroups(M, N, K)
+        workgroups, pieces = route[3] * route[4] * route[5], -(-M * 8 * -(-K // 128) // 64)
+        in_launch = route[0] == 2 and workgroups <= 256 and M * 8 * -(-K // 128) <= 512 * workgroups
+        assert holders == (min(workgroups, pieces if workgroups <= 128 else -(-pieces // 4)) if in_launch else 0), (M, K, N)
+        if in_launch:
+            seen += 1
+            assert pieces <= 8 * holders
+    assert seen >= 100
+    assert fgmp.lib().fgmp_selftest_quantizing_workgroups(8, 24, 24) == -2 and fgmp.lib().fgmp_selftest_quantizing_workgroups(0, 24, 16) == -1
 
 
 class _Pretend:

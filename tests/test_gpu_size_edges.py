@@ -193,6 +193,32 @@ def test_products_that_quantize_in_their_launch_are_those_of_packed_activations(
             assert int(ws[: fgmp.WORKSPACE_CONTROL_BYTES].count_nonzero()) == 0
 
 
+# (launches that hold half of the chip, most of it and all of it; shares for a third of the workgroups, most and all)
+@pytest.mark.parametrize("M,K,N", [(36, 5920, 1759), (64, 4096, 12288), (200, 4096, 22016), (207, 6496, 720)])
+def test_products_that_quantize_in_their_launch_overlap_on_four_streams(M, K, N):
+    """A workspace each, started together and followed by more, other inputs every time: launches that share the chip find shares
+    whose workgroups have not started, and make them.  Every result is that of packed activations, bit for bit."""
+    assert fgmp.selftest_quantizing_workgroups(M, N, K) > 0
+    g = torch.Generator(device=DEV).manual_seed(M + K + N)
+    w = torch.randn(N, K, generator=g, device=DEV) * 0.02
+    f = torch.exp(torch.randn(K, generator=g, device=DEV))
+    pW = fgmp.quantize_weights(w, f, 1e-5, float(w.abs().max()) / 448.0)
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    spaces = [fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV) for _ in streams]
+    xs = [[torch.randn(M, K, generator=g, device=DEV).bfloat16() for _ in range(3)] for _ in streams]
+    scales = [[float(x.abs().max()) / 448.0 for x in row] for row in xs]
+    want = [[fgmp.gemm(fgmp.quantize_activations(x, f, 0.5, s), pW) for x, s in zip(*row)] for row in zip(xs, scales)]
+    out = [[torch.empty(M, N, device=DEV) for _ in range(3)] for _ in streams]
+    torch.cuda.synchronize()
+    for call in range(3):
+        for i, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                fgmp.quant_gemm_fused(xs[i][call], f, 0.5, scales[i][call], pW, out=out[i][call], workspace=spaces[i])
+    torch.cuda.synchronize()
+    for i in range(len(streams)):
+        assert all(torch.equal(got, y) for got, y in zip(out[i], want[i])), i
+        assert int(spaces[i][: fgmp.WORKSPACE_CONTROL_BYTES].count_nonzero()) == 0
+
 
 def test_long_products_of_few_rows_quantize_the_results_of_the_plain_call():
     M, K, N = 28, 16384, 2048
