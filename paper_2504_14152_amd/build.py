@@ -19,7 +19,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfgmp.so")
 CALL_SOURCE = os.path.join(CSRC, "fgmp_call.c")
-CALL = os.path.join(HERE, "_fgmp_call.so")   # what the binding hands the fused call's arguments over with
+# what the binding hands the fused call's arguments over with; the name says for which interpreter
+CALL = os.path.join(HERE, "_fgmp_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["fgmp_quantize.hip", "fgmp_gemm.hip", "fgmp_gemm_skinny.hip", "fgmp_gemm_stream.hip", "fgmp_gemm_mid.hip",
            "fgmp_gemm_mixed.hip",
            "fgmp_select.hip", "fgmp_api.hip"]
@@ -85,20 +86,29 @@ def build_one(variant: str | None = None, verbose: bool = False, extra_flags: li
 
 
 def build_call() -> str:
-    """The extension module for the interpreter that runs this."""
-    cmd = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], CALL_SOURCE, "-o", CALL]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError(f"{cmd[0]} failed for {CALL_SOURCE}:\n{res.stderr}")
+    """The extension module for the interpreter that runs this.  Moved to its place when it is whole: other processes may look for it
+    there, or build it, too."""
+    part = f"{CALL}.{os.getpid()}"
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], CALL_SOURCE, "-o", part]
+    try:
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError(f"{cmd[0]} failed for {CALL_SOURCE}:\n{res.stderr}")
+        os.replace(part, CALL)
+    finally:
+        if os.path.exists(part):
+            os.remove(part)
     return CALL
 
 
 def build(verbose: bool = False, extra_flags: list[str] | None = None, out: str | None = None,
-          variants: bool = True) -> str:
+          variants: bool = True, extension: bool = True) -> str:
     """Build libfgmp.so (and, unless an explicit output is asked for, its two variants), then check the
-    compiled loops with hand-counted waits of this very compiler and flag set for load/wait hazards."""
+    compiled loops with hand-counted waits of this very compiler and flag set for load/wait hazards.  `extension`: and the
+    binding's extension module."""
     path = build_one(None, verbose, extra_flags, out)
-    build_call()
+    if extension:
+        build_call()
     if out is None and variants:
         for v in VARIANTS:
             build_one(v, verbose, extra_flags)

@@ -5,6 +5,7 @@ shared library is missing or a call fails, an exception is raised."""
 from __future__ import annotations
 
 import ctypes
+import functools
 import importlib.machinery
 import importlib.util
 import os
@@ -45,7 +46,7 @@ def _library_file() -> str:
     if _build.is_stale(path):
         have_compiler = os.path.exists(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"))
         if have_compiler:
-            _build.build()
+            _build.build(extension=False)   # (_load_call builds it, where that is possible)
         elif not os.path.exists(path):
             raise FgmpError(f"{path} is missing and there is no hipcc to build it")
         else:
@@ -62,14 +63,20 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+@functools.cache
 def _load_call():
-    """The extension module that passes the fused call's arguments on, built from its source where it is missing or older."""
-    path = _build.CALL
-    if not os.path.exists(path) or os.path.getmtime(path) < os.path.getmtime(_build.CALL_SOURCE):
-        _build.build_call()
-    loader = importlib.machinery.ExtensionFileLoader("_fgmp_call", path)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fgmp_call", loader))
-    loader.exec_module(module)
+    """The extension module that passes the fused call's arguments on, built from its source where it is missing or older.  None
+    where it cannot be built or loaded (no compiler, no Python headers, a folder that is not written to): it saves host time only,
+    and ctypes calls the same entry point."""
+    try:
+        path = _build.CALL
+        if not os.path.exists(path) or os.path.getmtime(path) < os.path.getmtime(_build.CALL_SOURCE):
+            _build.build_call()
+        loader = importlib.machinery.ExtensionFileLoader("_fgmp_call", path)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fgmp_call", loader))
+        loader.exec_module(module)
+    except (ImportError, OSError, RuntimeError):
+        return None
     return module
 
 
@@ -322,8 +329,8 @@ def quant_gemm_fused(X: torch.Tensor, fisher_k: torch.Tensor, threshold: float, 
     if out is not None and workspace is not None and score_mode is None:
         # (a server's call, which brings its buffers; None: something below has to be said about the arguments)
         L = lib()
-        rc = _call.quant_gemm_fused(L.fused_entry, torch.float32, torch.bfloat16, X, fisher_k, threshold, scale_x, pW, out,
-                                    workspace, _stream())
+        rc = None if _call is None else _call.quant_gemm_fused(L.fused_entry, torch.float32, torch.bfloat16, X, fisher_k, threshold,
+                                                               scale_x, pW, out, workspace, _stream())
         if rc is not None:
             if rc != 0:
                 _check(rc, "fgmp_quant_gemm_fused")

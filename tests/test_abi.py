@@ -234,3 +234,41 @@ def test_the_extension_hands_on_what_it_is_given(dtype, code):
            (_Pretend(16, (32,), dtype), f, 0.25, 1.5, w, Y, ws), (X, f, None, 1.5, w, Y, ws), (X, f, 0.25, 1.5, w, "out", ws),
            (X, f, 0.25, 1.5, w, Y, None), (X, f, 0.25, 1.5, None, Y, ws)]
     assert [call(*b) for b in bad] == [None] * len(bad) and len(got) == 1
+
+
+def test_without_a_c_compiler_the_binding_takes_ctypes(tmp_path, monkeypatch):
+    """The extension module saves host time and nothing else: where it is not there and cannot be built, libraries load and every
+    entry point works through ctypes."""
+    monkeypatch.setattr(build, "CALL", str(tmp_path / "module.so"))
+    monkeypatch.setenv("CC", str(tmp_path / "no-compiler"))
+    monkeypatch.setattr(fgmp, "_call", None)
+    fgmp._load_call.cache_clear()
+    try:
+        assert fgmp._load(build.lib_path()).fgmp_version() == fgmp.lib().fgmp_version() and fgmp._call is None
+        monkeypatch.setattr(fgmp, "_stream", lambda: 0)
+        X, f, w = _Pretend(16, (3, 48)), _Pretend(32, (48,)), fgmp.Packed(_Pretend(64, (999,)), 40, 32)
+        with pytest.raises(fgmp.FgmpError, match="K mismatch"):   # (what the general path says)
+            fgmp.quant_gemm_fused(X, f, 0.5, 1.0, w, out=_Pretend(48, (3, 40)), workspace=_Pretend(80, (12345,)))
+    finally:
+        fgmp._load_call.cache_clear()
+
+
+def test_the_extension_is_this_interpreters_and_appears_whole(tmp_path, monkeypatch):
+    """Named with the interpreter's tag, so that no other one loads it; compiled beside its place and moved there: who finds the file
+    finds all of it, and a build that fails leaves what was there."""
+    import sysconfig
+    assert build.CALL.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and "cpython" in os.path.basename(build.CALL)
+    place = tmp_path / "module.so"
+    place.write_text("before")
+    compiler = tmp_path / "cc"
+    compiler.write_text("#!/bin/sh\nwhile [ $# -gt 1 ]; do if [ $1 = -o ]; then out=$2; fi; shift; done\necho half > $out\ncp %s %s.seen\nexit $STATUS\n" % (place, place))
+    compiler.chmod(0o755)
+    monkeypatch.setattr(build, "CALL", str(place))
+    monkeypatch.setenv("CC", str(compiler))
+    monkeypatch.setenv("STATUS", "1")
+    with pytest.raises(RuntimeError):
+        build.build_call()
+    assert place.read_text() == "before"
+    monkeypatch.setenv("STATUS", "0")
+    assert build.build_call() == str(place) and place.read_text() == "half\n"
+    assert (tmp_path / "module.so.seen").read_text() == "before" and sorted(os.listdir(tmp_path)) == ["cc", "module.so", "module.so.seen"]
