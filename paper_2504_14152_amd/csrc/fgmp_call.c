@@ -36,13 +36,20 @@ static int64_t integer(PyObject *v, int *bad)
     return r;
 }
 
+/* (from here on: nothing is asked for once something was bad, an exception may be pending) */
+static int64_t attribute(PyObject *o, PyObject *name, int *bad)
+{
+    return *bad ? 0 : integer(PyObject_GetAttr(o, name), bad);
+}
+
 static void *pointer(PyObject *tensor, int *bad)
 {
+    if (*bad) return NULL;
     PyObject *const args[1] = {tensor};
     PyObject *v = PyObject_VectorcallMethod(s_data_ptr, args, 1, NULL);
     void *p = NULL;
     if (v != NULL && PyLong_Check(v)) p = PyLong_AsVoidPtr(v);
-    else *bad = 1;
+    if (v == NULL || !PyLong_Check(v) || PyErr_Occurred()) *bad = 1;
     Py_XDECREF(v);
     return p;
 }
@@ -50,11 +57,18 @@ static void *pointer(PyObject *tensor, int *bad)
 static int64_t row_stride(PyObject *tensor, int *bad)
 {
     PyObject *const args[2] = {tensor, zero};
-    return integer(PyObject_VectorcallMethod(s_stride, args, 2, NULL), bad);
+    return *bad ? 0 : integer(PyObject_VectorcallMethod(s_stride, args, 2, NULL), bad);
+}
+
+static int64_t elements(PyObject *tensor, int *bad)
+{
+    PyObject *const args[1] = {tensor};
+    return *bad ? 0 : integer(PyObject_VectorcallMethod(s_numel, args, 1, NULL), bad);
 }
 
 static double number(PyObject *o, int *bad)
 {
+    if (*bad) return 0.0;
     if (PyFloat_CheckExact(o)) return PyFloat_AS_DOUBLE(o);
     PyObject *v = PyNumber_Float(o);
     const double d = v != NULL ? PyFloat_AS_DOUBLE(v) : 0.0;
@@ -85,12 +99,14 @@ static PyObject *quant_gemm_fused(PyObject *self, PyObject *const *a, Py_ssize_t
     M = integer(PyTuple_GET_ITEM(v, 0), &bad);
     K = integer(PyTuple_GET_ITEM(v, 1), &bad);
     Py_CLEAR(v);
+    if (bad) goto general;
     v = PyObject_GetAttr(X, s_dtype);
     const int dt = v == a[1] ? 0 : v == a[2] ? 1 : -1;
     Py_CLEAR(v);
-    if (bad || dt < 0) goto general;
-    if (integer(PyObject_GetAttr(pW, s_K), &bad) != K || bad) goto general;
-    const int64_t N = integer(PyObject_GetAttr(pW, s_rows), &bad);
+    if (dt < 0) goto general;
+    if (attribute(pW, s_K, &bad) != K) goto general;
+    const int64_t N = attribute(pW, s_rows, &bad);
+    if (bad) goto general;
     v = PyObject_GetAttr(pW, s_buf);
     if (v == NULL) goto general;
     const void *const w = pointer(v, &bad);
@@ -101,19 +117,17 @@ static PyObject *quant_gemm_fused(PyObject *self, PyObject *const *a, Py_ssize_t
     float *const y = (float *)pointer(out, &bad);
     const int64_t ldy = row_stride(out, &bad);
     void *const ws = pointer(workspace, &bad);
-    {
-        PyObject *const args[1] = {workspace};
-        const int64_t ws_bytes = integer(PyObject_VectorcallMethod(s_numel, args, 1, NULL), &bad);
-        const float T = (float)number(a[5], &bad), S = (float)number(a[6], &bad);
-        const fused_fn fn = (fused_fn)PyLong_AsVoidPtr(a[0]);
-        void *const stream = PyLong_AsVoidPtr(a[10]);
-        if (bad || fn == NULL || PyErr_Occurred()) goto general;
-        int rc;
-        Py_BEGIN_ALLOW_THREADS
-        rc = fn(x, dt, M, K, ldx, f, T, S, w, N, y, ldy, ws, (size_t)ws_bytes, stream);
-        Py_END_ALLOW_THREADS
-        return PyLong_FromLong(rc);
-    }
+    const int64_t ws_bytes = elements(workspace, &bad);
+    const float T = (float)number(a[5], &bad), S = (float)number(a[6], &bad);
+    if (bad) goto general;
+    const fused_fn fn = (fused_fn)PyLong_AsVoidPtr(a[0]);
+    void *const stream = fn != NULL ? PyLong_AsVoidPtr(a[10]) : NULL;
+    if (fn == NULL || PyErr_Occurred()) goto general;
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = fn(x, dt, M, K, ldx, f, T, S, w, N, y, ldy, ws, (size_t)ws_bytes, stream);
+    Py_END_ALLOW_THREADS
+    return PyLong_FromLong(rc);
 general:
     Py_XDECREF(v);
     PyErr_Clear();

@@ -272,3 +272,31 @@ def test_the_extension_is_this_interpreters_and_appears_whole(tmp_path, monkeypa
     monkeypatch.setenv("STATUS", "0")
     assert build.build_call() == str(place) and place.read_text() == "half\n"
     assert (tmp_path / "module.so.seen").read_text() == "before" and sorted(os.listdir(tmp_path)) == ["cc", "module.so", "module.so.seen"]
+
+
+@pytest.mark.parametrize("what", ["X.is_cuda", "X.shape", "X.dtype", "X.data_ptr", "X.stride", "fisher.is_cuda", "fisher.data_ptr", "w.K", "w.rows",
+                                  "w.buf.data_ptr", "out.data_ptr", "out.stride", "workspace.data_ptr", "workspace.numel"])
+def test_the_extension_asks_nothing_more_once_something_failed(what):
+    """An argument that raises ends it: no other object is asked with that exception pending, and the general path says what is wrong."""
+    asked = []
+
+    class Asked:
+        def __init__(self, name, of):
+            self._name, self._of = name, of
+
+        def __getattr__(self, key):
+            asked.append(f"{self._name}.{key}")
+            if asked[-1] == what:
+                raise ValueError(key)
+            value = getattr(self._of, key)
+            if key == "buf":
+                return Asked(f"{self._name}.buf", value)
+            return value
+
+    fgmp.lib()
+    proto = ctypes.CFUNCTYPE(ctypes.c_int)
+    entry = proto(lambda: asked.append("called") or 0)
+    X, f, Y, ws = (Asked(n, _Pretend(16, shape)) for n, shape in (("X", (3, 32)), ("fisher", (32,)), ("out", (3, 40)), ("workspace", (99,))))
+    w = Asked("w", fgmp.Packed(_Pretend(64, (999,)), 40, 32))
+    rc = fgmp._call.quant_gemm_fused(ctypes.cast(entry, ctypes.c_void_p).value, torch.float32, torch.bfloat16, X, f, 0.5, 1.0, w, Y, ws, 0)
+    assert rc is None and asked[-1] == what and "called" not in asked
