@@ -474,9 +474,12 @@ __global__ __launch_bounds__(64 * kStWaves) void gemm_stream_kernel(StreamArgs a
     }
 
     // ---- prologue of the weight stream
-    // (plane T only where a run starts, as in a compact tensor; the few tensors that are not ask for the others below.  The
-    // requests that all waves make before their first product hold each other up: three fewer of nineteen are 1 x 4096 x 12288
-    // 9.8 / 9.6 us, 1 x 11008 x 4096 10.5 / 10.1, 4 x 4096 x 12288 11.0 / 10.65, nothing from 8 rows on, where quantizing is longer.)
+    // (plane T only where a run starts, as in a compact tensor; the few tensors that are not ask for the others below, behind the header.
+    // The requests that all waves make before their first product hold each other up.  us per call with a request for each of the
+    // four tiles / now: compact 1 x 4096 x 4096 5.82 / 5.72, 1 x 4096 x 12288 9.10 / 8.88, 1 x 11008 x 4096 9.82 / 9.51, 4 x 4096 x
+    // 12288 10.20 / 9.87, 8 x 4096 x 12288 11.61 / 11.50; not compact 5.80 / 5.97, 9.62 / 9.86, 10.18 / 10.02, 10.77 / 10.62, 12.09 / 12.20.
+    // The other words in the lanes of the first request, spread once the header is known: not compact 5.79, 9.54, 10.02, 10.52,
+    // 12.11, but compact 5.75 to 5.8, 8.95, 9.55, 9.89, 11.54; by scalar loads: 5.81, 9.68, 10.18, 10.68, 12.23 and 5.74, 8.99, 9.58, 9.90, 11.51.)
     uint32_t pt[kStRing], pbytes[kStRing];
     bool pfirst[kStRing];
 #pragma unroll

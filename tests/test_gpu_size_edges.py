@@ -193,6 +193,32 @@ def test_products_that_quantize_in_their_launch_are_those_of_packed_activations(
             assert int(ws[: fgmp.WORKSPACE_CONTROL_BYTES].count_nonzero()) == 0
 
 
+# (runs of one, two, three and more K-tiles, the last one shorter; a single run and several; an odd number of row-tiles; parts of K)
+@pytest.mark.parametrize("M,K,N", [(3, 128, 4096), (5, 256, 22016), (1, 4096, 4096), (1, 4096, 12288), (1, 11008, 1032), (8, 384, 6168), (2, 640, 72),
+                                   (20, 4096, 4104), (32, 11008, 520)])
+@pytest.mark.parametrize("source", ["bf16", "packed"])
+def test_decode_steps_over_weights_that_are_not_compact(M, K, N, source):
+    """The same codes with the upper halves where the activation quantizer puts them: every tile's plane-T word is needed, not a run's
+    first one only.  Every bit as from the compact tensor."""
+    assert fgmp.selftest_gemm_route(M, N, K)[0] == 0
+    g = torch.Generator(device=DEV).manual_seed(M + K + N)
+    w = torch.randn(N, K, generator=g, device=DEV) * 0.02
+    f = torch.exp(torch.randn(K, generator=g, device=DEV))
+    x = torch.randn(M, K, generator=g, device=DEV).bfloat16()
+    sw, sx = float(w.abs().max()) / 448.0, float(x.abs().max()) / 448.0
+    _, scores = fgmp.quantize_activations(w, f, float("inf"), sw, want_scores=True)
+    for fraction in (0.1, 0.6):
+        T = fgmp.threshold_for_fraction(scores, fraction)
+        compact, strided = fgmp.quantize_weights(w, f, T, sw), fgmp.quantize_activations(w, f, T, sw)
+        assert (fgmp.packed_info(compact)["compact"], fgmp.packed_info(strided)["compact"]) == (1, 0)
+        if source == "packed":
+            px = fgmp.quantize_activations(x, f, 0.5, sx)
+            got, want = fgmp.gemm(px, strided), fgmp.gemm(px, compact)
+        else:
+            got, want = (fgmp.quant_gemm_fused(x, f, 0.5, sx, p) for p in (strided, compact))
+        assert torch.equal(got, want) and bool(got.any())
+
+
 # (launches that hold half of the chip, most of it and all of it; shares for a third of the workgroups, most and all)
 @pytest.mark.parametrize("M,K,N", [(36, 5920, 1759), (64, 4096, 12288), (200, 4096, 22016), (207, 6496, 720)])
 def test_products_that_quantize_in_their_launch_overlap_on_four_streams(M, K, N):
