@@ -78,7 +78,7 @@ struct MidQuant {
     uint32_t x_bytes, row_bytes;
     uint32_t nb;                // blocks of a row
     uint32_t row_blocks, row_mul;   // blocks of a row in whole K-tiles, and its divisor's multiplier
-    uint32_t n_chunks, n_units;
+    uint32_t n_chunks, n_units, n_own;   // n_own: units whose workgroups make them (all; fewer only in a test)
     int patience;
     uint32_t *done;             // one word per unit, then counters (kMidPassed), words again (kMidBegun); zero between launches
 };
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
     };
     auto words = [&](uint32_t from) { return __builtin_amdgcn_make_buffer_rsrc(a.q.done + from, 0, (int)(kMidMaxUnits * 4u), kMidRsrc); };
     if constexpr (kQuantize) {
-        const uint32_t c = blockIdx.x < a.q.n_units ? (uint32_t)wave * a.q.n_units + blockIdx.x : a.q.n_chunks;
+        const uint32_t c = blockIdx.x < a.q.n_own ? (uint32_t)wave * a.q.n_units + blockIdx.x : a.q.n_chunks;
         if (c < a.q.n_chunks) {
             MidBlock b;
             mid_load_block(a, c, lane, b);
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 
         // this wave's values are in memory when only the loads above are outstanding; then the workgroup says so
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FGMP_MID_PENDING(4 * NT)) : "memory");
         barrier();
-        if (tid == 0 && blockIdx.x < a.q.n_units) set_word(0, blockIdx.x);
+        if (tid == 0 && blockIdx.x < a.q.n_own) set_word(0, blockIdx.x);
     }
     wait_meta(std::integral_constant<int, (kQuantize ? 0 : kALoads) + NT>{});
 #pragma unroll
@@ -848,11 +848,13 @@ fgmp_status_t gemm_mid(const MidPlan &p, const MidInput &in, _Float16 *x16, int6
         q.row_blocks = (uint32_t)(lw.n_kt * kTileBlocks);
         q.row_mul = (uint32_t)(0x100000000ull / q.row_blocks) + 1u;
         q.n_chunks = (uint32_t)((M * q.row_blocks + 63) / 64);
-        q.n_units = mid_units(p, q.n_chunks);
+        q.n_own = q.n_units = mid_units(p, q.n_chunks);
         q.done = static_cast<uint32_t *>(ctrl) + kMidDoneAt;
         q.patience = kMidPatience;
 #ifdef FGMP_MEASUREMENT_HOOKS
         if (const char *e = getenv("FGMP_MID_PATIENCE")) q.patience = atoi(e);   // (0: every workgroup makes what is missing at its first look)
+        // (the last ones make nothing and say nothing, as if they had not started)
+        if (const char *e = getenv("FGMP_MID_ABSENT")) q.n_own -= std::min(q.n_units, (uint32_t)atoi(e));
 #endif
     }
     a.w = w; a.xh = xh; a.x16 = x16; a.Y = Y; a.ldy = ldy;

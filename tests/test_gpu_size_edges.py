@@ -164,25 +164,27 @@ def test_products_between_decode_and_prefill_replay_in_a_graph():
         assert torch.equal(Y, want)
 
 
-# (M, K, N): a last chunk of 64 blocks that ends inside the tensor, rows in K-tiles of which part lies beyond K, fewer
-# chunks than workgroups and more, 256 workgroups, one block per thread exactly and one past it (which takes two launches), a
-# partial sum across workgroups
-@pytest.mark.parametrize("M,K,N", [(33, 144, 136), (77, 2064, 503), (64, 4096, 12288), (120, 368, 603), (96, 640, 72), (512, 4096, 4096),
-                                   (516, 4096, 4096), (49, 7696, 5491), (154, 10976, 4810)])
+# (M, K, N), workgroups that hold a share: a last chunk of 64 blocks that ends inside the tensor, rows in K-tiles of which part lies
+# beyond K, fewer chunks than workgroups and more, shares for some of the workgroups, most and all of them, 256 workgroups, one
+# block per thread almost and exactly, and more (none hold a share: two launches), partial sums across workgroups, 24 rows
+@pytest.mark.parametrize("M,K,N,holders", [(33, 144, 136, 3), (33, 160, 16503, 3), (65, 272, 12409, 7), (77, 2064, 5003, 41), (77, 2064, 503, 0),
+                                           (64, 4096, 12288, 64), (120, 368, 603, 30), (96, 640, 700, 22), (96, 640, 72, 0), (512, 4096, 4096, 256),
+                                           (516, 4096, 4096, 0), (49, 7696, 5491, 94), (154, 10976, 4810, 208), (24, 11008, 4096, 65)])
 @pytest.mark.parametrize("dtype,mode", [("bf16", None), ("f32", "delta")])
-@pytest.mark.parametrize("patience", [None, "0"])
-def test_products_that_quantize_in_their_launch_are_those_of_packed_activations(M, K, N, dtype, mode, patience, monkeypatch):
+@pytest.mark.parametrize("switch", [None, ("FGMP_MID_PATIENCE", "0"), ("FGMP_MID_ABSENT", "1"), ("FGMP_MID_ABSENT", "999")])
+def test_products_that_quantize_in_their_launch_are_those_of_packed_activations(M, K, N, holders, dtype, mode, switch, monkeypatch):
     """Against the product of activations packed beforehand, which the oracle pins above: the same kernel over the same values, so
-    every bit agrees.  Without patience (a switch of the build with measurement hooks) every workgroup makes the shares that it finds missing."""
-    assert fgmp.selftest_gemm_route(M, N, K)[0] == 2
+    every bit agrees.  Without patience (a switch of the build with measurement hooks, as the next) every workgroup makes the shares
+    that it finds missing; with the last holder absent, or all of them, the others make theirs."""
+    assert fgmp.selftest_gemm_route(M, N, K)[0] == 2 and fgmp.selftest_quantizing_workgroups(M, N, K) == holders
     g = torch.Generator(device=DEV).manual_seed(M + K + N)
     w = torch.randn(N, K, generator=g, device=DEV) * 0.02
     f = torch.exp(torch.randn(K, generator=g, device=DEV))
     pW = fgmp.quantize_weights(w, f, 1e-5, float(w.abs().max()) / 448.0)
     ws = fgmp.new_workspace(fgmp.workspace_bytes(M, N, K), DEV)
-    if patience is not None:
-        monkeypatch.setenv("FGMP_MID_PATIENCE", patience)
-    with fgmp.use_library(build.lib_path("hooks" if patience is not None else None)):
+    if switch is not None:
+        monkeypatch.setenv(*switch)
+    with fgmp.use_library(build.lib_path("hooks" if switch is not None else None)):
         for call in range(3):   # other inputs each time, in the place where the earlier ones' values lie
             x = torch.randn(M, K, generator=g, device=DEV).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
             s = float(x.float().abs().max()) / 448.0
@@ -191,6 +193,44 @@ def test_products_that_quantize_in_their_launch_are_those_of_packed_activations(
             want = fgmp.gemm(fgmp.quantize_activations(x, f, 0.5, s, score_mode=mode), pW)
             assert torch.equal(got, want), call
             assert int(ws[: fgmp.WORKSPACE_CONTROL_BYTES].count_nonzero()) == 0
+
+
+def test_products_that_quantize_in_their_launch_replay_in_a_graph_with_other_inputs():
+    """Three launches one behind the other on one workspace, nothing between them: each finds the words as the one before left them and,
+    where its values go, other ones, which the chip's caches may hold from the replay before.  Inputs change between replays."""
+    g = torch.Generator(device=DEV).manual_seed(17)
+    shapes = [(64, 4096, 12288), (64, 4096, 12288), (77, 2064, 5003)]
+    assert all(fgmp.selftest_quantizing_workgroups(M, N, K) > 0 for M, K, N in shapes)
+    weights, calls = {}, []
+    for M, K, N in shapes:
+        f = torch.exp(torch.randn(K, generator=g, device=DEV))
+        if (K, N) not in weights:
+            w = torch.randn(N, K, generator=g, device=DEV) * 0.02
+            weights[K, N] = fgmp.quantize_weights(w, f, 1e-5, float(w.abs().max()) / 448.0)
+        calls.append((torch.empty(M, K, dtype=torch.bfloat16, device=DEV), f, weights[K, N], torch.empty(M, N, device=DEV)))
+    ws = fgmp.new_workspace(max(fgmp.workspace_bytes(M, N, K) for M, K, N in shapes), DEV)
+
+    def step():
+        for x, f, pw, y in calls:
+            fgmp.quant_gemm_fused(x, f, 0.5, 0.011, pw, out=y, workspace=ws)
+
+    def fresh():
+        for x, _, _, _ in calls:
+            x.copy_(torch.randn(x.shape, generator=g, device=DEV))
+
+    fresh()
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for replay in range(5):
+        fresh()
+        graph.replay()
+        torch.cuda.synchronize()
+        for x, f, pw, y in calls:
+            assert torch.equal(y, fgmp.gemm(fgmp.quantize_activations(x, f, 0.5, 0.011), pw)), replay
+        assert int(ws[: fgmp.WORKSPACE_CONTROL_BYTES].count_nonzero()) == 0
 
 
 # (runs of one, two, three and more K-tiles, the last one shorter; a single run and several; an odd number of row-tiles; parts of K)
