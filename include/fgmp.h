@@ -20,8 +20,10 @@
  *   - Return value: FGMP_OK (0) or a negative fgmp_status_t.  After an error
  *     the outputs are unspecified; argument errors are detected on the host
  *     before anything is launched.
- *   - Inputs must be finite; NaN/Inf inputs give unspecified codes.
- *   - A workspace starts with FGMP_WORKSPACE_CONTROL_BYTES of arrival counters.  They must be zero
+ *   - Inputs must be finite; NaN/Inf inputs give unspecified codes.  Outputs and workspaces overlap neither each other nor inputs
+ *     (one kernel may still read an input when it writes the first results).
+ *   - A workspace starts with FGMP_WORKSPACE_CONTROL_BYTES of arrival counters and the words by which workgroups
+ *     wait for each other; products of all sizes may use them.  They must be zero
  *     when the workspace is first used (clear that much once after allocating it; nothing else in a
  *     workspace needs initializing) and every call leaves them zero, so a workspace can be reused
  *     for any sequence of calls and shapes, in or outside a captured graph.  Calls that may overlap
@@ -244,7 +246,7 @@ fgmp_status_t fgmp_quant_gemm_fused_packed_out(const void *X, fgmp_dtype_t dt, i
  * `epilogue | FGMP_EPILOGUE_ONE_LAUNCH` (with FGMP_EPILOGUE_NONE): a decode step quantizes its results
  * inside its launch whenever the one-launch kernel takes the shape (nothing is staged; a single kernel
  * per layer for callers who count launches); other shapes -- among them some of 20 to 32
- * rows of a long product, N K^2 >= 2^38, which the plain call computes in two launches, too -- are staged.
+ * rows of a long product, N K^2 >= 2^38, which the plain call computes on another kernel, too -- are staged.
  *   N          N % 64 == 0 with the gate; fisher_n, scores_y and packed_Y then refer to N/2 columns
  *   workspace  >= fgmp_workspace_bytes_packed_out_ex(M, N, K, epilogue)
  * Other arguments and errors as fgmp_quant_gemm_fused_packed_out; an unknown `epilogue` is

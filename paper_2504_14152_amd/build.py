@@ -1,7 +1,8 @@
 """Build libfgmp.so (HIP, gfx950) in-tree with hipcc, plus two variants of the same sources that only
 tests and the benchmark load:
   libfgmp_hooks.so     -DFGMP_MEASUREMENT_HOOKS: the per-launch timing hook of the prefill kernel and the
-                       environment switch for the two-pass prefill path (neither is in libfgmp.so)
+                       environment switches for the two-pass prefill path and for mid-size products whose
+                       workgroups make each other's shares (none of them is in libfgmp.so)
   libfgmp_fullwait.so  -DFGMP_FULL_WAITS: every hand-counted `s_waitcnt vmcnt(N)` of the assembly loads is
                        `vmcnt(0)`; the runtime guard requires its results to equal libfgmp.so's bit for bit
 """

@@ -283,8 +283,12 @@ static size_t skinny_x16_bytes(int64_t M, int64_t K)
 // 2048 32 rows (2) 24.0 / 18.3 | 24.4 / 17.0.  Over 420 such steps none is more than 1.5% slower than in one launch.  (From
 // N K^2 = 2^38 on, and only where it needs no more workspace than the step it replaces.)
 //
-// Steps that take two launches anyway -- K in more than 16 parts, the Eq. 8 score -- are faster on this kernel throughout: 32768 x
-// 256 32 rows 26.1 / 20.8, 11008 x 4096 with the Eq. 8 score 21.3 / 17.6.
+// Steps that the one-launch step does not serve -- K in more than 16 parts, the Eq. 8 score; on the older kernel they take two
+// launches -- are faster on this kernel throughout: 32768 x 256 32 rows 26.1 / 20.8, 11008 x 4096 with the Eq. 8 score 21.3 / 17.6.
+//
+// All these figures and both estimates are of this kernel behind a launch of the quantizer.  Where it quantizes the activations itself it is 1
+// to 3 us faster than they say (gemm_mid_quantizes), so that next to the lines some products stay on the other kernel that would now be faster
+// here; none takes this one for that.
 //
 // An odd number of row-tiles is nothing special to either kernel.  Of 1348 such products from N K^2 = 2^38 on, weights from HBM, the
 // estimates leave 511 to the one launch, which all took two: 6352 x 8788 22 rows (one launch / this kernel) 17.2 / 24.2, 6960 x 6195
@@ -316,9 +320,9 @@ GemmRoute gemm_route(int64_t M, int64_t N, int64_t K)
     if (!gemm_mid_applies(r.plan, N, K)) return r;
     if (M <= 32) {
         const bool stream = gemm_stream_applies(M, N, K);
-        r.mid_two_launch = r.plan.bytes(K) <= (stream && even_row_tiles(N) ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
+        r.mid_if_not_one_launch = r.plan.bytes(K) <= (stream && even_row_tiles(N) ? gemm_stream_scratch_bytes(M, N, K) : decode_bytes(M, N, K));
         int rounds = 0;
-        r.mid = r.mid_two_launch && (!stream || (gemm_mid_few_rows_micros(r.plan, N, K) <= gemm_stream_micros(M, N, K, &rounds) && rounds > 1));
+        r.mid = r.mid_if_not_one_launch && (!stream || (gemm_mid_few_rows_micros(r.plan, N, K) <= gemm_stream_micros(M, N, K, &rounds) && rounds > 1));
     } else {
         const double margin = M > 1024 ? 1.15 : 1.0;
         r.mid = margin * gemm_mid_micros(r.plan, M, N, K) <= gemm_mixed_micros(M, N, K) && (M <= 1024 || r.plan.bytes(K) <= fused);
@@ -452,7 +456,7 @@ fgmp_status_t quant_gemm(const void *X, fgmp_dtype_t dt, int64_t M, int64_t K, i
     // (the one-launch kernel addresses X with 32-bit byte offsets)
     const bool x_fits = ldx > 0 && ldx < (int64_t)0xFFFFFF00 / (M * 4);
     const bool one_launch = score_mode == FGMP_SCORE_NVFP4_ERROR && x_fits && gemm_stream_applies(M, N, K);
-    const bool mid = route.mid || (route.mid_two_launch && !one_launch);
+    const bool mid = route.mid || (route.mid_if_not_one_launch && !one_launch);
     // (the decode step quantizes its own results where the caller asks for it -- and where the plain call takes it, too: the
     // packed results are the same bit for bit either way)
     const bool stream_pack = pack_out != nullptr && !pack_out->gate && pack_out->one_launch && !mid && gemm_stream_packs(M, N, K);

@@ -21,8 +21,8 @@
 //   * The activations (FP16 values, written by the quantizer) go to LDS directly, two rounds deep, one barrier
 //     per round.  A row of a K-tile is 256 bytes = 16 chunks; stored in an order that
 //     makes the 16-byte operand reads free of bank conflicts.
-//   * Where the activations are at most one block per thread of the launch, the launch quantizes them (kQuantize): a workgroup
-//     makes its share of the FP16 values, says so, asks for its first weights and waits for the other shares.  A quantizer
+//   * Where the activations are at most one block per thread of the launch, the launch quantizes them (kQuantize): workgroups that
+//     hold a share (mid_units) make its FP16 values and say so; all ask for their first weights and wait for the other shares.  A quantizer
 //     launch costs 4 us of which 1.5 are work, this 2 us more before the first round: 64 rows 4096 x 12288 18.3 / 16.7, 77 rows 2064
 //     x 5003 13.2 / 11.5, 120 rows 368 x 603 8.5 / 7.2, 200 rows 4096 x 22016 44.7 / 43.7 us.  With two blocks per thread the
 //     shares take as long as the launch they replace (872 x 3408 x 764 (M, K, N) 22.8 / 23.2, 512 x 11008 x 4096 with three 56.8 /
@@ -177,7 +177,7 @@ __device__ __forceinline__ void mid_quantize_block(const MidArgs &a, uint32_t c,
         __builtin_amdgcn_raw_buffer_store_b128(v, out, (int)at, 0, kCoherent);
     }
 }
-// kQuantize: the activations are quantized by this launch (Sec. 4.2), a share by every workgroup, which then waits for the others'.
+// kQuantize: the activations are quantized by this launch (Sec. 4.2), a share by every workgroup that holds one; all wait for the others'.
 // No workgroup depends on another one running: a share that nobody has begun at its second look it makes itself, one that is begun
 // and does not come when its patience ends, too, the same values (two launches that fill the chip together on two streams would
 // wait for each other's workgroups to leave).  The values
@@ -715,8 +715,8 @@ constexpr int mid_most_nt(int mt) { return mt <= 4 ? 4 : 3; }
 // Which of the 16 MT x 16 NT WN tiles, and how many workgroups share one: the cheapest by a model of the launch, in
 // cycles of a compute unit.  A round costs what its matrix instructions, its vector instructions (two waves to a SIMD) or
 // its LDS accesses take, whichever is most -- 1.4 times that is measured --, a workgroup 15000 cycles before its first and
-// after its last round, partial sums that meet in memory 6000 and 2000 per part.  A launch takes 1.2 times the model (a
-// fused step 3 us more): 4096 x 12288, 64 rows, 4 x 2 tiles on 192 workgroups 16 us by the model, 19.6 measured (4 x 3 in
+// after its last round, partial sums that meet in memory 6000 and 2000 per part.  A launch took 1.2 times the model
+// when it was made (a fused step 3 us more, with a launch of the quantizer in front; both have become faster since, all plans alike): 4096 x 12288, 64 rows, 4 x 2 tiles on 192 workgroups 16 us by the model, 19.6 measured (4 x 3 in
 // two parts 21.7, 4 x 4 in two 24.1); 11008 x 4096, 512 rows, 8 x 2 in two parts 52 / 57 (8 x 3 in two 68, 4 x 4 63);
 // 4096 x 22016, 200 rows, 7 x 3 38 / 45 (5 x 3 66, 7 x 2 59).
 MidPlan gemm_mid_plan(int64_t M, int64_t N, int64_t K, size_t most_bytes)
@@ -764,7 +764,8 @@ double gemm_mid_micros(const MidPlan &p, int64_t M, int64_t N, int64_t K)
 }
 
 // The same for 20 to 32 rows with the weights coming from HBM, as those of a model's layers do: 2 to 4 us more than out of the
-// Infinity Cache, for the dependent loads before a workgroup's first round.  Fitted to 552 measured steps: 2% rms, 8% at most.
+// Infinity Cache, for the dependent loads before a workgroup's first round.  Fitted to 552 measured steps, a quantizer launch in front
+// of every one: 2% rms, 8% at most; steps that quantize in their launch take 1 to 3 us less.
 double gemm_mid_few_rows_micros(const MidPlan &p, int64_t N, int64_t K)
 {
     const int64_t waves = (p.tiles() * p.parts + 255) / 256, rounds = (p.rounds + p.parts - 1) / p.parts;
@@ -805,7 +806,7 @@ constexpr size_t kMidDoneAt = kWsCtrlRegion / 4 - kMidDoneWords;
 // four streams (a quantizer launch in front, all workgroups hold shares and make missing ones after eight looks, now): 64 x 4096 x
 // 12288 (M, K, N) 18.8 17.4 17.5 | 29.2 36.8 27.7 | 49.2 80.1 50.6, 77 x 2064 x 5003 12.8 12.2 12.0 | 22.3 30.5 18.9 | 34.1 72.6 31.6, 200 x
 // 4096 x 22016 45.2 42.9 43.2 | 83.4 86.3 81.3 | 169 206 176.  On one stream alone four chunks
-// to a workgroup cost up to 2% (one / four: 16.78 / 16.92, 11.77 / 11.91, 42.5 / 42.5).  Where shares take more than half of all waves, overlapping launches
+// to a workgroup cost up to 2.5% (one / four: 16.78 / 16.92, 11.77 / 11.91, 42.5 / 42.5).  Where shares take more than half of all waves, overlapping launches
 // still pay more than a quantizer launch (512 x 4096 x 4096 30.6 28.8 29.1 | 49.6 60.4 57.9 | 92 136 110, 207 x 6496 x 720 16.0 14.6 14.6 | 25.1
 // 32.8 33.3 | 41.2 91.5 63.9).  Eight chunks a workgroup, half as many: two streams up to 15% faster, one 1 to 10% slower.
 static uint32_t mid_units(const MidPlan &p, uint32_t n_chunks)

@@ -49,7 +49,7 @@ struct MidPlan {
 };
 struct GemmRoute {
     bool mid;              // faster than what the product takes otherwise
-    bool mid_two_launch;   // ... if that is two launches as well (up to 32 rows: where the one-launch step cannot serve)
+    bool mid_if_not_one_launch;   // ... where the one-launch step cannot serve (up to 32 rows)
     MidPlan plan;          // (valid where either)
 };
 GemmRoute gemm_route(int64_t M, int64_t N, int64_t K);
